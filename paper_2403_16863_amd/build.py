@@ -1,29 +1,42 @@
 """Compile the HIP sources of this package for gfx950 into libattn.so (in-tree)."""
 from __future__ import annotations
 
-import glob
 import os
 import subprocess
+import tempfile
+from concurrent.futures import ThreadPoolExecutor
 
 _HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(_HERE, "csrc")
 OUT = os.path.join(_HERE, "libattn.so")
 
 HIPCC_FLAGS = [
-    "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-shared",
+    "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC",
     # keep the compiler from forming packed-fp32 VALU instructions
     "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
 ]
+ATTN_PARTS = 8          # parts of the attention variant table (csrc/attn_variants.h)
+
+# (object, source, extra flags)
+UNITS = [("attn_fwd.o", "attn_fwd.hip", []), ("gemm_lrelu.o", "gemm_lrelu.hip", [])] + \
+        [(f"attn_kernels_{p}.o", "attn_kernels.hip", [f"-DATTN_PART={p}"]) for p in range(ATTN_PARTS)]
 
 
-def build_library(verbose: bool = False) -> str:
-    sources = sorted(glob.glob(os.path.join(CSRC, "*.hip")))
-    cmd = ["hipcc", *HIPCC_FLAGS, "-o", OUT, *sources]
+def _run(cmd, verbose):
     if verbose:
         print(" ".join(cmd), flush=True)
     res = subprocess.run(cmd, cwd=CSRC, capture_output=True, text=True)
     if res.returncode != 0:
         raise RuntimeError(f"hipcc failed:\n{res.stdout}\n{res.stderr}")
+
+
+def build_library(verbose: bool = False) -> str:
+    jobs = min(len(UNITS), os.cpu_count() or 1, 8)
+    with tempfile.TemporaryDirectory(prefix="attn_build_") as tmp:
+        with ThreadPoolExecutor(jobs) as pool:
+            list(pool.map(lambda u: _run(["hipcc", *HIPCC_FLAGS, *u[2], "-c", "-o", os.path.join(tmp, u[0]), u[1]], verbose),
+                          sorted(UNITS, key=lambda u: not u[2])))
+        _run(["hipcc", "--offload-arch=gfx950", "-shared", "-fPIC", "-o", OUT, *(os.path.join(tmp, u[0]) for u in UNITS)], verbose)
     return OUT
 
 

@@ -1,7 +1,7 @@
 // C ABI of the fused attention-forward library: argument checking, the table of
 // schedule variants (the search space of Sec. 3.1 as compile-time instantiations of
 // one kernel) and the event-timed measurement used as search feedback (Sec. 3.3).
-#include "attn_kernel.h"
+#include "attn_variants.h"
 
 #include <math.h>
 #include <stdio.h>
@@ -13,13 +13,16 @@ namespace {
 
 using attn::Params;
 
-typedef void (*KernelFn)(const Params);
-
 struct Variant {
     int bn, nw, qb, occ, ldp, pipe, pf, prio, ilv, ldpos;  // knob values
     int coords[10];                                     // lattice coordinates (indices into the knob value lists)
-    // kernels indexed [d == 128][dtype][causal]; null = not built for that combination
-    KernelFn fn[2][2][2];
+    // kernels by [dtype][causal] for head dimension 64 and 128; null = not built for it
+    const attn::KernelFn (*fn64)[2];
+    const attn::KernelFn (*fn128)[2];
+    attn::KernelFn fn(int d, int dtype, int causal) const {
+        const attn::KernelFn(*f)[2] = d == 128 ? fn128 : fn64;
+        return f ? f[dtype][causal ? 1 : 0] : nullptr;
+    }
 };
 
 // Knob value lists (lattice axes): bn {32,64,128}  nw {4,8}  qb {1,2}  ldp {0,1}
@@ -40,16 +43,6 @@ const char* const kKnobNames[] = {"bn", "nw", "qb", "ldp", "pipe", "pf", "prio",
 const int kKnobSizes[] = {3, 2, 2, 2, 4, 4, 3, 2, 3, 3};
 constexpr int kNumKnobs = 10;
 
-#define ATTN_KN(BN, NW, QB, OCC, LDP, PIPE, PF, PRIO, ILV, LDPOS) attn::Knobs<BN, NW, QB, OCC, LDP, PIPE, PF, PRIO, ILV, LDPOS>
-#define ATTN_KERNELS_FOR(D, ...)                                                        \
-    {                                                                                   \
-        {(KernelFn)attn::attn_fwd_kernel<attn::F16, D, false, ATTN_KN(__VA_ARGS__)>,      \
-         (KernelFn)attn::attn_fwd_kernel<attn::F16, D, true, ATTN_KN(__VA_ARGS__)>},      \
-        {(KernelFn)attn::attn_fwd_kernel<attn::BF16, D, false, ATTN_KN(__VA_ARGS__)>,     \
-         (KernelFn)attn::attn_fwd_kernel<attn::BF16, D, true, ATTN_KN(__VA_ARGS__)>}      \
-    }
-#define ATTN_NO_KERNELS {{nullptr, nullptr}, {nullptr, nullptr}}
-
 // index helpers for the coordinate lists above
 #define IDX_BN(x) ((x) == 32 ? 0 : (x) == 64 ? 1 : 2)
 #define IDX_NW(x) ((x) == 4 ? 0 : 1)
@@ -60,71 +53,12 @@ constexpr int kNumKnobs = 10;
     BN, NW, QB, OCC, LDP, PIPE, PF, PRIO, ILV, LDPOS,                                               \
     {IDX_BN(BN), IDX_NW(NW), IDX_QB(QB), LDP, PIPE, IDX_PF(PF), PRIO, IDX_DENSE(NW, QB, OCC), ILV, LDPOS}
 
-// variants of the first three loop orders have no interleave pattern and no load position
-#define VARIANT_BOTH(BN, NW, QB, OCC, LDP, PIPE, PF, PRIO)                                          \
-    {VARIANT_HEAD(BN, NW, QB, OCC, LDP, PIPE, PF, PRIO, 0, 0),                                      \
-     {ATTN_KERNELS_FOR(64, BN, NW, QB, OCC, LDP, PIPE, PF, PRIO, 0, 0),                             \
-      ATTN_KERNELS_FOR(128, BN, NW, QB, OCC, LDP, PIPE, PF, PRIO, 0, 0)}}
-#define VARIANT_D64(BN, NW, QB, OCC, LDP, PIPE, PF, PRIO)                                           \
-    {VARIANT_HEAD(BN, NW, QB, OCC, LDP, PIPE, PF, PRIO, 0, 0),                                      \
-     {ATTN_KERNELS_FOR(64, BN, NW, QB, OCC, LDP, PIPE, PF, PRIO, 0, 0), ATTN_NO_KERNELS}}
-#define VARIANT_D128(BN, NW, QB, OCC, LDP, PIPE, PF, PRIO)                                          \
-    {VARIANT_HEAD(BN, NW, QB, OCC, LDP, PIPE, PF, PRIO, 0, 0),                                      \
-     {ATTN_NO_KERNELS, ATTN_KERNELS_FOR(128, BN, NW, QB, OCC, LDP, PIPE, PF, PRIO, 0, 0)}}
-// the interleaved order (pipe 3), d = 128: 256-row query tiles, 64-key tiles
-#define VARIANT_ILV(LDP, PF, PRIO, ILV, LDPOS)                                                      \
-    {VARIANT_HEAD(64, 8, 1, 1, LDP, 3, PF, PRIO, ILV, LDPOS),                                       \
-     {ATTN_NO_KERNELS, ATTN_KERNELS_FOR(128, 64, 8, 1, 1, LDP, 3, PF, PRIO, ILV, LDPOS)}}
+#define ROW_D64(...) {VARIANT_HEAD(__VA_ARGS__), attn::KernelSet<64, attn::Knobs<__VA_ARGS__>>::fn, nullptr},
+#define ROW_D128(...) {VARIANT_HEAD(__VA_ARGS__), nullptr, attn::KernelSet<128, attn::Knobs<__VA_ARGS__>>::fn},
+#define ROW_BOTH(...) \
+    {VARIANT_HEAD(__VA_ARGS__), attn::KernelSet<64, attn::Knobs<__VA_ARGS__>>::fn, attn::KernelSet<128, attn::Knobs<__VA_ARGS__>>::fn},
 
-// the ping-pong order of variant 11 with another order of the V cluster's vector instructions (d = 128)
-#define VARIANT_PP_ILV(ILV)                                                                         \
-    {VARIANT_HEAD(64, 8, 1, 1, 1, 1, 4, 1, ILV, 0),                                                 \
-     {ATTN_NO_KERNELS, ATTN_KERNELS_FOR(128, 64, 8, 1, 1, 1, 1, 4, 1, ILV, 0)}}
-
-// the ping-pong order with three buffers and one barrier per tile (ldpos 1 on that order; d = 128)
-#define VARIANT_PP_3BUF(PF)                                                                         \
-    {VARIANT_HEAD(64, 8, 1, 1, 1, 1, PF, 1, 0, 1),                                                  \
-     {ATTN_NO_KERNELS, ATTN_KERNELS_FOR(128, 64, 8, 1, 1, 1, 1, PF, 1, 0, 1)}}
-
-const Variant kVariants[] = {
-    VARIANT_BOTH(64, 4, 1, 2, 1, 0, 4, 0),   // 0: the hand-written default
-    VARIANT_BOTH(64, 4, 1, 2, 1, 0, 2, 0),
-    VARIANT_BOTH(64, 4, 1, 2, 1, 0, 6, 0),
-    VARIANT_BOTH(64, 4, 1, 2, 1, 0, 4, 1),
-    VARIANT_BOTH(64, 4, 1, 2, 0, 0, 4, 0),
-    VARIANT_BOTH(32, 4, 1, 2, 1, 0, 4, 0),
-    VARIANT_BOTH(32, 4, 1, 2, 1, 0, 2, 0),
-    VARIANT_BOTH(64, 8, 1, 1, 1, 0, 4, 0),
-    VARIANT_BOTH(64, 8, 1, 1, 1, 0, 6, 0),
-    VARIANT_BOTH(64, 8, 1, 1, 1, 1, 2, 0),
-    VARIANT_BOTH(64, 8, 1, 1, 1, 1, 4, 0),
-    VARIANT_BOTH(64, 8, 1, 1, 1, 1, 4, 1),
-    VARIANT_BOTH(64, 8, 1, 1, 0, 1, 4, 0),
-    VARIANT_BOTH(64, 4, 2, 1, 1, 0, 4, 0),
-    VARIANT_D64(128, 4, 1, 2, 1, 0, 4, 0),
-    VARIANT_D128(64, 8, 1, 1, 1, 2, 2, 1),   // 15, 16: MFMA work in both ping-pong clusters
-    VARIANT_D128(64, 8, 1, 1, 1, 2, 4, 1),
-    VARIANT_D64(64, 4, 1, 3, 1, 0, 4, 0),    // 17 .. 19: three free-running workgroups per CU (d = 64)
-    VARIANT_D64(64, 4, 1, 3, 1, 0, 4, 1),
-    VARIANT_D64(64, 4, 1, 3, 1, 0, 2, 1),
-    VARIANT_BOTH(64, 8, 1, 1, 1, 1, 4, 2),   // 20: ping-pong, priority raised while a wave issues tile loads
-    VARIANT_ILV(0, 4, 0, 0, 0),              // 21 ..: the interleaved order, tiles through registers
-    VARIANT_ILV(0, 4, 0, 0, 1),
-    VARIANT_ILV(0, 4, 0, 0, 2),
-    VARIANT_ILV(0, 2, 0, 0, 1),
-    VARIANT_ILV(0, 8, 0, 0, 1),
-    VARIANT_ILV(0, 4, 1, 0, 1),
-    VARIANT_ILV(0, 4, 2, 0, 1),
-    VARIANT_ILV(0, 4, 0, 1, 1),
-    VARIANT_ILV(0, 4, 0, 2, 1),
-    VARIANT_ILV(1, 4, 0, 0, 0),              // 30 .. 32: the interleaved order, tiles straight to LDS
-    VARIANT_ILV(1, 4, 0, 0, 1),
-    VARIANT_ILV(1, 4, 1, 0, 0),              // (one knob away from variant 16: the lattice stays connected)
-    VARIANT_PP_ILV(1),                       // 33, 34: the default ping-pong kernel with the other orders of the softmax
-    VARIANT_PP_ILV(2),                       //         instructions (a second pinned order; the compiler's own order)
-    VARIANT_PP_3BUF(4),                      // 35, 36: ping-pong with three K/V buffers, loads one tile further ahead,
-    VARIANT_PP_3BUF(2),                      //         one workgroup barrier per tile (pf 4 / 2)
-};
+const Variant kVariants[] = {ATTN_ALL_VARIANTS(ROW_BOTH, ROW_D64, ROW_D128)};
 constexpr int kNumVariants = (int)(sizeof(kVariants) / sizeof(kVariants[0]));
 
 // Compute units of the current device (queried once per device).
@@ -190,7 +124,7 @@ int launch(const void* q, const void* k, const void* v, void* out, float* lse, i
     const int rc = check_args(q, k, v, out, lse, B, H, N, d, scale, dtype, variant_id);
     if (rc != ATTN_OK) return rc;
     const Variant& var = kVariants[variant_id];
-    const KernelFn fn = var.fn[d == 128][dtype][causal ? 1 : 0];
+    const attn::KernelFn fn = var.fn(d, dtype, causal);
     if (!fn) return ATTN_EUNSUPPORTED;
     const int bm = 32 * var.qb * var.nw;
     const long long nqt = ((long long)N + bm - 1) / bm;
@@ -553,7 +487,7 @@ int attn_schedule_item(int grid, int workgroup, int BH, int nqt, int round, int*
 int attn_variant_supported(int variant_id, int d, int dtype, int causal) {
     if (variant_id < 0 || variant_id >= kNumVariants) return ATTN_EINVAL;
     if ((d != 64 && d != 128) || (dtype != ATTN_F16 && dtype != ATTN_BF16)) return 0;
-    return kVariants[variant_id].fn[d == 128][dtype][causal ? 1 : 0] != nullptr;
+    return kVariants[variant_id].fn(d, dtype, causal) != nullptr;
 }
 
 int attn_variant_desc(int variant_id, char* buf, int buflen) {
@@ -651,7 +585,7 @@ int attn_fwd(const void* q, const void* k, const void* v, void* out, float* lse,
 int attn_deploy_variant(int variant_id, int d, int dtype, int causal, int n_min, int n_max) {
     if (variant_id < 0 || variant_id >= kNumVariants || n_min < 1 || n_max < n_min) return ATTN_EINVAL;
     if ((d != 64 && d != 128) || (dtype != ATTN_F16 && dtype != ATTN_BF16)) return ATTN_EINVAL;
-    if (!kVariants[variant_id].fn[d == 128][dtype][causal ? 1 : 0]) return ATTN_EUNSUPPORTED;
+    if (!kVariants[variant_id].fn(d, dtype, causal)) return ATTN_EUNSUPPORTED;
     Deployment e;
     e.used = true;
     e.variant_id = variant_id;
@@ -702,7 +636,7 @@ int attn_time_variant(const void* q, const void* k, const void* v, void* out, fl
 int attn_codeobj_load(const char* path, const char* kernel_name, int variant_id, int d, int dtype, int causal) {
     if (!path || !kernel_name || variant_id < 0 || variant_id >= kNumVariants) return ATTN_EINVAL;
     if ((d != 64 && d != 128) || (dtype != ATTN_F16 && dtype != ATTN_BF16)) return ATTN_EINVAL;
-    if (!kVariants[variant_id].fn[d == 128][dtype][causal ? 1 : 0]) return ATTN_EUNSUPPORTED;
+    if (!kVariants[variant_id].fn(d, dtype, causal)) return ATTN_EUNSUPPORTED;
     int slot = -1;
     for (int i = 0; i < kMaxLoaded; ++i)
         if (!g_loaded[i].fn) { slot = i; break; }
