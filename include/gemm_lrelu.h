@@ -33,11 +33,13 @@ extern "C" {
 #define GEMM_F16 0
 #define GEMM_BF16 1
 
-/* C = leaky_relu(A B) with the library's default schedule for the shape. */
+/* C = leaky_relu(A B).  The library picks the tile of C a workgroup computes (32 x 32 to 256 x 256) from
+ * the shape. */
 int gemm_lrelu(const void* a, const void* b, void* c, int M, int N, int K, float slope, int dtype, void* stream);
 
-/* The same with schedule variant `variant_id` in [0, gemm_lrelu_num_variants()): the variants
- * are the points the schedule search (Alg. 1) walks for this workload. */
+/* The same on 32 x 32 tiles of C with schedule variant `variant_id` in [0, gemm_lrelu_num_variants()):
+ * the variants are the points the schedule search (Alg. 1) walks for the paper's shape;
+ * gemm_lrelu_default_variant is the one it starts from. */
 int gemm_lrelu_variant(const void* a, const void* b, void* c, int M, int N, int K, float slope, int dtype,
                        void* stream, int variant_id);
 
