@@ -96,9 +96,29 @@ __device__ __forceinline__ void swap_halves(float x, float& lo_vals, float& hi_v
 // keeps for the whole kernel.  Written out by hand so that consecutive loads share no
 // address VGPR: with a freshly computed 64-bit VGPR address per load, the VALU write of
 // the next address has to wait until the previous load has left the issue queue.
+// None of the loads to LDS uses the compiler's builtins: it tracks those as writes to LDS and puts a
+// wait for every load in flight in front of the next LDS read it cannot prove apart, in the middle of
+// the tile loops.  The builtin on the ragged-tile path alone cost (its wait merges into the common path)
+// 19 us of 299 at 1 x 4 heads x 16384 keys, d = 64, 1 us of 21 at 4 x 16 x 1024 causal; on the interleaved
+// order, where all loads were builtins, 640 us of 2450 at 32 x 16384, d = 128 (variant 31).
 __device__ __forceinline__ void load_to_lds_16(const char* base, unsigned voff, unsigned lds_base) {
     asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1"
                  :: "v"(voff), "s"(base), "s"(lds_base) : "memory", "m0");
+}
+// The same from a per-lane 64-bit address.
+__device__ __forceinline__ void load_to_lds_16(const char* src, unsigned lds_base) {
+    asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, off"
+                 :: "v"(src), "s"(lds_base) : "memory", "m0");
+}
+// The same through a buffer descriptor: lane l reads at offset  voff + soff,  and delivers zeros if that is
+// not below the descriptor's size.
+__device__ __forceinline__ void buffer_to_lds_16(u32x4 rsrc, unsigned voff, unsigned soff, unsigned lds_base) {
+    asm volatile("s_mov_b32 m0, %3\n\ts_nop 0\n\tbuffer_load_dwordx4 %0, %1, %2 offen lds"
+                 :: "v"(voff), "s"(rsrc), "s"(soff), "s"(lds_base) : "memory", "m0");
+}
+__device__ __forceinline__ u32x4 buffer_resource(const void* base, unsigned size) {
+    const unsigned long long b = (unsigned long long)base;
+    return u32x4{(unsigned)b, (unsigned)(b >> 32), size, 0x00020000u};  // stride 0, untyped 32-bit elements
 }
 __device__ __forceinline__ unsigned lds_address(const void* p) {
     return (unsigned)(unsigned long)(const __attribute__((address_space(3))) char*)p;
@@ -364,7 +384,7 @@ __global__ __launch_bounds__(KN::NW * 64, KN::OCC) void attn_fwd_kernel(const Pa
                 const int r = min(kt0 + (int)(goff0 / RB) + i * ROWS_PER_PIECE, N - 1);
                 const char* src = head + (size_t)r * RB + goff0 % RB;
                 if constexpr (LDP == 1)
-                    __builtin_amdgcn_global_load_lds((global_void_ptr)src, (lds_void_ptr)dst, 16, 0, 0);
+                    load_to_lds_16(src, lds_address(dst));
                 else
                     stage = *reinterpret_cast<const u32x4*>(src);
             }
@@ -831,15 +851,14 @@ __global__ __launch_bounds__(KN::NW * 64, KN::OCC) void attn_fwd_kernel(const Pa
             const int head_bytes = (int)((unsigned)N * (unsigned)RB);  // below 2^32: checked by the host before the launch
             const __amdgpu_buffer_rsrc_t k_rsrc = __builtin_amdgcn_make_buffer_rsrc(const_cast<char*>(Kh), 0, head_bytes, 0x00020000);
             const __amdgpu_buffer_rsrc_t v_rsrc = __builtin_amdgcn_make_buffer_rsrc(const_cast<char*>(Vh), 0, head_bytes, 0x00020000);
+            const u32x4 k_words = buffer_resource(Kh, head_bytes), v_words = buffer_resource(Vh, head_bytes);
             auto tile_load = [&](int which, int tile, int buf, int piece) __attribute__((always_inline)) {
                 constexpr int ROWS_PER_PIECE = NT / CPR;
                 char* dst = smem_b + buf * 2 * TILE_BYTES + which * TILE_BYTES + (piece * NT + wave * 64) * 16;
                 const unsigned soff = (unsigned)tile * (BN * RB) + piece * (ROWS_PER_PIECE * RB);
-                __builtin_amdgcn_raw_ptr_buffer_load_lds(which ? v_rsrc : k_rsrc, (lds_void_ptr)dst, 16, which ? goffV0 : goffK0, soff, 0, 0);
+                buffer_to_lds_16(which ? v_words : k_words, which ? goffV0 : goffK0, soff, lds_address(dst));
             };
-            // The same piece through registers (LDP = 0): a wave's LDS reads queue behind its own loads
-            // to LDS that are still in flight, which stalls a stream that reads LDS all the time; a
-            // load into registers does not, and the piece is written to LDS when the stream is over.
+            // The same piece through registers (LDP = 0), written to LDS when the stream is over.
             auto tile_load_reg = [&](int which, int tile, int piece) __attribute__((always_inline)) -> u32x4 {
                 constexpr int ROWS_PER_PIECE = NT / CPR;
                 const unsigned soff = (unsigned)tile * (BN * RB) + piece * (ROWS_PER_PIECE * RB);
@@ -1070,9 +1089,9 @@ __global__ __launch_bounds__(KN::NW * 64, KN::OCC) void attn_fwd_kernel(const Pa
             // LDS: M_j reads K(j+1) from K buffer (j+1)&1 and V(j) from V buffer j&1.  The loads
             // of K(j+2) and V(j+1) may start in slot 2j (their targets were last read in slot
             // 2j-1) and must have landed when slot 2j+1 ends.  Every wave issues its share at
-            // the start of one of its V clusters (group B in slot 2j, group A in slot 2j+1):
-            // a wave that has LDS-direct loads in flight gets its own LDS reads queued behind
-            // them, which would stall an MFMA cluster but costs a VALU cluster nothing.
+            // the start of one of its V clusters (group B in slot 2j, group A in slot 2j+1): the
+            // texture path holds a wave while it takes its loads, which would starve the matrix
+            // pipe in an M cluster.
             static_assert(NW == 8, "the ping-pong order needs two waves per SIMD in one workgroup");
             const bool grp_b = wave >= NW / 2;
             auto cluster_m = [&](auto par_c, int j) __attribute__((always_inline)) {  // par = j & 1
@@ -1293,6 +1312,8 @@ __global__ __launch_bounds__(KN::NW * 64, KN::OCC) void attn_fwd_kernel(const Pa
         // per instruction.  Chunk k of row r sits at chunk k ^ (r mod CPR): conflict-free
         // row-wise reads, two-way conflicts on the column-wise writes.
         static_assert(BM * RB <= 4 * TILE_BYTES, "the O tile must fit into the K/V buffers");
+        // (interleaved order: the loads of the last iteration, past the end of the keys, are still in flight)
+        if constexpr (PIPE == 3) asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
         __syncthreads();  // every wave has finished reading the last K/V tiles
         {
             char* stage = smem_b + wave * (32 * QB * RB);

@@ -59,14 +59,6 @@ struct Block {
     static constexpr int OCC = OCC_;          // workgroups per compute unit
 };
 
-// 16 bytes per lane straight into LDS at lds_base + 16 * lane; a lane whose offset is not below
-// the descriptor's size delivers zeros.  Inline asm, not the builtin: the compiler tracks the builtin
-// as a write to LDS and puts a wait for every load in flight in front of the next LDS read.
-__device__ __forceinline__ void buffer_to_lds_16(u32x4 rsrc, unsigned voff, unsigned lds_base) {
-    asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tbuffer_load_dwordx4 %0, %1, 0 offen lds"
-                 :: "v"(voff), "s"(rsrc), "s"(lds_base) : "memory", "m0");
-}
-
 // Size of the descriptors and, as a lane's offset, the mark of a chunk outside the matrix.  Real offsets
 // stay below it: (BM - 1) * K * 2 and (BK - 1) * N * 2, checked by the host.
 constexpr unsigned kBufferSize = 0x80000000u;
@@ -126,16 +118,12 @@ __global__ __launch_bounds__(BL::WM * BL::WN * BL::WK * 64, (BL::OCC * BL::WM * 
     const int nkt = (K + WK * BK - 1) / (WK * BK);
     const char* pa = p.a + (size_t)m0 * K * 2 + wk * BK * 2;
     const char* pb = p.b + (size_t)n0 * 2 + (size_t)(wk * BK) * N * 2;
-    auto rsrc = [](const char* base, unsigned size) __attribute__((always_inline)) {
-        const unsigned long long b = (unsigned long long)base;
-        return u32x4{(unsigned)b, (unsigned)(b >> 32), size, 0x00020000u};
-    };
     int kload = wk * BK;  // first k of the next stage to be requested
     auto issue_a = [&](int i, unsigned buf, u32x4 r) __attribute__((always_inline)) {
-        buffer_to_lds_16(r, voffA[i], lds0 + buf * A_STAGE + (wave * LA + i) * 1024);
+        attn::buffer_to_lds_16(r, voffA[i], 0, lds0 + buf * A_STAGE + (wave * LA + i) * 1024);
     };
     auto issue_b = [&](int i, unsigned buf, u32x4 r) __attribute__((always_inline)) {
-        buffer_to_lds_16(r, voffB[i], lds0 + NB * A_STAGE + buf * B_STAGE + (wave * LB + i) * 1024);
+        attn::buffer_to_lds_16(r, voffB[i], 0, lds0 + NB * A_STAGE + buf * B_STAGE + (wave * LB + i) * 1024);
     };
     // the last, partial stage: chunks past K deliver zeros on both sides
     auto clip_tail = [&]() __attribute__((always_inline)) {
@@ -190,7 +178,7 @@ __global__ __launch_bounds__(BL::WM * BL::WN * BL::WK * 64, (BL::OCC * BL::WM * 
     auto next_stage = [&](int t) __attribute__((always_inline)) {
         clip_tail();
         const unsigned size = t < nkt ? kBufferSize : 0u;
-        ra = rsrc(pa, size), rb = rsrc(pb, size);
+        ra = attn::buffer_resource(pa, size), rb = attn::buffer_resource(pb, size);
         advance();
     };
     auto issue = [&](auto l_c) __attribute__((always_inline)) {
