@@ -105,6 +105,24 @@ def lib():
     return _lib
 
 
+_native = None
+
+
+def native():
+    """The native call path (csrc/native.cpp), bound to the loaded library; raises if it is not built."""
+    global _native
+    if _native is None:
+        L = lib()
+        try:
+            from . import _native as n
+        except ImportError as e:
+            raise ImportError("_native.so is not built; run `python -c 'import __graft_entry__ as g; g.build()'` "
+                              "from the repository root") from e
+        n.bind(ctypes.cast(L.attn_fwd, ctypes.c_void_p).value, ctypes.cast(L.gemm_lrelu, ctypes.c_void_p).value)
+        _native = n
+    return _native
+
+
 def attn_strerror(code: int) -> str:
     return lib().attn_strerror(int(code)).decode()
 
@@ -144,6 +162,12 @@ def _marshal(q, k, v, out, lse, stream):
 def attn_fwd(q, k, v, out, lse, causal: bool, scale: float, stream=None) -> None:
     """out, lse <- fused attention forward of device tensors q, k, v ([B,H,N,d]).
     Asynchronous on `stream` (an integer hipStream_t; default: torch's current stream)."""
+    rc = (_native or native()).attn_fwd(q, k, v, out, lse, causal, scale, stream)
+    if rc == ATTN_OK:
+        return
+    if rc < 0:
+        raise AttnError(rc, "attn_fwd")
+    # not a plain call: the steps one by one, each of which says what it refuses
     (ptrs_shape), dt, st = _marshal(q, k, v, out, lse, stream)
     rc = lib().attn_fwd(*ptrs_shape, int(bool(causal)), float(scale), dt, st)
     if rc != ATTN_OK:

@@ -88,6 +88,12 @@ def _marshal(a, b, c, stream):
 def gemm_lrelu(a, b, c, slope: float, stream=None) -> None:
     """c <- leaky_relu(a @ b) for device tensors a [M,K], b [K,N], c [M,N]; asynchronous on `stream`
     (an integer hipStream_t; default: torch's current stream)."""
+    rc = (binding._native or binding.native()).gemm_lrelu(a, b, c, slope, stream)
+    if rc == GEMM_OK:
+        return
+    if rc < 0:
+        raise GemmError(rc, "gemm_lrelu")
+    # not a plain call: the steps one by one, each of which says what it refuses
     args, dt, st = _marshal(a, b, c, stream)
     rc = lib().gemm_lrelu(*args, float(slope), dt, st)
     if rc != GEMM_OK:
