@@ -52,8 +52,19 @@ PyObject* not_plain() {
     return PyLong_FromLong(kNotPlain);
 }
 
+// No exception of torch's may leave an entry point of C: a tensor without storage (inside torch.func.vmap, say)
+// throws where its sizes, its data pointer or its stream are asked for.  The Python path then raises its own.
+template <PyObject* (*F)(PyObject* const*, Py_ssize_t)>
+PyObject* guarded(PyObject*, PyObject* const* args, Py_ssize_t nargs) {
+    try {
+        return F(args, nargs);
+    } catch (const std::exception&) {
+        return not_plain();
+    }
+}
+
 // attn_fwd(q, k, v, out, lse, causal, scale, stream)
-PyObject* attn_fwd(PyObject*, PyObject* const* args, Py_ssize_t nargs) {
+PyObject* attn_fwd(PyObject* const* args, Py_ssize_t nargs) {
     if (nargs != 8 || !g_attn) return not_plain();
     const at::Tensor *q = plain_tensor(args[0], 4), *k = plain_tensor(args[1], 4), *v = plain_tensor(args[2], 4),
                      *out = plain_tensor(args[3], 4), *lse = plain_tensor(args[4], 3);
@@ -67,16 +78,18 @@ PyObject* attn_fwd(PyObject*, PyObject* const* args, Py_ssize_t nargs) {
     const double scale = PyFloat_AsDouble(args[6]);
     void* stream;
     if (causal < 0 || (scale == -1.0 && PyErr_Occurred()) || !stream_of(args[7], *q, &stream)) return not_plain();
+    void *const pq = q->data_ptr(), *const pk = k->data_ptr(), *const pv = v->data_ptr(), *const po = out->data_ptr(),
+               *const pl = lse->data_ptr();
+    const int B = (int)q->size(0), H = (int)q->size(1), N = (int)q->size(2), d = (int)q->size(3);
     int rc;
     Py_BEGIN_ALLOW_THREADS
-    rc = g_attn(q->data_ptr(), k->data_ptr(), v->data_ptr(), out->data_ptr(), (float*)lse->data_ptr(), (int)q->size(0),
-                (int)q->size(1), (int)q->size(2), (int)q->size(3), causal, (float)scale, dt, stream);
+    rc = g_attn(pq, pk, pv, po, (float*)pl, B, H, N, d, causal, (float)scale, dt, stream);
     Py_END_ALLOW_THREADS
     return PyLong_FromLong(rc);
 }
 
 // gemm_lrelu(a, b, c, slope, stream)
-PyObject* gemm_lrelu(PyObject*, PyObject* const* args, Py_ssize_t nargs) {
+PyObject* gemm_lrelu(PyObject* const* args, Py_ssize_t nargs) {
     if (nargs != 5 || !g_gemm) return not_plain();
     const at::Tensor *a = plain_tensor(args[0], 2), *b = plain_tensor(args[1], 2), *c = plain_tensor(args[2], 2);
     if (!a || !b || !c) return not_plain();
@@ -87,9 +100,11 @@ PyObject* gemm_lrelu(PyObject*, PyObject* const* args, Py_ssize_t nargs) {
     const double slope = PyFloat_AsDouble(args[3]);
     void* stream;
     if ((slope == -1.0 && PyErr_Occurred()) || !stream_of(args[4], *a, &stream)) return not_plain();
+    void *const pa = a->data_ptr(), *const pb = b->data_ptr(), *const pc = c->data_ptr();
+    const int M = (int)a->size(0), N = (int)b->size(1), K = (int)a->size(1);
     int rc;
     Py_BEGIN_ALLOW_THREADS
-    rc = g_gemm(a->data_ptr(), b->data_ptr(), c->data_ptr(), (int)a->size(0), (int)b->size(1), (int)a->size(1), (float)slope, dt, stream);
+    rc = g_gemm(pa, pb, pc, M, N, K, (float)slope, dt, stream);
     Py_END_ALLOW_THREADS
     return PyLong_FromLong(rc);
 }
@@ -103,8 +118,8 @@ PyObject* bind(PyObject*, PyObject* args) {
     Py_RETURN_NONE;
 }
 
-PyMethodDef methods[] = {{"attn_fwd", (PyCFunction)(void (*)(void))attn_fwd, METH_FASTCALL, "0, a library error, or NOT_PLAIN"},
-                         {"gemm_lrelu", (PyCFunction)(void (*)(void))gemm_lrelu, METH_FASTCALL, "0, a library error, or NOT_PLAIN"},
+PyMethodDef methods[] = {{"attn_fwd", (PyCFunction)(void (*)(void))guarded<attn_fwd>, METH_FASTCALL, "0, a library error, or NOT_PLAIN"},
+                         {"gemm_lrelu", (PyCFunction)(void (*)(void))guarded<gemm_lrelu>, METH_FASTCALL, "0, a library error, or NOT_PLAIN"},
                          {"bind", bind, METH_VARARGS, "addresses of the library's entry points"},
                          {nullptr, nullptr, 0, nullptr}};
 PyModuleDef module = {PyModuleDef_HEAD_INIT, "_native", nullptr, -1, methods, nullptr, nullptr, nullptr, nullptr};

@@ -25,6 +25,23 @@ def test_errors_are_those_of_the_python_path():
         gemm.gemm_lrelu(t[0, 0], t[0, 0], t[0, 0], 0.1)
 
 
+def test_tensors_without_storage_raise_in_python():
+    """Inside vmap a tensor has no data pointer: torch's exception must not end the process."""
+    from torch._subclasses.fake_tensor import FakeTensorMode
+    n = binding.native()
+    with FakeTensorMode():
+        x, y = torch.empty(2, 1, 1, 8, 64, dtype=torch.float16, device="cuda"), torch.empty(2, 1, 1, 8, device="cuda")
+
+        def native_calls(t, l):
+            s = torch.empty_like(t[0, 0, :, :8].contiguous())
+            assert n.attn_fwd(t, t, t, t, l, False, 1.0, 0) == n.NOT_PLAIN
+            assert n.gemm_lrelu(s, s, s, 1.0, 0) == n.NOT_PLAIN
+            with pytest.raises(RuntimeError):
+                A.attn_fwd(t, t, t, t, l, False, 1.0, stream=0)
+            return l
+        torch.func.vmap(native_calls)(x, y)
+
+
 @pytest.mark.gpu
 def test_native_and_python_paths_agree_on_results_errors_and_streams():
     g = torch.Generator(device="cuda")
