@@ -63,7 +63,7 @@ enum {
  *            scaled scores over the visible keys.  Every element is written.
  *  B,H,N   : >= 1, any N (ragged last tiles are masked).  Limits, reported as
  *            ATTN_EUNSUPPORTED: B*H*N*d <= 2^40 elements, and B*H*ceil(N/bm) <= 2^31-1
- *            work items (bm = the variant's query tile, 128 or 256 rows).
+ *            work items (bm = the variant's query tile, 32, 128 or 256 rows).
  *  d       : 64 or 128.
  *  causal  : 0 = every key visible, otherwise key j is visible to query i iff j <= i.
  *  scale   : finite; multiplies q.k before the softmax (callers pass 1/sqrt(d)).
@@ -145,8 +145,10 @@ int attn_schedule_item(int grid, int workgroup, int BH, int nqt, int round, int*
 
 /* The variant attn_fwd uses for this shape: the best admitted variant of the stored searches
  * on MI355X (Sec. 4.1: candidates are ranked offline and the best one is deployed, at no
- * run-time cost).  The choice depends on d and N only; dtype and causal are accepted so that a
- * later ranking may use them, and are ignored today. */
+ * run-time cost).  attn_fwd also counts the heads: launches of few query tiles take the variants
+ * that split the keys between the waves of a workgroup.  What is named here is the choice for
+ * many heads, and below 1024 keys the one for eight.  dtype is accepted so that a later ranking
+ * may use it, and is ignored today. */
 int attn_default_variant(int N, int d, int dtype, int causal);
 
 /* Feedback measurement of Sec. 3.3: `warmup` untimed launches, then `iters`

@@ -18,7 +18,7 @@ HIPCC_FLAGS = [
     # keep the compiler from forming packed-fp32 VALU instructions
     "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
 ]
-ATTN_PARTS = 8          # parts of the attention variant table (csrc/attn_variants.h)
+ATTN_PARTS = 9          # parts of the attention variant table (csrc/attn_variants.h)
 
 # (object, source, extra flags)
 UNITS = [("attn_fwd.o", "attn_fwd.hip", []), ("gemm_lrelu.o", "gemm_lrelu.hip", [])] + \

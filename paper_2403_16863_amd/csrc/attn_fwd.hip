@@ -19,6 +19,8 @@ struct Variant {
     // kernels by [dtype][causal] for head dimension 64 and 128; null = not built for it
     const attn::KernelFn (*fn64)[2];
     const attn::KernelFn (*fn128)[2];
+    bool keysplit() const { return pipe == 0 && ldpos == 1; }
+    int bm() const { return 32 * qb * (keysplit() ? 1 : nw); }  // query rows of a work item
     attn::KernelFn fn(int d, int dtype, int causal) const {
         const attn::KernelFn(*f)[2] = d == 128 ? fn128 : fn64;
         return f ? f[dtype][causal ? 1 : 0] : nullptr;
@@ -38,7 +40,8 @@ struct Variant {
 // wave issues its tile loads (all after the barrier, after fixed MFMA slots, after slots that
 // depend on the wave): the position of the memory instructions, which is what Sec. 3.1 perturbs.
 // On the ping-pong order ldpos 1 moves the tile loads one tile further ahead, into a third pair of
-// buffers, which leaves one workgroup barrier per tile instead of two.
+// buffers, which leaves one workgroup barrier per tile instead of two.  On the free-running order
+// ldpos 1 is the key split: every wave loads tiles of its own, of the same 32 query rows.
 const char* const kKnobNames[] = {"bn", "nw", "qb", "ldp", "pipe", "pf", "prio", "dense", "ilv", "ldpos"};
 const int kKnobSizes[] = {3, 2, 2, 2, 4, 4, 3, 2, 3, 3};
 constexpr int kNumKnobs = 10;
@@ -76,8 +79,12 @@ int cu_count() {
 
 // Persistent workgroups: as many as the device keeps resident (occ per CU), a multiple of 8
 // when every XCD can be given whole heads, never more than there are work items.
-long long grid_size(int cus, int occ, int BH, long long nqt) {
-    const long long total = (long long)BH * nqt, resident = (long long)cus * occ;
+// The key split's workgroups are not persistent, one per item: they come in the order of the schedule, the
+// heaviest of a head first, as units become free (dealt out ahead, 4 heads x 8000 causal keys, d = 128, took
+// 170 us instead of 122).
+long long grid_size(int cus, const Variant& var, int BH, long long nqt) {
+    const long long total = (long long)BH * nqt, resident = (long long)cus * var.occ;
+    if (var.keysplit()) return total;
     if ((BH & 7) == 0 && (resident & 7) == 0) {
         const long long per_xcd_items = (long long)(BH >> 3) * nqt, per_xcd_wg = resident >> 3;
         return 8 * (per_xcd_items < per_xcd_wg ? per_xcd_items : per_xcd_wg);
@@ -126,12 +133,14 @@ int launch(const void* q, const void* k, const void* v, void* out, float* lse, i
     const Variant& var = kVariants[variant_id];
     const attn::KernelFn fn = var.fn(d, dtype, causal);
     if (!fn) return ATTN_EUNSUPPORTED;
-    const int bm = 32 * var.qb * var.nw;
+    const int bm = var.bm();
     const long long nqt = ((long long)N + bm - 1) / bm;
     const long long total = nqt * B * H;
     if (total > 0x7fffffffLL) return ATTN_EUNSUPPORTED;
     // the interleaved order addresses K and V of a head through a buffer descriptor: 32-bit byte offsets
     if (var.pipe == 3 && (long long)N * d * 2 > 0xffffffffLL) return ATTN_EUNSUPPORTED;
+    // the key split too, and counts past the end of the keys (two rounds of its waves' tiles)
+    if (var.keysplit() && (long long)N * d * 2 > 0x7fffffffLL) return ATTN_EUNSUPPORTED;
 
     Params p;
     p.q = (const uint16_t*)q;
@@ -149,7 +158,7 @@ int launch(const void* q, const void* k, const void* v, void* out, float* lse, i
     p.qmode = scale > 0.f ? 0 : (scale < 0.f ? 1 : 2);
     p.scale = scale > 0.f ? scale : (scale < 0.f ? -scale : 1.0f);
     p.scale_l2 = p.scale * 1.44269504088896340736f;
-    const long long grid = grid_size(cu_count(), var.occ, p.BH, nqt);
+    const long long grid = grid_size(cu_count(), var, p.BH, nqt);
     // The launch's own return code is used (not hipGetLastError, which can report a
     // stale, unrelated status left behind by another library's earlier call).
     void* args[] = {&p};
@@ -469,8 +478,8 @@ int attn_num_variants(void) { return kNumVariants; }
 int attn_schedule_grid(int variant_id, int compute_units, int B, int H, int N) {
     if (variant_id < 0 || variant_id >= kNumVariants || compute_units < 1 || B < 1 || H < 1 || N < 1) return ATTN_EINVAL;
     const Variant& var = kVariants[variant_id];
-    const int bm = 32 * var.qb * var.nw;
-    const long long nqt = ((long long)N + bm - 1) / bm, g = grid_size(compute_units, var.occ, B * H, nqt);
+    const int bm = var.bm();
+    const long long nqt = ((long long)N + bm - 1) / bm, g = grid_size(compute_units, var, B * H, nqt);
     if ((long long)B * H > 0x7fffffffLL / nqt || g > 0x7fffffffLL) return ATTN_EUNSUPPORTED;
     return (int)g;
 }
@@ -494,7 +503,7 @@ int attn_variant_desc(int variant_id, char* buf, int buflen) {
     if (variant_id < 0 || variant_id >= kNumVariants || !buf || buflen < 1) return ATTN_EINVAL;
     const Variant& v = kVariants[variant_id];
     return snprintf(buf, (size_t)buflen, "bm=%d bn=%d nw=%d qb=%d occ=%d ldp=%d pipe=%d pf=%d prio=%d ilv=%d ldpos=%d",
-                    32 * v.qb * v.nw, v.bn, v.nw, v.qb, v.occ, v.ldp, v.pipe, v.pf, v.prio, v.ilv, v.ldpos);
+                    v.bm(), v.bn, v.nw, v.qb, v.occ, v.ldp, v.pipe, v.pf, v.prio, v.ilv, v.ldpos);
 }
 
 int attn_num_knobs(void) { return kNumKnobs; }
@@ -527,10 +536,32 @@ constexpr int kDefaultD128 = 36;
 constexpr int kDefaultD64Long = 18;
 constexpr int kDefaultD64Short = 3;
 
-int attn_default_variant(int N, int d, int dtype, int causal) {
-    (void)dtype; (void)causal;
+// The key split (workgroups of 32 rows; 37: four waves, two workgroups per compute unit, 38: eight waves, one)
+// is the better one while the tiles of the defaults leave compute units idle.  Measured on 256 units,
+// us, default / 37 / 38 (heads x keys; g = workgroups of 32 rows):
+//   d = 128          32 x 512 (g 512)  15.1 / 11.3 / 14.8    3 x 5000 (471)    88.8 / 64.1 / 66.8    4 x 5000 (628)    90.8 / 91.9 / 94.1
+//   d = 128, causal  32 x 512 (512)    15.7 / 10.7 / 12.6    64 x 512 (1024)   17.3 / 18.0 / 23.8    24 x 1500 (1128)  34.3 / 30.8 / 37.9
+//                    5 x 2900 (455)    54.0 / 30.1 / 31.9    2 x 8000 (500)   133.1 / 76.7 / 55.9    13 x 2900 (1183)  59.2 / 60.8 / 65.0
+//   d = 64           24 x 512 (384)     8.8 /  7.1 /  9.2    8 x 2900 (728)    35.0 / 30.6 / 35.0    30 x 800 (750)    13.5 / 15.2 / 17.2
+//   d = 64, causal   48 x 512 (768)     9.7 /  8.8 / 11.4    64 x 512 (1024)   10.0 / 10.8 / 14.6    16 x 2900 (1456)  38.3 / 33.8 / 42.0
+//                    6 x 1500 (282)    20.0 /  9.9 /  9.0    2 x 8000 (500)    87.1 / 45.2 / 31.2    32 x 1500 (1504)  24.8 / 23.3 / 30.8
+// The lines lie where the two sides meet: a masked workgroup is half as heavy on average while the
+// default's time is that of its heaviest, so they lie twice as high there; with few keys the split's
+// start and its sum at the end count for more.  Eight waves pay while each workgroup has a compute
+// unit to itself (4 x 2048, d = 64: 10.7 against 12.8) and where the heaviest one decides (long, masked).
+constexpr int kKeySplit4 = 37, kKeySplit8 = 38;
+
+static int choose_variant(long long heads, int N, int d, int causal) {
+    const long long g = heads * ((N + 31LL) / 32);
+    const int most = causal ? (N < 768 ? 896 : d == 128 ? 1152 : 1408) : d == 128 ? 640 : 704;
+    if (g <= most) return N >= 512 && (g <= 256 || (causal && N >= 6000)) ? kKeySplit8 : kKeySplit4;
     if (d == 128) return kDefaultD128;
     return N >= 2048 ? kDefaultD64Long : kDefaultD64Short;
+}
+
+int attn_default_variant(int N, int d, int dtype, int causal) {
+    (void)dtype;
+    return choose_variant(N < 1024 ? 8 : 1 << 20, N, d, causal);
 }
 
 int attn_fwd_variant(const void* q, const void* k, const void* v, void* out, float* lse, int B, int H,
@@ -579,7 +610,7 @@ int attn_fwd(const void* q, const void* k, const void* v, void* out, float* lse,
         }
     }
     return launch(q, k, v, out, lse, B, H, N, d, causal, scale, dtype, stream,
-                  attn_default_variant(N, d, dtype, causal));
+                  choose_variant((long long)B * H, N, d, causal));
 }
 
 int attn_deploy_variant(int variant_id, int d, int dtype, int causal, int n_min, int n_max) {

@@ -37,6 +37,7 @@ typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
 typedef float f32x16 __attribute__((ext_vector_type(16)));
 typedef float f32x2 __attribute__((ext_vector_type(2)));
+typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef short s16x4 __attribute__((ext_vector_type(4)));
 typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
 typedef unsigned u32x2 __attribute__((ext_vector_type(2)));
@@ -222,20 +223,27 @@ struct Knobs {
                                         // MFMA stream, 2 = while it issues tile loads (PIPE 1) / in the second wave of every SIMD (PIPE 3)
     static constexpr int ILV = ILV_;    // PIPE 3: how MFMA, LDS-read and softmax instructions are grouped (see there)
     static constexpr int LDPOS = LDPOS_;  // PIPE 3: where a wave issues its four tile loads of an iteration: 0 = all after the
-                                          // barrier, 1 = after MFMA slots 3, 11, 19, 27, 2 = after slots that depend on the wave
+                                          // barrier, 1 = after MFMA slots 3, 11, 19, 27, 2 = after slots that depend on the wave;
+                                          // PIPE 1: 1 = one tile further ahead (three buffers); PIPE 0: 1 = key split, every wave
+                                          // loads tiles of its own
+    static constexpr bool KEYSPLIT = PIPE == 0 && LDPOS == 1;
+    static constexpr int BM = 32 * QB * (KEYSPLIT ? 1 : NW);  // query rows of a workgroup
+    // second argument of the launch bounds: waves per SIMD
+    static constexpr int WAVES = KEYSPLIT ? OCC * NW / 4 : OCC;
 };
 
 template <class T, int D, bool CAUSAL, class KN>
-__global__ __launch_bounds__(KN::NW * 64, KN::OCC) void attn_fwd_kernel(const Params p) {
+__global__ __launch_bounds__(KN::NW * 64, KN::WAVES) void attn_fwd_kernel(const Params p) {
     constexpr int BN = KN::BN, NW = KN::NW, QB = KN::QB, LDP = KN::LDP, PIPE = KN::PIPE, PF = KN::PF, PRIO = KN::PRIO;
     constexpr int ILV = KN::ILV, LDPOS = KN::LDPOS;
     // Ping-pong order with LDPOS 1: three K and three V buffers, tile loads one tile further ahead,
     // ONE workgroup barrier per tile (see there).  Layout then K0 K1 K2 V0 V1 V2, so that the
     // immediate offsets of the K reads and of the V reads each stay inside their 64 KB.
     constexpr bool NB3 = PIPE == 1 && LDPOS == 1;
+    constexpr bool KEYSPLIT = KN::KEYSPLIT;
     constexpr int NB = NB3 ? 3 : 2;  // K buffers and V buffers in LDS
     constexpr int NT = NW * 64;
-    constexpr int BM = 32 * QB * NW;
+    constexpr int BM = KN::BM;
     constexpr int KS = D / 16;       // k-steps of the first contraction
     constexpr int DT = D / 32;       // 32-wide d tiles of O^T
     constexpr int KT = BN / 32;      // 32-key sub-tiles of one K/V tile
@@ -243,7 +251,7 @@ __global__ __launch_bounds__(KN::NW * 64, KN::OCC) void attn_fwd_kernel(const Pa
     constexpr int RB = D * 2;        // bytes per row
     constexpr int TILE_CHUNKS = BN * CPR;
     constexpr int LD_PER_THREAD = TILE_CHUNKS / NT;
-    static_assert(TILE_CHUNKS % NT == 0, "tile must divide over the workgroup");
+    static_assert(KEYSPLIT || TILE_CHUNKS % NT == 0, "tile must divide over the workgroup");
     constexpr int TILE_BYTES = TILE_CHUNKS * 16;
     constexpr int NVF = KT * 2 * DT;  // V fragments (MFMA steps of the second contraction) per tile
     constexpr int NKF = KS * KT;      // K fragments (MFMA steps of the first contraction) per tile
@@ -256,7 +264,8 @@ __global__ __launch_bounds__(KN::NW * 64, KN::OCC) void attn_fwd_kernel(const Pa
     // (Also for the free-running order at d = 64, where the staging area fits next to the tiles
     // of three workgroups per compute unit; at d = 128 two such workgroups would need 192 KB.)
     constexpr bool QSTAGE = LDP == 1 && QB == 1 && (PIPE == 1 || (PIPE == 0 && D == 64));
-    __shared__ __attribute__((aligned(256))) u32x4 smem[2 * NB * TILE_CHUNKS + (QSTAGE ? BM * CPR : 0)];  // K0 V0 K1 V1 (three buffers: K0 K1 K2 V0 V1 V2), then the Q staging area
+    // (key split: K and V tile of wave 0, of wave 1 ..., the Q rows, then every wave's row maxima and sums)
+    __shared__ __attribute__((aligned(256))) u32x4 smem[KEYSPLIT ? NW * 2 * TILE_CHUNKS + BM * CPR + NW * BM / 2 : 2 * NB * TILE_CHUNKS + (QSTAGE ? BM * CPR : 0)];  // K0 V0 K1 V1 (three buffers: K0 K1 K2 V0 V1 V2), then the Q staging area
     char* const smem_b = reinterpret_cast<char*>(smem);
 
     auto k_off = [](int b) { return NB3 ? b * TILE_BYTES : b * 2 * TILE_BYTES; };                       // K buffer b, bytes from the start of LDS
@@ -288,7 +297,7 @@ __global__ __launch_bounds__(KN::NW * 64, KN::OCC) void attn_fwd_kernel(const Pa
         // Row block of this wave inside the query tile.  Waves w and w + NW/2 share a SIMD; under a
         // causal mask the interleaved order (PIPE 3) gives them the blocks s and NW-1-s, so every SIMD
         // gets the same number of visible keys on the diagonal tiles.
-        const int rblk = (PIPE == 3 && CAUSAL) ? (wave < NW / 2 ? wave : NW + NW / 2 - 1 - wave) : wave;
+        const int rblk = KEYSPLIT ? 0 : (PIPE == 3 && CAUSAL) ? (wave < NW / 2 ? wave : NW + NW / 2 - 1 - wave) : wave;
         const int qw0 = q0 + rblk * (32 * QB);  // first query row of this wave
         const int qw_last = qw0 + 32 * QB - 1;  // causal: tile j is active for this wave iff j*BN <= qw_last
 
@@ -385,7 +394,7 @@ __global__ __launch_bounds__(KN::NW * 64, KN::OCC) void attn_fwd_kernel(const Pa
         auto issue_piece = [&](auto lnt_c, bool whole, const char* head, unsigned goff0, int lwave, int kt0, char* lds_tile,
                                int i, u32x4& stage) __attribute__((always_inline)) {
             constexpr int LNT = decltype(lnt_c)::value;
-            static_assert(LNT % 256 == 0 && TILE_CHUNKS % LNT == 0, "load mapping assumes whole swizzle periods per piece");
+            static_assert(KEYSPLIT || (LNT % 256 == 0 && TILE_CHUNKS % LNT == 0), "load mapping assumes whole swizzle periods per piece");
             constexpr int ROWS_PER_PIECE = LNT / CPR;
             char* dst = lds_tile + (i * LNT + lwave * 64) * 16;
             if (whole) {
@@ -655,9 +664,9 @@ __global__ __launch_bounds__(KN::NW * 64, KN::OCC) void attn_fwd_kernel(const Pa
             for (int qb = 0; qb < QB; ++qb) l_run[qb] += rs[qb];
         };
 
-        // Tile 0 always takes the slow path (m_use = -inf): go there directly.
-        auto softmax_first_tile = [&](f32x16(&s)[QB][KT], u32x4(&pk)[QB][KT][2]) __attribute__((always_inline)) {
-            mask(s, 0);
+        // The first tile always takes the slow path (m_use = -inf): go there directly.
+        auto softmax_first_tile = [&](f32x16(&s)[QB][KT], u32x4(&pk)[QB][KT][2], int k0 = 0) __attribute__((always_inline)) {
+            mask(s, k0);
             float rs[QB];
             raise_reference(s);
             exp_pack(s, pk, rs);
@@ -755,7 +764,156 @@ __global__ __launch_bounds__(KN::NW * 64, KN::OCC) void attn_fwd_kernel(const Pa
         f32x16 s[QB][KT];
         u32x4 pk[QB][KT][2];
 
-        if constexpr (PIPE == 0) {
+        if constexpr (KEYSPLIT) {
+            // Key split, for launches with fewer query tiles than compute units: all waves of a workgroup
+            // take the same 32 query rows, and wave w the key tiles w, w + NW, ... (32 keys each),
+            // with one K and one V tile buffer of its own.  Nothing is shared until the end, so
+            // there is no barrier and no wait for anybody else's loads in the loop: K(t + NW) is requested
+            // when the S MFMAs have read K(t) and lands under the softmax and the PV MFMAs, V(t + NW)
+            // when the PV MFMAs have read V(t) and lands under the next S and softmax.  Each wave
+            // keeps a reference maximum, a row sum and an O of its own; they meet in LDS once.
+            // The bound is the compute unit's path from L2: a workgroup reads every visible key for
+            // 32 rows only, 4 D bytes per key at 64 bytes per clock (8 clocks per key at d = 128), where
+            // a workgroup of 256 rows needs 40; so it is the better one while it is spread over
+            // about five times as many compute units (the rule is with the launch).
+            static_assert(LDP == 1 && QB == 1 && BN == 32, "the key split is written for 32 query rows and 32-key tiles straight to LDS");
+            constexpr int PPT = TILE_CHUNKS / 64;  // load instructions of a wave per tile
+            const unsigned head_bytes = (unsigned)N * (unsigned)RB;  // below 2^31: checked by the host
+            const unsigned own = wave * 2 * TILE_BYTES;
+            const unsigned lds_k = lds_address(smem_b) + own, lds_v = lds_k + TILE_BYTES;
+            // Load i fills chunks 64 i .. 64 i + 63 of a tile; the K swizzle repeats every 256 chunks, the V
+            // swizzle every 4 rows.  Rows past the end arrive as zeros (range check), and so do tiles past
+            // the last one (descriptor of size 0).
+            unsigned kvoff[4];
+#pragma unroll
+            for (int i = 0; i < 4; ++i) kvoff[i] = (unsigned)(k_swz(i * 64 + lane) - i * 64) * 16;
+            const unsigned vvoff = goff_v(lane);
+            auto load_tile = [&](const char* head, int t, unsigned lds, auto is_k) __attribute__((always_inline)) {
+                const u32x4 r = buffer_resource(head, t < nkt ? head_bytes : 0u);
+                unsigned soff = t * TILE_BYTES;
+                asm volatile("" : "+s"(lds));  // (or the compiler keeps all targets in scalar registers, and spills them)
+#pragma unroll
+                for (int i = 0; i < PPT; ++i) buffer_to_lds_16(r, decltype(is_k)::value ? kvoff[i & 3] : vvoff, soff + i * 1024, lds + i * 1024);
+            };
+            auto load_k = [&](int t) __attribute__((always_inline)) { load_tile(Kh, t, lds_k, yes); };
+            auto load_v = [&](int t) __attribute__((always_inline)) { load_tile(Vh, t, lds_v, no); };
+            constexpr int Q_OFF = NW * 2 * TILE_BYTES;
+#pragma unroll
+            for (int i = 0; i < (PPT + NW - 1) / NW; ++i) {
+                const int piece = i * NW + wave;  // the waves share the Q rows; (uniform) & 3 picks the offset
+                if (PPT % NW == 0 || piece < PPT)
+                    buffer_to_lds_16(buffer_resource(Qh, head_bytes), piece & 2 ? (piece & 1 ? kvoff[3] : kvoff[2]) : (piece & 1 ? kvoff[1] : kvoff[0]),
+                                     q0 * RB + piece * 1024, lds_address(smem_b) + Q_OFF + piece * 1024);
+            }
+            load_k(wave);
+            load_v(wave);
+            asm volatile("s_waitcnt vmcnt(%0)\n\ts_barrier" ::"n"(2 * PPT) : "memory");  // Q has landed
+            {
+                const unsigned flip = p.qmode == 1 ? 0x80008000u : 0u, keep = p.qmode == 2 ? 0u : 0xffffffffu;
+#pragma unroll
+                for (int ks = 0; ks < KS; ++ks) {
+                    const u32x4 val = *reinterpret_cast<const u32x4*>(smem_b + Q_OFF + koff[ks]);
+                    qreg[0][ks] = (val ^ flip) & keep;
+                }
+            }
+#pragma unroll
+            for (int ks = 0; ks < KS; ++ks) koff[ks] += own;
+#pragma unroll
+            for (int dt = 0; dt < DT; ++dt) voff[dt] += own;
+            if (wave < nkt) {
+                int t = wave;
+                // All fragments of a tile go to registers first: the tile's buffer is free, and the next one
+                // requested, before the first MFMA.
+                auto scores = [&]() __attribute__((always_inline)) {
+                    asm volatile("s_waitcnt vmcnt(%0)" ::"n"(PPT) : "memory");  // K(t)
+                    u32x4 f[KS];
+#pragma unroll
+                    for (int ks = 0; ks < KS; ++ks) f[ks] = *reinterpret_cast<const u32x4*>(smem_b + koff[ks]);
+                    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+                    load_k(t + NW);
+#pragma unroll
+                    for (int v = 0; v < 16; ++v) s[0][0][v] = 0.f;
+#pragma unroll
+                    for (int ks = 0; ks < KS; ++ks) s[0][0] = T::mfma(f[ks], qreg[0][ks], s[0][0]);
+                };
+                auto outputs = [&]() __attribute__((always_inline)) {
+                    asm volatile("s_waitcnt vmcnt(%0)" ::"n"(PPT) : "memory");  // V(t)
+                    u32x4 f[NVF];
+#pragma unroll
+                    for (int i = 0; i < NVF; ++i) {
+                        const char* const base = smem_b + TILE_BYTES + (i / DT) * 16 * RB + voff[i % DT];
+                        const u32x2 lo = __builtin_bit_cast(u32x2, __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4_ptr)(base)));
+                        const u32x2 hi = __builtin_bit_cast(u32x2, __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4_ptr)(base + 8 * RB)));
+                        f[i] = u32x4{lo[0], lo[1], hi[0], hi[1]};
+                    }
+                    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+                    load_v(t + NW);
+#pragma unroll
+                    for (int i = 0; i < NVF; ++i) o[0][i % DT] = T::mfma(f[i], pk[0][0][i / DT], o[0][i % DT]);
+                };
+                scores();
+                softmax_first_tile(s, pk, t * BN);
+                for (;;) {
+                    outputs();
+                    t += NW;
+                    if (t >= nkt) break;
+                    scores();
+                    softmax_tile(s, pk, t * BN);
+                }
+            }
+            asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // (the requests past the end)
+
+            // The waves' results meet: O as [32][D] floats over the wave's own tiles (16-byte chunk k of row r
+            // at chunk k ^ r), the row statistics behind Q.
+            constexpr int CPF = D / 4;  // 16-byte chunks per row of floats
+            constexpr int STAT_OFF = Q_OFF + BM * RB;
+            int te = tid;  // (opaque: the addresses below are formed here, not ahead of the item loop)
+            asm volatile("" : "+v"(te));
+            {
+                const float l_tot = xhalf_sum(l_run[0]);
+                const int ce = te & 31, ge = (te >> 5) & 1;
+#pragma unroll
+                for (int dt = 0; dt < DT; ++dt)
+#pragma unroll
+                    for (int v4 = 0; v4 < 4; ++v4)
+                        *reinterpret_cast<f32x4*>(smem_b + own + ce * (D * 4) + (((dt * 8 + v4 * 2 + ge) ^ (ce & (CPF - 1))) * 16)) =
+                            f32x4{o[0][dt][4 * v4], o[0][dt][4 * v4 + 1], o[0][dt][4 * v4 + 2], o[0][dt][4 * v4 + 3]};
+                float* const stat = reinterpret_cast<float*>(smem_b + STAT_OFF) + wave * 64;
+                if (ge == 0) stat[ce] = m_use[0], stat[32 + ce] = l_tot;
+            }
+            __syncthreads();
+            // D / 16 columns (D / 64 chunks of floats) per thread of eight waves, 16 threads per row; with four
+            // waves in two passes
+            for (int e = te; e < 512; e += NT) {
+                const int row = e >> 4, j = e & 15;
+                const float* const stat = reinterpret_cast<const float*>(smem_b + STAT_OFF) + row;
+                float m = stat[0], f[NW], l = 0.f;
+#pragma unroll
+                for (int w = 1; w < NW; ++w) m = fmaxf(m, stat[w * 64]);
+                f32x4 x[D / 64];
+#pragma unroll
+                for (int q = 0; q < D / 64; ++q) x[q] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+                for (int w = 0; w < NW; ++w) {  // (a wave without tiles: m = -inf, weight 0; wave 0 has tile 0, so m is not)
+                    f[w] = __builtin_amdgcn_exp2f((stat[w * 64] - m) * p.scale_l2);
+                    l += f[w] * stat[w * 64 + 32];
+#pragma unroll
+                    for (int q = 0; q < D / 64; ++q)
+                        x[q] += f[w] * *reinterpret_cast<const f32x4*>(smem_b + w * 2 * TILE_BYTES + row * (D * 4) + (((j * (D / 64) + q) ^ (row & (CPF - 1))) * 16));
+                }
+                const float inv = 1.0f / l;
+                if (q0 + row < N) {
+                    uint16_t* const dst = p.out + head_off + (size_t)(q0 + row) * D + j * (D / 16);
+                    if constexpr (D == 128)
+                        *reinterpret_cast<u32x4*>(dst) = u32x4{T::pack2(x[0][0] * inv, x[0][1] * inv), T::pack2(x[0][2] * inv, x[0][3] * inv),
+                                                               T::pack2(x[1][0] * inv, x[1][1] * inv), T::pack2(x[1][2] * inv, x[1][3] * inv)};
+                    else
+                        *reinterpret_cast<u32x2*>(dst) = u32x2{T::pack2(x[0][0] * inv, x[0][1] * inv), T::pack2(x[0][2] * inv, x[0][3] * inv)};
+                    if (j == 0) p.lse[(size_t)bh * N + q0 + row] = m * p.scale + (__logf(l) + T::kBias * 0.693147180559945309f);
+                }
+            }
+            continue;
+        } else if constexpr (PIPE == 0) {
             // Plain order: every tile is loaded one iteration ahead; per tile S, softmax, PV.
             // Overlap of MFMA and VALU work comes from the other waves resident on the SIMD.
             auto step = [&](auto buf_c, int j) __attribute__((always_inline)) {
@@ -1325,7 +1483,8 @@ __global__ __launch_bounds__(KN::NW * 64, KN::OCC) void attn_fwd_kernel(const Pa
         // tiles are dead by now) and writes whole rows, 16 bytes per lane, 1 KB contiguous
         // per instruction.  Chunk k of row r sits at chunk k ^ (r mod CPR): conflict-free
         // row-wise reads, two-way conflicts on the column-wise writes.
-        static_assert(BM * RB <= 4 * TILE_BYTES, "the O tile must fit into the K/V buffers");
+        if constexpr (!KEYSPLIT) {
+        static_assert(KEYSPLIT || BM * RB <= 4 * TILE_BYTES, "the O tile must fit into the K/V buffers");
         // (interleaved order: the loads of the last iteration, past the end of the keys, are still in flight)
         if constexpr (PIPE == 3) asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
         __syncthreads();  // every wave has finished reading the last K/V tiles
@@ -1362,6 +1521,7 @@ __global__ __launch_bounds__(KN::NW * 64, KN::OCC) void attn_fwd_kernel(const Pa
                 const u32x4 val = *reinterpret_cast<const u32x4*>(stage + row * RB + ((k ^ (row & (CPR - 1))) * 16));
                 if (qw0 + row < N) *reinterpret_cast<u32x4*>(obase + (size_t)row * D + k * 8) = val;
             }
+        }
         }
     }
 }

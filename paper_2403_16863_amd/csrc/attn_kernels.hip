@@ -1,4 +1,4 @@
-// The attention kernels of one part of the variant table (compile with -DATTN_PART=0 .. 7).
+// The attention kernels of one part of the variant table (compile with -DATTN_PART=0 .. 8).
 #include "attn_variants.h"
 
 namespace attn {

@@ -1,5 +1,5 @@
 // The table of schedule variants: what every row's knobs are.  One list per part: attn_kernels.hip compiles
-// the kernels of one part, so that the build runs its eight parts side by side (the kernels take four
+// the kernels of one part, so that the build runs its parts side by side (the kernels take four
 // minutes to compile one after the other).
 #pragma once
 #include "attn_kernel.h"
@@ -71,6 +71,10 @@ struct KernelSet {
     D128(64, 8, 1, 1, 1, 1, 4, 1, 0, 1) /* 35, 36: ping-pong with three K/V buffers, loads one tile further ahead, one barrier per tile */ \
     D128(64, 8, 1, 1, 1, 1, 2, 1, 0, 1)
 
+#define ATTN_VARIANTS_8(BOTH, D64, D128) \
+    BOTH(32, 4, 1, 2, 1, 0, 4, 0, 0, 1) /* 37, 38: free-running, the waves split the keys instead of the queries */ \
+    BOTH(32, 8, 1, 1, 1, 0, 4, 0, 0, 1)
+
 #define ATTN_ALL_VARIANTS(BOTH, D64, D128) \
     ATTN_VARIANTS_0(BOTH, D64, D128) \
     ATTN_VARIANTS_1(BOTH, D64, D128) \
@@ -79,4 +83,5 @@ struct KernelSet {
     ATTN_VARIANTS_4(BOTH, D64, D128) \
     ATTN_VARIANTS_5(BOTH, D64, D128) \
     ATTN_VARIANTS_6(BOTH, D64, D128) \
-    ATTN_VARIANTS_7(BOTH, D64, D128)
+    ATTN_VARIANTS_7(BOTH, D64, D128) \
+    ATTN_VARIANTS_8(BOTH, D64, D128)

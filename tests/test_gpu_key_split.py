@@ -1,0 +1,69 @@
+"""The key split of the free-running order, which attn_fwd takes for launches of few query tiles: the choice,
+and the two variants against the fp64 oracle where they can go wrong: fewer key tiles than waves, one key or
+row past a 32-row tile, waves that see their first tile late or never, scores that climb from wave to wave."""
+import numpy as np
+import pytest
+
+import paper_2403_16863_amd as A
+from oracle import ref
+from paper_2403_16863_amd import inputs as I
+
+SPLIT = [v for v in range(A.attn_num_variants()) if "pipe=0" in A.attn_variant_desc(v) and "ldpos=1" in A.attn_variant_desc(v)]
+DESC = {v: dict(kv.split("=") for kv in A.attn_variant_desc(v).split()) for v in SPLIT}
+
+
+def test_few_query_tiles_take_the_split_and_many_do_not():
+    assert len(SPLIT) == 2 and all(DESC[v]["bm"] == "32" for v in SPLIT)
+    for d in (64, 128):
+        for causal in (False, True):
+            assert A.attn_default_variant(300, d, A.ATTN_F16, causal) in SPLIT
+            for N in (1024, 4096, 1 << 20):          # named for many heads
+                assert A.attn_default_variant(N, d, A.ATTN_F16, causal) not in SPLIT
+
+
+def test_every_row_block_has_a_workgroup():
+    for B, H, N in ((1, 3, 1000), (2, 4, 129), (1, 1, 1), (1, 16, 64)):
+        for v in SPLIT:
+            nqt = -(-N // 32)
+            grid = A.attn_schedule_grid(v, 256, B, H, N)
+            assert grid == B * H * nqt
+            items = [A.attn_schedule_item(grid, g, B * H, nqt, 0) for g in range(grid)]
+            assert len(set(items)) == grid and all(A.attn_schedule_item(grid, g, B * H, nqt, 1) is None for g in range(grid))
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("causal", [False, True], ids=["full", "causal"])
+@pytest.mark.parametrize("dtype", [I.F16, I.BF16], ids=["f16", "bf16"])
+@pytest.mark.parametrize("d", [64, 128])
+def test_split_against_the_oracle(d, dtype, causal):
+    from gpu_util import check, run_gpu
+    for N in (1, 31, 32, 33, 127, 129, 257, 289, 600):
+        for kind in ("normal", "rising_scores", "peaked"):
+            if kind == "normal":
+                qb, kb, vb = I.make_qkv(I.Workload("split", 1, 3, N, d, causal, dtype, qk_sigma=2.0), seed=N)
+            else:
+                qb, kb, vb = I.make_adversarial(kind, 1, 3, N, d, dtype, seed=N)
+            for scale in (float(np.float32(d ** -0.5)), -0.1, 0.0):
+                O_ref, l_ref, _ = ref.attn_ref(qb, kb, vb, causal, float(np.float32(scale)), dtype)
+                out_scale = max(1.0, float(np.abs(I.bits_to_f64(vb, dtype)).max()))
+                for v in SPLIT:
+                    print(f"case {kind} N={N} d={d} causal={causal} dtype={dtype} scale={scale} variant={v}", flush=True)
+                    O, l = run_gpu(qb, kb, vb, causal, scale, dtype, variant=v)
+                    check(O, l, O_ref, l_ref, dtype, out_scale=out_scale, what=f"{kind} N={N} scale={scale} variant {v}")
+
+
+@pytest.mark.gpu
+def test_non_finite_scores_stay_in_their_rows():
+    """A NaN or an infinity in one query reaches that row alone, whichever wave's keys meet it (bfloat16; with
+    the overflow mode of binary16 no variant delivers NaN for it)."""
+    import torch
+    from gpu_util import run_gpu
+    for bad in (float("nan"), float("inf")):
+        qb, kb, vb = I.make_qkv(I.Workload("split", 1, 2, 200, 64, False, I.BF16), seed=3)
+        q = torch.from_numpy(qb.view(np.int16)).view(torch.bfloat16)
+        q[0, 1, 77, 5] = bad
+        for v in SPLIT:
+            O, l = run_gpu(q.view(torch.int16).numpy().view(np.uint16), kb, vb, False, 0.125, I.BF16, variant=v)
+            assert np.isnan(O[0, 1, 77]).all() and np.isnan(l[0, 1, 77])
+            O[0, 1, 77], l[0, 1, 77] = 0, 0
+            assert np.isfinite(O).all() and np.isfinite(l).all()
