@@ -543,7 +543,7 @@ constexpr int kDefaultD64Short = 3;
 //   d = 128, causal  32 x 512 (512)    15.7 / 10.7 / 12.6    64 x 512 (1024)   17.3 / 18.0 / 23.8    24 x 1500 (1128)  34.3 / 30.8 / 37.9
 //                    5 x 2900 (455)    54.0 / 30.1 / 31.9    2 x 8000 (500)   133.1 / 76.7 / 55.9    13 x 2900 (1183)  59.2 / 60.8 / 65.0
 //   d = 64           24 x 512 (384)     8.8 /  7.1 /  9.2    8 x 2900 (728)    35.0 / 30.6 / 35.0    30 x 800 (750)    13.5 / 15.2 / 17.2
-//   d = 64, causal   48 x 512 (768)     9.7 /  8.8 / 11.4    64 x 512 (1024)   10.0 / 10.8 / 14.6    16 x 2900 (1456)  38.3 / 33.8 / 42.0
+//   d = 64, causal   48 x 512 (768)     9.9 /  8.3 / 12.1    64 x 512 (1024)   10.1 / 10.9 / 15.5    16 x 2900 (1456)  37.6 / 35.5 / 43.9
 //                    6 x 1500 (282)    20.0 /  9.9 /  9.0    2 x 8000 (500)    87.1 / 45.2 / 31.2    32 x 1500 (1504)  24.8 / 23.3 / 30.8
 // The lines lie where the two sides meet: a masked workgroup is half as heavy on average while the
 // default's time is that of its heaviest, so they lie twice as high there; with few keys the split's

@@ -56,6 +56,19 @@ def test_balanced_and_local(grid, BH, nqt):
             assert len(heads) <= -(-per_xcd // nqt) + 1
 
 
+@pytest.mark.parametrize("grid,BH,nqt", [(512, 64, 8), (512, 32, 16), (400, 50, 8), (768, 64, 32), (320, 8, 40)])
+def test_units_that_hold_several_workgroups_get_even_sums(grid, BH, nqt):
+    """Workgroups g, g + 256 and g + 512 share a compute unit: every item once, and (grids of whole layers)
+    the items of the first two of them at mirrored weights."""
+    sched = items_of(grid, BH, nqt)
+    seen = [it for seq in sched.values() for it in seq]
+    assert len(seen) == len(set(seen)) == BH * nqt
+    for g in range(min(256, grid - 256)):
+        if grid % 256 == 0:
+            weights = [sum(qt + 1 for _, qt in sched[g + l][:1]) for l in (0, 256)]
+            assert abs(sum(weights) - (nqt + 1)) <= (0 if nqt <= 32 else nqt)
+
+
 def test_grid_size():
     v = A.attn_default_variant(4096, 128, A.ATTN_BF16, True)
     assert A.attn_schedule_grid(v, 256, 2, 32, 4096) == 256           # one persistent workgroup per CU
