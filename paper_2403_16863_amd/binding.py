@@ -118,7 +118,8 @@ def native():
         except ImportError as e:
             raise ImportError("_native.so is not built; run `python -c 'import __graft_entry__ as g; g.build()'` "
                               "from the repository root") from e
-        n.bind(ctypes.cast(L.attn_fwd, ctypes.c_void_p).value, ctypes.cast(L.gemm_lrelu, ctypes.c_void_p).value)
+        n.bind(*(ctypes.cast(f, ctypes.c_void_p).value
+                 for f in (L.attn_fwd, L.gemm_lrelu_in, L.gemm_lrelu_workspace, L.gemm_lrelu_capturing)))
         _native = n
     return _native
 

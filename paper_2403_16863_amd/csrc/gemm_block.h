@@ -63,8 +63,16 @@ struct Block {
 // stay below it: (BM - 1) * K * 2 and (BK - 1) * N * 2, checked by the host.
 constexpr unsigned kBufferSize = 0x80000000u;
 
-template <class T, class BL>
-__global__ __launch_bounds__(BL::WM * BL::WN * BL::WK * 64, (BL::OCC * BL::WM * BL::WN * BL::WK + 3) / 4) void gemm_block_kernel(Params p) {
+// Arguments of the split form: workgroup b computes the products of k range b / (ntm ntn) (kc values of k,
+// a multiple of 64 WK) into its part of the workspace, [range][M][N] floats; gemm_sum_kernel adds them.
+struct SplitParams : Params {
+    float* parts;
+    int kc;
+};
+
+template <class T, class BL, class Args = Params>
+__global__ __launch_bounds__(BL::WM * BL::WN * BL::WK * 64, (BL::OCC * BL::WM * BL::WN * BL::WK + 3) / 4) void gemm_block_kernel(Args p) {
+    constexpr bool SPLIT = std::is_same_v<Args, SplitParams>;
     constexpr int BM = BL::BM, BN = BL::BN, WM = BL::WM, WN = BL::WN, WK = BL::WK, NB = BL::NB;
     constexpr int NW = WM * WN, BK = BL::BK, KS = BK / 32;
     constexpr int TM = BM / WM, TN = BN / WN, MT = TM / 16, NT = TN / 16;
@@ -85,8 +93,16 @@ __global__ __launch_bounds__(BL::WM * BL::WN * BL::WK * 64, (BL::OCC * BL::WM * 
     const int wk = wave_wg / NW, wave = wave_wg % NW;
     const unsigned lds0 = lds_address(smem_b) + wk * RING;
     const int wm = wave / WN, wn = wave % WN;
-    int tm, tn;
-    tile_of_block((int)blockIdx.x, p.ntm, p.ntn, tm, tn);
+    int tm, tn, range = 0, k0 = 0, K1 = p.K;  // (K1: end of the k range)
+    if constexpr (SPLIT) {
+        const int tiles = p.ntm * p.ntn;
+        range = (int)blockIdx.x / tiles;
+        tile_of_block((int)blockIdx.x - range * tiles, p.ntm, p.ntn, tm, tn);
+        k0 = range * p.kc;
+        K1 = min(p.K, k0 + p.kc);
+    } else {
+        tile_of_block((int)blockIdx.x, p.ntm, p.ntn, tm, tn);
+    }
     const int m0 = tm * BM, n0 = tn * BN;
     const int M = p.M, N = p.N, K = p.K;
 
@@ -115,10 +131,10 @@ __global__ __launch_bounds__(BL::WM * BL::WN * BL::WK * 64, (BL::OCC * BL::WM * 
         kB[i] = row;
         voffB[i] = n0 + col < N ? (unsigned)row * (unsigned)(N * 2) + col * 2 : kBufferSize;
     }
-    const int nkt = (K + WK * BK - 1) / (WK * BK);
-    const char* pa = p.a + (size_t)m0 * K * 2 + wk * BK * 2;
-    const char* pb = p.b + (size_t)n0 * 2 + (size_t)(wk * BK) * N * 2;
-    int kload = wk * BK;  // first k of the next stage to be requested
+    const int nkt = (K1 - k0 + WK * BK - 1) / (WK * BK);
+    const char* pa = p.a + (size_t)m0 * K * 2 + (size_t)(k0 + wk * BK) * 2;
+    const char* pb = p.b + (size_t)n0 * 2 + (size_t)(k0 + wk * BK) * N * 2;
+    int kload = k0 + wk * BK;  // first k of the next stage to be requested
     auto issue_a = [&](int i, unsigned buf, u32x4 r) __attribute__((always_inline)) {
         attn::buffer_to_lds_16(r, voffA[i], 0, lds0 + buf * A_STAGE + (wave * LA + i) * 1024);
     };
@@ -127,11 +143,11 @@ __global__ __launch_bounds__(BL::WM * BL::WN * BL::WK * 64, (BL::OCC * BL::WM * 
     };
     // the last, partial stage: chunks past K deliver zeros on both sides
     auto clip_tail = [&]() __attribute__((always_inline)) {
-        if (kload + BK > K) {
+        if (kload + BK > K1) {
 #pragma unroll
-            for (int i = 0; i < LA; ++i) if (kload + kA[i] >= K) voffA[i] = kBufferSize;
+            for (int i = 0; i < LA; ++i) if (kload + kA[i] >= K1) voffA[i] = kBufferSize;
 #pragma unroll
-            for (int i = 0; i < LB; ++i) if (kload + kB[i] >= K) voffB[i] = kBufferSize;
+            for (int i = 0; i < LB; ++i) if (kload + kB[i] >= K1) voffB[i] = kBufferSize;
         }
     };
     auto advance = [&]() __attribute__((always_inline)) {
@@ -254,6 +270,13 @@ __global__ __launch_bounds__(BL::WM * BL::WN * BL::WK * 64, (BL::OCC * BL::WM * 
     auto act = [&](float x) __attribute__((always_inline)) { return x >= 0.f ? x : slope * x; };
     auto store_pair = [&](int mt, int nt, f32x4 x, f32x4 y) __attribute__((always_inline)) {
         const int m = m0 + wm * TM + mt * 16 + (lane & 15);
+        if constexpr (SPLIT) {
+            const int n = n0 + wn * TN + nt * 16 + g * 4;
+            float* const row = p.parts + ((size_t)range * M + m) * N;
+            if (m < M && n < N) *reinterpret_cast<f32x4*>(row + n) = x;
+            if (m < M && n + 16 < N) *reinterpret_cast<f32x4*>(row + n + 16) = y;
+            return;
+        }
         const auto s0 = __builtin_amdgcn_permlane16_swap(T::pack2(act(x[0]), act(x[1])), T::pack2(act(y[0]), act(y[1])), false, false);
         const auto s1 = __builtin_amdgcn_permlane16_swap(T::pack2(act(x[2]), act(x[3])), T::pack2(act(y[2]), act(y[3])), false, false);
         const int n = n0 + wn * TN + nt * 16 + (g & 1) * 16 + (g >> 1) * 8;
@@ -285,6 +308,24 @@ __global__ __launch_bounds__(BL::WM * BL::WN * BL::WK * 64, (BL::OCC * BL::WM * 
             store_pair(pr / (NT / 2), pr % (NT / 2) * 2, x, y);
         }
     }
+}
+
+// C = leaky_relu(sum of the parts), in range order; one thread per eight consecutive elements.
+template <class T>
+__global__ __launch_bounds__(64) void gemm_sum_kernel(const float* parts, uint16_t* c, int ranges, unsigned chunks, float slope) {
+    const unsigned i = blockIdx.x * 64 + threadIdx.x;
+    if (i >= chunks) return;
+    const f32x4* src = reinterpret_cast<const f32x4*>(parts) + (size_t)i * 2;
+    f32x4 x = src[0], y = src[1];
+#pragma unroll 4
+    for (int r = 1; r < ranges; ++r) {
+        src += (size_t)chunks * 2;
+        x += src[0];
+        y += src[1];
+    }
+    auto act = [&](float v) __attribute__((always_inline)) { return v >= 0.f ? v : slope * v; };
+    reinterpret_cast<u32x4*>(c)[i] = u32x4{T::pack2(act(x[0]), act(x[1])), T::pack2(act(x[2]), act(x[3])),
+                                           T::pack2(act(y[0]), act(y[1])), T::pack2(act(y[2]), act(y[3]))};
 }
 
 }  // namespace gemm

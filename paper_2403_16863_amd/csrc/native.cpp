@@ -11,6 +11,7 @@
 #include <limits.h>
 
 #include <ATen/core/Tensor.h>
+#include <c10/hip/HIPCachingAllocator.h>
 #include <c10/hip/HIPStream.h>
 #include <torch/csrc/autograd/python_variable.h>
 
@@ -19,9 +20,39 @@ namespace {
 constexpr long kNotPlain = 1;  // library codes are 0 or negative
 
 typedef int (*AttnFn)(const void*, const void*, const void*, void*, float*, int, int, int, int, int, float, int, void*);
-typedef int (*GemmFn)(const void*, const void*, void*, int, int, int, float, int, void*);
+typedef int (*GemmFn)(const void*, const void*, void*, int, int, int, float, int, void*, void*, long long);
+typedef long long (*WorkspaceFn)(int, int, int);
+typedef int (*CapturingFn)(void*);
 AttnFn g_attn = nullptr;
 GemmFn g_gemm = nullptr;
+WorkspaceFn g_workspace = nullptr;
+CapturingFn g_capturing = nullptr;
+
+// Scratch memory of one call, from torch's caching allocator: it belongs to the stream the call runs on, so it
+// may go back as soon as the kernels are enqueued (the next owner on that stream comes after them).  None
+// while the stream is captured, on a device that is not the current one, or when there is no memory left;
+// the call then does without.
+class Workspace {
+  public:
+    Workspace(long long bytes, void* stream, int device) : bytes_(bytes) {
+        if (bytes <= 0 || c10::hip::current_device() != device || g_capturing(stream)) return;
+        try {
+            p_ = c10::hip::HIPCachingAllocator::raw_alloc_with_stream((size_t)bytes, (hipStream_t)stream);
+        } catch (const std::exception&) {
+        }
+    }
+    ~Workspace() {
+        if (p_) c10::hip::HIPCachingAllocator::raw_delete(p_);
+    }
+    Workspace(const Workspace&) = delete;
+    Workspace& operator=(const Workspace&) = delete;
+    void* ptr() const { return p_; }
+    long long bytes() const { return p_ ? bytes_ : 0; }
+
+  private:
+    long long bytes_;
+    void* p_ = nullptr;
+};
 
 const at::Tensor* plain_tensor(PyObject* o, int dim) {
     if (!THPVariable_Check(o)) return nullptr;
@@ -102,18 +133,21 @@ PyObject* gemm_lrelu(PyObject* const* args, Py_ssize_t nargs) {
     if ((slope == -1.0 && PyErr_Occurred()) || !stream_of(args[4], *a, &stream)) return not_plain();
     void *const pa = a->data_ptr(), *const pb = b->data_ptr(), *const pc = c->data_ptr();
     const int M = (int)a->size(0), N = (int)b->size(1), K = (int)a->size(1);
+    const Workspace ws(g_workspace(M, N, K), stream, a->device().index());
     int rc;
     Py_BEGIN_ALLOW_THREADS
-    rc = g_gemm(pa, pb, pc, M, N, K, (float)slope, dt, stream);
+    rc = g_gemm(pa, pb, pc, M, N, K, (float)slope, dt, stream, ws.ptr(), ws.bytes());
     Py_END_ALLOW_THREADS
     return PyLong_FromLong(rc);
 }
 
-// bind(address of the library's attn_fwd, address of its gemm_lrelu)
+// bind(addresses of the library's attn_fwd, gemm_lrelu_in, gemm_lrelu_workspace and gemm_lrelu_capturing)
 PyObject* bind(PyObject*, PyObject* args) {
-    unsigned long long attn = 0, gemm = 0;
-    if (!PyArg_ParseTuple(args, "KK", &attn, &gemm)) return nullptr;
+    unsigned long long attn = 0, gemm = 0, workspace = 0, capturing = 0;
+    if (!PyArg_ParseTuple(args, "KKKK", &attn, &gemm, &workspace, &capturing)) return nullptr;
     g_attn = (AttnFn)attn;
+    g_workspace = (WorkspaceFn)workspace;
+    g_capturing = (CapturingFn)capturing;
     g_gemm = (GemmFn)gemm;
     Py_RETURN_NONE;
 }

@@ -37,6 +37,12 @@ def lib():
         common = [vp, vp, vp, i, i, i, f, i, vp]
         L.gemm_lrelu.restype = i
         L.gemm_lrelu.argtypes = common
+        L.gemm_lrelu_in.restype = i
+        L.gemm_lrelu_in.argtypes = common + [vp, ctypes.c_longlong]
+        L.gemm_lrelu_workspace.restype = ctypes.c_longlong
+        L.gemm_lrelu_workspace.argtypes = [i, i, i]
+        L.gemm_lrelu_capturing.restype = i
+        L.gemm_lrelu_capturing.argtypes = [vp]
         L.gemm_lrelu_variant.restype = i
         L.gemm_lrelu_variant.argtypes = common + [i]
         L.gemm_lrelu_time.restype = i

@@ -1,0 +1,102 @@
+"""GEMM + LeakyReLU with K split between workgroups (few tiles of C, a long K): the shapes that take it, against
+the fp64 oracle at ragged edges of every tile, and the calls that must do without scratch memory."""
+import numpy as np
+import pytest
+
+from paper_2403_16863_amd import gemm
+from paper_2403_16863_amd import inputs as I
+
+# (M, N, K): one past and one short of a tile, last k range short, one key of K past a stage
+SPLIT = [(1, 64, 4864), (4, 72, 8136), (33, 40, 5000), (31, 2056, 4872), (3, 3000, 4104), (24, 4096, 4096),
+         (65, 1096, 4616), (63, 3592, 4104), (129, 328, 8192), (500, 200, 6008)]
+WHOLE = [(1, 64, 4856), (24, 8192, 1024), (512, 512, 2048), (10, 7472, 7680), (4096, 4096, 4096), (24, 4096, 1 << 17)]
+
+
+def test_few_tiles_and_a_long_k_ask_for_scratch_memory():
+    L = gemm.lib()
+    for M, N, K in SPLIT:
+        need = L.gemm_lrelu_workspace(M, N, K)
+        assert need % (M * N * 4) == 0 and 2 <= need // (M * N * 4) <= 16 and need <= 4 << 20, (M, N, K)
+    for M, N, K in WHOLE + [(0, 8, 8), (8, 0, 8), (-1, 64, 8192)]:
+        assert L.gemm_lrelu_workspace(M, N, K) == 0, (M, N, K)
+
+
+def test_bad_scratch_memory_is_refused_before_any_launch():
+    """(fake pointers: nothing is dereferenced)"""
+    L = gemm.lib()
+    M, N, K = 24, 4096, 4096
+    a, b, c, need = 1 << 40, 1 << 41, 1 << 42, L.gemm_lrelu_workspace(M, N, K)
+    for ws in ((1 << 43) + 8, a, a - 16, b + 2 * K * N - 16, c, c - need + 16):
+        assert L.gemm_lrelu_in(a, b, c, M, N, K, 0.1, 0, None, ws, need) == gemm.GEMM_EINVAL
+    assert L.gemm_lrelu_in(a, b, a, M, N, K, 0.1, 0, None, 1 << 43, need) == gemm.GEMM_EINVAL
+    assert L.gemm_lrelu_in(a, b, c, M, N, K + 4, 0.1, 0, None, 1 << 43, need) == gemm.GEMM_EINVAL
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("dtype", [I.F16, I.BF16], ids=["f16", "bf16"])
+def test_split_against_the_oracle(dtype):
+    from test_gpu_gemm import check, run_gpu
+    for n, (M, N, K) in enumerate(SPLIT):
+        print(f"M{M} N{N} K{K} dtype {dtype}", flush=True)
+        ab, bb = I.make_gemm(M, N, K, dtype, seed=500 + n)
+        check(run_gpu(ab, bb, 0.1, dtype), ab, bb, 0.1, dtype, f"split M{M} N{N} K{K}")
+
+
+@pytest.mark.gpu
+def test_without_scratch_memory_the_plain_kernel_runs():
+    import torch
+    L = gemm.lib()
+    M, N, K = 33, 40, 5000
+    g = torch.Generator(device="cuda")
+    g.manual_seed(1)
+    a, b = (torch.randn(s, device="cuda", generator=g).half() for s in ((M, K), (K, N)))
+    plain, out, split = (torch.empty(M, N, device="cuda", dtype=torch.float16) for _ in range(3))
+    args = (M, N, K, 0.1, 0, torch.cuda.current_stream().cuda_stream)
+    assert L.gemm_lrelu(a.data_ptr(), b.data_ptr(), plain.data_ptr(), *args) == 0
+    need = L.gemm_lrelu_workspace(M, N, K)
+    ws = torch.full((need // 4,), float("nan"), device="cuda")
+    for p, bytes_ in ((None, 0), (None, need), (ws.data_ptr(), need - 1)):
+        out.fill_(float("nan"))
+        assert L.gemm_lrelu_in(a.data_ptr(), b.data_ptr(), out.data_ptr(), *args, p, bytes_) == 0
+        torch.cuda.synchronize()
+        assert torch.equal(out.view(torch.int16), plain.view(torch.int16))
+    assert L.gemm_lrelu_in(a.data_ptr(), b.data_ptr(), split.data_ptr(), *args, ws.data_ptr(), need) == 0
+    gemm.gemm_lrelu(a, b, out, 0.1)
+    torch.cuda.synchronize()
+    assert torch.equal(out.view(torch.int16), split.view(torch.int16))       # what gemm_lrelu does by itself
+    # two fp32 sums of 5000 products each, rounded once: half an ulp of binary16 apart and a little
+    assert (split.float() - plain.float()).abs().max() <= 2.0 ** -10 * plain.float().abs().max()
+    # a recorded call keeps to the plain kernel, and replays right
+    side = torch.cuda.Stream()
+    side.wait_stream(torch.cuda.current_stream())
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.stream(side), torch.cuda.graph(graph, stream=side):
+        gemm.gemm_lrelu(a, b, out, 0.1)
+    for _ in range(3):
+        out.fill_(float("nan"))
+        graph.replay()
+        gemm.gemm_lrelu(a, b, split, 0.1)
+        torch.cuda.synchronize()
+        assert torch.equal(out.view(torch.int16), plain.view(torch.int16))
+
+
+@pytest.mark.gpu
+def test_calls_on_several_streams_keep_their_parts_apart():
+    import torch
+    shapes = [(24, 4096, 4096), (16, 512, 8192), (65, 1096, 4616)]
+    work = []
+    for n, (M, N, K) in enumerate(shapes * 2):
+        g = torch.Generator(device="cuda")
+        g.manual_seed(n)
+        a, b = (torch.randn(s, device="cuda", generator=g).bfloat16() for s in ((M, K), (K, N)))
+        want, got = (torch.empty(M, N, device="cuda", dtype=torch.bfloat16) for _ in range(2))
+        gemm.gemm_lrelu(a, b, want, 0.01)
+        work.append((a, b, want, got, torch.cuda.Stream()))
+    torch.cuda.synchronize()
+    for rep in range(10):
+        for a, b, _, got, st in work:
+            with torch.cuda.stream(st):
+                gemm.gemm_lrelu(a, b, got, 0.01)
+    torch.cuda.synchronize()
+    for a, b, want, got, _ in work:
+        assert torch.equal(want.view(torch.int16), got.view(torch.int16))
