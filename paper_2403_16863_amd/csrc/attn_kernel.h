@@ -191,21 +191,30 @@ __device__ __forceinline__ int v_swz_slot(int row, int slot) {
 // of a unit come out even, and at any time the workgroups of a round work on few heads, whose K and V
 // stay in L2.  (With all workgroups of a round in one order, a unit held two heavy or two light items:
 // 64 heads x 1024 causal keys, d = 64, took 22.9 us instead of 19.4, 32 x 2048 38.4 instead of 30.7,
-// 16 x 8192 on three layers 183 instead of 159.  Grids that are not resident at once, those of the key
-// split, stay in order: there the heaviest first matters, 30 x 800 took 14.3 us in layers instead of 11.)
+// 16 x 8192 on three layers 183 instead of 159.)
+// The sawtooth only evens out over pairs of whole rounds.  Under a causal mask, a deal of few rounds that
+// are no such pairs, or of three layers at once, goes by weight over all heads instead, heaviest first: the
+// last, partial pass then holds the lightest items and falls to the units with least (32 x 2950, d = 128, 384
+// items on 256 units: 115 us by heads, 77 by weight; 48 x 2554, d = 64: 63 and 47).  Grids of more than three layers (the key split's,
+// one item per workgroup) go by weight and unmirrored: the units take them as they become free (6 x 4295, d = 128:
+// 61 us by heads, 50 by weight).
 // Workgroups are placed round-robin on the 8 XCDs, each with its own L2: when G and the number of heads
 // BH are multiples of 8, the deal runs inside each XCD (32 units) over that XCD's heads (x, x+8, ...), so
 // all query tiles of a head share one L2.  Every item is named exactly once over all (gidx, round).
-__host__ __device__ inline bool schedule_item(int G, int gidx, int BH, int nqt, int round, int& bh, int& qt) {
+__host__ __device__ inline bool schedule_item(int G, int gidx, int BH, int nqt, int round, int& bh, int& qt, bool causal = true) {
     const bool by_xcd = (G & 7) == 0 && (BH & 7) == 0;
-    const int C = by_xcd ? G >> 3 : G, idx = by_xcd ? gidx >> 3 : gidx, units = by_xcd ? 32 : 256;
-    const bool layers = C <= 2 * units || C == 3 * units;
-    const int first = layers ? idx / units * units : 0, last = (layers && first + units < C ? first + units : C) - 1;
-    const int r = round * C + (((round + (layers ? idx / units : 0)) & 1) ? first + last - idx : idx);
+    const int C = by_xcd ? G >> 3 : G, idx = by_xcd ? gidx >> 3 : gidx, shift = by_xcd ? 5 : 8, units = 1 << shift;
+    const bool layers = C <= 3 * units;
+    const int layer = layers ? idx >> shift : 0, first = layer << shift;
+    const int last = (layers && first + units < C ? first + units : C) - 1;
+    const int r = round * C + (((round + layer) & 1) ? first + last - idx : idx);
     const int nh = by_xcd ? BH >> 3 : BH, h0 = by_xcd ? gidx & 7 : 0, hs = by_xcd ? 8 : 1;
-    if (r >= nh * nqt) return false;
-    qt = nqt - 1 - r % nqt;
-    bh = h0 + hs * (r / nqt);
+    const int n = nh * nqt;
+    if (r >= n) return false;
+    const bool by_weight = causal && (n > C ? n / 6 < C && n % (2u * (unsigned)C) != 0 : C > 2 * units);
+    const int per = by_weight ? nh : nqt, q = r / per, rest = r - q * per;
+    qt = nqt - 1 - (by_weight ? q : rest);
+    bh = h0 + hs * (by_weight ? rest : q);
     return true;
 }
 
@@ -282,7 +291,7 @@ __global__ __launch_bounds__(KN::NW * 64, KN::WAVES) void attn_fwd_kernel(const 
     const int c = lane & 31;
 
     auto item_of_round = [&](int round, int& bh, int& qt) __attribute__((always_inline)) -> bool {
-        return schedule_item((int)gridDim.x, (int)blockIdx.x, p.BH, p.nqt, round, bh, qt);
+        return schedule_item((int)gridDim.x, (int)blockIdx.x, p.BH, p.nqt, round, bh, qt, CAUSAL);
     };
     const int N = p.N;
     // binary16 only: a finite result above the largest finite binary16 value is stored as that

@@ -56,17 +56,26 @@ def test_balanced_and_local(grid, BH, nqt):
             assert len(heads) <= -(-per_xcd // nqt) + 1
 
 
-@pytest.mark.parametrize("grid,BH,nqt", [(512, 64, 8), (512, 32, 16), (400, 50, 8), (768, 64, 32), (320, 8, 40)])
-def test_units_that_hold_several_workgroups_get_even_sums(grid, BH, nqt):
-    """Workgroups g, g + 256 and g + 512 share a compute unit: every item once, and (grids of whole layers)
-    the items of the first two of them at mirrored weights."""
+@pytest.mark.parametrize("grid,BH,nqt", [
+    (512, 64, 8), (512, 32, 16), (400, 50, 8), (768, 64, 32), (320, 8, 40), (552, 24, 23),   # layers of 256, whole and partial
+    (256, 32, 12), (256, 64, 12), (512, 12, 50), (768, 128, 18), (256, 3, 100), (768, 48, 20),  # rounds that are no whole pairs
+])
+def test_causal_sums_per_compute_unit(grid, BH, nqt):
+    """Workgroups g, g + 256 and g + 512 share a compute unit: every item once, and no unit has more than about
+    one item above the mean (whole deals) or above a unit's fair share (a single, partial one)."""
     sched = items_of(grid, BH, nqt)
     seen = [it for seq in sched.values() for it in seq]
     assert len(seen) == len(set(seen)) == BH * nqt
-    for g in range(min(256, grid - 256)):
-        if grid % 256 == 0:
-            weights = [sum(qt + 1 for _, qt in sched[g + l][:1]) for l in (0, 256)]
-            assert abs(sum(weights) - (nqt + 1)) <= (0 if nqt <= 32 else nqt)
+    units = [0] * 256
+    for g, seq in sched.items():
+        units[g % 256] += sum(qt + 1 for _, qt in seq)
+    assert max(units) <= sum(units) / min(256, grid) + nqt
+
+
+def test_rounds_by_weight_go_from_heavy_to_light():
+    """384 items on 256 workgroups: the second, partial round holds the lightest third."""
+    sched = items_of(256, 32, 12)
+    assert min(seq[0][1] for seq in sched.values()) >= max(seq[1][1] for seq in sched.values() if len(seq) > 1)
 
 
 def test_grid_size():
