@@ -131,7 +131,8 @@ int attn_variant_from_coords(const int* coords);
  * after round from a fixed schedule: items sorted by weight (under a causal mask the
  * last query tiles see the most keys) are dealt to the workgroups in serpentine
  * order, inside each of the 8 XCDs over that XCD's own heads when the grid and the
- * number of heads are multiples of 8.
+ * number of heads are multiples of 8 (what attn_schedule_item names is the order under a
+ * causal mask; without one the items of a head always follow each other).
  * attn_schedule_grid returns the grid size a launch of this variant uses for the
  * shape on a device with `compute_units` CUs (ATTN_EINVAL / ATTN_EUNSUPPORTED on bad
  * or oversized arguments).
@@ -145,9 +146,9 @@ int attn_schedule_item(int grid, int workgroup, int BH, int nqt, int round, int*
 
 /* The variant attn_fwd uses for this shape: the best admitted variant of the stored searches
  * on MI355X (Sec. 4.1: candidates are ranked offline and the best one is deployed, at no
- * run-time cost).  attn_fwd also counts the heads: launches of few query tiles take the variants
- * that split the keys between the waves of a workgroup.  What is named here is the choice for
- * many heads, and below 1024 keys the one for eight.  dtype is accepted so that a later ranking
+ * run-time cost).  attn_fwd also counts the heads: launches of few query tiles take variants with
+ * smaller tiles, the fewest those that split the keys between the waves of a workgroup.  What is
+ * named here is the choice for many heads, and below 1024 keys the one for eight.  dtype is accepted so that a later ranking
  * may use it, and is ignored today. */
 int attn_default_variant(int N, int d, int dtype, int causal);
 

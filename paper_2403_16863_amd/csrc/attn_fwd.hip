@@ -84,7 +84,7 @@ int cu_count() {
 // 170 us instead of 122).
 long long grid_size(int cus, const Variant& var, int BH, long long nqt) {
     const long long total = (long long)BH * nqt, resident = (long long)cus * var.occ;
-    if (var.keysplit()) return total;
+    if (var.keysplit()) return total > 512 && total <= 768 ? 776 : total;  // (more than three layers: the schedule's order for those)
     if ((BH & 7) == 0 && (resident & 7) == 0) {
         const long long per_xcd_items = (long long)(BH >> 3) * nqt, per_xcd_wg = resident >> 3;
         return 8 * (per_xcd_items < per_xcd_wg ? per_xcd_items : per_xcd_wg);
@@ -536,32 +536,40 @@ constexpr int kDefaultD128 = 36;
 constexpr int kDefaultD64Long = 18;
 constexpr int kDefaultD64Short = 3;
 
-// The key split (workgroups of 32 rows; 37: four waves, two workgroups per compute unit, 38: eight waves, one)
-// is the better one while the tiles of the defaults leave compute units idle.  Measured on 256 units,
-// us, default / 37 / 38 (heads x keys; g = workgroups of 32 rows):
-//   d = 128          32 x 512 (g 512)  15.1 / 11.3 / 14.8    3 x 5000 (471)    88.8 / 64.1 / 66.8    4 x 5000 (628)    90.8 / 91.9 / 94.1
-//   d = 128, causal  32 x 512 (512)    15.7 / 10.7 / 12.6    64 x 512 (1024)   17.3 / 18.0 / 23.8    24 x 1500 (1128)  34.3 / 30.8 / 37.9
-//                    5 x 2900 (455)    54.0 / 30.1 / 31.9    2 x 8000 (500)   133.1 / 76.7 / 55.9    13 x 2900 (1183)  59.2 / 60.8 / 65.0
-//   d = 64           24 x 512 (384)     8.8 /  7.1 /  9.2    8 x 2900 (728)    35.0 / 30.6 / 35.0    30 x 800 (750)    13.5 / 15.2 / 17.2
-//   d = 64, causal   48 x 512 (768)     9.9 /  8.3 / 12.1    64 x 512 (1024)   10.1 / 10.9 / 15.5    16 x 2900 (1456)  37.6 / 35.5 / 43.9
-//                    6 x 1500 (282)    20.0 /  9.9 /  9.0    2 x 8000 (500)    87.1 / 45.2 / 31.2    32 x 1500 (1504)  24.8 / 23.3 / 30.8
-// The lines lie where the two sides meet: a masked workgroup is half as heavy on average while the
-// default's time is that of its heaviest, so they lie twice as high there; with few keys the split's
-// start and its sum at the end count for more.  Eight waves pay while each workgroup has a compute
-// unit to itself (4 x 2048, d = 64: 10.7 against 12.8) and where the heaviest one decides (long, masked).
-constexpr int kKeySplit4 = 37, kKeySplit8 = 38;
+// The choice by the number of query tiles, measured on 256 units, us (heads x keys; g = tiles of 32 rows, the
+// key split's; j = tiles of 128 rows).
+// The key split (37: four waves, two workgroups per compute unit, 38: eight waves, one) against the defaults:
+//   d = 128          32 x 512 (g 512)  15.1 / 37: 11.3 / 38: 14.8     3 x 5000 (471)    88.8 / 64.1 / 66.8
+//   d = 128, causal  32 x 512 (512)    15.7 / 10.7 / 12.6             6 x 5753 (1080)   99.3 / 81.5 / 86.1
+//                    2 x 8000 (500)   133.1 / 76.7 / 55.9             32 x 1270 (1280)  29.5 / 28.6 / 37.3
+//   d = 64           24 x 512 (384)     8.8 /  7.1 /  9.2             4 x 5259 (660)    60.6 / 52.2 / 57.4
+//   d = 64, causal   8 x 4065 (1024)   46.1 / 32.9 / 36.8             48 x 905 (1392)   16.3 / 14.9 / -
+//                    6 x 1500 (282)    20.0 /  9.9 /  9.0             64 x 768 (1536)   14.1 / 14.5 / -
+//                    64 x 512 (1024)   10.1 / 10.9 / 15.5             48 x 661 (1008)   12.4 / 11.0 / -
+// The lines lie where the two sides meet: a masked tile is half as heavy on average while the default's time
+// is that of its heaviest; with few keys the split's start and its sum at the end count for more.  Eight
+// waves pay while each workgroup has a compute unit to itself (4 x 2048, d = 64: 10.7 against 12.8) and
+// where the heaviest one decides.
+// d = 128 between the split and full rounds of 256-row tiles, on 128-row tiles of the free-running order (1):
+//   12 x 1486 (j 144)  32.8 -> 29.3    64 x 329 (192)  14.7 -> 11.9    32 x 1011 (256)  25.8 -> 23.8
+//   96 x 751 (576)  47.6 -> 41.4 (a second round of few tiles either way); but 16 x 2649 (336)  61.3 -> 72.3
+//   causal  128 x 256 (256)  12.7 -> 11.0    8 x 6159 (392)  114.7 -> 108.2    32 x 1984 (512)  45.9 -> 43.9;  64 x 1196 (640)  34.6 -> 36.1
+// d = 64, three workgroups per unit (18) against two (3): 24 x 2809 (j 528) 73.9 / 81.4, 64 x 1706 (896) 60.7 / 63.3;
+//   causal  32 x 2581 (672) 59.7 / 39.9, 96 x 1397 (1056) 33.1 / 36.7.
+constexpr int kKeySplit4 = 37, kKeySplit8 = 38, kRows128 = 1;
 
 static int choose_variant(long long heads, int N, int d, int causal) {
-    const long long g = heads * ((N + 31LL) / 32);
-    const int most = causal ? (N < 768 ? 896 : d == 128 ? 1152 : 1408) : d == 128 ? 640 : 704;
-    if (g <= most) return N >= 512 && (g <= 256 || (causal && N >= 6000)) ? kKeySplit8 : kKeySplit4;
-    if (d == 128) return kDefaultD128;
-    return N >= 2048 ? kDefaultD64Long : kDefaultD64Short;
+    const long long g = heads * ((N + 31LL) / 32), j = heads * ((N + 127LL) / 128);
+    const int most = d == 128 ? (causal ? (N < 768 ? 736 : 1152) : 512) : causal ? (N < 600 ? 960 : 1536) : N < 640 ? 704 : 768;
+    if (g <= most) return N >= 512 && (g <= 256 || (causal && N >= 6000 && g <= 512)) ? kKeySplit8 : kKeySplit4;
+    if (d == 128) return (causal ? j <= 576 : j <= 256 || (j > 512 && j <= 640)) ? kRows128 : kDefaultD128;
+    return j > (causal ? 895 : 512) ? kDefaultD64Long : kDefaultD64Short;
 }
 
 int attn_default_variant(int N, int d, int dtype, int causal) {
     (void)dtype;
-    return choose_variant(N < 1024 ? 8 : 1 << 20, N, d, causal);
+    if (N < 1024) return choose_variant(8, N, d, causal);
+    return d == 128 ? kDefaultD128 : N >= 2048 ? kDefaultD64Long : kDefaultD64Short;
 }
 
 int attn_fwd_variant(const void* q, const void* k, const void* v, void* out, float* lse, int B, int H,
