@@ -125,11 +125,24 @@ __device__ __forceinline__ void load_to_lds_16(const char* src, unsigned lds_bas
     asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, off"
                  :: "v"(src), "s"(lds_base) : "memory", "m0");
 }
-// The same through a buffer descriptor: lane l reads at offset  voff + soff,  and delivers zeros if that is
-// not below the descriptor's size.
-__device__ __forceinline__ void buffer_to_lds_16(u32x4 rsrc, unsigned voff, unsigned soff, unsigned lds_base) {
-    asm volatile("s_mov_b32 m0, %3\n\ts_nop 0\n\tbuffer_load_dwordx4 %0, %1, %2 offen lds"
-                 :: "v"(voff), "s"(rsrc), "s"(soff), "s"(lds_base) : "memory", "m0");
+// The same through a buffer descriptor: lane l reads at offset  voff,  and delivers zeros if that is not
+// below the descriptor's size.  There is no scalar offset: the range check compares with the size less the
+// scalar offset, and what it does where that difference is below zero (rows past the end of a ragged
+// tile, tiles past the last one) is not documented.  What all lanes share goes into the base, and
+// off the size, or into voff.
+__device__ __forceinline__ void buffer_to_lds_16(u32x4 rsrc, unsigned voff, unsigned lds_base) {
+    asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tbuffer_load_dwordx4 %0, %1, 0 offen lds"
+                 :: "v"(voff), "s"(rsrc), "s"(lds_base) : "memory", "m0");
+}
+// Four of them in a row, 1024 bytes apart on both sides (the instruction's own offset counts for the memory
+// address, for the range check and for the LDS address).
+__device__ __forceinline__ void buffer_to_lds_4x16(u32x4 rsrc, unsigned v0, unsigned v1, unsigned v2, unsigned v3, unsigned lds_base) {
+    asm volatile("s_mov_b32 m0, %5\n\ts_nop 0\n\t"
+                 "buffer_load_dwordx4 %0, %4, 0 offen lds\n\t"
+                 "buffer_load_dwordx4 %1, %4, 0 offen offset:1024 lds\n\t"
+                 "buffer_load_dwordx4 %2, %4, 0 offen offset:2048 lds\n\t"
+                 "buffer_load_dwordx4 %3, %4, 0 offen offset:3072 lds"
+                 :: "v"(v0), "v"(v1), "v"(v2), "v"(v3), "s"(rsrc), "s"(lds_base) : "memory", "m0");
 }
 __device__ __forceinline__ u32x4 buffer_resource(const void* base, unsigned size) {
     const unsigned long long b = (unsigned long long)base;
@@ -790,22 +803,25 @@ __global__ __launch_bounds__(KN::NW * 64, KN::WAVES) void attn_fwd_kernel(const 
             // about five times as many compute units (the rule is with the launch).
             static_assert(LDP == 1 && QB == 1 && BN == 32, "the key split is written for 32 query rows and 32-key tiles straight to LDS");
             constexpr int PPT = TILE_CHUNKS / 64;  // load instructions of a wave per tile
+            static_assert(PPT % 4 == 0, "a tile is loaded four instructions at a time");
             const unsigned head_bytes = (unsigned)N * (unsigned)RB;  // below 2^31: checked by the host
             const unsigned own = wave * 2 * TILE_BYTES;
             const unsigned lds_k = lds_address(smem_b) + own, lds_v = lds_k + TILE_BYTES;
             // Load i fills chunks 64 i .. 64 i + 63 of a tile; the K swizzle repeats every 256 chunks, the V
-            // swizzle every 4 rows.  Rows past the end arrive as zeros (range check), and so do tiles past
-            // the last one (descriptor of size 0).
+            // swizzle every 4 rows.  A descriptor starts at the tile and ends with the head: rows past the
+            // end arrive as zeros (range check), and so do tiles past the last one (size 0).
             unsigned kvoff[4];
 #pragma unroll
             for (int i = 0; i < 4; ++i) kvoff[i] = (unsigned)(k_swz(i * 64 + lane) - i * 64) * 16;
             const unsigned vvoff = goff_v(lane);
             auto load_tile = [&](const char* head, int t, unsigned lds, auto is_k) __attribute__((always_inline)) {
-                const u32x4 r = buffer_resource(head, t < nkt ? head_bytes : 0u);
-                unsigned soff = t * TILE_BYTES;
+                constexpr bool K = decltype(is_k)::value;
+                const unsigned first = (unsigned)t * TILE_BYTES, left = t < nkt ? head_bytes - first : 0u;
                 asm volatile("" : "+s"(lds));  // (or the compiler keeps all targets in scalar registers, and spills them)
 #pragma unroll
-                for (int i = 0; i < PPT; ++i) buffer_to_lds_16(r, decltype(is_k)::value ? kvoff[i & 3] : vvoff, soff + i * 1024, lds + i * 1024);
+                for (int i = 0; i < PPT; i += 4)
+                    buffer_to_lds_4x16(buffer_resource(head + first + i * 1024, left > i * 1024u ? left - i * 1024u : 0u),
+                                       K ? kvoff[0] : vvoff, K ? kvoff[1] : vvoff, K ? kvoff[2] : vvoff, K ? kvoff[3] : vvoff, lds + i * 1024);
             };
             auto load_k = [&](int t) __attribute__((always_inline)) { load_tile(Kh, t, lds_k, yes); };
             auto load_v = [&](int t) __attribute__((always_inline)) { load_tile(Vh, t, lds_v, no); };
@@ -813,9 +829,11 @@ __global__ __launch_bounds__(KN::NW * 64, KN::WAVES) void attn_fwd_kernel(const 
 #pragma unroll
             for (int i = 0; i < (PPT + NW - 1) / NW; ++i) {
                 const int piece = i * NW + wave;  // the waves share the Q rows; (uniform) & 3 picks the offset
+                const unsigned first = (unsigned)q0 * RB + piece * 1024;
                 if (PPT % NW == 0 || piece < PPT)
-                    buffer_to_lds_16(buffer_resource(Qh, head_bytes), piece & 2 ? (piece & 1 ? kvoff[3] : kvoff[2]) : (piece & 1 ? kvoff[1] : kvoff[0]),
-                                     q0 * RB + piece * 1024, lds_address(smem_b) + Q_OFF + piece * 1024);
+                    buffer_to_lds_16(buffer_resource(reinterpret_cast<const char*>(Qh) + first, head_bytes > first ? head_bytes - first : 0u),
+                                     piece & 2 ? (piece & 1 ? kvoff[3] : kvoff[2]) : (piece & 1 ? kvoff[1] : kvoff[0]),
+                                     lds_address(smem_b) + Q_OFF + piece * 1024);
             }
             load_k(wave);
             load_v(wave);
@@ -1025,8 +1043,9 @@ __global__ __launch_bounds__(KN::NW * 64, KN::WAVES) void attn_fwd_kernel(const 
             };
 
             // Tile movement of this order: buffer loads straight into LDS.  The buffer descriptor
-            // covers the head's N rows, the tile and piece go into the scalar offset, the lane's
-            // share (with the swizzle) is the one vector offset kept for the whole kernel.  Rows
+            // covers the head's N rows, the lane's share of the offset (with the swizzle) is kept for
+            // the whole kernel, the tile and piece are added to it (not passed as the scalar
+            // offset: see buffer_to_lds_16).  Rows
             // past the end of the sequence, and whole tiles past it, arrive as zeros (the range
             // check of the buffer descriptor), so ragged tails need neither a branch nor a clamp;
             // their scores are masked.  which = 0: K, 1: V; piece = 0, 1 (NT chunks each).
@@ -1039,14 +1058,14 @@ __global__ __launch_bounds__(KN::NW * 64, KN::WAVES) void attn_fwd_kernel(const 
             auto tile_load = [&](int which, int tile, int buf, int piece) __attribute__((always_inline)) {
                 constexpr int ROWS_PER_PIECE = NT / CPR;
                 char* dst = smem_b + buf * 2 * TILE_BYTES + which * TILE_BYTES + (piece * NT + wave * 64) * 16;
-                const unsigned soff = (unsigned)tile * (BN * RB) + piece * (ROWS_PER_PIECE * RB);
-                buffer_to_lds_16(which ? v_words : k_words, which ? goffV0 : goffK0, soff, lds_address(dst));
+                const unsigned first = (unsigned)tile * (BN * RB) + piece * (ROWS_PER_PIECE * RB);
+                buffer_to_lds_16(which ? v_words : k_words, (which ? goffV0 : goffK0) + first, lds_address(dst));
             };
             // The same piece through registers (LDP = 0), written to LDS when the stream is over.
             auto tile_load_reg = [&](int which, int tile, int piece) __attribute__((always_inline)) -> u32x4 {
                 constexpr int ROWS_PER_PIECE = NT / CPR;
-                const unsigned soff = (unsigned)tile * (BN * RB) + piece * (ROWS_PER_PIECE * RB);
-                return __builtin_amdgcn_raw_buffer_load_b128(which ? v_rsrc : k_rsrc, which ? goffV0 : goffK0, soff, 0);
+                const unsigned first = (unsigned)tile * (BN * RB) + piece * (ROWS_PER_PIECE * RB);
+                return __builtin_amdgcn_raw_buffer_load_b128(which ? v_rsrc : k_rsrc, (which ? goffV0 : goffK0) + first, 0, 0);
             };
             auto tile_store_reg = [&](int which, int buf, int piece, u32x4 val) __attribute__((always_inline)) {
                 *reinterpret_cast<u32x4*>(smem_b + buf * 2 * TILE_BYTES + which * TILE_BYTES + (piece * NT + tid) * 16) = val;

@@ -136,10 +136,10 @@ __global__ __launch_bounds__(BL::WM * BL::WN * BL::WK * 64, (BL::OCC * BL::WM * 
     const char* pb = p.b + (size_t)n0 * 2 + (size_t)(k0 + wk * BK) * N * 2;
     int kload = k0 + wk * BK;  // first k of the next stage to be requested
     auto issue_a = [&](int i, unsigned buf, u32x4 r) __attribute__((always_inline)) {
-        attn::buffer_to_lds_16(r, voffA[i], 0, lds0 + buf * A_STAGE + (wave * LA + i) * 1024);
+        attn::buffer_to_lds_16(r, voffA[i], lds0 + buf * A_STAGE + (wave * LA + i) * 1024);
     };
     auto issue_b = [&](int i, unsigned buf, u32x4 r) __attribute__((always_inline)) {
-        attn::buffer_to_lds_16(r, voffB[i], 0, lds0 + NB * A_STAGE + buf * B_STAGE + (wave * LB + i) * 1024);
+        attn::buffer_to_lds_16(r, voffB[i], lds0 + NB * A_STAGE + buf * B_STAGE + (wave * LB + i) * 1024);
     };
     // the last, partial stage: chunks past K deliver zeros on both sides
     auto clip_tail = [&]() __attribute__((always_inline)) {

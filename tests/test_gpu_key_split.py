@@ -53,6 +53,33 @@ def test_split_against_the_oracle(d, dtype, causal):
 
 
 @pytest.mark.gpu
+@pytest.mark.parametrize("d", [64, 128])
+def test_memory_behind_the_last_row_is_never_used(d):
+    """Rows past the end and tiles past the last one arrive as zeros (the range check of the buffer loads): NaN
+    behind the tensors changes nothing, for the variants that load that way (the split, the interleaved order)."""
+    import torch
+    ids = SPLIT + [v for v in range(A.attn_num_variants()) if "pipe=3" in A.attn_variant_desc(v) and A.attn_variant_supported(v, d, A.ATTN_F16, False)]
+    for N in (1, 31, 33, 65, 95, 129, 200, 257):
+        g = torch.Generator(device="cuda")
+        g.manual_seed(N)
+        data = [torch.randn(N * d, device="cuda", generator=g).half() for _ in range(3)]
+        for v in ids:
+            print(f"case N={N} d={d} variant={v}", flush=True)
+            got = []
+            for behind in (0.0, float("nan")):
+                flat = [torch.full((N * d + (1 << 19),), behind, device="cuda", dtype=torch.float16) for _ in range(3)]
+                for f, x in zip(flat, data):
+                    f[:N * d] = x
+                q, k, v_ = (f[:N * d].view(1, 1, N, d) for f in flat)
+                out, lse = torch.empty(1, 1, N, d, device="cuda", dtype=torch.float16), torch.empty(1, 1, N, device="cuda")
+                A.attn_fwd_variant(q, k, v_, out, lse, False, d ** -0.5, v)
+                torch.cuda.synchronize()
+                got.append((out, lse))
+            assert torch.isfinite(got[0][0]).all() and torch.isfinite(got[0][1]).all()
+            assert torch.equal(got[0][0].view(torch.int16), got[1][0].view(torch.int16)) and torch.equal(got[0][1], got[1][1]), (N, v)
+
+
+@pytest.mark.gpu
 def test_non_finite_scores_stay_in_their_rows():
     """A NaN or an infinity in one query reaches that row alone, whichever wave's keys meet it (bfloat16; with
     the overflow mode of binary16 no variant delivers NaN for it)."""
