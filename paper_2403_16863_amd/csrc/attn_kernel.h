@@ -814,13 +814,19 @@ __global__ __launch_bounds__(KN::NW * 64, KN::WAVES) void attn_fwd_kernel(const 
 #pragma unroll
             for (int i = 0; i < 4; ++i) kvoff[i] = (unsigned)(k_swz(i * 64 + lane) - i * 64) * 16;
             const unsigned vvoff = goff_v(lane);
+            // Bytes from `first` on, none past the end.  (Through the first lane: the difference and the maximum in
+            // one would be a vector instruction, and a descriptor has to be in scalar registers.)
+            auto rest = [](unsigned bytes, unsigned first) __attribute__((always_inline)) {
+                return (unsigned)max(__builtin_amdgcn_readfirstlane((int)(bytes - first)), 0);
+            };
             auto load_tile = [&](const char* head, int t, unsigned lds, auto is_k) __attribute__((always_inline)) {
                 constexpr bool K = decltype(is_k)::value;
-                const unsigned first = (unsigned)t * TILE_BYTES, left = t < nkt ? head_bytes - first : 0u;
                 asm volatile("" : "+s"(lds));  // (or the compiler keeps all targets in scalar registers, and spills them)
+                t = __builtin_amdgcn_readfirstlane(t);  // (or it steps the sources of consecutive tiles in vector registers)
+                const unsigned first = (unsigned)t * TILE_BYTES, left = t < nkt ? head_bytes - first : 0u;
 #pragma unroll
                 for (int i = 0; i < PPT; i += 4)
-                    buffer_to_lds_4x16(buffer_resource(head + first + i * 1024, left > i * 1024u ? left - i * 1024u : 0u),
+                    buffer_to_lds_4x16(buffer_resource(head + first + i * 1024, rest(left, i * 1024)),
                                        K ? kvoff[0] : vvoff, K ? kvoff[1] : vvoff, K ? kvoff[2] : vvoff, K ? kvoff[3] : vvoff, lds + i * 1024);
             };
             auto load_k = [&](int t) __attribute__((always_inline)) { load_tile(Kh, t, lds_k, yes); };
@@ -831,7 +837,7 @@ __global__ __launch_bounds__(KN::NW * 64, KN::WAVES) void attn_fwd_kernel(const 
                 const int piece = i * NW + wave;  // the waves share the Q rows; (uniform) & 3 picks the offset
                 const unsigned first = (unsigned)q0 * RB + piece * 1024;
                 if (PPT % NW == 0 || piece < PPT)
-                    buffer_to_lds_16(buffer_resource(reinterpret_cast<const char*>(Qh) + first, head_bytes > first ? head_bytes - first : 0u),
+                    buffer_to_lds_16(buffer_resource(reinterpret_cast<const char*>(Qh) + first, rest(head_bytes, first)),
                                      piece & 2 ? (piece & 1 ? kvoff[3] : kvoff[2]) : (piece & 1 ? kvoff[1] : kvoff[0]),
                                      lds_address(smem_b) + Q_OFF + piece * 1024);
             }
