@@ -170,6 +170,15 @@ __device__ __forceinline__ float xhalf_max(float x) {
     return fmaxf(a, b);
 }
 
+// Key split: whether the sums of a wave (row sum l, reference maximum m) weigh nothing (factor 0) among those
+// they are added to and may hold anything.  Any wave's first tiles may be keys that are masked by their scores
+// (-inf, or finite and far below all others).  Their scaled reference is then -inf, or so large that its
+// rounding alone (a binade at 2^24, the range of fp32 at 2^31) makes the probabilities infinite, and 0 times
+// that is NaN.  Sums against any other reference are finite unless the inputs are not, and such a NaN stays.
+__device__ __forceinline__ bool no_weight(float factor, float l, float m, float scale_l2) {
+    return factor == 0.f && l != 0.f && m * scale_l2 < -16777216.f;
+}
+
 // ---- LDS layouts ------------------------------------------------------------
 // A K/V tile is BN rows of D 16-bit elements, addressed in 16-byte chunks.  Both
 // swizzles below are involutions that keep a chunk inside its 256-byte line (K) or
@@ -663,9 +672,20 @@ __global__ __launch_bounds__(KN::NW * 64, KN::WAVES) void attn_fwd_kernel(const 
 #pragma unroll
                     for (int v = 0; v < 16; ++v) mx = fmaxf(mx, s[qb][kt][v]);
                 const float m_new = fmaxf(m_use[qb], xhalf_max(mx));
-                // m_new is finite: key 0 is visible to every query and lives in tile 0, the first
-                // tile every wave processes.  There m_use = -inf and alpha = exp2(-inf) = 0.
+                // m_new is finite if the scores are: every tile a wave processes holds a key that is visible to
+                // all its queries (tile 0: key 0; key split: key tile * 32, no later than the rows).
+                // In a wave's first tile m_use = -inf and alpha = exp2(-inf) = 0.
                 const float alpha = __builtin_amdgcn_exp2f((m_use[qb] - m_new) * p.scale_l2);
+                if constexpr (KEYSPLIT) {
+                    const bool drop = no_weight(alpha, l_run[qb], m_use[qb], p.scale_l2);
+                    if (__builtin_amdgcn_ballot_w64(drop) != 0) {
+                        l_run[qb] = drop ? 0.f : l_run[qb];
+#pragma unroll
+                        for (int dt = 0; dt < DT; ++dt)
+#pragma unroll
+                            for (int v = 0; v < 16; ++v) o[qb][dt][v] = drop ? 0.f : o[qb][dt][v];
+                    }
+                }
                 m_use[qb] = m_new;
                 l_run[qb] *= alpha;
 #pragma unroll
@@ -929,13 +949,33 @@ __global__ __launch_bounds__(KN::NW * 64, KN::WAVES) void attn_fwd_kernel(const 
                 f32x4 x[D / 64];
 #pragma unroll
                 for (int q = 0; q < D / 64; ++q) x[q] = f32x4{0.f, 0.f, 0.f, 0.f};
+                auto part = [&](int w, int q) __attribute__((always_inline)) -> f32x4 {
+                    return *reinterpret_cast<const f32x4*>(smem_b + w * 2 * TILE_BYTES + row * (D * 4) + (((j * (D / 64) + q) ^ (row & (CPF - 1))) * 16));
+                };
 #pragma unroll
-                for (int w = 0; w < NW; ++w) {  // (a wave without tiles: m = -inf, weight 0; wave 0 has tile 0, so m is not)
+                for (int w = 0; w < NW; ++w) {  // (a wave without tiles: m = -inf, weight 0; wave 0 has tile 0)
                     f[w] = __builtin_amdgcn_exp2f((stat[w * 64] - m) * p.scale_l2);
                     l += f[w] * stat[w * 64 + 32];
 #pragma unroll
-                    for (int q = 0; q < D / 64; ++q)
-                        x[q] += f[w] * *reinterpret_cast<const f32x4*>(smem_b + w * 2 * TILE_BYTES + row * (D * 4) + (((j * (D / 64) + q) ^ (row & (CPF - 1))) * 16));
+                    for (int q = 0; q < D / 64; ++q) x[q] += f[w] * part(w, q);
+                }
+                bool odd = l != l;
+#pragma unroll
+                for (int q = 0; q < D / 64; ++q)
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) odd = odd || x[q][i] != x[q][i];
+                if (__builtin_amdgcn_ballot_w64(odd) != 0) {  // rare: once more, without the sums that weigh nothing
+                    l = 0.f;
+#pragma unroll
+                    for (int q = 0; q < D / 64; ++q) x[q] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll 1
+                    for (int w = 0; w < NW; ++w) {
+                        const float mw = stat[w * 64], lw = stat[w * 64 + 32], fw = __builtin_amdgcn_exp2f((mw - m) * p.scale_l2);
+                        if (no_weight(fw, lw, mw, p.scale_l2)) continue;
+                        l += fw * lw;
+#pragma unroll
+                        for (int q = 0; q < D / 64; ++q) x[q] += fw * part(w, q);
+                    }
                 }
                 const float inv = 1.0f / l;
                 if (q0 + row < N) {

@@ -53,6 +53,40 @@ def test_split_against_the_oracle(d, dtype, causal):
 
 
 @pytest.mark.gpu
+@pytest.mark.parametrize("causal", [False, True], ids=["full", "causal"])
+@pytest.mark.parametrize("dtype", [I.F16, I.BF16], ids=["f16", "bf16"])
+@pytest.mark.parametrize("d", [64, 128])
+def test_keys_masked_by_their_scores(d, dtype, causal):
+    """Scores of -inf (or of the lowest finite number, with a scale that takes it past the range of fp32, or so low
+    that its scaled value is rounded by more than that range) in all keys a wave meets first, or in all it ever
+    meets: no weight, whatever the wave."""
+    from gpu_util import check, run_gpu
+    lowest = float(np.float32(-65504.0)) if dtype == I.F16 else float(np.array(0xFF7F0000, np.uint32).view(np.float32))
+    for v in SPLIT:
+        nw = int(DESC[v]["nw"])
+        N = 32 * 2 * nw + 5
+        tile = np.arange(N) // 32
+        masks = [(f"wave {w} never", tile % nw == w) for w in range(nw)] + [(f"wave {w} late", tile == w) for w in range(nw)]
+        masks += [("all but tile 0", tile > 0), ("all but the last wave", tile % nw != nw - 1)]
+        w = I.Workload("masked", 1, 2, N, d, causal, dtype)
+        qb, kb, vb = I.make_qkv(w, seed=5)
+        one = I.f32_to_bits(np.ones(1, np.float32), dtype)[0]
+        for value, scale in [(-np.inf, w.scale), (lowest, 0.9)] + [(-1e30, w.scale)] * (dtype == I.BF16):
+            low = I.f32_to_bits(np.array([value], np.float32), dtype)[0]
+            for name, m in masks:
+                q, k = qb.copy(), kb.copy()
+                q[..., 0] = one
+                k[:, :, m, 0] = low
+                seen = np.cumsum(~m) > 0 if causal else np.ones(N, bool)      # rows that see an unmasked key
+                print(f"case {name} value={value} N={N} d={d} causal={causal} dtype={dtype} variant={v}", flush=True)
+                O_ref, l_ref, _ = ref.attn_ref(q, k, vb, causal, float(np.float32(scale)), dtype)
+                O, l = run_gpu(q, k, vb, causal, scale, dtype, variant=v)
+                check(O[:, :, seen], l[:, :, seen], O_ref[:, :, seen], l_ref[:, :, seen], dtype, what=f"{name} {value} variant {v}")
+                if value == -np.inf:                              # no weight at all: 0 / 0, as every variant gives it
+                    assert np.isnan(O[:, :, ~seen]).all() and not np.isfinite(l[:, :, ~seen]).any(), name
+
+
+@pytest.mark.gpu
 @pytest.mark.parametrize("d", [64, 128])
 def test_memory_behind_the_last_row_is_never_used(d):
     """Rows past the end and tiles past the last one arrive as zeros (the range check of the buffer loads): NaN
