@@ -11,7 +11,9 @@ extern "C" {
  * split K and write fp32 parts, which a second kernel on the same stream adds in a fixed order.
  * gemm_lrelu_workspace names the bytes a shape asks for (0: none, at most 4 MB).  workspace: device memory
  * aligned to 16 bytes that meets none of A, B, C, with any contents, not used by anybody else until the
- * call's two kernels have run; null or fewer bytes than asked for make it the plain call. */
+ * call's two kernels have run (a pool that goes by the stream's handle does not see to that where a handle
+ * is several queues, as the per-thread stream's, or is destroyed while its work runs); null or fewer
+ * bytes than asked for make it the plain call. */
 long long gemm_lrelu_workspace(int M, int N, int K);
 int gemm_lrelu_in(const void* a, const void* b, void* c, int M, int N, int K, float slope, int dtype, void* stream,
                   void* workspace, long long workspace_bytes);

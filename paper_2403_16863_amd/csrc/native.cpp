@@ -29,13 +29,17 @@ WorkspaceFn g_workspace = nullptr;
 CapturingFn g_capturing = nullptr;
 
 // Scratch memory of one call, from torch's caching allocator: it belongs to the stream the call runs on, so it
-// may go back as soon as the kernels are enqueued (the next owner on that stream comes after them).  None
-// while the stream is captured, on a device that is not the current one, or when there is no memory left;
-// the call then does without.
+// may go back as soon as the kernels are enqueued (the next owner on that stream comes after them).  That holds
+// where a handle is one queue and outlives its work: torch's current stream, but not a handle that only the
+// caller knows, nor the per-thread stream, one handle for a queue of every thread.  No memory either
+// while the stream is captured, on a device that is not the current one, or when there is none left; the
+// call then does without.
 class Workspace {
   public:
     Workspace(long long bytes, void* stream, int device) : bytes_(bytes) {
-        if (bytes <= 0 || c10::hip::current_device() != device || g_capturing(stream)) return;
+        if (bytes <= 0 || stream != (void*)c10::hip::getCurrentHIPStream(device).stream() || stream == (void*)hipStreamPerThread ||
+            c10::hip::current_device() != device || g_capturing(stream))
+            return;
         try {
             p_ = c10::hip::HIPCachingAllocator::raw_alloc_with_stream((size_t)bytes, (hipStream_t)stream);
         } catch (const std::exception&) {

@@ -93,7 +93,9 @@ def _marshal(a, b, c, stream):
 
 def gemm_lrelu(a, b, c, slope: float, stream=None) -> None:
     """c <- leaky_relu(a @ b) for device tensors a [M,K], b [K,N], c [M,N]; asynchronous on `stream`
-    (an integer hipStream_t; default: torch's current stream)."""
+    (an integer hipStream_t; default: torch's current stream).  On the current stream, few tiles of c and a long
+    K take up to 4 MB of scratch memory from torch's allocator for the call (gemm_workspace.h); other streams,
+    the per-thread stream and recordings do without."""
     rc = (binding._native or binding.native()).gemm_lrelu(a, b, c, slope, stream)
     if rc == GEMM_OK:
         return

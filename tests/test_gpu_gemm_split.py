@@ -100,3 +100,36 @@ def test_calls_on_several_streams_keep_their_parts_apart():
     torch.cuda.synchronize()
     for a, b, want, got, _ in work:
         assert torch.equal(want.view(torch.int16), got.view(torch.int16))
+
+
+def _case():
+    import torch
+    M, N, K = 33, 40, 5000
+    g = torch.Generator(device="cuda")
+    g.manual_seed(2)
+    a, b = (torch.randn(s, device="cuda", generator=g).half() for s in ((M, K), (K, N)))
+    plain, split, out = (torch.empty(M, N, device="cuda", dtype=torch.float16) for _ in range(3))
+    L = gemm.lib()
+    assert L.gemm_lrelu(a.data_ptr(), b.data_ptr(), plain.data_ptr(), M, N, K, 0.1, 0, torch.cuda.current_stream().cuda_stream) == 0
+    gemm.gemm_lrelu(a, b, split, 0.1)
+    torch.cuda.synchronize()
+    assert not torch.equal(plain, split)               # (other sums: the two can be told apart)
+    return a, b, out, plain, split
+
+
+@pytest.mark.gpu
+def test_scratch_memory_only_on_torchs_current_stream():
+    """A handle of the caller's own may name another queue than the allocator thinks (2, the per-thread stream, a
+    different one in every thread) or be destroyed while its work runs: such calls do without."""
+    import torch
+    a, b, out, plain, split = _case()
+    pool, ext = torch.cuda.Stream(), torch.cuda.ExternalStream(2)
+    for stream, current, want in ((None, None, split), (torch.cuda.current_stream().cuda_stream, None, split), (pool.cuda_stream, pool, split),
+                                  (None, pool, split), (pool.cuda_stream, None, plain), (2, None, plain), (1, None, plain), (None, ext, plain),
+                                  (2, ext, plain)):
+        out.fill_(float("nan"))
+        torch.cuda.synchronize()
+        with torch.cuda.stream(current):
+            gemm.gemm_lrelu(a, b, out, 0.1, stream=stream)
+        torch.cuda.synchronize()
+        assert torch.equal(out.view(torch.int16), want.view(torch.int16)), (stream, current)
