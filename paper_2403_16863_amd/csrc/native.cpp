@@ -12,6 +12,7 @@
 
 #include <ATen/core/Tensor.h>
 #include <c10/hip/HIPCachingAllocator.h>
+#include <c10/hip/HIPGraphsC10Utils.h>
 #include <c10/hip/HIPStream.h>
 #include <torch/csrc/autograd/python_variable.h>
 
@@ -41,12 +42,18 @@ class Workspace {
             c10::hip::current_device() != device || g_capturing(stream))
             return;
         try {
+            // A recording in another thread (in the default mode) forbids this thread the allocator's calls to the
+            // device, and one such call would end it; they have nothing to do with it.
+            const c10::hip::HIPStreamCaptureModeGuard beside(hipStreamCaptureModeRelaxed);
             p_ = c10::hip::HIPCachingAllocator::raw_alloc_with_stream((size_t)bytes, (hipStream_t)stream);
         } catch (const std::exception&) {
         }
     }
     ~Workspace() {
-        if (p_) c10::hip::HIPCachingAllocator::raw_delete(p_);
+        try {
+            if (p_) c10::hip::HIPCachingAllocator::raw_delete(p_);
+        } catch (const std::exception&) {
+        }
     }
     Workspace(const Workspace&) = delete;
     Workspace& operator=(const Workspace&) = delete;

@@ -133,3 +133,41 @@ def test_scratch_memory_only_on_torchs_current_stream():
             gemm.gemm_lrelu(a, b, out, 0.1, stream=stream)
         torch.cuda.synchronize()
         assert torch.equal(out.view(torch.int16), want.view(torch.int16)), (stream, current)
+
+
+@pytest.mark.gpu
+def test_a_call_beside_a_recording_in_another_thread():
+    """A recording in torch's default mode refuses allocations of every thread; the call's scratch memory must not
+    end it, nor come from the recording's pool."""
+    import threading
+    import torch
+    a, b, out, plain, split = _case()
+    own, side = torch.cuda.Stream(), torch.cuda.Stream()
+    x, y = torch.arange(8.0, device="cuda"), torch.zeros(8, device="cuda")
+    errors = []
+
+    def call():
+        try:
+            with torch.cuda.stream(own):
+                gemm.gemm_lrelu(a, b, out, 0.1)
+        except Exception as e:
+            errors.append(e)
+
+    graph = torch.cuda.CUDAGraph()
+    torch.cuda.synchronize()
+    torch.cuda.empty_cache()
+    with torch.cuda.graph(graph, stream=side):
+        torch.add(x, 1, out=y)
+        t = threading.Thread(target=call)
+        t.start()
+        t.join()
+        y.mul_(2)
+    assert not errors
+    torch.cuda.synchronize()
+    assert torch.equal(out, split) or torch.equal(out, plain)
+    for _ in range(3):
+        y.zero_()
+        graph.replay()
+        gemm.gemm_lrelu(a, b, out, 0.1)
+        torch.cuda.synchronize()
+        assert torch.equal(y, 2 * (x + 1)) and torch.equal(out, split)
