@@ -63,7 +63,9 @@ enum {
  *            scaled scores over the visible keys.  Every element is written.
  *  B,H,N   : >= 1, any N (ragged last tiles are masked).  Limits, reported as
  *            ATTN_EUNSUPPORTED: B*H*N*d <= 2^40 elements, and B*H*ceil(N/bm) <= 2^31-1
- *            work items (bm = the variant's query tile, 32, 128 or 256 rows).
+ *            work items (bm = the variant's query tile, 32, 128 or 256 rows); with the key split,
+ *            which attn_fwd itself takes for a few hundred items only, fewer than 2^32 threads and
+ *            N*d*2 <= 2^31-1 bytes.
  *  d       : 64 or 128.
  *  causal  : 0 = every key visible, otherwise key j is visible to query i iff j <= i.
  *  scale   : finite; multiplies q.k before the softmax (callers pass 1/sqrt(d)).

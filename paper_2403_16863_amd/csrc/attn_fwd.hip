@@ -92,6 +92,9 @@ long long grid_size(int cus, const Variant& var, int BH, long long nqt) {
     return total < resident ? total : resident;
 }
 
+// A launch counts its threads in 32 bits (the key split's grids, one workgroup per item, are the only ones that can get there).
+bool launchable(long long grid, const Variant& var) { return grid * var.nw * 64 <= 0xffffffffLL; }
+
 bool aligned(const void* p, size_t a) { return ((uintptr_t)p & (a - 1)) == 0; }
 
 bool overlaps(const void* a, size_t na, const void* b, size_t nb) {
@@ -159,6 +162,7 @@ int launch(const void* q, const void* k, const void* v, void* out, float* lse, i
     p.scale = scale > 0.f ? scale : (scale < 0.f ? -scale : 1.0f);
     p.scale_l2 = p.scale * 1.44269504088896340736f;
     const long long grid = grid_size(cu_count(), var, p.BH, nqt);
+    if (!launchable(grid, var)) return ATTN_EUNSUPPORTED;
     // The launch's own return code is used (not hipGetLastError, which can report a
     // stale, unrelated status left behind by another library's earlier call).
     void* args[] = {&p};
@@ -480,7 +484,7 @@ int attn_schedule_grid(int variant_id, int compute_units, int B, int H, int N) {
     const Variant& var = kVariants[variant_id];
     const int bm = var.bm();
     const long long nqt = ((long long)N + bm - 1) / bm, g = grid_size(compute_units, var, B * H, nqt);
-    if ((long long)B * H > 0x7fffffffLL / nqt || g > 0x7fffffffLL) return ATTN_EUNSUPPORTED;
+    if ((long long)B * H > 0x7fffffffLL / nqt || !launchable(g, var)) return ATTN_EUNSUPPORTED;
     return (int)g;
 }
 

@@ -78,6 +78,23 @@ def test_rounds_by_weight_go_from_heavy_to_light():
     assert min(seq[0][1] for seq in sched.values()) >= max(seq[1][1] for seq in sched.values() if len(seq) > 1)
 
 
+def test_grids_beyond_the_thread_count_of_a_launch_are_refused():
+    """One workgroup per item: 2^32 threads are reached with 2^23 items of eight waves, 2^24 of four.  (Fake
+    pointers: the check comes before the launch.)"""
+    from paper_2403_16863_amd import binding
+    L = binding.lib()
+    split = [v for v in range(A.attn_num_variants()) if "pipe=0" in A.attn_variant_desc(v) and "ldpos=1" in A.attn_variant_desc(v)]
+    assert len(split) == 2
+    for v in split:
+        most = (2 ** 32 - 1) // (64 * int(A.attn_variant_desc(v).split("nw=")[1].split()[0]))
+        assert A.attn_schedule_grid(v, 256, 1, most, 1) == most
+        with pytest.raises(A.AttnError) as e:
+            A.attn_schedule_grid(v, 256, 1, most + 1, 1)
+        assert e.value.code == A.binding.ATTN_EUNSUPPORTED
+        q, k, v_, o, lse = (n << 40 for n in range(1, 6))
+        assert L.attn_fwd_variant(q, k, v_, o, lse, 1, most + 1, 1, 64, 0, 1.0, 0, None, v) == A.binding.ATTN_EUNSUPPORTED
+
+
 def test_grid_size():
     v = A.attn_default_variant(4096, 128, A.ATTN_BF16, True)
     assert A.attn_schedule_grid(v, 256, 2, 32, 4096) == 256           # one persistent workgroup per CU
