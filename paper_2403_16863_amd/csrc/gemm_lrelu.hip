@@ -43,11 +43,14 @@ static const Variant kVariants[] = {
 constexpr int kNumVariants = sizeof(kVariants) / sizeof(kVariants[0]);
 constexpr int kDefault = 1;  // where the schedule search starts
 
+// Tiles of `size` that cover n >= 1 (n may be the largest int).
+static int cover(int n, int size) { return 1 + (n - 1) / size; }
+
 static int check_args(const void* a, const void* b, const void* c, int M, int N, int K, int dtype, int variant_id) {
     if (!a || !b || !c) return GEMM_EINVAL;
     if (((uintptr_t)a | (uintptr_t)b | (uintptr_t)c) & 15) return GEMM_EINVAL;
     if (M < 1 || N < 8 || K < 8 || (N & 7) || (K & 7) || N >= (1 << 24) || K >= (1 << 24)) return GEMM_EINVAL;
-    if ((long long)((M + 31) / 32) * ((N + 31) / 32) > 0x7fffffffLL) return GEMM_EINVAL;
+    if ((long long)cover(M, 32) * cover(N, 32) > 0x7fffffffLL) return GEMM_EINVAL;
     if (dtype != GEMM_F16 && dtype != GEMM_BF16) return GEMM_EINVAL;
     // C is written while other workgroups still read A and B: it must not overlap them
     const uintptr_t c0 = (uintptr_t)c, c1 = c0 + (size_t)M * N * 2;
@@ -91,7 +94,7 @@ static const BlockShape& choose_block(int M, int N, int K) {
     float best_us = 0.f;
     for (const BlockShape& s : kBlocks) {
         if ((long long)(s.bm - 1) * K * 2 + s.bk * 2 >= (long long)kBufferSize) continue;  // 32-bit offsets in a tile's rows
-        const long long tiles = (long long)((M + s.bm - 1) / s.bm) * ((N + s.bn - 1) / s.bn);
+        const long long tiles = (long long)cover(M, s.bm) * cover(N, s.bn);
         const long long n = (tiles + kComputeUnits - 1) / kComputeUnits, stages = (K + s.bk * s.wk - 1) / (s.bk * s.wk);
         const float alone = (float)((n + s.occ - 1) / s.occ) * s.alone, full = (float)n * s.full;
         const float us = (float)stages * (alone > full ? alone : full) + (float)n * s.ends;
@@ -122,7 +125,7 @@ struct Split {
     int shape, ranges, kc;  // ranges of kc values of k; 0: not split
 };
 static Split choose_split(int M, int N, int K) {
-    auto tiles = [&](int s) { return (long long)((M + kBlocks[s].bm - 1) / kBlocks[s].bm) * ((N + kBlocks[s].bn - 1) / kBlocks[s].bn); };
+    auto tiles = [&](int s) { return (long long)cover(M, kBlocks[s].bm) * cover(N, kBlocks[s].bn); };
     const int s = tiles(0) <= 64 ? 0 : M <= 32 ? 1 : 2;
     const long long n = tiles(s);
     if (K < (s == 0 ? 4864 : M <= 64 ? 4000 : 4608) || n > (s == 1 ? 96 : 128) || K > (1 << 16)) return {s, 0, K};
@@ -141,7 +144,7 @@ static int launch_split(const Split& sp, const void* a, const void* b, void* c, 
     p.b = (const char*)b;
     p.c = (uint16_t*)c;
     p.M = M, p.N = N, p.K = K;
-    p.ntm = (M + s.bm - 1) / s.bm, p.ntn = (N + s.bn - 1) / s.bn;
+    p.ntm = cover(M, s.bm), p.ntn = cover(N, s.bn);
     p.slope = slope;
     p.parts = (float*)workspace;
     p.kc = sp.kc;
@@ -168,7 +171,7 @@ static int launch_block(const void* a, const void* b, void* c, int M, int N, int
     p.b = (const char*)b;
     p.c = (uint16_t*)c;
     p.M = M, p.N = N, p.K = K;
-    p.ntm = (M + s.bm - 1) / s.bm, p.ntn = (N + s.bn - 1) / s.bn;
+    p.ntm = cover(M, s.bm), p.ntn = cover(N, s.bn);
     p.slope = slope;
     void* args[] = {&p};
     if (hipLaunchKernel((const void*)s.fn[dtype], dim3(p.ntm * p.ntn), dim3(s.threads), args, 0, (hipStream_t)stream) != hipSuccess) {
@@ -187,7 +190,7 @@ static int launch(const void* a, const void* b, void* c, int M, int N, int K, fl
     p.b = (const char*)b;
     p.c = (uint16_t*)c;
     p.M = M, p.N = N, p.K = K;
-    p.ntm = (M + 31) / 32, p.ntn = (N + 31) / 32;
+    p.ntm = cover(M, 32), p.ntn = cover(N, 32);
     p.slope = slope;
     const Variant& v = kVariants[variant_id];
     void* args[] = {&p};

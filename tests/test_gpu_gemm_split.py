@@ -21,6 +21,13 @@ def test_few_tiles_and_a_long_k_ask_for_scratch_memory():
         assert L.gemm_lrelu_workspace(M, N, K) == 0, (M, N, K)
 
 
+def test_sizes_near_the_largest_int_ask_for_none():
+    """The number of tiles must not overflow (a negative one ended the process with a division by zero)."""
+    L = gemm.lib()
+    for M, N, K in ((2 ** 31 - 1, 8, 8192), (2 ** 31 - 20, 4096, 8192), (64, 2 ** 31 - 1, 8192), (2 ** 31 - 1,) * 3):
+        assert L.gemm_lrelu_workspace(M, N, K) == 0, (M, N, K)
+
+
 def test_bad_scratch_memory_is_refused_before_any_launch():
     """(fake pointers: nothing is dereferenced)"""
     L = gemm.lib()
