@@ -350,7 +350,11 @@ def main():
     def run_workload(idx, variant=None, sample_device=False):
         w = I.WORKLOADS[idx]
         bits, tensors = device_tensors(w, seed=idx)
-        var = variant if variant is not None else A.attn_deployed(w.N, w.d, w.dtype, w.causal)[1]
+        matched, var, _ = A.attn_deployed(w.N, w.d, w.dtype, w.causal)
+        if variant is not None:
+            var = variant
+        elif not matched:
+            var = A.attn_choose_variant(w.B, w.H, w.N, w.d, w.dtype, w.causal)
         settled = (0, 0.0) if args.no_settle else settle(A, w, tensors, var)
         t = time_steps(A, w, tensors, var, args.warmup, args.steps, sample_device=sample_device)
         return w, bits, tensors, var, settled, t

@@ -52,8 +52,8 @@ enum {
     ATTN_ELAUNCH = -3       /* the HIP runtime refused the launch */
 };
 
-/* Fused attention forward with the library's default schedule variant for the
- * shape (attn_default_variant).
+/* Fused attention forward with the schedule variant the library chooses for the
+ * shape (attn_choose_variant), or the deployed one (attn_deploy_*).
  *
  *  q, k, v : device, [B,H,N,d] contiguous row-major, 16-bit elements of `dtype`,
  *            16-byte aligned.  Read only.
@@ -146,12 +146,17 @@ int attn_variant_from_coords(const int* coords);
 int attn_schedule_grid(int variant_id, int compute_units, int B, int H, int N);
 int attn_schedule_item(int grid, int workgroup, int BH, int nqt, int round, int* bh, int* qt);
 
-/* The variant attn_fwd uses for this shape: the best admitted variant of the stored searches
- * on MI355X (Sec. 4.1: candidates are ranked offline and the best one is deployed, at no
- * run-time cost).  attn_fwd also counts the heads: launches of few query tiles take variants with
- * smaller tiles, the fewest those that split the keys between the waves of a workgroup.  What is
- * named here is the choice for many heads, and below 1024 keys the one for eight.  dtype is accepted so that a later ranking
- * may use it, and is ignored today. */
+/* The variant attn_fwd launches for this problem where nothing is deployed: the best admitted
+ * variant of the stored searches on MI355X (Sec. 4.1: candidates are ranked offline and the best
+ * one is deployed, at no run-time cost) where there are query tiles enough, variants with smaller
+ * tiles for fewer, and for the fewest those that split the keys between the waves of a workgroup.
+ * dtype is accepted so that a later ranking may use it, and only checked today.  ATTN_EINVAL and
+ * ATTN_EUNSUPPORTED for what attn_fwd would refuse. */
+int attn_choose_variant(int B, int H, int N, int d, int dtype, int causal);
+
+/* A variant for a caller that does not know the number of heads: attn_choose_variant's for eight
+ * heads below 1024 keys, the searches' best from there on (d = 64: up to 2047 keys the one for
+ * fewer).  What attn_fwd launches depends on the heads: attn_choose_variant. */
 int attn_default_variant(int N, int d, int dtype, int causal);
 
 /* Feedback measurement of Sec. 3.3: `warmup` untimed launches, then `iters`
@@ -187,15 +192,16 @@ int attn_time_codeobj(int handle, const void* q, const void* k, const void* v, v
 /* Deployment of a searched schedule (Sec. 4.1: the candidates of the offline searches are
  * ranked, and the best one that passed the tests is what the application runs, chosen once,
  * at no cost per call).  After attn_deploy_variant, attn_fwd launches `variant_id` for every
- * problem with this d, dtype and causal flag (0 / non-zero) and n_min <= N <= n_max, instead
- * of attn_default_variant's choice; attn_deploy_codeobj does the same for a loaded code object
+ * problem with this d, dtype and causal flag (0 / non-zero) and n_min <= N <= n_max, whatever
+ * its heads, instead of attn_choose_variant's; attn_deploy_codeobj does the same for a loaded code object
  * (the instruction-level search's winner), for the d, dtype and causal flag it was loaded for.
  * The newest matching entry wins.  A deployed schedule that refuses a problem
  * (ATTN_EUNSUPPORTED, e.g. the interleaved order beyond 4 GiB per head) is replaced by the
- * library default for that call.  attn_deployed reports what attn_fwd would launch for a
- * shape: returns 1 and writes *variant_id (the schedule, or the schedule the code object was
- * derived from) and *handle (the code object, -1 if none) when an entry matches, 0 when the
- * default applies (*variant_id = the default, *handle = -1); either pointer may be NULL.
+ * library's choice for that call.  attn_deployed reports what is deployed for a shape class:
+ * returns 1 and writes *variant_id (the schedule, or the schedule the code object was
+ * derived from) and *handle (the code object, -1 if none) when an entry matches, 0 when none does
+ * and attn_fwd launches attn_choose_variant's (*variant_id = attn_default_variant's, which is for
+ * no particular number of heads, *handle = -1); either pointer may be NULL.
  * attn_deploy_clear removes every entry; attn_codeobj_unload removes the entries of its handle.
  * Up to 16 entries (ATTN_EUNSUPPORTED beyond, or if the variant was not built for the
  * shape); ATTN_EINVAL for bad ids, handles or an empty range.  Host logic only: no device

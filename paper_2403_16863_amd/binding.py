@@ -18,7 +18,7 @@ ATTN_OK, ATTN_EINVAL, ATTN_EUNSUPPORTED, ATTN_ELAUNCH = 0, -1, -2, -3
 # every symbol include/attn.h declares
 SYMBOLS = ("attn_fwd", "attn_fwd_variant", "attn_num_variants", "attn_variant_supported",
            "attn_variant_desc", "attn_num_knobs", "attn_knob_name", "attn_knob_size",
-           "attn_variant_coords", "attn_variant_from_coords", "attn_default_variant",
+           "attn_variant_coords", "attn_variant_from_coords", "attn_choose_variant", "attn_default_variant",
            "attn_time_variant", "attn_strerror", "attn_schedule_grid", "attn_schedule_item", "attn_mfma_ceiling",
            "attn_valu_ceiling", "attn_mix_ceiling",
            "attn_codeobj_load", "attn_codeobj_unload", "attn_fwd_codeobj", "attn_time_codeobj",
@@ -68,6 +68,8 @@ def lib():
         L.attn_variant_coords.argtypes = [i, ctypes.POINTER(i)]
         L.attn_variant_from_coords.restype = i
         L.attn_variant_from_coords.argtypes = [ctypes.POINTER(i)]
+        L.attn_choose_variant.restype = i
+        L.attn_choose_variant.argtypes = [i, i, i, i, i, i]
         L.attn_default_variant.restype = i
         L.attn_default_variant.argtypes = [i, i, i, i]
         L.attn_schedule_grid.restype = i
@@ -231,8 +233,9 @@ def attn_deploy_clear() -> None:
 
 
 def attn_deployed(N: int, d: int, dtype: int, causal: bool):
-    """(matched, variant_id, handle): what attn_fwd launches for this shape; handle is -1
-    unless a deployed code object matches, matched is False when the library default applies."""
+    """(matched, variant_id, handle): what is deployed for this shape class; handle is -1 unless a
+    deployed code object matches.  matched is False when nothing is deployed: attn_fwd then launches
+    attn_choose_variant's, and variant_id is attn_default_variant's."""
     v, h = ctypes.c_int(-1), ctypes.c_int(-1)
     rc = lib().attn_deployed(int(N), int(d), int(dtype), int(bool(causal)), ctypes.byref(v), ctypes.byref(h))
     if rc < 0:
@@ -367,6 +370,14 @@ def attn_valu_ceiling(waves_per_simd: int, iters: int = 200000):
     if rc != 0:
         raise AttnError(rc, "attn_valu_ceiling")
     return eps.value, ghz.value
+
+
+def attn_choose_variant(B: int, H: int, N: int, d: int, dtype: int, causal: bool) -> int:
+    """The variant attn_fwd launches for this problem where nothing is deployed."""
+    rc = lib().attn_choose_variant(int(B), int(H), int(N), int(d), int(dtype), int(bool(causal)))
+    if rc < 0:
+        raise AttnError(rc, "attn_choose_variant")
+    return rc
 
 
 def attn_default_variant(N: int, d: int, dtype: int, causal: bool) -> int:

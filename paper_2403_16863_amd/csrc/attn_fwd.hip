@@ -570,6 +570,12 @@ static int choose_variant(long long heads, int N, int d, int causal) {
     return j > (causal ? 895 : 512) ? kDefaultD64Long : kDefaultD64Short;
 }
 
+int attn_choose_variant(int B, int H, int N, int d, int dtype, int causal) {
+    if (B < 1 || H < 1 || N < 1 || (dtype != ATTN_F16 && dtype != ATTN_BF16)) return ATTN_EINVAL;
+    if (d != 64 && d != 128) return ATTN_EUNSUPPORTED;
+    return choose_variant((long long)B * H, N, d, causal);
+}
+
 int attn_default_variant(int N, int d, int dtype, int causal) {
     (void)dtype;
     if (N < 1024) return choose_variant(8, N, d, causal);

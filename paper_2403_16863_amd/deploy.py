@@ -47,13 +47,15 @@ def default_range(N: int):
 def deploy_ranking(path: str, n_min: Optional[int] = None, n_max: Optional[int] = None,
                    min_gain: float = 1.02) -> Optional[dict]:
     """Deploys the best variant of one stored ranking; returns what was deployed, or None when
-    the ranking's best is the library default or its gain is inside the noise."""
+    the ranking's best is what attn_fwd launches for its shape anyway, when its gain is inside the
+    noise, or when it was measured against another variant than that."""
     with open(path) as fh:
         summary = json.load(fh)
     shape = shape_of_ranking(summary)
     best, gain = int(summary["best_variant"]), float(summary["best_vs_default"])
-    default = B.attn_default_variant(shape["N"], shape["d"], shape["dtype"], shape["causal"])
-    if best == default or gain < min_gain:
+    cls = (shape["N"], shape["d"], shape["dtype"], shape["causal"])
+    default = B.attn_choose_variant(shape["B"], shape["H"], *cls) if "B" in shape and "H" in shape else B.attn_default_variant(*cls)
+    if best == default or gain < min_gain or summary.get("default_variant", default) != default:
         return None
     lo, hi = default_range(shape["N"])
     lo, hi = (lo if n_min is None else n_min), (hi if n_max is None else n_max)

@@ -241,7 +241,7 @@ def attn_space(widx: int):
     out = torch.empty_like(q)
     lse = torch.empty(q.shape[:3], dtype=torch.float32, device="cuda")
     names = tuple(Bd.attn_knob_name(i) for i in range(Bd.attn_num_knobs()))
-    start = tuple(Bd.attn_variant_coords(Bd.attn_default_variant(w.N, w.d, w.dtype, w.causal)))
+    start = tuple(Bd.attn_variant_coords(Bd.attn_choose_variant(w.B, w.H, w.N, w.d, w.dtype, w.causal)))
     return (w.label, names, sorted(lat.points), start,
             lambda c: S.measure_variant((q, k, v, out, lse), w.causal, w.scale, lat.points[c], iters=20),
             lambda c: S.admit_against_default(lat.points[c], w.d, w.dtype, w.causal, samples=7), "ms")

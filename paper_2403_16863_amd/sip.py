@@ -545,7 +545,7 @@ def search_workload(widx: int, seed: int = 0, t_max: float = 0.05, t_min: float 
     from . import inputs as I
     from .search import anneal_states
     w = I.WORKLOADS[widx]
-    variant = B.attn_default_variant(w.N, w.d, w.dtype, w.causal) if variant is None else variant
+    variant = B.attn_choose_variant(w.B, w.H, w.N, w.d, w.dtype, w.causal) if variant is None else variant
     workdir = tempfile.mkdtemp(prefix="sip_")
     run = None
     try:

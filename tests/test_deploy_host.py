@@ -89,6 +89,17 @@ def test_a_ranking_is_deployed_only_for_a_gain_beyond_the_noise(tmp_path):
     assert A.attn_deployed(4096, 128, A.ATTN_BF16, True) == (True, other, -1)
     assert A.attn_deployed(2049, 128, A.ATTN_BF16, True)[0] and not A.attn_deployed(2048, 128, A.ATTN_BF16, True)[0]
     assert not A.attn_deployed(8192, 128, A.ATTN_BF16, True)[0]
+    # a gain over another variant than the one attn_fwd launches for these heads says nothing
+    A.attn_deploy_clear()
+    few = {"B": 1, "H": 4, "N": 4096, "d": 128, "causal": True, "dtype": I.BF16}
+    p = _ranking(tmp_path, "e", label, other, 1.05, few)
+    body = json.loads(open(p).read())
+    assert A.attn_choose_variant(1, 4, 4096, 128, A.ATTN_BF16, True) != default
+    for measured, taken in ((default, False), (A.attn_choose_variant(1, 4, 4096, 128, A.ATTN_BF16, True), True)):
+        with open(p, "w") as fh:
+            json.dump({**body, "default_variant": measured}, fh)
+        assert (deploy.deploy_ranking(p) is not None) == taken
+    os.remove(p)
     # the explicit shape entry wins over the label, and a directory is walked in file-name order
     A.attn_deploy_clear()
     _ranking(tmp_path, "d", "no shape in this label", 3 if A.attn_default_variant(512, 64, A.ATTN_F16, False) != 3 else 0, 1.1,
