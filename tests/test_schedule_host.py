@@ -78,6 +78,44 @@ def test_rounds_by_weight_go_from_heavy_to_light():
     assert min(seq[0][1] for seq in sched.values()) >= max(seq[1][1] for seq in sched.values() if len(seq) > 1)
 
 
+@pytest.mark.parametrize("causal", [False, True], ids=["full", "causal"])
+@pytest.mark.parametrize("grid,BH,nqt", [
+    (300, 5, 60), (304, 8, 38), (512, 16, 32), (776, 9, 57), (776, 8, 96), (776, 3, 171), (769, 1, 769), (776, 8, 97), (1008, 16, 63),  # key split
+    (256, 32, 12), (256, 64, 16), (512, 64, 16), (512, 12, 50), (768, 128, 18), (768, 48, 20), (256, 3, 100), (255, 64, 16), (8, 8, 1),
+])
+def test_either_mask_names_every_item_once(grid, BH, nqt, causal):
+    """Grids of one workgroup per item (a second layer; 513 to 768 items padded to 776; more than three layers) and
+    persistent ones.  Without a mask the items of a head follow each other."""
+    import ctypes
+    L = A.binding.lib()
+    bh, qt, seen, rounds = ctypes.c_int(0), ctypes.c_int(0), [], 0
+    while True:
+        this = []
+        for g in range(grid):
+            rc = L.attn_schedule_item_of(grid, g, BH, nqt, rounds, int(causal), ctypes.byref(bh), ctypes.byref(qt))
+            assert rc in (0, 1)
+            if rc:
+                this.append((bh.value, qt.value))
+                if causal:
+                    assert A.attn_schedule_item(grid, g, BH, nqt, rounds) == this[-1]
+        if not this:
+            break
+        if not causal:                                  # the items of a round are those of as few heads as hold them
+            by_xcd = grid % 8 == 0 and BH % 8 == 0
+            heads = {b for b, _ in this}
+            assert len(heads) <= (8 if by_xcd else 1) * (-(-len(this) // (nqt * (8 if by_xcd else 1))) + 1)
+        seen += this
+        rounds += 1
+    assert len(seen) == BH * nqt and set(seen) == {(b, q) for b in range(BH) for q in range(nqt)}
+    assert rounds == -(-BH * nqt // grid)
+
+
+def test_the_split_pads_its_grid_between_two_and_three_layers():
+    v = 37
+    for n, want in ((512, 512), (513, 776), (768, 776), (769, 769), (300, 300)):
+        assert A.attn_schedule_grid(v, 256, 1, 1, 32 * n) == want
+
+
 def test_grids_beyond_the_thread_count_of_a_launch_are_refused():
     """One workgroup per item: 2^32 threads are reached with 2^23 items of eight waves, 2^24 of four.  (Fake
     pointers: the check comes before the launch.)"""
