@@ -546,31 +546,44 @@ constexpr int kDefaultD64Long = 18;
 constexpr int kDefaultD64Short = 3;
 
 // The choice by the number of query tiles, measured on 256 units, us (heads x keys; g = tiles of 32 rows, the
-// key split's; j = tiles of 128 rows).
-// The key split (37: four waves, two workgroups per compute unit, 38: eight waves, one) against the defaults:
-//   d = 128          32 x 512 (g 512)  15.1 / 37: 11.3 / 38: 14.8     3 x 5000 (471)    88.8 / 64.1 / 66.8
-//   d = 128, causal  32 x 512 (512)    15.7 / 10.7 / 12.6             6 x 5753 (1080)   99.3 / 81.5 / 86.1
-//                    2 x 8000 (500)   133.1 / 76.7 / 55.9             32 x 1270 (1280)  29.5 / 28.6 / 37.3
-//   d = 64           24 x 512 (384)     8.8 /  7.1 /  9.2             4 x 5259 (660)    60.6 / 52.2 / 57.4
-//   d = 64, causal   8 x 4065 (1024)   46.1 / 32.9 / 36.8             48 x 905 (1392)   16.3 / 14.9 / -
-//                    6 x 1500 (282)    20.0 /  9.9 /  9.0             64 x 768 (1536)   14.1 / 14.5 / -
-//                    64 x 512 (1024)   10.1 / 10.9 / 15.5             48 x 661 (1008)   12.4 / 11.0 / -
-// The lines lie where the two sides meet: a masked tile is half as heavy on average while the default's time
-// is that of its heaviest; with few keys the split's start and its sum at the end count for more.  Eight
-// waves pay while each workgroup has a compute unit to itself (4 x 2048, d = 64: 10.7 against 12.8) and
-// where the heaviest one decides.
+// key split's; j = tiles of 128 rows).  Calls back to back, after 70 ms of the same: out of idle every one is up to
+// 20 % slower, the key split most.
+// The key split (37: four waves, two workgroups per compute unit, 38: eight waves, one) against the defaults; where two
+// figures stand they are of two cards, which differ by up to 15 % here and by 1 % for the others:
+//   d = 128          32 x 512 (g 512)  15.2 / 37: 11.0 / 38: 12.9     3 x 5000 (471)    87.4 / 60.5 / 66.0
+//   d = 128, causal  32 x 512 (512)    15.8 /  8.9 / 12.6             6 x 5753 (1080)  101.2 / 83.2
+//                    40 x 768 (960)    20.4 / 16.8, 18.2              48 x 768 (1152)   20.9 / 19.8, 22.1
+//                    36 x 1024 (1152)  25.7 / 23.6                    32 x 1150 (1152)  26.8 / 25.0, 27.0
+//                    64 x 350 (704)    13.8 / 12.0                    96 x 286 (864)    12.8 / 12.5
+//   d = 64           24 x 512 (384)     8.9 /  6.7 /  8.5             4 x 5259 (660)    59.7 / 51.0
+//                    40 x 554 (720)    10.2 / 10.3
+//   d = 64, causal   8 x 4065 (1024)   47.2 / 33.6 / 36.7             24 x 2048 (1536)  27.2 / 24.4, 26.0
+//                    64 x 512 (1024)   10.2 / 10.5                    64 x 600 (1216)   12.7 / 12.4
+//                    64 x 620 (1280)   12.7 / 11.5                    70 x 610 (1400)   13.4 / 15.5
+//                    72 x 640 (1440)   12.4 / 12.3, 13.8              60 x 768 (1440)   15.1 / 13.1
+//                    64 x 768 (1536)   13.9 / 13.4, 15.3              48 x 1024 (1536)  16.9 / 15.6, 17.6
+//                    48 x 905 (1392)   15.9 / 13.9, 15.7              40 x 1200 (1520)  18.6 / 17.0
+// The lines lie where the slower card's two sides meet: a masked tile is half as heavy on average while the
+// default's time is that of its heaviest; with few keys the split's start and its sum at the end count for more.
+// Eight waves pay while each workgroup has a compute unit to itself (4 x 2048, d = 64: 9.5 against 10.9), and
+// under a mask a little beyond, where the units' sums are uneven anyway (g; 37 / 38 at d = 64, at d = 128):
+//   2 x 6000 (376)  26.1 / 25.2, 40.4 / 40.8    2 x 6656 (416)   29.2 / 30.7, 45.4 / 49.4    2 x 8000 (500)  36.8 / 41.7, 57.4 / 67.3
+//   1 x 12000 (375) 47.9 / 38.1, 75.6 / 63.2    1 x 14000 (438)  57.5 / 51.9, 92.3 / 86.7    1 x 16000 (500) 68.6 / 66.2, 110.4 / 111.0
 // d = 128 between the split and full rounds of 256-row tiles, on 128-row tiles of the free-running order (1):
-//   12 x 1486 (j 144)  32.8 -> 29.3    64 x 329 (192)  14.7 -> 11.9    32 x 1011 (256)  25.8 -> 23.8
-//   96 x 751 (576)  47.6 -> 41.4 (a second round of few tiles either way); but 16 x 2649 (336)  61.3 -> 72.3
-//   causal  128 x 256 (256)  12.7 -> 11.0    8 x 6159 (392)  114.7 -> 108.2    32 x 1984 (512)  45.9 -> 43.9;  64 x 1196 (640)  34.6 -> 36.1
-// d = 64, three workgroups per unit (18) against two (3): 24 x 2809 (j 528) 73.9 / 81.4, 64 x 1706 (896) 60.7 / 63.3;
-//   causal  32 x 2581 (672) 59.7 / 39.9, 96 x 1397 (1056) 33.1 / 36.7.
+//   12 x 1486 (j 144)  32.8 -> 29.6    64 x 329 (192)  14.2 -> 11.7    32 x 1011 (256)  25.5 -> 23.4;  33 x 1000 (264)  27.1 -> 34.2
+//   a second round of few tiles either way: 10 x 7000 (550)  306 -> 298    96 x 751 (576)  47.5 -> 42.3    64 x 1250 (640)  68.7 -> 63.4
+//   causal  128 x 256 (256)  12.3 -> 10.6    32 x 1270 (320)  29.6 -> 27.5    8 x 6159 (392)  112.3 -> 107.9    32 x 1984 (512)  45.8 -> 44.9
+//           96 x 767 (576)  27.4 -> 26.6;  64 x 1196 (640)  35.2 -> 36.5
+// d = 64, three workgroups per unit (18) against two (3): 4 x 16384 (j 512)  281 / 281, 6 x 10900 (516)  257 / 286, 24 x 2809 (528)  70.4 / 77.5;
+//   causal  32 x 2581 (672)  39.8 / 39.5, 64 x 1706 (896)  34.3 / 35.9, 96 x 1397 (1056)  34.7 / 37.4.
 constexpr int kKeySplit4 = 37, kKeySplit8 = 38, kRows128 = 1;
 
 static int choose_variant(long long heads, int N, int d, int causal) {
     const long long g = heads * ((N + 31LL) / 32), j = heads * ((N + 127LL) / 128);
-    const int most = d == 128 ? (causal ? (N < 768 ? 736 : 1152) : 512) : causal ? (N < 600 ? 960 : 1536) : N < 640 ? 704 : 768;
-    if (g <= most) return N >= 512 && (g <= 256 || (causal && N >= 6000 && g <= 512)) ? kKeySplit8 : kKeySplit4;
+    const int most = d == 128 ? (!causal ? 512 : N < 768 ? 736 : N < 1024 ? 1056 : 1152)
+                              : !causal ? (N < 640 ? 704 : 768) : N < 600 ? 960 : N < 768 ? 1280 : N < 1200 ? 1440 : 1536;
+    const int alone = causal && N >= 6000 ? (N >= 12000 ? 512 : 384) : 256;  // the eight-wave form's line
+    if (g <= most) return N >= 512 && g <= alone ? kKeySplit8 : kKeySplit4;
     if (d == 128) return (causal ? j <= 576 : j <= 256 || (j > 512 && j <= 640)) ? kRows128 : kDefaultD128;
     return j > (causal ? 895 : 512) ? kDefaultD64Long : kDefaultD64Short;
 }

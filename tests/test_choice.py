@@ -13,11 +13,16 @@ SPLIT4, SPLIT8, ROWS128, D128, D64_LONG, D64_SHORT = 37, 38, 1, 36, 18, 3
 @pytest.mark.parametrize("heads,N,d,causal,want", [
     # key split: up to so many tiles of 32 rows
     (512, 32, 128, False, SPLIT4), (513, 32, 128, False, ROWS128),
-    (736, 32, 128, True, SPLIT4), (737, 32, 128, True, D128), (48, 768, 128, True, SPLIT4), (49, 768, 128, True, ROWS128),
+    (736, 32, 128, True, SPLIT4), (737, 32, 128, True, D128), (44, 768, 128, True, SPLIT4), (45, 768, 128, True, ROWS128),
+    (36, 1024, 128, True, SPLIT4), (37, 1024, 128, True, ROWS128),
     (704, 32, 64, False, SPLIT4), (705, 32, 64, False, D64_LONG), (38, 640, 64, False, SPLIT4), (39, 640, 64, False, D64_SHORT),
     (960, 32, 64, True, SPLIT4), (961, 32, 64, True, D64_LONG),
+    (64, 640, 64, True, SPLIT4), (65, 640, 64, True, D64_SHORT), (60, 768, 64, True, SPLIT4), (61, 768, 64, True, D64_SHORT),
+    (40, 1200, 64, True, SPLIT4), (41, 1200, 64, True, D64_SHORT),
     # eight waves while every workgroup has a unit to itself
     (16, 512, 64, False, SPLIT8), (17, 512, 64, False, SPLIT4), (16, 511, 128, True, SPLIT4), (16, 512, 128, True, SPLIT8),
+    (2, 6144, 128, True, SPLIT8), (2, 6145, 128, True, SPLIT4), (2, 5999, 64, True, SPLIT4), (1, 12288, 64, False, SPLIT4),
+    (1, 16384, 64, True, SPLIT8), (1, 16385, 128, True, SPLIT4), (1, 11999, 64, True, SPLIT8),
     # d = 128: 128-row tiles
     (256, 128, 128, False, ROWS128), (257, 128, 128, False, D128), (512, 128, 128, False, D128), (513, 128, 128, False, ROWS128),
     (640, 128, 128, False, ROWS128), (641, 128, 128, False, D128), (576, 128, 128, True, ROWS128), (577, 128, 128, True, D128),
