@@ -575,7 +575,8 @@ constexpr int kDefaultD64Short = 3;
 //   causal  128 x 256 (256)  12.3 -> 10.6    32 x 1270 (320)  29.6 -> 27.5    8 x 6159 (392)  112.3 -> 107.9    32 x 1984 (512)  45.8 -> 44.9
 //           96 x 767 (576)  27.4 -> 26.6;  64 x 1196 (640)  35.2 -> 36.5
 // d = 64, three workgroups per unit (18) against two (3): 4 x 16384 (j 512)  281 / 281, 6 x 10900 (516)  257 / 286, 24 x 2809 (528)  70.4 / 77.5;
-//   causal  32 x 2581 (672)  39.8 / 39.5, 64 x 1706 (896)  34.3 / 35.9, 96 x 1397 (1056)  34.7 / 37.4.
+//   causal  26 x 3000 (624)  43.1 / 41.5, 16 x 6000 (752)  85.4 / 83.4, 40 x 2400 (760)  39.2 / 39.6, 36 x 2800 (792)  45.5 / 46.8,
+//           48 x 2300 (864)  38.2 / 40.2, 64 x 1706 (896)  34.3 / 35.9, 96 x 1397 (1056)  34.7 / 37.4.
 constexpr int kKeySplit4 = 37, kKeySplit8 = 38, kRows128 = 1;
 
 static int choose_variant(long long heads, int N, int d, int causal) {
@@ -585,7 +586,7 @@ static int choose_variant(long long heads, int N, int d, int causal) {
     const int alone = causal && N >= 6000 ? (N >= 12000 ? 512 : 384) : 256;  // the eight-wave form's line
     if (g <= most) return N >= 512 && g <= alone ? kKeySplit8 : kKeySplit4;
     if (d == 128) return (causal ? j <= 576 : j <= 256 || (j > 512 && j <= 640)) ? kRows128 : kDefaultD128;
-    return j > (causal ? 895 : 512) ? kDefaultD64Long : kDefaultD64Short;
+    return j > (causal ? 755 : 512) ? kDefaultD64Long : kDefaultD64Short;
 }
 
 int attn_choose_variant(int B, int H, int N, int d, int dtype, int causal) {

@@ -27,7 +27,7 @@ SPLIT4, SPLIT8, ROWS128, D128, D64_LONG, D64_SHORT = 37, 38, 1, 36, 18, 3
     (256, 128, 128, False, ROWS128), (257, 128, 128, False, D128), (512, 128, 128, False, D128), (513, 128, 128, False, ROWS128),
     (640, 128, 128, False, ROWS128), (641, 128, 128, False, D128), (576, 128, 128, True, ROWS128), (577, 128, 128, True, D128),
     # d = 64: three workgroups per unit
-    (512, 128, 64, False, D64_SHORT), (513, 128, 64, False, D64_LONG), (895, 128, 64, True, D64_SHORT), (896, 128, 64, True, D64_LONG),
+    (512, 128, 64, False, D64_SHORT), (513, 128, 64, False, D64_LONG), (755, 128, 64, True, D64_SHORT), (756, 128, 64, True, D64_LONG),
     # the shapes of the benchmark and of the paper's attention kernel
     (64, 4096, 128, True, D128), (32, 16384, 128, True, D128), (128, 2048, 64, False, D64_LONG), (4, 16384, 64, False, D64_SHORT),
 ])
