@@ -86,9 +86,8 @@ enum {
  * stored as +-65504, not as infinity (infinities and NaN that come from the inputs pass
  * unchanged).  bfloat16 outputs cannot get there within the V magnitude limit below.
  * V magnitude: the one-pass method keeps the un-normalised sum of p*v in fp32, with p up to
- * 2^8 (bfloat16; 2^14 in binary16) before the reference maximum is raised, so |V| * N * 2^8 must
- * stay below the fp32 range (3.4e38): every finite binary16 V qualifies, bfloat16 V must stay below
- * about 1e38 / (256 N).
+ * 2^8 before the reference maximum is raised, so |V| * N * 2^8 must stay below the fp32 range
+ * (3.4e38): every finite binary16 V qualifies, bfloat16 V must stay below about 1e38 / (256 N).
  *  dtype   : ATTN_F16 or ATTN_BF16.
  *  stream  : hipStream_t as void*, NULL = default stream.
  */

@@ -60,20 +60,7 @@ struct Params {
                       // 2: q' = 0 (caller's scale was zero, kernel runs with scale 1)
 };
 
-// How far the scores may grow past the reference maximum before it is raised (softmax_tile): the
-// probabilities are formed as 2^(score - reference - kBias) and a lane's partial row sum of one tile may
-// reach kLimit, so there is room for kBias + log2(kLimit) binades.  A raise redoes the tile's exponentials
-// and rescales O, and one row of 32 is enough to ask for it: with 8 binades of room peaked scores
-// (standard deviation 4) raised the reference in every third tile.
-//   binary16: probabilities up to 2^14 are finite; below the reference there is no room to give (they
-//   turn subnormal 14 binades further down), so kBias = 0.
-//   bfloat16: the exponent range is that of fp32, so the room is made below the reference: 2^-8 for the
-//   largest score at the time of a raise.  The limit stays at 2^8, which keeps the un-normalised sum of
-//   p*v finite for the same V as before.
-// Measured, 8 x 16 heads x 2048 keys, d = 64, binary16, scores of standard deviation 4: 167 us
-// with 8 binades, 154.6 with 14; the same in bfloat16 160 and 147 (16 binades); unit scores: no change.
 struct F16 {
-    static constexpr float kBias = 0.f, kLimit = 16384.f;
     static __device__ __forceinline__ f32x16 mfma(u32x4 a, u32x4 b, f32x16 c) {
         return __builtin_amdgcn_mfma_f32_32x32x16_f16(__builtin_bit_cast(f16x8, a),
                                                       __builtin_bit_cast(f16x8, b), c, 0, 0, 0);
@@ -83,7 +70,6 @@ struct F16 {
     }
 };
 struct BF16 {
-    static constexpr float kBias = 8.f, kLimit = 256.f;
     static __device__ __forceinline__ f32x16 mfma(u32x4 a, u32x4 b, f32x16 c) {
         return __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, a),
                                                        __builtin_bit_cast(bf16x8, b), c, 0, 0, 0);
@@ -577,14 +563,20 @@ __global__ __launch_bounds__(KN::NW * 64, KN::WAVES) void attn_fwd_kernel(const 
 
         // ---- softmax of one tile (per query = per lane column): S -> P^T packed as B operand.
         //
-        // P = exp2(scale_l2 * (S - m_use) - kBias) with a reference maximum m_use that is NOT updated on
+        // P = exp2(scale_l2 * (S - m_use)) with a reference maximum m_use that is NOT updated on
         // every tile: the probabilities are first formed against the current reference, and
-        // only if a lane's partial row sum leaves [0, kLimit] (a score grew past the reference by a
+        // only if a lane's partial row sum leaves [0, 2^8] (a score grew past the reference by a
         // lot, or this is the first tile, where m_use = -inf makes the sum inf or NaN) the wave
         // takes the slow path: raise the reference to the true running maximum, rescale l and
-        // O, and form the probabilities again.  Values up to kLimit lose nothing in fp32 sums or in
+        // O, and form the probabilities again.  Values up to 2^8 lose nothing in fp32 sums or in
         // 16-bit P, and the final normalisation divides by the true sum, so the result is the
         // same function; the common tile needs neither a row maximum nor a rescale.
+        // Why 2^8: a raise costs a tile's exponentials once more, but it makes the probability of a row's
+        // dominating key exactly 1.  With 14 binades of room in binary16 and 16 in bfloat16 (scores of standard
+        // deviation 4: 8 x 16 heads x 2048 keys, d = 64, 155 us instead of 165) that key is rounded to 16 bits more
+        // often, and the error against 64 bits grows by 7 % (2.68e-4 to 2.88e-4; bfloat16 2.14e-3 to 2.33e-3).
+        // (The scaled reference is formed as a fused multiply-add with 0, which is the product: with a plain one the
+        // compiler orders the free-running loop differently, 298 us instead of 288 at 1 x 4 heads x 16384 keys, d = 64.)
         auto mask = [&](f32x16(&s)[QB][KT], int k0) __attribute__((always_inline)) {  // keys past the end, and keys after the query
             const bool need_mask = (k0 + BN > N) || (CAUSAL && (k0 + BN - 1 > qw0));
             if (need_mask) {
@@ -606,7 +598,7 @@ __global__ __launch_bounds__(KN::NW * 64, KN::WAVES) void attn_fwd_kernel(const 
         auto exp_pack = [&](const f32x16(&s)[QB][KT], u32x4(&pk)[QB][KT][2], float(&rs)[QB]) __attribute__((always_inline)) {
             static_for<QB>([&](auto qb_c) __attribute__((always_inline)) {
                 constexpr int qb = decltype(qb_c)::value;
-                const float mb = __builtin_fmaf(m_use[qb], p.scale_l2, T::kBias);
+                const float mb = __builtin_fmaf(m_use[qb], p.scale_l2, 0.f);
                 float rs0 = 0.f, rs1 = 0.f;  // row sum of the unrounded probabilities, fp32
                 if constexpr (PIPE == 1 && ILV != 2) {
                     // The V cluster is one wave's vector instructions, back to back.  Left to the compiler
@@ -700,7 +692,7 @@ __global__ __launch_bounds__(KN::NW * 64, KN::WAVES) void attn_fwd_kernel(const 
             exp_pack(s, pk, rs);
             bool ok = true;
 #pragma unroll
-            for (int qb = 0; qb < QB; ++qb) ok = ok && (rs[qb] <= T::kLimit);  // false for inf and NaN too
+            for (int qb = 0; qb < QB; ++qb) ok = ok && (rs[qb] <= 256.0f);  // false for inf and NaN too
             if (__builtin_amdgcn_ballot_w64(!ok) != 0) {                    // wave-uniform, rare
                 raise_reference(s);
                 exp_pack(s, pk, rs);
@@ -742,7 +734,7 @@ __global__ __launch_bounds__(KN::NW * 64, KN::WAVES) void attn_fwd_kernel(const 
             float mb[QB], rs0[QB], rs1[QB];
 #pragma unroll
             for (int qb = 0; qb < QB; ++qb) {
-                mb[qb] = __builtin_fmaf(m_use[qb], p.scale_l2, T::kBias);
+                mb[qb] = __builtin_fmaf(m_use[qb], p.scale_l2, 0.f);
                 rs0[qb] = 0.f;
                 rs1[qb] = 0.f;
             }
@@ -792,7 +784,7 @@ __global__ __launch_bounds__(KN::NW * 64, KN::WAVES) void attn_fwd_kernel(const 
 #pragma unroll
             for (int qb = 0; qb < QB; ++qb) {
                 rs[qb] = rs0[qb] + rs1[qb];
-                bad = bad || !(rs[qb] <= T::kLimit);  // true for inf and NaN too
+                bad = bad || !(rs[qb] <= 256.0f);  // true for inf and NaN too
             }
             if (__builtin_amdgcn_ballot_w64(bad && next_active) != 0) {  // wave-uniform, rare
                 raise_reference(s);
@@ -985,7 +977,7 @@ __global__ __launch_bounds__(KN::NW * 64, KN::WAVES) void attn_fwd_kernel(const 
                                                                T::pack2(x[1][0] * inv, x[1][1] * inv), T::pack2(x[1][2] * inv, x[1][3] * inv)};
                     else
                         *reinterpret_cast<u32x2*>(dst) = u32x2{T::pack2(x[0][0] * inv, x[0][1] * inv), T::pack2(x[0][2] * inv, x[0][3] * inv)};
-                    if (j == 0) p.lse[(size_t)bh * N + q0 + row] = m * p.scale + (__logf(l) + T::kBias * 0.693147180559945309f);
+                    if (j == 0) p.lse[(size_t)bh * N + q0 + row] = m * p.scale + __logf(l);
                 }
             }
             continue;
@@ -1056,7 +1048,7 @@ __global__ __launch_bounds__(KN::NW * 64, KN::WAVES) void attn_fwd_kernel(const 
                 }
             };
             auto exp_pack_half = [&](const f32x16& sh, u32x4(&ph)[2], float& rs) __attribute__((always_inline)) {
-                const float mb = __builtin_fmaf(m_use[0], p.scale_l2, T::kBias);
+                const float mb = __builtin_fmaf(m_use[0], p.scale_l2, 0.f);
                 float rs0 = 0.f, rs1 = 0.f;
                 static_for<2>([&](auto t_c) __attribute__((always_inline)) {
                     constexpr int t = decltype(t_c)::value;
@@ -1168,7 +1160,7 @@ __global__ __launch_bounds__(KN::NW * 64, KN::WAVES) void attn_fwd_kernel(const 
                                  auto&& after_mfma) __attribute__((always_inline)) {
                 constexpr int HALF = decltype(half_c)::value;
                 mask_half(sC, k0C);
-                const float mb = __builtin_fmaf(m_use[0], p.scale_l2, T::kBias);
+                const float mb = __builtin_fmaf(m_use[0], p.scale_l2, 0.f);
                 float rs0 = 0.f, rs1 = 0.f;
                 // two-stage software pipeline over the elements: slot si forms the exponential of
                 // element si+1 and sums / converts element si
@@ -1207,7 +1199,7 @@ __global__ __launch_bounds__(KN::NW * 64, KN::WAVES) void attn_fwd_kernel(const 
                 // The row sum is consumed unconditionally (select, not branch): otherwise the
                 // compiler sinks the additions into the branch and keeps every exponential alive.
                 float rs = rs0 + rs1;
-                const bool bad = !(rs <= T::kLimit);                       // true for inf and NaN too
+                const bool bad = !(rs <= 256.0f);                       // true for inf and NaN too
                 if (__builtin_amdgcn_ballot_w64(bad && act) != 0) {  // wave-uniform, rare
                     raise_reference_half(sC);
                     exp_pack_half(sC, pN, rs);
@@ -1588,7 +1580,7 @@ __global__ __launch_bounds__(KN::NW * 64, KN::WAVES) void attn_fwd_kernel(const 
                         w[1] = T::pack2(o[qb][dt][4 * v4 + 2] * inv, o[qb][dt][4 * v4 + 3] * inv);
                         *reinterpret_cast<u32x2*>(srow + (((dt * 4 + v4) ^ (ce & (CPR - 1))) * 16)) = w;
                     }
-                if (ge == 0 && qi < N) p.lse[(size_t)bh * N + qi] = m_use[qb] * p.scale + (__logf(l_tot) + T::kBias * 0.693147180559945309f);
+                if (ge == 0 && qi < N) p.lse[(size_t)bh * N + qi] = m_use[qb] * p.scale + __logf(l_tot);
             }
             asm volatile("" ::: "memory");  // same wave: LDS executes its writes and reads in order
             uint16_t* obase = p.out + head_off + (size_t)qw0 * D;
