@@ -43,7 +43,7 @@ PROFILE_HBM_BYTES = {
     "cfg2": ((141957 * 2.0 + 66560 * 1.0) * 1024, "profiles/attn_fwd_cfg2_B2_H32_N4096_d128_causal_bf16.md"),
     "cfg3": ((311040 * 2.0 + 133120 * 1.0) * 1024, "profiles/attn_fwd_cfg3_B1_H32_N16384_d128_causal_bf16.md"),
 }
-GEMM_PROFILE_HBM_BYTES = ((6185.0 * 2.0 + 512.0 * 1.0) * 1024, "profiles/gemm_lrelu_M512_N512_K2048_f16.md")
+GEMM_PROFILE_HBM_BYTES = ((6174.5 * 2.0 + 512.0 * 1.0) * 1024, "profiles/calls_kernel_stats.md")
 
 
 def device_tensors(w, seed):
@@ -268,8 +268,9 @@ def ceilings(A, achieved):
 
 
 def gemm_leg(steps=5000, warmup=200, with_oracle=True):
-    """The second workload (GEMM + LeakyReLU, M, N, K = 512, 512, 2048, binary16): latency per launch,
-    the cost of a launch that does no work, the algorithmic-bytes roofline, and the oracle's time."""
+    """The second workload (GEMM + LeakyReLU, M, N, K = 512, 512, 2048, binary16): latency per call,
+    the cost of a call that does no work, the schedule the search starts from, the algorithmic-bytes
+    roofline, and the oracle's time."""
     import numpy as np
     import torch
     from paper_2403_16863_amd import gemm, inputs as I
@@ -277,14 +278,27 @@ def gemm_leg(steps=5000, warmup=200, with_oracle=True):
     ab, bb = I.make_gemm(M, N, K, I.F16, seed=0)
     a, b = (torch.from_numpy(x.view(np.int16)).to("cuda").view(torch.float16) for x in (ab, bb))
     c = torch.empty((M, N), dtype=torch.float16, device="cuda")
+
+    def timed(x, y, z):
+        for _ in range(warmup):
+            gemm.gemm_lrelu(x, y, z, slope)
+        e0, e1 = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+        e0.record()
+        for _ in range(steps):
+            gemm.gemm_lrelu(x, y, z, slope)
+        e1.record()
+        e1.synchronize()
+        return e0.elapsed_time(e1) / steps * 1e3
+
     variant = gemm.gemm_lrelu_default_variant(M, N, K)
-    dev_us = gemm.gemm_lrelu_time(a, b, c, slope, variant, warmup, steps) / steps * 1e3
+    start_us = gemm.gemm_lrelu_time(a, b, c, slope, variant, warmup, steps) / steps * 1e3
     ta, tb = a[:32, :8].contiguous(), b[:8, :32].contiguous()
     tc = torch.empty((32, 32), dtype=torch.float16, device="cuda")
-    floor_us = gemm.gemm_lrelu_time(ta, tb, tc, slope, variant, warmup, steps) / steps * 1e3
+    floor_us = timed(ta, tb, tc)
+    dev_us = timed(a, b, c)
     alg_bytes = 2.0 * (M * K + K * N + M * N)
-    leg = {"workload": f"gemm_lrelu M{M} N{N} K{K} f16, slope {slope}", "variant": variant,
-           "latency_us": dev_us, "launch_floor_us": floor_us, "TFLOP/s": 2.0 * M * N * K / dev_us / 1e6,
+    leg = {"workload": f"gemm_lrelu M{M} N{N} K{K} f16, slope {slope}",
+           "latency_us": dev_us, "launch_floor_us": floor_us, "search_start": {"variant": variant, "latency_us": start_us}, "TFLOP/s": 2.0 * M * N * K / dev_us / 1e6,
            "steps": steps, "warmup": warmup,
            "roofline": {"bound": "hbm", "achieved": alg_bytes / dev_us / 1e3, "peak": HBM_PEAK_GBS, "unit": "GB/s",
                         "frac": alg_bytes / dev_us / 1e3 / HBM_PEAK_GBS, "algorithmic_bytes": alg_bytes,

@@ -2,8 +2,9 @@
 """Benchmark of the second workload, fused GEMM + LeakyReLU (Sec. 5, Table 3: M, N, K = 512, 512,
 2048, binary16), on one MI355X.  The paper's metric for it is the kernel's latency.
 
-A step is one launch of the whole path (tile loads through LDS, MFMA, cross-wave sum, activation,
-rounding, store) on seeded synthetic A, B already resident in device memory.  Prints ONE JSON line.
+A step is one call of gemm_lrelu (tile loads through LDS, MFMA, cross-wave sum, activation, rounding,
+store) on seeded synthetic A, B already resident in device memory; with --variant one launch of that
+schedule of the search's table, issued by the library's own loop.  Prints ONE JSON line.
 
   python bench_gemm.py [--steps K] [--warmup W] [--variant ID] [--dtype f16|bf16] [--no-cpu-baseline]
 """
@@ -20,8 +21,8 @@ if ROOT not in sys.path:
 HBM_PEAK_GBS = 8000.0
 # Bytes per launch that cross the L2 boundary, from `rocprofv3 --pmc FETCH_SIZE` and `--pmc WRITE_SIZE`
 # runs of this script scaled by the same counters on a 256 MiB device copy (FETCH_SIZE counts
-# 2 KiB, WRITE_SIZE 1 KiB); default variant, binary16.  Written up under profiles/.
-MEASURED_HBM_BYTES = (6185.0 * 2.0 + 512.0 * 1.0) * 1024
+# 2 KiB, WRITE_SIZE 1 KiB); gemm_lrelu, binary16.  Written up under profiles/.
+MEASURED_HBM_BYTES = (6174.5 * 2.0 + 512.0 * 1.0) * 1024
 
 
 def main():
@@ -47,26 +48,36 @@ def main():
     tdt = torch.float16 if dtype == I.F16 else torch.bfloat16
     a, b = (torch.from_numpy(x.view(np.int16)).to("cuda").view(tdt) for x in (ab, bb))
     c = torch.empty((M, N), dtype=tdt, device="cuda")
-    variant = gemm.gemm_lrelu_default_variant(M, N, K) if args.variant is None else args.variant
+    variant = args.variant
 
-    stream = torch.cuda.current_stream()
-    for _ in range(args.warmup):
-        gemm.gemm_lrelu_variant(a, b, c, slope, variant)
-    e0, e1 = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
-    torch.cuda.synchronize()
-    t0 = time.perf_counter()
-    e0.record(stream)
-    for _ in range(args.steps):
-        gemm.gemm_lrelu_variant(a, b, c, slope, variant)
-    e1.record(stream)
-    torch.cuda.synchronize()
-    wall_us = (time.perf_counter() - t0) / args.steps * 1e6
-    # the same launches issued by the library itself, without the interpreter between them
-    dev_us = gemm.gemm_lrelu_time(a, b, c, slope, variant, 50, args.steps) / args.steps * 1e3
+    def call(x, y, z):
+        if variant is None:
+            gemm.gemm_lrelu(x, y, z, slope)
+        else:
+            gemm.gemm_lrelu_variant(x, y, z, slope, variant)
+
+    def timed(x, y, z):
+        """(us per call on the device's clock, on the host's), calls back to back"""
+        for _ in range(args.warmup):
+            call(x, y, z)
+        e0, e1 = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+        torch.cuda.synchronize()
+        t0 = time.perf_counter()
+        e0.record()
+        for _ in range(args.steps):
+            call(x, y, z)
+        e1.record()
+        torch.cuda.synchronize()
+        return e0.elapsed_time(e1) / args.steps * 1e3, (time.perf_counter() - t0) / args.steps * 1e6
+
+    dev_us, wall_us = timed(a, b, c)
     # what one launch costs on this device before it does any work: a single-tile problem
     ta, tb = a[:32, :8].contiguous(), b[:8, :32].contiguous()
     tc = torch.empty((32, 32), dtype=tdt, device="cuda")
-    floor_us = gemm.gemm_lrelu_time(ta, tb, tc, slope, variant, 50, args.steps) / args.steps * 1e3
+    floor_us = timed(ta, tb, tc)[0]
+    if variant is not None:      # the launches issued by the library itself, without the interpreter between them
+        dev_us = gemm.gemm_lrelu_time(a, b, c, slope, variant, 50, args.steps) / args.steps * 1e3
+        floor_us = gemm.gemm_lrelu_time(ta, tb, tc, slope, variant, 50, args.steps) / args.steps * 1e3
 
     alg_bytes = 2.0 * (M * K + K * N + M * N)          # every operand element once, 16 bits each
     flops = 2.0 * M * N * K
@@ -75,7 +86,7 @@ def main():
         "warmup": args.warmup, "ms_per_step": dev_us * 1e-3, "higher_is_better": False, "scaling": "weak",
         "vs_baseline": None, "dtype": args.dtype, "data": "synthetic",
         "config": {"workload": f"gemm_lrelu M{M} N{N} K{K} {args.dtype}", "slope": slope, "variant": variant,
-                   "knobs": dict(zip(gemm.KNOB_NAMES, gemm.gemm_lrelu_variant_knobs(variant)))},
+                   "knobs": None if variant is None else dict(zip(gemm.KNOB_NAMES, gemm.gemm_lrelu_variant_knobs(variant)))},
         "tflops": flops / dev_us / 1e6,
         "latency_us_with_python_launch": wall_us,
         "launch_floor_us": floor_us,
