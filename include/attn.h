@@ -83,8 +83,14 @@ enum {
  * |x_j| * 2^-22 on top of the above: nothing up to |x| ~ 1e4, a per cent at |x| ~ 1e5.
  * Overflow: the exact O never exceeds max |V| (a convex combination), but the computed one may
  * by the error above; in binary16 a finite result beyond the largest finite value (65504) is
- * stored as +-65504, not as infinity (infinities and NaN that come from the inputs pass
- * unchanged).  bfloat16 outputs cannot get there within the V magnitude limit below.
+ * stored as +-65504, not as infinity.  bfloat16 outputs cannot get there within the V magnitude
+ * limit below.
+ * Infinities and NaN: keys may be masked by scores of -inf (a row is then what it is without those
+ * keys; NaN if it sees no others.  In bfloat16 the variants that do not split the keys need a
+ * finite score in the first key tile.)  Otherwise inputs are finite: in bfloat16 a NaN or +inf
+ * among a row's scores makes the row NaN, and a NaN or infinity in V passes into its column; in
+ * binary16 the mode behind the clamping leaves no such rule (an infinity in V comes out as
+ * +-65504, a NaN as a finite number).
  * V magnitude: the one-pass method keeps the un-normalised sum of p*v in fp32, with p up to
  * 2^8 before the reference maximum is raised, so |V| * N * 2^8 must stay below the fp32 range
  * (3.4e38): every finite binary16 V qualifies, bfloat16 V must stay below about 1e38 / (256 N).

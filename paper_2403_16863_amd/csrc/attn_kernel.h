@@ -99,9 +99,9 @@ __device__ __forceinline__ void swap_halves(float x, float& lo_vals, float& hi_v
 // the next address has to wait until the previous load has left the issue queue.
 // None of the loads to LDS uses the compiler's builtins: it tracks those as writes to LDS and puts a
 // wait for every load in flight in front of the next LDS read it cannot prove apart, in the middle of
-// the tile loops.  The builtin on the ragged-tile path alone cost (its wait merges into the common path)
-// 19 us of 299 at 1 x 4 heads x 16384 keys, d = 64, 1 us of 21 at 4 x 16 x 1024 causal; on the interleaved
-// order, where all loads were builtins, 640 us of 2450 at 32 x 16384, d = 128 (variant 31).
+// the tile loops.  The builtin on the ragged-tile path alone (its wait merges into the common path) costs
+// 13 us of 299 at 1 x 4 heads x 16384 keys, d = 64, 0.5 of 18.8 at 4 x 16 x 1024 causal, 1 of 165 at 8 x 16 x 2048; on the
+// interleaved order, where all loads were builtins, 640 us of 2450 at 32 x 16384, d = 128 (variant 31).
 __device__ __forceinline__ void load_to_lds_16(const char* base, unsigned voff, unsigned lds_base) {
     asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1"
                  :: "v"(voff), "s"(base), "s"(lds_base) : "memory", "m0");
@@ -303,7 +303,8 @@ __global__ __launch_bounds__(KN::NW * 64, KN::WAVES) void attn_fwd_kernel(const 
     };
     const int N = p.N;
     // binary16 only: a finite result above the largest finite binary16 value is stored as that
-    // value, not as infinity (mode bit FP16_OVFL; true infinities and NaN pass unchanged).  The
+    // value, not as infinity (mode bit FP16_OVFL; what it makes of infinities and NaN in the inputs is not
+    // IEEE arithmetic: an infinity in V comes out as 65504, a NaN as a finite number).  The
     // exact O is a convex combination of V values, so it never exceeds max |V|; the computed one
     // can, by a rounding error: P is rounded to 16 bits before the second contraction while the
     // row sum keeps the unrounded values, and with V at the largest finite value a few

@@ -115,8 +115,8 @@ def test_memory_behind_the_last_row_is_never_used(d):
 
 @pytest.mark.gpu
 def test_non_finite_scores_stay_in_their_rows():
-    """A NaN or an infinity in one query reaches that row alone, whichever wave's keys meet it (bfloat16; with
-    the overflow mode of binary16 no variant delivers NaN for it)."""
+    """A NaN or an infinity in one query reaches that row alone, whichever wave's keys meet it (bfloat16; in
+    binary16 the overflow mode leaves no rule for what a NaN or an infinity in the inputs becomes)."""
     import torch
     from gpu_util import run_gpu
     for bad in (float("nan"), float("inf")):
