@@ -156,14 +156,12 @@ __device__ __forceinline__ float xhalf_max(float x) {
     return fmaxf(a, b);
 }
 
-// Key split: whether the sums of a wave (row sum l, reference maximum m) weigh nothing (factor 0) among those
-// they are added to and may hold anything.  Any wave's first tiles may be keys that are masked by their scores
+// Key split: whether the sums of a wave against the reference maximum m weigh nothing (factor 0) among those they
+// are added to and may hold anything.  Any wave's first tiles may be keys that are masked by their scores
 // (-inf, or finite and far below all others).  Their scaled reference is then -inf, or so large that its
 // rounding alone (a binade at 2^24, the range of fp32 at 2^31) makes the probabilities infinite, and 0 times
 // that is NaN.  Sums against any other reference are finite unless the inputs are not, and such a NaN stays.
-__device__ __forceinline__ bool no_weight(float factor, float l, float m, float scale_l2) {
-    return factor == 0.f && l != 0.f && m * scale_l2 < -16777216.f;
-}
+__device__ __forceinline__ bool no_weight(float factor, float m, float scale_l2) { return factor == 0.f && m * scale_l2 < -16777216.f; }
 
 // ---- LDS layouts ------------------------------------------------------------
 // A K/V tile is BN rows of D 16-bit elements, addressed in 16-byte chunks.  Both
@@ -670,7 +668,7 @@ __global__ __launch_bounds__(KN::NW * 64, KN::WAVES) void attn_fwd_kernel(const 
                 // In a wave's first tile m_use = -inf and alpha = exp2(-inf) = 0.
                 const float alpha = __builtin_amdgcn_exp2f((m_use[qb] - m_new) * p.scale_l2);
                 if constexpr (KEYSPLIT) {
-                    const bool drop = no_weight(alpha, l_run[qb], m_use[qb], p.scale_l2);
+                    const bool drop = no_weight(alpha, m_use[qb], p.scale_l2);  // (O of a lane holds the keys of both halves of the wave, its l does not)
                     if (__builtin_amdgcn_ballot_w64(drop) != 0) {
                         l_run[qb] = drop ? 0.f : l_run[qb];
 #pragma unroll
@@ -964,7 +962,7 @@ __global__ __launch_bounds__(KN::NW * 64, KN::WAVES) void attn_fwd_kernel(const 
 #pragma unroll 1
                     for (int w = 0; w < NW; ++w) {
                         const float mw = stat[w * 64], lw = stat[w * 64 + 32], fw = __builtin_amdgcn_exp2f((mw - m) * p.scale_l2);
-                        if (no_weight(fw, lw, mw, p.scale_l2)) continue;
+                        if (no_weight(fw, mw, p.scale_l2)) continue;
                         l += fw * lw;
 #pragma unroll
                         for (int q = 0; q < D / 64; ++q) x[q] += fw * part(w, q);

@@ -71,12 +71,13 @@ def test_keys_masked_by_their_scores(d, dtype, causal):
         w = I.Workload("masked", 1, 2, N, d, causal, dtype)
         qb, kb, vb = I.make_qkv(w, seed=5)
         one = I.f32_to_bits(np.ones(1, np.float32), dtype)[0]
-        for value, scale in [(-np.inf, w.scale), (lowest, 0.9)] + [(-1e30, w.scale)] * (dtype == I.BF16):
-            low = I.f32_to_bits(np.array([value], np.float32), dtype)[0]
+        for value, scale in [(-np.inf, w.scale), (lowest, 0.9)] + [(-1e30, w.scale), (-1.5e30, w.scale)] * (dtype == I.BF16):
+            # (the last one twice as low in every other group of four keys, which is one half of the wave)
+            low = I.f32_to_bits(np.where((np.arange(N) & 4 == 0) & (value == -1.5e30), 2 * value, value).astype(np.float32), dtype)
             for name, m in masks:
                 q, k = qb.copy(), kb.copy()
                 q[..., 0] = one
-                k[:, :, m, 0] = low
+                k[:, :, m, 0] = low[m]
                 seen = np.cumsum(~m) > 0 if causal else np.ones(N, bool)      # rows that see an unmasked key
                 print(f"case {name} value={value} N={N} d={d} causal={causal} dtype={dtype} variant={v}", flush=True)
                 O_ref, l_ref, _ = ref.attn_ref(q, k, vb, causal, float(np.float32(scale)), dtype)
