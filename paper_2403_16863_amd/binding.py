@@ -126,6 +126,15 @@ def native():
     return _native
 
 
+def _first_call(*args):
+    global _plain_call
+    _plain_call = native().attn_fwd
+    return _plain_call(*args)
+
+
+_plain_call = _first_call       # the native module's attn_fwd from the first call on (one lookup a call)
+
+
 def attn_strerror(code: int) -> str:
     return lib().attn_strerror(int(code)).decode()
 
@@ -165,8 +174,8 @@ def _marshal(q, k, v, out, lse, stream):
 def attn_fwd(q, k, v, out, lse, causal: bool, scale: float, stream=None) -> None:
     """out, lse <- fused attention forward of device tensors q, k, v ([B,H,N,d]).
     Asynchronous on `stream` (an integer hipStream_t; default: torch's current stream)."""
-    rc = (_native or native()).attn_fwd(q, k, v, out, lse, causal, scale, stream)
-    if rc == ATTN_OK:
+    rc = _plain_call(q, k, v, out, lse, causal, scale, stream)
+    if not rc:
         return
     if rc < 0:
         raise AttnError(rc, "attn_fwd")

@@ -43,8 +43,9 @@ static const Variant kVariants[] = {
 constexpr int kNumVariants = sizeof(kVariants) / sizeof(kVariants[0]);
 constexpr int kDefault = 1;  // where the schedule search starts
 
-// Tiles of `size` that cover n >= 1 (n may be the largest int).
-static int cover(int n, int size) { return 1 + (n - 1) / size; }
+// Tiles of `size` (a power of two) that cover n >= 1 (n may be the largest int).  Shifts, here and below: the choices
+// run on every call, and their forty divisions took 0.1 us of it.
+static int cover(int n, int size) { return 1 + ((n - 1) >> __builtin_ctz(size)); }
 
 static int check_args(const void* a, const void* b, const void* c, int M, int N, int K, int dtype, int variant_id) {
     if (!a || !b || !c) return GEMM_EINVAL;
@@ -89,14 +90,14 @@ static const BlockShape kBlocks[] = {
 };
 
 static const BlockShape& choose_block(int M, int N, int K) {
-    constexpr long long kComputeUnits = 256;
+    constexpr unsigned long long kComputeUnits = 256;
     const BlockShape* best = &kBlocks[0];
     float best_us = 0.f;
     for (const BlockShape& s : kBlocks) {
         if ((long long)(s.bm - 1) * K * 2 + s.bk * 2 >= (long long)kBufferSize) continue;  // 32-bit offsets in a tile's rows
-        const long long tiles = (long long)cover(M, s.bm) * cover(N, s.bn);
-        const long long n = (tiles + kComputeUnits - 1) / kComputeUnits, stages = (K + s.bk * s.wk - 1) / (s.bk * s.wk);
-        const float alone = (float)((n + s.occ - 1) / s.occ) * s.alone, full = (float)n * s.full;
+        const unsigned long long tiles = (unsigned long long)cover(M, s.bm) * cover(N, s.bn);
+        const long long n = (tiles + kComputeUnits - 1) / kComputeUnits, stages = cover(K, s.bk * s.wk);
+        const float alone = (float)(n <= s.occ ? 1 : (n + s.occ - 1) / s.occ) * s.alone, full = (float)n * s.full;
         const float us = (float)stages * (alone > full ? alone : full) + (float)n * s.ends;
         if (&s == &kBlocks[0] || us < best_us) best = &s, best_us = us;
     }
@@ -125,6 +126,7 @@ struct Split {
     int shape, ranges, kc;  // ranges of kc values of k; 0: not split
 };
 static Split choose_split(int M, int N, int K) {
+    if (K < 4000) return {0, 0, K};
     auto tiles = [&](int s) { return (long long)cover(M, kBlocks[s].bm) * cover(N, kBlocks[s].bn); };
     const int s = tiles(0) <= 64 ? 0 : M <= 32 ? 1 : 2;
     const long long n = tiles(s);
@@ -162,9 +164,8 @@ static int launch_split(const Split& sp, const void* a, const void* b, void* c, 
     return GEMM_OK;
 }
 
+// (arguments checked by the caller)
 static int launch_block(const void* a, const void* b, void* c, int M, int N, int K, float slope, int dtype, void* stream) {
-    const int rc = check_args(a, b, c, M, N, K, dtype, 0);
-    if (rc != GEMM_OK) return rc;
     const BlockShape& s = choose_block(M, N, K);
     Params p;
     p.a = (const char*)a;
@@ -261,7 +262,8 @@ int gemm_lrelu_variant(const void* a, const void* b, void* c, int M, int N, int 
 }
 
 int gemm_lrelu(const void* a, const void* b, void* c, int M, int N, int K, float slope, int dtype, void* stream) {
-    return gemm::launch_block(a, b, c, M, N, K, slope, dtype, stream);
+    const int rc = gemm::check_args(a, b, c, M, N, K, dtype, 0);
+    return rc == GEMM_OK ? gemm::launch_block(a, b, c, M, N, K, slope, dtype, stream) : rc;
 }
 
 static long long parts_bytes(const gemm::Split& sp, int M, int N) { return (long long)sp.ranges * M * N * 4; }

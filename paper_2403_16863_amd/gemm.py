@@ -91,13 +91,22 @@ def _marshal(a, b, c, stream):
     return (a.data_ptr(), b.data_ptr(), c.data_ptr(), M, b.shape[1], K), dt, stream
 
 
+def _first_call(*args):
+    global _plain_call
+    _plain_call = binding.native().gemm_lrelu
+    return _plain_call(*args)
+
+
+_plain_call = _first_call       # the native module's gemm_lrelu from the first call on (one lookup a call)
+
+
 def gemm_lrelu(a, b, c, slope: float, stream=None) -> None:
     """c <- leaky_relu(a @ b) for device tensors a [M,K], b [K,N], c [M,N]; asynchronous on `stream`
     (an integer hipStream_t; default: torch's current stream).  On the current stream, few tiles of c and a long
     K take up to 4 MB of scratch memory from torch's allocator for the call (gemm_workspace.h); other streams,
     the per-thread stream and recordings do without."""
-    rc = (binding._native or binding.native()).gemm_lrelu(a, b, c, slope, stream)
-    if rc == GEMM_OK:
+    rc = _plain_call(a, b, c, slope, stream)
+    if not rc:
         return
     if rc < 0:
         raise GemmError(rc, "gemm_lrelu")
