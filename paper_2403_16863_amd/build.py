@@ -17,6 +17,8 @@ HIPCC_FLAGS = [
     "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC",
     # keep the compiler from forming packed-fp32 VALU instructions
     "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
+    # kernel arguments arrive in scalar registers (csrc/attn_kernel.h)
+    "-mllvm", "-amdgpu-kernarg-preload-count=16",
 ]
 ATTN_PARTS = 9          # parts of the attention variant table (csrc/attn_variants.h)
 

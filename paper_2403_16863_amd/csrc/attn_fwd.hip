@@ -151,7 +151,6 @@ int launch(const void* q, const void* k, const void* v, void* out, float* lse, i
     p.v = (const uint16_t*)v;
     p.out = (uint16_t*)out;
     p.lse = lse;
-    p.H = H;
     p.N = N;
     p.nqt = (int)nqt;
     p.BH = B * H;
@@ -163,12 +162,17 @@ int launch(const void* q, const void* k, const void* v, void* out, float* lse, i
     p.scale_l2 = p.scale * 1.44269504088896340736f;
     const long long grid = grid_size(var.keysplit() ? 0 : cu_count(), var, p.BH, nqt);  // (the key split's does not depend on the device)
     if (!launchable(grid, var)) return ATTN_EUNSUPPORTED;
+    p.grid = (int)grid;
     // The launch's own return code is used (not hipGetLastError, which can report a
     // stale, unrelated status left behind by another library's earlier call).
-    void* args[] = {&p};
+    // A code object gets the arguments as one block, which is laid out alike whether its kernel takes them one by
+    // one or, built before they were split up, as one struct.
+    attn::KernelArguments args = attn::kernel_arguments(p);
+    size_t bytes = sizeof p;
+    void* block[] = {HIP_LAUNCH_PARAM_BUFFER_POINTER, &p, HIP_LAUNCH_PARAM_BUFFER_SIZE, &bytes, HIP_LAUNCH_PARAM_END};
     const hipError_t e =
-        module_fn ? hipModuleLaunchKernel(module_fn, (unsigned)grid, 1, 1, var.nw * 64, 1, 1, 0, (hipStream_t)stream, args, nullptr)
-                  : hipLaunchKernel((const void*)fn, dim3((unsigned)grid), dim3(var.nw * 64), args, 0, (hipStream_t)stream);
+        module_fn ? hipModuleLaunchKernel(module_fn, (unsigned)grid, 1, 1, var.nw * 64, 1, 1, 0, (hipStream_t)stream, nullptr, block)
+                  : hipLaunchKernel((const void*)fn, dim3((unsigned)grid), dim3(var.nw * 64), args.list, 0, (hipStream_t)stream);
     if (e != hipSuccess) fprintf(stderr, "attn: kernel launch failed: %s (%d), grid=%lld block=%d\n", hipGetErrorString(e), (int)e, grid, var.nw * 64);
     return e == hipSuccess ? ATTN_OK : ATTN_ELAUNCH;
 }

@@ -25,6 +25,7 @@
 // receives column i, i.e. four consecutive rows of one column.
 #pragma once
 #include <hip/hip_runtime.h>
+#include <stddef.h>
 #include <stdint.h>
 
 #include <type_traits>
@@ -45,13 +46,20 @@ typedef __attribute__((address_space(3))) void* lds_void_ptr;
 typedef const __attribute__((address_space(1))) void* global_void_ptr;
 typedef s16x4 __attribute__((address_space(3))) * lds_s16x4_ptr;
 
+// The kernel's arguments, in this order (kernel_arguments points at them for a launch).  They are arguments of
+// their own, not one struct, because the command processor can then place them in scalar registers
+// before the first wave starts (-amdgpu-kernarg-preload-count; the first 14 words: up to BH): a kernel that
+// fetches them begins with a load from memory that everything waits for, 0.1 to 0.25 us of every launch
+// (a 512 x 512 x 512 GEMM: 3.38 us, preloaded 3.15).  Pairs of numbers travel as one 64-bit argument: an
+// argument costs the host 7 ns a launch.
 struct Params {
     const uint16_t* q;
     const uint16_t* k;
     const uint16_t* v;
     uint16_t* out;
     float* lse;
-    int H, N;
+    int grid;         // workgroups of the launch (an argument, because gridDim is one that is fetched)
+    int N;
     int nqt;          // query tiles per head
     int BH;           // B * H
     float scale;      // multiplies q'.k, always > 0 (see qmode)
@@ -59,6 +67,14 @@ struct Params {
     int qmode;        // 0: q' = q;  1: q' = -q (caller's scale was negative);
                       // 2: q' = 0 (caller's scale was zero, kernel runs with scale 1)
 };
+
+static_assert(offsetof(Params, grid) == 40 && offsetof(Params, nqt) == 48 && offsetof(Params, scale) == 56 && offsetof(Params, qmode) == 64, "pairs");
+struct KernelArguments {
+    void* list[9];
+};
+inline KernelArguments kernel_arguments(Params& p) {
+    return {{&p.q, &p.k, &p.v, &p.out, &p.lse, &p.grid, &p.nqt, &p.scale, &p.qmode}};
+}
 
 struct F16 {
     static __device__ __forceinline__ f32x16 mfma(u32x4 a, u32x4 b, f32x16 c) {
@@ -251,7 +267,11 @@ struct Knobs {
 };
 
 template <class T, int D, bool CAUSAL, class KN>
-__global__ __launch_bounds__(KN::NW * 64, KN::WAVES) void attn_fwd_kernel(const Params p) {
+__global__ __launch_bounds__(KN::NW * 64, KN::WAVES) void attn_fwd_kernel(
+    const uint16_t* q, const uint16_t* k, const uint16_t* v, uint16_t* out, float* lse, uint64_t grid_n, uint64_t nqt_bh,
+    uint64_t scales, int qmode) {
+    const Params p{q, k, v, out, lse, (int)grid_n, (int)(grid_n >> 32), (int)nqt_bh, (int)(nqt_bh >> 32),
+                   __builtin_bit_cast(float, (unsigned)scales), __builtin_bit_cast(float, (unsigned)(scales >> 32)), qmode};
     constexpr int BN = KN::BN, NW = KN::NW, QB = KN::QB, LDP = KN::LDP, PIPE = KN::PIPE, PF = KN::PF, PRIO = KN::PRIO;
     constexpr int ILV = KN::ILV, LDPOS = KN::LDPOS;
     // Ping-pong order with LDPOS 1: three K and three V buffers, tile loads one tile further ahead,
@@ -297,7 +317,7 @@ __global__ __launch_bounds__(KN::NW * 64, KN::WAVES) void attn_fwd_kernel(const 
     const int c = lane & 31;
 
     auto item_of_round = [&](int round, int& bh, int& qt) __attribute__((always_inline)) -> bool {
-        return schedule_item((int)gridDim.x, (int)blockIdx.x, p.BH, p.nqt, round, bh, qt, CAUSAL);
+        return schedule_item(p.grid, (int)blockIdx.x, p.BH, p.nqt, round, bh, qt, CAUSAL);
     };
     const int N = p.N;
     // binary16 only: a finite result above the largest finite binary16 value is stored as that

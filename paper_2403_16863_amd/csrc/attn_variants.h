@@ -6,7 +6,7 @@
 
 namespace attn {
 
-typedef void (*KernelFn)(const Params);
+typedef void (*KernelFn)(const uint16_t*, const uint16_t*, const uint16_t*, uint16_t*, float*, uint64_t, uint64_t, uint64_t, int);
 
 // The kernels of one variant for one head dimension, by [dtype][causal]; defined in attn_kernels.hip.
 template <int D, class KN>

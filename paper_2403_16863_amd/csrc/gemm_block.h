@@ -63,16 +63,16 @@ struct Block {
 // stay below it: (BM - 1) * K * 2 and (BK - 1) * N * 2, checked by the host.
 constexpr unsigned kBufferSize = 0x80000000u;
 
-// Arguments of the split form: workgroup b computes the products of k range b / (ntm ntn) (kc values of k,
-// a multiple of 64 WK) into its part of the workspace, [range][M][N] floats; gemm_sum_kernel adds them.
-struct SplitParams : Params {
-    float* parts;
-    int kc;
-};
+// SPLIT: workgroup b computes the products of k range b / (ntm ntn) (kc values of k, a multiple of 64 WK) into its
+// part of the workspace, [range][M][N] floats; gemm_sum_kernel adds them.  `out` is C, or that workspace.
+// The arguments arrive in scalar registers (see Params in attn_kernel.h).
+typedef void (*BlockFn)(const char* a, const char* b, void* out, uint64_t m_n, uint64_t k_kc, float slope);
+inline uint64_t two(int low, int high) { return (unsigned)low | (uint64_t)(unsigned)high << 32; }
 
-template <class T, class BL, class Args = Params>
-__global__ __launch_bounds__(BL::WM * BL::WN * BL::WK * 64, (BL::OCC * BL::WM * BL::WN * BL::WK + 3) / 4) void gemm_block_kernel(Args p) {
-    constexpr bool SPLIT = std::is_same_v<Args, SplitParams>;
+template <class T, class BL, bool SPLIT = false>
+__global__ __launch_bounds__(BL::WM * BL::WN * BL::WK * 64, (BL::OCC * BL::WM * BL::WN * BL::WK + 3) / 4) void gemm_block_kernel(
+    const char* a, const char* b, void* out, uint64_t m_n, uint64_t k_kc, float slope) {
+    const int M = (int)m_n, N = (int)(m_n >> 32), K = (int)k_kc, kc = (int)(k_kc >> 32);
     constexpr int BM = BL::BM, BN = BL::BN, WM = BL::WM, WN = BL::WN, WK = BL::WK, NB = BL::NB;
     constexpr int NW = WM * WN, BK = BL::BK, KS = BK / 32;
     constexpr int TM = BM / WM, TN = BN / WN, MT = TM / 16, NT = TN / 16;
@@ -93,18 +93,18 @@ __global__ __launch_bounds__(BL::WM * BL::WN * BL::WK * 64, (BL::OCC * BL::WM * 
     const int wk = wave_wg / NW, wave = wave_wg % NW;
     const unsigned lds0 = lds_address(smem_b) + wk * RING;
     const int wm = wave / WN, wn = wave % WN;
-    int tm, tn, range = 0, k0 = 0, K1 = p.K;  // (K1: end of the k range)
+    const int ntm = 1 + (M - 1) / BM, ntn = 1 + (N - 1) / BN;
+    int tm, tn, range = 0, k0 = 0, K1 = K;  // (K1: end of the k range)
     if constexpr (SPLIT) {
-        const int tiles = p.ntm * p.ntn;
+        const int tiles = ntm * ntn;
         range = (int)blockIdx.x / tiles;
-        tile_of_block((int)blockIdx.x - range * tiles, p.ntm, p.ntn, tm, tn);
-        k0 = range * p.kc;
-        K1 = min(p.K, k0 + p.kc);
+        tile_of_block((int)blockIdx.x - range * tiles, ntm, ntn, tm, tn);
+        k0 = range * kc;
+        K1 = min(K, k0 + kc);
     } else {
-        tile_of_block((int)blockIdx.x, p.ntm, p.ntn, tm, tn);
+        tile_of_block((int)blockIdx.x, ntm, ntn, tm, tn);
     }
     const int m0 = tm * BM, n0 = tn * BN;
-    const int M = p.M, N = p.N, K = p.K;
 
     // B piece: rows (k) of 32-byte slots, one slot per 16 columns.  The transposing read takes 4 rows x 32
     // bytes per 16 lanes and two such groups, 8 rows apart, per clock: the slot index is XOR-ed with a
@@ -132,8 +132,8 @@ __global__ __launch_bounds__(BL::WM * BL::WN * BL::WK * 64, (BL::OCC * BL::WM * 
         voffB[i] = n0 + col < N ? (unsigned)row * (unsigned)(N * 2) + col * 2 : kBufferSize;
     }
     const int nkt = (K1 - k0 + WK * BK - 1) / (WK * BK);
-    const char* pa = p.a + (size_t)m0 * K * 2 + (size_t)(k0 + wk * BK) * 2;
-    const char* pb = p.b + (size_t)n0 * 2 + (size_t)(k0 + wk * BK) * N * 2;
+    const char* pa = a + (size_t)m0 * K * 2 + (size_t)(k0 + wk * BK) * 2;
+    const char* pb = b + (size_t)n0 * 2 + (size_t)(k0 + wk * BK) * N * 2;
     int kload = k0 + wk * BK;  // first k of the next stage to be requested
     auto issue_a = [&](int i, unsigned buf, u32x4 r) __attribute__((always_inline)) {
         attn::buffer_to_lds_16(r, voffA[i], lds0 + buf * A_STAGE + (wave * LA + i) * 1024);
@@ -265,14 +265,13 @@ __global__ __launch_bounds__(BL::WM * BL::WN * BL::WK * 64, (BL::OCC * BL::WM * 
 
     // ---- a lane holds rows n = 4g .. 4g+3 of each 16 x 16 tile of C^T; exchanged between the odd and even
     // 16-lane groups of two neighbouring tiles it has eight consecutive n: one 16-byte store.
-    const float slope = p.slope;
     const int g = lane >> 4;
     auto act = [&](float x) __attribute__((always_inline)) { return x >= 0.f ? x : slope * x; };
     auto store_pair = [&](int mt, int nt, f32x4 x, f32x4 y) __attribute__((always_inline)) {
         const int m = m0 + wm * TM + mt * 16 + (lane & 15);
         if constexpr (SPLIT) {
             const int n = n0 + wn * TN + nt * 16 + g * 4;
-            float* const row = p.parts + ((size_t)range * M + m) * N;
+            float* const row = reinterpret_cast<float*>(out) + ((size_t)range * M + m) * N;
             if (m < M && n < N) *reinterpret_cast<f32x4*>(row + n) = x;
             if (m < M && n + 16 < N) *reinterpret_cast<f32x4*>(row + n + 16) = y;
             return;
@@ -280,7 +279,7 @@ __global__ __launch_bounds__(BL::WM * BL::WN * BL::WK * 64, (BL::OCC * BL::WM * 
         const auto s0 = __builtin_amdgcn_permlane16_swap(T::pack2(act(x[0]), act(x[1])), T::pack2(act(y[0]), act(y[1])), false, false);
         const auto s1 = __builtin_amdgcn_permlane16_swap(T::pack2(act(x[2]), act(x[3])), T::pack2(act(y[2]), act(y[3])), false, false);
         const int n = n0 + wn * TN + nt * 16 + (g & 1) * 16 + (g >> 1) * 8;
-        if (m < M && n < N) *reinterpret_cast<u32x4*>(p.c + (size_t)m * N + n) = u32x4{s0[0], s1[0], s0[1], s1[1]};
+        if (m < M && n < N) *reinterpret_cast<u32x4*>(reinterpret_cast<uint16_t*>(out) + (size_t)m * N + n) = u32x4{s0[0], s1[0], s0[1], s1[1]};
     };
     if constexpr (WK == 1) {
 #pragma unroll

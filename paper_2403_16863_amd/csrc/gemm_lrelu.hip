@@ -72,7 +72,7 @@ static int check_args(const void* a, const void* b, const void* c, int M, int N,
 struct BlockShape {
     int bm, bn, bk, wk, threads, occ;
     float alone, full, ends;
-    KernelFn fn[2];
+    BlockFn fn[2];
 };
 template <class BL>
 constexpr BlockShape block_shape(float alone, float full, float ends) {
@@ -116,11 +116,10 @@ static const BlockShape& choose_block(int M, int N, int K) {
 //   64 x 64   428 x 728 x 6168   22.4 / 16.3 (28.3 / 18.9)   170 x 456 x 4736   12.4 / 8.9 (14.1 / 9.5)
 //             130 x 2448 x 6576  23.7 / 21.1 (30.0 / 27.0)   64 x 4096 x 4096   13.4 / 12.4 (20.7 / 14.8)
 // Over 60 random shapes that the rule below takes: 1.2 times as fast on one set, 1.7 on fresh ones.
-typedef void (*SplitFn)(SplitParams);
-static const SplitFn kSplitFns[][2] = {  // tiles of kBlocks[0], [1], [2]
-    {gemm_block_kernel<Mfma16F16, Block<32, 32, 32, 1, 1, 4, 4, 2>, SplitParams>, gemm_block_kernel<Mfma16BF16, Block<32, 32, 32, 1, 1, 4, 4, 2>, SplitParams>},
-    {gemm_block_kernel<Mfma16F16, Block<32, 64, 64, 1, 2, 2, 3, 2>, SplitParams>, gemm_block_kernel<Mfma16BF16, Block<32, 64, 64, 1, 2, 2, 3, 2>, SplitParams>},
-    {gemm_block_kernel<Mfma16F16, Block<64, 64, 64, 2, 2, 1, 3, 3>, SplitParams>, gemm_block_kernel<Mfma16BF16, Block<64, 64, 64, 2, 2, 1, 3, 3>, SplitParams>},
+static const BlockFn kSplitFns[][2] = {  // tiles of kBlocks[0], [1], [2]
+    {gemm_block_kernel<Mfma16F16, Block<32, 32, 32, 1, 1, 4, 4, 2>, true>, gemm_block_kernel<Mfma16BF16, Block<32, 32, 32, 1, 1, 4, 4, 2>, true>},
+    {gemm_block_kernel<Mfma16F16, Block<32, 64, 64, 1, 2, 2, 3, 2>, true>, gemm_block_kernel<Mfma16BF16, Block<32, 64, 64, 1, 2, 2, 3, 2>, true>},
+    {gemm_block_kernel<Mfma16F16, Block<64, 64, 64, 2, 2, 1, 3, 3>, true>, gemm_block_kernel<Mfma16BF16, Block<64, 64, 64, 2, 2, 1, 3, 3>, true>},
 };
 struct Split {
     int shape, ranges, kc;  // ranges of kc values of k; 0: not split
@@ -141,22 +140,13 @@ static Split choose_split(int M, int N, int K) {
 static int launch_split(const Split& sp, const void* a, const void* b, void* c, int M, int N, int K, float slope, int dtype,
                         void* stream, void* workspace) {
     const BlockShape& s = kBlocks[sp.shape];
-    SplitParams p;
-    p.a = (const char*)a;
-    p.b = (const char*)b;
-    p.c = (uint16_t*)c;
-    p.M = M, p.N = N, p.K = K;
-    p.ntm = cover(M, s.bm), p.ntn = cover(N, s.bn);
-    p.slope = slope;
-    p.parts = (float*)workspace;
-    p.kc = sp.kc;
-    void* args[] = {&p};
-    const float* parts = p.parts;
     int ranges = sp.ranges;
+    uint64_t m_n = two(M, N), k_kc = two(K, sp.kc);
     unsigned chunks = (unsigned)((long long)M * N / 8);
-    void* sum_args[] = {&parts, &p.c, &ranges, &chunks, &slope};
+    void* args[] = {&a, &b, &workspace, &m_n, &k_kc, &slope};
+    void* sum_args[] = {&workspace, &c, &ranges, &chunks, &slope};
     const void* const sum = dtype == GEMM_F16 ? (const void*)gemm_sum_kernel<Mfma16F16> : (const void*)gemm_sum_kernel<Mfma16BF16>;
-    if (hipLaunchKernel((const void*)kSplitFns[sp.shape][dtype], dim3(p.ntm * p.ntn * ranges), dim3(s.threads), args, 0, (hipStream_t)stream) != hipSuccess ||
+    if (hipLaunchKernel((const void*)kSplitFns[sp.shape][dtype], dim3(cover(M, s.bm) * cover(N, s.bn) * ranges), dim3(s.threads), args, 0, (hipStream_t)stream) != hipSuccess ||
         hipLaunchKernel(sum, dim3((chunks + 63) / 64), dim3(64), sum_args, 0, (hipStream_t)stream) != hipSuccess) {
         (void)hipGetLastError();
         return GEMM_ELAUNCH;
@@ -167,15 +157,9 @@ static int launch_split(const Split& sp, const void* a, const void* b, void* c, 
 // (arguments checked by the caller)
 static int launch_block(const void* a, const void* b, void* c, int M, int N, int K, float slope, int dtype, void* stream) {
     const BlockShape& s = choose_block(M, N, K);
-    Params p;
-    p.a = (const char*)a;
-    p.b = (const char*)b;
-    p.c = (uint16_t*)c;
-    p.M = M, p.N = N, p.K = K;
-    p.ntm = cover(M, s.bm), p.ntn = cover(N, s.bn);
-    p.slope = slope;
-    void* args[] = {&p};
-    if (hipLaunchKernel((const void*)s.fn[dtype], dim3(p.ntm * p.ntn), dim3(s.threads), args, 0, (hipStream_t)stream) != hipSuccess) {
+    uint64_t m_n = two(M, N), k_kc = two(K, K);
+    void* args[] = {&a, &b, &c, &m_n, &k_kc, &slope};
+    if (hipLaunchKernel((const void*)s.fn[dtype], dim3(cover(M, s.bm) * cover(N, s.bn)), dim3(s.threads), args, 0, (hipStream_t)stream) != hipSuccess) {
         (void)hipGetLastError();
         return GEMM_ELAUNCH;
     }

@@ -45,7 +45,7 @@ _HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(_HERE, "csrc")
 LLVM_BIN = "/opt/rocm/llvm/bin"
 HIPCC_S_FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-Xclang", "-target-feature", "-Xclang",
-                 "-packed-fp32-ops", "-S", "--cuda-device-only"]
+                 "-packed-fp32-ops", "-mllvm", "-amdgpu-kernarg-preload-count=16", "-S", "--cuda-device-only"]
 
 # ------------------------------------------------------------------------------ parsing
 
@@ -428,7 +428,8 @@ def kernel_source(d: int, dtype: int, causal: bool, knobs: Sequence[int]) -> str
     kn = ", ".join(str(int(k)) for k in knobs)
     return ('#include "attn_kernel.h"\n'
             f"template __global__ void attn::attn_fwd_kernel<{t}, {int(d)}, {'true' if causal else 'false'}, "
-            f"attn::Knobs<{kn}>>(const attn::Params);\n")
+            f"attn::Knobs<{kn}>>(const uint16_t*, const uint16_t*, const uint16_t*, uint16_t*, float*, uint64_t, uint64_t, "
+            "uint64_t, int);\n")
 
 
 def compile_base(workdir: str, d: int, dtype: int, causal: bool, knobs: Sequence[int]) -> str:
