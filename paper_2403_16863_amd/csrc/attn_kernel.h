@@ -223,17 +223,34 @@ __device__ __forceinline__ int v_swz_slot(int row, int slot) {
 // Workgroups are placed round-robin on the 8 XCDs, each with its own L2: when G and the number of heads
 // BH are multiples of 8, the deal runs inside each XCD (32 units) over that XCD's heads (x, x+8, ...), so
 // all query tiles of a head share one L2.  Every item is named exactly once over all (gidx, round).
-__host__ __device__ inline bool schedule_item(int G, int gidx, int BH, int nqt, int round, int& bh, int& qt, bool causal = true) {
-    const bool by_xcd = (G & 7) == 0 && (BH & 7) == 0;
-    const int C = by_xcd ? G >> 3 : G, idx = by_xcd ? gidx >> 3 : gidx, shift = by_xcd ? 5 : 8, units = 1 << shift;
+// `free`: workgroups of one item that come as units become free, G at least the number of items.  For them, heads
+// that do not divide by 8 are kept on few XCDs too (short launches read K and V from memory once per XCD that works
+// on the head: 6 heads x 1000 keys, d = 128, 26 MB for 4.6).  Without a mask, where all items weigh the same, every XCD
+// takes an eighth of the items in head-major order: 11.2 us dealt over all heads, 9.9 this way; 36 x 400, d = 64: 8.7 and
+// 6.9.  With one, where 2 or 4 divide both, groups of 4 or 2 XCDs have heads of their own: 4 x 2354, d = 64, eight
+// waves 11.4 and 9.9; 4 x 865, d = 128: 9.0 and 8.0.  (Persistent workgroups, whose weights come out even over all
+// units only, lose 1 to 5 % that way, and the longer code costs a short launch 3 %.)
+__host__ __device__ inline bool schedule_item(int G, int gidx, int BH, int nqt, int round, int& bh, int& qt, bool causal = true, bool free = false) {
+    const int both = G | BH;
+    int split = (both & 1) ? 0 : (both & 2) ? 1 : (both & 4) ? 2 : 3;  // 2^split groups of XCDs
+    if (split < 3 && free && !causal) {
+        const int total = BH * nqt, per = total >> 3, more = total & 7, x = gidx & 7, i = gidx >> 3;
+        if (round > 0 || i >= per + (x < more)) return false;
+        const int item = x * per + (x < more ? x : more) + i;
+        bh = item / nqt;
+        qt = nqt - 1 - (item - bh * nqt);
+        return true;
+    }
+    if (split < 3 && !free) split = 0;
+    const int C = G >> split, idx = gidx >> split, shift = 8 - split, units = 1 << shift;
     const bool layers = C <= 3 * units;
     const int layer = layers ? idx >> shift : 0, first = layer << shift;
     const int last = (layers && first + units < C ? first + units : C) - 1;
     const int r = round * C + (((round + layer) & 1) ? first + last - idx : idx);
-    const int nh = by_xcd ? BH >> 3 : BH, h0 = by_xcd ? gidx & 7 : 0, hs = by_xcd ? 8 : 1;
+    const int nh = BH >> split, h0 = gidx & ((1 << split) - 1), hs = 1 << split;
     const int n = nh * nqt;
     if (r >= n) return false;
-    const bool by_weight = causal && (n > C ? n / 6 < C && n % (2u * (unsigned)C) != 0 : C > 2 * units);
+    const bool by_weight = causal && (!free && n > C ? n / 6 < C && n % (2u * (unsigned)C) != 0 : C > 2 * units);
     const int per = by_weight ? nh : nqt, q = r / per, rest = r - q * per;
     qt = nqt - 1 - (by_weight ? q : rest);
     bh = h0 + hs * (by_weight ? rest : q);
@@ -317,7 +334,7 @@ __global__ __launch_bounds__(KN::NW * 64, KN::WAVES) void attn_fwd_kernel(
     const int c = lane & 31;
 
     auto item_of_round = [&](int round, int& bh, int& qt) __attribute__((always_inline)) -> bool {
-        return schedule_item(p.grid, (int)blockIdx.x, p.BH, p.nqt, round, bh, qt, CAUSAL);
+        return schedule_item(p.grid, (int)blockIdx.x, p.BH, p.nqt, round, bh, qt, CAUSAL, KEYSPLIT);
     };
     const int N = p.N;
     // binary16 only: a finite result above the largest finite binary16 value is stored as that
@@ -999,7 +1016,7 @@ __global__ __launch_bounds__(KN::NW * 64, KN::WAVES) void attn_fwd_kernel(
                     if (j == 0) p.lse[(size_t)bh * N + q0 + row] = m * p.scale + __logf(l);
                 }
             }
-            continue;
+            break;  // (one item per workgroup)
         } else if constexpr (PIPE == 0) {
             // Plain order: every tile is loaded one iteration ahead; per tile S, softmax, PV.
             // Overlap of MFMA and VALU work comes from the other waves resident on the SIMD.

@@ -145,3 +145,27 @@ def test_grid_size():
         A.attn_schedule_grid(v, 0, 1, 1, 1)
     with pytest.raises(A.AttnError):
         A.attn_schedule_item(4, 4, 1, 1, 0)
+
+
+@pytest.mark.parametrize("grid,BH,nqt", [(192, 6, 32), (7, 7, 1), (9, 3, 3), (776, 36, 20), (1030, 10, 103), (12, 2, 6), (1002, 6, 167), (1204, 4, 301)])
+def test_short_launches_keep_a_head_on_few_xcds(grid, BH, nqt):
+    """One workgroup per item: without a mask every XCD has a run of the items in head-major order, with one the key
+    split's deal (bit 1) gives groups of XCDs heads of their own; every item once either way."""
+    import ctypes
+    L = A.binding.lib()
+    bh, qt = ctypes.c_int(0), ctypes.c_int(0)
+    for causal in (2, 3):
+        items, ran = {}, []
+        for g in range(grid):
+            if L.attn_schedule_item_of(grid, g, BH, nqt, 0, causal, ctypes.byref(bh), ctypes.byref(qt)):
+                items.setdefault(g % 8, []).append((bh.value, qt.value))
+                ran.append((bh.value, qt.value))
+            assert L.attn_schedule_item_of(grid, g, BH, nqt, 1, causal, ctypes.byref(bh), ctypes.byref(qt)) == 0
+        assert sorted(ran) == [(b, q) for b in range(BH) for q in range(nqt)]
+        groups = next(n for n in (8, 4, 2, 1) if grid % n == 0 and BH % n == 0)
+        for x, seq in items.items():
+            if causal == 3:
+                assert all(b % groups == x % groups for b, _ in seq)
+            else:
+                place = [b * nqt + nqt - 1 - q for b, q in seq]
+                assert groups == 8 or place == list(range(place[0], place[0] + len(seq)))
