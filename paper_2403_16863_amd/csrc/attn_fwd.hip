@@ -20,7 +20,8 @@ struct Variant {
     const attn::KernelFn (*fn64)[2];
     const attn::KernelFn (*fn128)[2];
     bool keysplit() const { return pipe == 0 && ldpos == 1; }
-    int bm() const { return 32 * qb * (keysplit() ? 1 : nw); }  // query rows of a work item
+    int groups() const { return keysplit() ? nw : pipe == 0 && ldpos == 2 ? 2 << ilv : 1; }  // of waves that split the keys
+    int bm() const { return 32 * qb * nw / groups(); }  // query rows of a work item
     attn::KernelFn fn(int d, int dtype, int causal) const {
         const attn::KernelFn(*f)[2] = d == 128 ? fn128 : fn64;
         return f ? f[dtype][causal ? 1 : 0] : nullptr;
@@ -41,7 +42,8 @@ struct Variant {
 // depend on the wave): the position of the memory instructions, which is what Sec. 3.1 perturbs.
 // On the ping-pong order ldpos 1 moves the tile loads one tile further ahead, into a third pair of
 // buffers, which leaves one workgroup barrier per tile instead of two.  On the free-running order
-// ldpos 1 is the key split: every wave loads tiles of its own, of the same 32 query rows.
+// ldpos 1 is the key split: every wave loads tiles of its own, of the same 32 query rows; ldpos 2 the wave groups,
+// which share every tile and split its keys (ilv 0: two groups, 1: four).
 const char* const kKnobNames[] = {"bn", "nw", "qb", "ldp", "pipe", "pf", "prio", "dense", "ilv", "ldpos"};
 const int kKnobSizes[] = {3, 2, 2, 2, 4, 4, 3, 2, 3, 3};
 constexpr int kNumKnobs = 10;
@@ -79,12 +81,12 @@ int cu_count() {
 
 // Persistent workgroups: as many as the device keeps resident (occ per CU), a multiple of 8
 // when every XCD can be given whole heads, never more than there are work items.
-// The key split's workgroups are not persistent, one per item: they come in the order of the schedule, the
+// The workgroups of the key split and of the wave groups are not persistent, one per item: they come in the order of the schedule, the
 // heaviest of a head first, as units become free (dealt out ahead, 4 heads x 8000 causal keys, d = 128, took
 // 170 us instead of 122).
 long long grid_size(int cus, const Variant& var, int BH, long long nqt) {
     const long long total = (long long)BH * nqt, resident = (long long)cus * var.occ;
-    if (var.keysplit()) return total > 512 && total <= 768 ? 776 : total;  // (more than three layers: the schedule's order for those)
+    if (var.groups() > 1) return total > 512 && total <= 768 ? 776 : total;  // (more than three layers: the schedule's order for those)
     if ((BH & 7) == 0 && (resident & 7) == 0) {
         const long long per_xcd_items = (long long)(BH >> 3) * nqt, per_xcd_wg = resident >> 3;
         return 8 * (per_xcd_items < per_xcd_wg ? per_xcd_items : per_xcd_wg);
@@ -92,7 +94,7 @@ long long grid_size(int cus, const Variant& var, int BH, long long nqt) {
     return total < resident ? total : resident;
 }
 
-// A launch counts its threads in 32 bits (the key split's grids, one workgroup per item, are the only ones that can get there).
+// A launch counts its threads in 32 bits (the grids of one workgroup per item are the only ones that can get there).
 bool launchable(long long grid, const Variant& var) { return grid * var.nw * 64 <= 0xffffffffLL; }
 
 bool aligned(const void* p, size_t a) { return ((uintptr_t)p & (a - 1)) == 0; }
@@ -160,7 +162,7 @@ int launch(const void* q, const void* k, const void* v, void* out, float* lse, i
     p.qmode = scale > 0.f ? 0 : (scale < 0.f ? 1 : 2);
     p.scale = scale > 0.f ? scale : (scale < 0.f ? -scale : 1.0f);
     p.scale_l2 = p.scale * 1.44269504088896340736f;
-    const long long grid = grid_size(var.keysplit() ? 0 : cu_count(), var, p.BH, nqt);  // (the key split's does not depend on the device)
+    const long long grid = grid_size(var.groups() > 1 ? 0 : cu_count(), var, p.BH, nqt);  // (one item per workgroup: no question of the device)
     if (!launchable(grid, var)) return ATTN_EUNSUPPORTED;
     p.grid = (int)grid;
     // The launch's own return code is used (not hipGetLastError, which can report a
@@ -581,14 +583,49 @@ constexpr int kDefaultD64Short = 3;
 // d = 64, three workgroups per unit (18) against two (3): 4 x 16384 (j 512)  281 / 281, 6 x 10900 (516)  257 / 286, 24 x 2809 (528)  70.4 / 77.5;
 //   causal  26 x 3000 (624)  43.1 / 41.5, 16 x 6000 (752)  85.4 / 83.4, 40 x 2400 (760)  39.2 / 39.6, 36 x 2800 (792)  45.5 / 46.8,
 //           48 x 2300 (864)  38.2 / 40.2, 64 x 1706 (896)  34.3 / 35.9, 96 x 1397 (1056)  34.7 / 37.4.
-constexpr int kKeySplit4 = 37, kKeySplit8 = 38, kRows128 = 1;
+// The wave groups (39: two groups, 128 rows; 40: four, 64 rows), one workgroup of eight waves per compute unit, three at
+// d = 64: they pay where the tiles of their rows fill the units about once, where 128-row tiles of four waves leave
+// half the waves of a unit out and the key split reads K and V two to four times as often.  us, replays of a graph of
+// thirty calls; heads x keys (g, j): the best of the others / 39 / 40
+//   d = 128          24 x 500 (384)    10.5 / 12.6 / 10.1      32 x 350 (352)     8.9 / 10.9 /  8.9    12 x 1151 (432)    18.6 / 20.4 / 16.0
+//                    8 x 1120 (280)    15.0 / 19.3 / 14.4      24 x 624 (480)    13.3 / 14.3 / 11.5    16 x 535 (272)     10.4 / 13.0 / 10.4
+//                    16 x 1028 (j 144) 22.9 / 20.0 / 28.3      8 x 2183 (j 144)  40.5 / 33.2 / 47.4    12 x 2625 (j 252)  53.7 / 47.4 / 58.9
+//                    48 x 450 (j 192)  14.4 / 13.8 / 19.3      64 x 499 (j 256)  15.9 / 16.1 / 20.5    16 x 2080 (j 272)  45.6 / 65.5 / 68.3
+//   d = 128, causal  32 x 661 (672)    14.9 / 15.1 / 19.3      32 x 727 (736)    18.1 / 16.6 / 21.0    32 x 960 (960)     21.7 / 19.2 / 25.0
+//                    12 x 1923 (732)   28.3 / 29.4 / 32.9      8 x 3394 (856)    43.9 / 46.7 / 44.2    6 x 5374 (1008)    75.4 / 71.5 / 78.6
+//                    12 x 3278 (1236)  59.6 / 48.2 / 54.3      24 x 1575 (1200)  32.5 / 30.8 / 33.9    24 x 2043 (1536)   43.1 / 48.9 / 45.1
+//   d = 64           8 x 1074 (272)     9.7 / 15.0 / 10.0      16 x 999 (512)    10.3 / 14.7 /  9.9    2 x 5390 (338)     33.0 / 54.2 / 30.8
+//                    24 x 1009 (768)   15.4 / 15.0 / 15.6      48 x 553 (864)    11.1 / 11.1 / 11.5    6 x 4849 (912)     56.8 / 51.7 / 50.4
+//                    16 x 1916 (960)   25.9 / 24.1 / 23.9      16 x 2221 (1120)  33.4 / 39.9 / 38.0
+//   d = 64, causal   16 x 1376 (688)   11.2 / 17.7 / 12.0      8 x 3002 (752)    20.9 / 31.8 / 20.8    16 x 1885 (944)    19.7 / 22.8 / 16.9
+//                    24 x 1429 (1080)  19.4 / 18.9 / 16.3      6 x 7550 (1416)   71.7 / 75.4 / 61.0    32 x 1755 (1760)   26.7 / 26.1 / 25.8
+//                    6 x 11620 (2184)  142.5 / 138 / 129.7     48 x 1306 (1968)  21.7 / 23.1 / 23.8    64 x 991 (1984)    19.0 / 19.4 / 21.1
+// With heads on few XCDs eight waves (38) gain more than four (37), measured in the same way: d = 64 8 x 427 (112) 5.5 / 5.3, 12 x 224
+// (84) 4.3 / 4.5; causal 8 x 199 4.3 / 4.2, 8 x 1957 (496) 12.5 / 11.2, 3 x 3663 (345) 17.5 / 16.0, 8 x 2076 (520) 13.3 / 13.1; d = 128 causal
+// 4 x 2085 (264) 17.4 / 15.1, 4 x 2682 (336) 21.1 / 19.8, 4 x 2871 (360) 22.5 / 22.6; d = 128 6 x 1094 (210) 11.5 / 10.7, 6 x 1277 (240) 11.9 / 14.3.
+constexpr int kKeySplit4 = 37, kKeySplit8 = 38, kGroups2 = 39, kGroups4 = 40, kRows128 = 1;
 
 static int choose_variant(long long heads, int N, int d, int causal) {
     const long long g = heads * ((N + 31LL) / 32), j = heads * ((N + 127LL) / 128);
     const int most = d == 128 ? (!causal ? 512 : N < 768 ? 736 : N < 1024 ? 1056 : 1152)
                               : !causal ? (N < 640 ? 704 : 768) : N < 600 ? 960 : N < 768 ? 1280 : N < 1200 ? 1440 : 1536;
-    const int alone = causal && N >= 6000 ? (N >= 12000 ? 512 : 384) : 256;  // the eight-wave form's line
-    if (g <= most) return N >= 512 && g <= alone ? kKeySplit8 : kKeySplit4;
+    // the wave groups
+    if (d == 128 && !causal) {
+        if (N >= 400 && g > 256 && g <= 512) return kGroups4;
+        if (N >= 400 && g > 512 && j <= 256) return kGroups2;
+    } else if (d == 128) {
+        if (N < 1500 ? N >= 300 && g > 700 && j <= 256 : g > 950 && g <= 1400) return kGroups2;
+    } else if (!causal) {
+        if (N >= 960 && N < 12000 && g > 300 && g <= 700) return kGroups4;
+        if (N >= 700 && (N >= 960 ? g > 700 : g > most) && j <= 256) return N >= 1500 ? kGroups4 : kGroups2;
+    } else if (N >= 1000 && g > 850 && g <= (N < 1250 ? 1500 : N < 4000 ? 1800 : 2200)) {
+        return kGroups4;
+    }
+    // the key split: eight waves up to the line `alone`
+    const int alone = causal && N >= 6000 ? (N >= 12000 ? 512 : 384)
+                      : causal && d == 64 && N >= 1200 && N <= 5000 ? 512
+                      : causal && d == 128 && N >= 2000 && N <= 5500 ? 352 : !causal && d == 128 ? 224 : 256;
+    if (g <= most) return N >= (d == 128 ? 512 : causal ? 160 : 400) && g <= alone ? kKeySplit8 : kKeySplit4;
     if (d == 128) return (causal ? j <= 576 : j <= 256 || (j > 512 && j <= 640)) ? kRows128 : kDefaultD128;
     return j > (causal ? 755 : 512) ? kDefaultD64Long : kDefaultD64Short;
 }

@@ -276,11 +276,13 @@ struct Knobs {
     static constexpr int LDPOS = LDPOS_;  // PIPE 3: where a wave issues its four tile loads of an iteration: 0 = all after the
                                           // barrier, 1 = after MFMA slots 3, 11, 19, 27, 2 = after slots that depend on the wave;
                                           // PIPE 1: 1 = one tile further ahead (three buffers); PIPE 0: 1 = key split, every wave
-                                          // loads tiles of its own
+                                          // loads tiles of its own, 2 = wave groups (ILV 0: two, 1: four)
     static constexpr bool KEYSPLIT = PIPE == 0 && LDPOS == 1;
-    static constexpr int BM = 32 * QB * (KEYSPLIT ? 1 : NW);  // query rows of a workgroup
+    static constexpr bool GROUPS = PIPE == 0 && LDPOS == 2;
+    static constexpr int KG = KEYSPLIT ? NW : GROUPS ? 2 << ILV : 1;  // wave groups that split the keys
+    static constexpr int BM = 32 * QB * NW / KG;                     // query rows of a workgroup
     // second argument of the launch bounds: waves per SIMD
-    static constexpr int WAVES = KEYSPLIT ? OCC * NW / 4 : OCC;
+    static constexpr int WAVES = KG > 1 ? OCC * NW / 4 : OCC;
 };
 
 template <class T, int D, bool CAUSAL, class KN>
@@ -295,13 +297,15 @@ __global__ __launch_bounds__(KN::NW * 64, KN::WAVES) void attn_fwd_kernel(
     // ONE workgroup barrier per tile (see there).  Layout then K0 K1 K2 V0 V1 V2, so that the
     // immediate offsets of the K reads and of the V reads each stay inside their 64 KB.
     constexpr bool NB3 = PIPE == 1 && LDPOS == 1;
-    constexpr bool KEYSPLIT = KN::KEYSPLIT;
+    constexpr bool KEYSPLIT = KN::KEYSPLIT, GROUPS = KN::GROUPS;
+    constexpr int KG = KN::KG;
     constexpr int NB = NB3 ? 3 : 2;  // K buffers and V buffers in LDS
     constexpr int NT = NW * 64;
     constexpr int BM = KN::BM;
     constexpr int KS = D / 16;       // k-steps of the first contraction
     constexpr int DT = D / 32;       // 32-wide d tiles of O^T
-    constexpr int KT = BN / 32;      // 32-key sub-tiles of one K/V tile
+    constexpr int KT = (GROUPS ? BN / KG : BN) / 32;  // 32-key sub-tiles of one K/V tile, as far as one wave works on them
+    constexpr int BNW = KT * 32;     // keys of a tile that one wave works on
     constexpr int CPR = D / 8;       // 16-byte chunks per row
     constexpr int RB = D * 2;        // bytes per row
     constexpr int TILE_CHUNKS = BN * CPR;
@@ -318,10 +322,15 @@ __global__ __launch_bounds__(KN::NW * 64, KN::WAVES) void attn_fwd_kernel(
     // like a K tile of BM rows, and each wave reads its fragments from there.
     // (Also for the free-running order at d = 64, where the staging area fits next to the tiles
     // of three workgroups per compute unit; at d = 128 two such workgroups would need 192 KB.)
-    constexpr bool QSTAGE = LDP == 1 && QB == 1 && (PIPE == 1 || (PIPE == 0 && D == 64));
+    constexpr bool QSTAGE = LDP == 1 && QB == 1 && (PIPE == 1 || (PIPE == 0 && (D == 64 || GROUPS)));
     // (key split: K and V tile of wave 0, of wave 1 ..., the Q rows, then every wave's row maxima and sums)
-    __shared__ __attribute__((aligned(256))) u32x4 smem[KEYSPLIT ? NW * 2 * TILE_CHUNKS + BM * CPR + NW * BM / 2 : 2 * NB * TILE_CHUNKS + (QSTAGE ? BM * CPR : 0)];  // K0 V0 K1 V1 (three buffers: K0 K1 K2 V0 V1 V2), then the Q staging area
+    // (wave groups: as the others, or their sums and statistics, whichever is more)
+    constexpr int SUMS = GROUPS ? KG * BM * D * 4 : 0;
+    constexpr int PLAIN_CHUNKS = 2 * NB * TILE_CHUNKS + (QSTAGE ? BM * CPR : 0), SUM_CHUNKS = GROUPS ? (SUMS + KG * BM * 8) / 16 : 0;
+    __shared__ __attribute__((aligned(256))) u32x4 smem[KEYSPLIT ? NW * 2 * TILE_CHUNKS + BM * CPR + NW * BM / 2 : PLAIN_CHUNKS > SUM_CHUNKS ? PLAIN_CHUNKS : SUM_CHUNKS];  // K0 V0 K1 V1 (three buffers: K0 K1 K2 V0 V1 V2), then the Q staging area
     char* const smem_b = reinterpret_cast<char*>(smem);
+    // key split: where the Q rows are; it and the wave groups: where the row statistics go (the groups' over the Q rows, which are in registers by then)
+    constexpr int Q_OFF = NW * 2 * TILE_BYTES, STAT_OFF = KEYSPLIT ? Q_OFF + BM * RB : SUMS > 2 * NB * TILE_BYTES ? SUMS : 2 * NB * TILE_BYTES;
 
     auto k_off = [](int b) { return NB3 ? b * TILE_BYTES : b * 2 * TILE_BYTES; };                       // K buffer b, bytes from the start of LDS
     auto v_off = [](int b) { return NB3 ? (NB + b) * TILE_BYTES : b * 2 * TILE_BYTES + TILE_BYTES; };  // V buffer b
@@ -334,7 +343,7 @@ __global__ __launch_bounds__(KN::NW * 64, KN::WAVES) void attn_fwd_kernel(
     const int c = lane & 31;
 
     auto item_of_round = [&](int round, int& bh, int& qt) __attribute__((always_inline)) -> bool {
-        return schedule_item(p.grid, (int)blockIdx.x, p.BH, p.nqt, round, bh, qt, CAUSAL, KEYSPLIT);
+        return schedule_item(p.grid, (int)blockIdx.x, p.BH, p.nqt, round, bh, qt, CAUSAL, KG > 1);
     };
     const int N = p.N;
     // binary16 only: a finite result above the largest finite binary16 value is stored as that
@@ -353,7 +362,7 @@ __global__ __launch_bounds__(KN::NW * 64, KN::WAVES) void attn_fwd_kernel(
         // Row block of this wave inside the query tile.  Waves w and w + NW/2 share a SIMD; under a
         // causal mask the interleaved order (PIPE 3) gives them the blocks s and NW-1-s, so every SIMD
         // gets the same number of visible keys on the diagonal tiles.
-        const int rblk = KEYSPLIT ? 0 : (PIPE == 3 && CAUSAL) ? (wave < NW / 2 ? wave : NW + NW / 2 - 1 - wave) : wave;
+        const int rblk = KG > 1 ? wave % (NW / KG) : (PIPE == 3 && CAUSAL) ? (wave < NW / 2 ? wave : NW + NW / 2 - 1 - wave) : wave;
         const int qw0 = q0 + rblk * (32 * QB);  // first query row of this wave
         const int qw_last = qw0 + 32 * QB - 1;  // causal: tile j is active for this wave iff j*BN <= qw_last
 
@@ -396,7 +405,11 @@ __global__ __launch_bounds__(KN::NW * 64, KN::WAVES) void attn_fwd_kernel(
         // key tiles this workgroup visits
         const int kend = CAUSAL ? min(N, q0 + BM) : N;  // keys [0, kend)
         const int nkt = (kend + BN - 1) / BN;
-        auto tile_active = [&](int j) __attribute__((always_inline)) { return j < nkt && (!CAUSAL || j * BN <= qw_last); };
+        const int kgrp = wave / (NW / KG);  // (wave groups: its 32 keys of every tile)
+        auto tile_active = [&](int j) __attribute__((always_inline)) {
+            if constexpr (GROUPS) return j * BN + kgrp * BNW <= (CAUSAL ? min(qw_last, N - 1) : N - 1);
+            return j < nkt && (!CAUSAL || j * BN <= qw_last);
+        };
 
         // ---- per-lane LDS read offsets (bytes inside one K or V tile), loop invariant.
         // K: lane reads row (kt*32 + c), logical chunk (2*ks + g); moving kt by one adds
@@ -514,7 +527,7 @@ __global__ __launch_bounds__(KN::NW * 64, KN::WAVES) void attn_fwd_kernel(
             static_assert(QB == 1 || !QSTAGE, "one 32-row block per wave");
             // (the offset is made opaque here: otherwise the compiler forms the eight addresses
             // once, ahead of the item loop, and spills them)
-            int mine = 2 * NB * TILE_BYTES + wave * (32 * RB);
+            int mine = 2 * NB * TILE_BYTES + rblk * (32 * RB);
             asm volatile("" : "+s"(mine));
             const unsigned flip = p.qmode == 1 ? 0x80008000u : 0u, keep = p.qmode == 2 ? 0u : 0xffffffffu;
 #pragma unroll
@@ -614,7 +627,7 @@ __global__ __launch_bounds__(KN::NW * 64, KN::WAVES) void attn_fwd_kernel(
         // (The scaled reference is formed as a fused multiply-add with 0, which is the product: with a plain one the
         // compiler orders the free-running loop differently, 298 us instead of 288 at 1 x 4 heads x 16384 keys, d = 64.)
         auto mask = [&](f32x16(&s)[QB][KT], int k0) __attribute__((always_inline)) {  // keys past the end, and keys after the query
-            const bool need_mask = (k0 + BN > N) || (CAUSAL && (k0 + BN - 1 > qw0));
+            const bool need_mask = (k0 + BNW > N) || (CAUSAL && (k0 + BNW - 1 > qw0));
             if (need_mask) {
 #pragma unroll
                 for (int qb = 0; qb < QB; ++qb) {
@@ -704,7 +717,7 @@ __global__ __launch_bounds__(KN::NW * 64, KN::WAVES) void attn_fwd_kernel(
                 // all its queries (tile 0: key 0; key split: key tile * 32, no later than the rows).
                 // In a wave's first tile m_use = -inf and alpha = exp2(-inf) = 0.
                 const float alpha = __builtin_amdgcn_exp2f((m_use[qb] - m_new) * p.scale_l2);
-                if constexpr (KEYSPLIT) {
+                if constexpr (KG > 1) {
                     const bool drop = no_weight(alpha, m_use[qb], p.scale_l2);  // (O of a lane holds the keys of both halves of the wave, its l does not)
                     if (__builtin_amdgcn_ballot_w64(drop) != 0) {
                         l_run[qb] = drop ? 0.f : l_run[qb];
@@ -837,6 +850,79 @@ __global__ __launch_bounds__(KN::NW * 64, KN::WAVES) void attn_fwd_kernel(
         f32x16 s[QB][KT];
         u32x4 pk[QB][KT][2];
 
+        // The results of the KG wave groups meet: O as [BM][D] floats over the tiles, a group behind the other (16-byte
+        // chunk k of row r at chunk k ^ r), and the row statistics.
+        auto merge = [&]() __attribute__((always_inline)) {
+            constexpr int CPF = D / 4;  // 16-byte chunks per row of floats
+            constexpr int PART = BM * D * 4;
+            static_assert(KG == 1 || KG * PART <= STAT_OFF, "the sums end ahead of the statistics");
+            int te = tid;  // (opaque: the addresses below are formed here, not ahead of the item loop)
+            asm volatile("" : "+v"(te));
+            float* const stats = reinterpret_cast<float*>(smem_b + STAT_OFF);  // per group: BM maxima, BM sums
+            {
+                const float l_tot = xhalf_sum(l_run[0]);
+                const int ce = te & 31, ge = (te >> 5) & 1;
+#pragma unroll
+                for (int dt = 0; dt < DT; ++dt)
+#pragma unroll
+                    for (int v4 = 0; v4 < 4; ++v4)
+                        *reinterpret_cast<f32x4*>(smem_b + kgrp * PART + (rblk * 32 + ce) * (D * 4) + (((dt * 8 + v4 * 2 + ge) ^ (ce & (CPF - 1))) * 16)) =
+                            f32x4{o[0][dt][4 * v4], o[0][dt][4 * v4 + 1], o[0][dt][4 * v4 + 2], o[0][dt][4 * v4 + 3]};
+                float* const stat = stats + kgrp * (2 * BM) + rblk * 32;
+                if (ge == 0) stat[ce] = m_use[0], stat[BM + ce] = l_tot;
+            }
+            __syncthreads();
+            // D / 16 columns (D / 64 chunks of floats) per thread, 16 threads per row
+            for (int e = te; e < 16 * BM; e += NT) {
+                const int row = e >> 4, j = e & 15;
+                const float* const stat = stats + row;
+                float m = stat[0], f[KG], l = 0.f;
+#pragma unroll
+                for (int w = 1; w < KG; ++w) m = fmaxf(m, stat[w * (2 * BM)]);
+                f32x4 x[D / 64];
+#pragma unroll
+                for (int q = 0; q < D / 64; ++q) x[q] = f32x4{0.f, 0.f, 0.f, 0.f};
+                auto part = [&](int w, int q) __attribute__((always_inline)) -> f32x4 {
+                    return *reinterpret_cast<const f32x4*>(smem_b + w * PART + row * (D * 4) + (((j * (D / 64) + q) ^ (row & 31 & (CPF - 1))) * 16));
+                };
+#pragma unroll
+                for (int w = 0; w < KG; ++w) {  // (a group without tiles: m = -inf, weight 0; group 0 has tile 0)
+                    f[w] = __builtin_amdgcn_exp2f((stat[w * (2 * BM)] - m) * p.scale_l2);
+                    l += f[w] * stat[w * (2 * BM) + BM];
+#pragma unroll
+                    for (int q = 0; q < D / 64; ++q) x[q] += f[w] * part(w, q);
+                }
+                bool odd = l != l;
+#pragma unroll
+                for (int q = 0; q < D / 64; ++q)
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) odd = odd || x[q][i] != x[q][i];
+                if (__builtin_amdgcn_ballot_w64(odd) != 0) {  // rare: once more, without the sums that weigh nothing
+                    l = 0.f;
+#pragma unroll
+                    for (int q = 0; q < D / 64; ++q) x[q] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll 1
+                    for (int w = 0; w < KG; ++w) {
+                        const float mw = stat[w * (2 * BM)], lw = stat[w * (2 * BM) + BM], fw = __builtin_amdgcn_exp2f((mw - m) * p.scale_l2);
+                        if (no_weight(fw, mw, p.scale_l2)) continue;
+                        l += fw * lw;
+#pragma unroll
+                        for (int q = 0; q < D / 64; ++q) x[q] += fw * part(w, q);
+                    }
+                }
+                const float inv = 1.0f / l;
+                if (q0 + row < N) {
+                    uint16_t* const dst = p.out + head_off + (size_t)(q0 + row) * D + j * (D / 16);
+                    if constexpr (D == 128)
+                        *reinterpret_cast<u32x4*>(dst) = u32x4{T::pack2(x[0][0] * inv, x[0][1] * inv), T::pack2(x[0][2] * inv, x[0][3] * inv),
+                                                               T::pack2(x[1][0] * inv, x[1][1] * inv), T::pack2(x[1][2] * inv, x[1][3] * inv)};
+                    else
+                        *reinterpret_cast<u32x2*>(dst) = u32x2{T::pack2(x[0][0] * inv, x[0][1] * inv), T::pack2(x[0][2] * inv, x[0][3] * inv)};
+                    if (j == 0) p.lse[(size_t)bh * N + q0 + row] = m * p.scale + __logf(l);
+                }
+            }
+        };
+
         if constexpr (KEYSPLIT) {
             // Key split, for launches with fewer query tiles than compute units: all waves of a workgroup
             // take the same 32 query rows, and wave w the key tiles w, w + NW, ... (32 keys each),
@@ -879,7 +965,6 @@ __global__ __launch_bounds__(KN::NW * 64, KN::WAVES) void attn_fwd_kernel(
             };
             auto load_k = [&](int t) __attribute__((always_inline)) { load_tile(Kh, t, lds_k, yes); };
             auto load_v = [&](int t) __attribute__((always_inline)) { load_tile(Vh, t, lds_v, no); };
-            constexpr int Q_OFF = NW * 2 * TILE_BYTES;
 #pragma unroll
             for (int i = 0; i < (PPT + NW - 1) / NW; ++i) {
                 const int piece = i * NW + wave;  // the waves share the Q rows; (uniform) & 3 picks the offset
@@ -947,75 +1032,46 @@ __global__ __launch_bounds__(KN::NW * 64, KN::WAVES) void attn_fwd_kernel(
             }
             asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // (the requests past the end)
 
-            // The waves' results meet: O as [32][D] floats over the wave's own tiles (16-byte chunk k of row r
-            // at chunk k ^ r), the row statistics behind Q.
-            constexpr int CPF = D / 4;  // 16-byte chunks per row of floats
-            constexpr int STAT_OFF = Q_OFF + BM * RB;
-            int te = tid;  // (opaque: the addresses below are formed here, not ahead of the item loop)
-            asm volatile("" : "+v"(te));
-            {
-                const float l_tot = xhalf_sum(l_run[0]);
-                const int ce = te & 31, ge = (te >> 5) & 1;
-#pragma unroll
-                for (int dt = 0; dt < DT; ++dt)
-#pragma unroll
-                    for (int v4 = 0; v4 < 4; ++v4)
-                        *reinterpret_cast<f32x4*>(smem_b + own + ce * (D * 4) + (((dt * 8 + v4 * 2 + ge) ^ (ce & (CPF - 1))) * 16)) =
-                            f32x4{o[0][dt][4 * v4], o[0][dt][4 * v4 + 1], o[0][dt][4 * v4 + 2], o[0][dt][4 * v4 + 3]};
-                float* const stat = reinterpret_cast<float*>(smem_b + STAT_OFF) + wave * 64;
-                if (ge == 0) stat[ce] = m_use[0], stat[32 + ce] = l_tot;
-            }
+            merge();
+            break;  // (one item per workgroup)
+        } else if constexpr (GROUPS) {
+            // Wave groups, between the key split and the long launches: eight waves as KG groups of 8 / KG row
+            // blocks; every tile of BN keys comes to LDS once for all, and a group takes BN / KG of them.  Each wave
+            // keeps a reference maximum, a row sum and an O of its own, and the groups meet in LDS at the end, as
+            // the waves of the key split do.  Launches whose 128-row tiles go to four waves on some of the units
+            // (one wave per SIMD: 1500 clocks a tile of 64 keys at d = 64, against 1150 for two) get twice
+            // the waves on a row this way; against the key split a unit's loads are spread over two or four row blocks
+            // (that bound d = 128: 50 of the 64 bytes a clock).  d = 128, two groups: 16 x 1028 22.9 -> 20.0 us, 8 x 2183 40.5 ->
+            // 33.2; four: 12 x 1151 18.6 -> 16.0; d = 64 causal, four: 6 x 7550 71.7 -> 61.0.  One barrier per tile: the
+            // groups one cluster apart (ping-pong) are 5 to 60 % slower, 64-key shares need more registers than
+            // four waves per SIMD have at d = 64 and gain nothing at d = 128.
+            static_assert(LDP == 1 && QB == 1 && NW == 8, "eight waves, tiles straight to LDS");
+            auto step = [&](auto buf_c, int j) __attribute__((always_inline)) {
+                constexpr int BUF = decltype(buf_c)::value;
+                if (j + 1 < nkt) issue_tiles(j + 1, BUF ^ 1, j + 1, BUF ^ 1);
+                if (tile_active(j)) {
+                    mfma_stream(no, yes, buf_c, buf_c, pk, s);
+                    softmax_tile(s, pk, j * BN + kgrp * BNW);
+                    mfma_stream(yes, no, buf_c, buf_c, pk, s);
+                }
+                land_loads(BUF ^ 1, BUF ^ 1);
+                __syncthreads();
+            };
+            request_q();
+            issue_k(0, 0);
+            issue_v(0, 0);
+            land_loads(0, 0);
             __syncthreads();
-            // D / 16 columns (D / 64 chunks of floats) per thread of eight waves, 16 threads per row; with four
-            // waves in two passes
-            for (int e = te; e < 512; e += NT) {
-                const int row = e >> 4, j = e & 15;
-                const float* const stat = reinterpret_cast<const float*>(smem_b + STAT_OFF) + row;
-                float m = stat[0], f[NW], l = 0.f;
+            read_q();
 #pragma unroll
-                for (int w = 1; w < NW; ++w) m = fmaxf(m, stat[w * 64]);
-                f32x4 x[D / 64];
+            for (int ks = 0; ks < KS; ++ks) koff[ks] += kgrp * BNW * RB;
 #pragma unroll
-                for (int q = 0; q < D / 64; ++q) x[q] = f32x4{0.f, 0.f, 0.f, 0.f};
-                auto part = [&](int w, int q) __attribute__((always_inline)) -> f32x4 {
-                    return *reinterpret_cast<const f32x4*>(smem_b + w * 2 * TILE_BYTES + row * (D * 4) + (((j * (D / 64) + q) ^ (row & (CPF - 1))) * 16));
-                };
-#pragma unroll
-                for (int w = 0; w < NW; ++w) {  // (a wave without tiles: m = -inf, weight 0; wave 0 has tile 0)
-                    f[w] = __builtin_amdgcn_exp2f((stat[w * 64] - m) * p.scale_l2);
-                    l += f[w] * stat[w * 64 + 32];
-#pragma unroll
-                    for (int q = 0; q < D / 64; ++q) x[q] += f[w] * part(w, q);
-                }
-                bool odd = l != l;
-#pragma unroll
-                for (int q = 0; q < D / 64; ++q)
-#pragma unroll
-                    for (int i = 0; i < 4; ++i) odd = odd || x[q][i] != x[q][i];
-                if (__builtin_amdgcn_ballot_w64(odd) != 0) {  // rare: once more, without the sums that weigh nothing
-                    l = 0.f;
-#pragma unroll
-                    for (int q = 0; q < D / 64; ++q) x[q] = f32x4{0.f, 0.f, 0.f, 0.f};
-#pragma unroll 1
-                    for (int w = 0; w < NW; ++w) {
-                        const float mw = stat[w * 64], lw = stat[w * 64 + 32], fw = __builtin_amdgcn_exp2f((mw - m) * p.scale_l2);
-                        if (no_weight(fw, mw, p.scale_l2)) continue;
-                        l += fw * lw;
-#pragma unroll
-                        for (int q = 0; q < D / 64; ++q) x[q] += fw * part(w, q);
-                    }
-                }
-                const float inv = 1.0f / l;
-                if (q0 + row < N) {
-                    uint16_t* const dst = p.out + head_off + (size_t)(q0 + row) * D + j * (D / 16);
-                    if constexpr (D == 128)
-                        *reinterpret_cast<u32x4*>(dst) = u32x4{T::pack2(x[0][0] * inv, x[0][1] * inv), T::pack2(x[0][2] * inv, x[0][3] * inv),
-                                                               T::pack2(x[1][0] * inv, x[1][1] * inv), T::pack2(x[1][2] * inv, x[1][3] * inv)};
-                    else
-                        *reinterpret_cast<u32x2*>(dst) = u32x2{T::pack2(x[0][0] * inv, x[0][1] * inv), T::pack2(x[0][2] * inv, x[0][3] * inv)};
-                    if (j == 0) p.lse[(size_t)bh * N + q0 + row] = m * p.scale + __logf(l);
-                }
+            for (int dt = 0; dt < DT; ++dt) voff[dt] += kgrp * BNW * RB;
+            for (int j = 0; j < nkt; j += 2) {
+                step(c0, j);
+                if (j + 1 < nkt) step(c1, j + 1);
             }
+            merge();
             break;  // (one item per workgroup)
         } else if constexpr (PIPE == 0) {
             // Plain order: every tile is loaded one iteration ahead; per tile S, softmax, PV.
@@ -1588,8 +1644,8 @@ __global__ __launch_bounds__(KN::NW * 64, KN::WAVES) void attn_fwd_kernel(
         // tiles are dead by now) and writes whole rows, 16 bytes per lane, 1 KB contiguous
         // per instruction.  Chunk k of row r sits at chunk k ^ (r mod CPR): conflict-free
         // row-wise reads, two-way conflicts on the column-wise writes.
-        if constexpr (!KEYSPLIT) {
-        static_assert(KEYSPLIT || BM * RB <= 4 * TILE_BYTES, "the O tile must fit into the K/V buffers");
+        if constexpr (KG == 1) {
+        static_assert(KG > 1 || BM * RB <= 4 * TILE_BYTES, "the O tile must fit into the K/V buffers");
         // (interleaved order: the loads of the last iteration, past the end of the keys, are still in flight)
         if constexpr (PIPE == 3) asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
         __syncthreads();  // every wave has finished reading the last K/V tiles

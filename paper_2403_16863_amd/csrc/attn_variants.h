@@ -73,7 +73,9 @@ struct KernelSet {
 
 #define ATTN_VARIANTS_8(BOTH, D64, D128) \
     BOTH(32, 4, 1, 2, 1, 0, 4, 0, 0, 1) /* 37, 38: free-running, the waves split the keys instead of the queries */ \
-    BOTH(32, 8, 1, 1, 1, 0, 4, 0, 0, 1)
+    BOTH(32, 8, 1, 1, 1, 0, 4, 0, 0, 1) \
+    BOTH(64, 8, 1, 1, 1, 0, 4, 0, 0, 2) /* 39, 40: two wave groups of 128 query rows, four of 64, that split the keys of every tile */ \
+    BOTH(128, 8, 1, 1, 1, 0, 4, 0, 1, 2)
 
 #define ATTN_ALL_VARIANTS(BOTH, D64, D128) \
     ATTN_VARIANTS_0(BOTH, D64, D128) \

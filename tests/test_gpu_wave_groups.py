@@ -1,0 +1,107 @@
+"""The wave groups of the free-running order (variants whose groups of waves split the keys of every tile): the choice,
+and the variants against the fp64 oracle where they can go wrong: fewer keys than groups, a key or row past a
+group's or a tile's share, groups that see their first key late or never, keys masked by their scores."""
+import numpy as np
+import pytest
+
+import paper_2403_16863_amd as A
+from oracle import ref
+from paper_2403_16863_amd import inputs as I
+
+GROUPS = [v for v in range(A.attn_num_variants()) if "pipe=0" in A.attn_variant_desc(v) and "ldpos=2" in A.attn_variant_desc(v)]
+TWO, FOUR = 39, 40
+
+
+def test_the_groups_rows_and_grids():
+    assert GROUPS == [TWO, FOUR]
+    for v, rows in ((TWO, 128), (FOUR, 64)):
+        assert f"bm={rows} " in A.attn_variant_desc(v)
+        for H, N in ((3, 1000), (8, 129), (1, 1)):
+            assert A.attn_schedule_grid(v, 256, 1, H, N) == H * -(-N // rows)     # one workgroup per item
+
+
+@pytest.mark.parametrize("heads,N,d,causal,want", [
+    (20, 399, 128, False, 37), (20, 400, 128, False, FOUR), (8, 1024, 128, False, 37), (8, 1025, 128, False, FOUR),
+    (16, 1024, 128, False, FOUR), (16, 1025, 128, False, TWO), (16, 2048, 128, False, TWO), (16, 2049, 128, False, 36),
+    (28, 800, 128, True, 37), (29, 800, 128, True, TWO), (64, 300, 128, True, 37), (71, 299, 128, True, 37), (71, 300, 128, True, TWO),
+    (20, 1500, 128, True, 37), (21, 1500, 128, True, TWO), (29, 1500, 128, True, TWO), (30, 1500, 128, True, 1),
+    (10, 960, 64, False, 37), (11, 960, 64, False, FOUR), (11, 959, 64, False, 37), (1, 11999, 64, False, FOUR), (1, 12000, 64, False, 37),
+    (23, 960, 64, False, FOUR), (24, 960, 64, False, TWO), (21, 1500, 64, False, FOUR), (22, 1500, 64, False, 3), (40, 700, 64, False, TWO),
+    (40, 699, 64, False, 3),
+    (26, 1000, 64, True, 37), (27, 1000, 64, True, FOUR), (27, 992, 64, True, 37), (46, 1000, 64, True, FOUR), (47, 1000, 64, True, 3),
+    (45, 1250, 64, True, FOUR), (46, 1250, 64, True, 3), (17, 4000, 64, True, FOUR), (18, 4000, 64, True, 3),
+])
+def test_both_sides_of_every_line(heads, N, d, causal, want):
+    for dtype in (A.ATTN_F16, A.ATTN_BF16):
+        assert A.attn_choose_variant(1, heads, N, d, dtype, causal) == want
+        assert A.attn_variant_supported(want, d, dtype, causal)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("causal", [False, True], ids=["full", "causal"])
+@pytest.mark.parametrize("dtype", [I.F16, I.BF16], ids=["f16", "bf16"])
+@pytest.mark.parametrize("d", [64, 128])
+def test_groups_against_the_oracle(d, dtype, causal):
+    from gpu_util import check, run_gpu
+    for N in (1, 31, 33, 63, 65, 96, 127, 129, 193, 257, 385, 600):
+        for kind in ("normal", "rising_scores", "peaked"):
+            if kind == "normal":
+                qb, kb, vb = I.make_qkv(I.Workload("groups", 1, 3, N, d, causal, dtype, qk_sigma=2.0), seed=N)
+            else:
+                qb, kb, vb = I.make_adversarial(kind, 1, 3, N, d, dtype, seed=N)
+            for scale in (float(np.float32(d ** -0.5)), -0.1, 0.0):
+                O_ref, l_ref, _ = ref.attn_ref(qb, kb, vb, causal, float(np.float32(scale)), dtype)
+                out_scale = max(1.0, float(np.abs(I.bits_to_f64(vb, dtype)).max()))
+                for v in GROUPS:
+                    print(f"case {kind} N={N} d={d} causal={causal} dtype={dtype} scale={scale} variant={v}", flush=True)
+                    O, l = run_gpu(qb, kb, vb, causal, scale, dtype, variant=v)
+                    check(O, l, O_ref, l_ref, dtype, out_scale=out_scale, what=f"{kind} N={N} scale={scale} variant {v}")
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("causal", [False, True], ids=["full", "causal"])
+@pytest.mark.parametrize("d", [64, 128])
+def test_keys_masked_by_their_scores(d, causal):
+    """Scores of -inf, or so low that their scaled value is rounded by more than the range of fp32, in all keys that a
+    group meets first, or in all it ever meets: no weight."""
+    from gpu_util import check, run_gpu
+    for v, groups in ((TWO, 2), (FOUR, 4)):
+        N = 32 * 3 * groups + 5
+        share = np.arange(N) // 32
+        masks = [(f"group {w} never", share % groups == w) for w in range(groups)] + [(f"group {w} late", share == w) for w in range(groups)]
+        masks += [("all but the first share", share > 0), ("all but the last group", share % groups != groups - 1)]
+        w = I.Workload("masked", 1, 2, N, d, causal, I.BF16)
+        qb, kb, vb = I.make_qkv(w, seed=5)
+        one = I.f32_to_bits(np.ones(1, np.float32), I.BF16)[0]
+        for value in (-np.inf, -1e30, -1.5e30):
+            low = I.f32_to_bits(np.where((np.arange(N) & 4 == 0) & (value == -1.5e30), 2 * value, value).astype(np.float32), I.BF16)
+            for name, m in masks:
+                q, k = qb.copy(), kb.copy()
+                q[..., 0] = one
+                k[:, :, m, 0] = low[m]
+                seen = np.cumsum(~m) > 0 if causal else np.ones(N, bool)      # rows that see an unmasked key
+                print(f"case {name} value={value} N={N} d={d} causal={causal} variant={v}", flush=True)
+                O_ref, l_ref, _ = ref.attn_ref(q, k, vb, causal, float(np.float32(w.scale)), I.BF16)
+                O, l = run_gpu(q, k, vb, causal, w.scale, I.BF16, variant=v)
+                check(O[:, :, seen], l[:, :, seen], O_ref[:, :, seen], l_ref[:, :, seen], I.BF16, what=f"{name} {value} variant {v}")
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("B,H,N,d,causal,dtype", [
+    (1, 12, 1151, 128, False, I.F16),    # four groups, one workgroup per unit at most
+    (2, 8, 1500, 128, False, I.BF16),    # two
+    (1, 12, 3278, 128, True, I.BF16),    # two, by weight over groups of XCDs
+    (4, 4, 1900, 64, False, I.F16),      # four at d = 64, more than one workgroup per unit
+    (3, 11, 1291, 64, True, I.BF16),     # the padded grid, heads that divide by nothing
+])
+def test_attn_fwd_takes_the_groups(B, H, N, d, causal, dtype):
+    from gpu_util import check, run_gpu
+    w = I.Workload("groups", B, H, N, d, causal, dtype)
+    assert A.attn_choose_variant(B, H, N, d, dtype, causal) in GROUPS
+    qb, kb, vb = I.make_qkv(w, seed=N)
+    O, l = run_gpu(qb, kb, vb, causal, w.scale, dtype)
+    tiles = -(-N // 32)
+    rows = {bh * N + min(N - 1, 32 * t + (7 * t + 3 * bh) % 32) for bh in range(B * H) for t in range(tiles)}
+    rows = np.array(sorted(rows), dtype=np.int64)
+    O_ref, l_ref, _ = ref.attn_ref(qb, kb, vb, causal, w.scale, dtype, rows=rows)
+    check(O.reshape(-1, d)[rows], l.reshape(-1)[rows], O_ref, l_ref, dtype, what=w.label)
