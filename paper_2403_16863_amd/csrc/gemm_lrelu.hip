@@ -67,8 +67,12 @@ static int check_args(const void* a, const void* b, const void* c, int M, int N,
 // (alone: a stage of one tile, latency included; full: its share when the unit's tiles run side by
 // side; ends: prologue and epilogue).  The three numbers are fitted to 85 shapes over M 1 .. 8192, N
 // and K 64 .. 8192, ragged and whole, timed with every tile shape.  On 60 other shapes drawn from the same
-// ranges the model's choice is 1.4 % (mean) above the best of these seven, most of it the noise of calls of
+// ranges the model's choice is 1.4 % (mean) above the best of the other seven, most of it the noise of calls of
 // 3.5 us (above 5 us: 0.2 %, 8 % at most); always 32 x 32 tiles: 31 %.
+// (The 64 x 64 tile on eight waves, two groups of four that split K, came later; its numbers are from 36 to 144 tiles
+// with K from 2056 to 8200.  It pays while a unit has one tile: four waves there draw 60 to 65 GB/s, as much as one wave per SIMD
+// has LDS reads and loads in flight for, eight 83.  768 x 768 x 3072 14.8 -> 12.2 us, 533 x 1152 x 3976 18.8 -> 16.3, 3802 x 200 x
+// 2560 13.5 -> 12.9.  Rings of six and nine stages in place of three: nothing.)
 struct BlockShape {
     int bm, bn, bk, wk, threads, occ;
     float alone, full, ends;
@@ -83,6 +87,7 @@ static const BlockShape kBlocks[] = {
     block_shape<Block<32, 32, 32, 1, 1, 4, 4, 2>>(0.21f, 0.22f, 0.5f),
     block_shape<Block<32, 64, 64, 1, 2, 2, 3, 2>>(0.27f, 0.31f, 0.58f),
     block_shape<Block<64, 64, 64, 2, 2, 1, 3, 3>>(0.24f, 0.17f, 0.22f),
+    block_shape<Block<64, 64, 64, 2, 2, 2, 4, 1>>(0.40f, 0.f, 0.9f),
     block_shape<Block<64, 128, 64, 1, 4, 1, 3, 2>>(0.27f, 0.28f, 0.88f),
     block_shape<Block<128, 128, 64, 2, 4, 1, 4, 1>>(0.41f, 0.f, 0.9f),
     block_shape<Block<128, 256, 64, 2, 4, 1, 3, 1>>(0.64f, 0.f, 1.8f),
@@ -286,6 +291,9 @@ int gemm_lrelu_block_of(int M, int N, int K, int* bm, int* bn) {
     *bn = s.bn;
     return GEMM_OK;
 }
+
+// The threads of its workgroups (the same).
+int gemm_lrelu_block_threads_of(int M, int N, int K) { return M < 1 || N < 1 || K < 1 ? GEMM_EINVAL : gemm::choose_block(M, N, K).threads; }
 
 int gemm_lrelu_time(const void* a, const void* b, void* c, int M, int N, int K, float slope, int dtype, void* stream,
                     int variant_id, int warmup, int iters, float* ms_total) {
