@@ -600,6 +600,9 @@ constexpr int kDefaultD64Short = 3;
 //   d = 64, causal   16 x 1376 (688)   11.2 / 17.7 / 12.0      8 x 3002 (752)    20.9 / 31.8 / 20.8    16 x 1885 (944)    19.7 / 22.8 / 16.9
 //                    24 x 1429 (1080)  19.4 / 18.9 / 16.3      6 x 7550 (1416)   71.7 / 75.4 / 61.0    32 x 1755 (1760)   26.7 / 26.1 / 25.8
 //                    6 x 11620 (2184)  142.5 / 138 / 129.7     48 x 1306 (1968)  21.7 / 23.1 / 23.8    64 x 991 (1984)    19.0 / 19.4 / 21.1
+//                    24 x 1200 (912)   11.9 / 16.1 / 12.5      40 x 1100 (1400)  17.0 / 17.9 / 17.7
+// d = 64, causal, 37 / 3 / 18: 64 x 500 (1024)  8.8 / 10.5 / 10.5   128 x 300 (1280)  10.0 / 9.4 / 9.5   64 x 591 (1216)  14.0 / 13.6 / 13.3;  3 / 18:
+// 64 x 1024 (j 512)  19.5 / 19.2   128 x 512 (512)  13.4 / 13.1   96 x 767 (576)  16.8 / 15.8   48 x 1306 (528)  21.1 / 21.1.
 // With heads on few XCDs eight waves (38) gain more than four (37), measured in the same way: d = 64 8 x 427 (112) 5.5 / 5.3, 12 x 224
 // (84) 4.3 / 4.5; causal 8 x 199 4.3 / 4.2, 8 x 1957 (496) 12.5 / 11.2, 3 x 3663 (345) 17.5 / 16.0, 8 x 2076 (520) 13.3 / 13.1; d = 128 causal
 // 4 x 2085 (264) 17.4 / 15.1, 4 x 2682 (336) 21.1 / 19.8, 4 x 2871 (360) 22.5 / 22.6; d = 128 6 x 1094 (210) 11.5 / 10.7, 6 x 1277 (240) 11.9 / 14.3.
@@ -608,7 +611,7 @@ constexpr int kKeySplit4 = 37, kKeySplit8 = 38, kGroups2 = 39, kGroups4 = 40, kR
 static int choose_variant(long long heads, int N, int d, int causal) {
     const long long g = heads * ((N + 31LL) / 32), j = heads * ((N + 127LL) / 128);
     const int most = d == 128 ? (!causal ? 512 : N < 768 ? 736 : N < 1024 ? 1056 : 1152)
-                              : !causal ? (N < 640 ? 704 : 768) : N < 600 ? 960 : N < 768 ? 1280 : N < 1200 ? 1440 : 1536;
+                              : !causal ? (N < 640 ? 704 : 768) : N < 300 ? 960 : N < 600 ? 1100 : N < 768 ? 1280 : N < 1200 ? 1440 : 1536;
     // the wave groups
     if (d == 128 && !causal) {
         if (N >= 400 && g > 256 && g <= 512) return kGroups4;
@@ -618,7 +621,7 @@ static int choose_variant(long long heads, int N, int d, int causal) {
     } else if (!causal) {
         if (N >= 960 && N < 12000 && g > 300 && g <= 700) return kGroups4;
         if (N >= 700 && (N >= 960 ? g > 700 : g > most) && j <= 256) return N >= 1500 ? kGroups4 : kGroups2;
-    } else if (N >= 1000 && g > 850 && g <= (N < 1250 ? 1500 : N < 4000 ? 1800 : 2200)) {
+    } else if (N >= 1250 && g > 850 && g <= (N < 4000 ? 1800 : 2200)) {
         return kGroups4;
     }
     // the key split: eight waves up to the line `alone`
@@ -627,7 +630,7 @@ static int choose_variant(long long heads, int N, int d, int causal) {
                       : causal && d == 128 && N >= 2000 && N <= 5500 ? 352 : !causal && d == 128 ? 224 : 256;
     if (g <= most) return N >= (d == 128 ? 512 : causal ? 160 : 400) && g <= alone ? kKeySplit8 : kKeySplit4;
     if (d == 128) return (causal ? j <= 576 : j <= 256 || (j > 512 && j <= 640)) ? kRows128 : kDefaultD128;
-    return j > (causal ? 755 : 512) ? kDefaultD64Long : kDefaultD64Short;
+    return j > (!causal ? 512 : N >= 256 && N < 1600 ? 410 : 755) ? kDefaultD64Long : kDefaultD64Short;
 }
 
 int attn_choose_variant(int B, int H, int N, int d, int dtype, int causal) {

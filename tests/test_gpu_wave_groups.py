@@ -28,8 +28,11 @@ def test_the_groups_rows_and_grids():
     (10, 960, 64, False, 37), (11, 960, 64, False, FOUR), (11, 959, 64, False, 37), (1, 11999, 64, False, FOUR), (1, 12000, 64, False, 37),
     (23, 960, 64, False, FOUR), (24, 960, 64, False, TWO), (21, 1500, 64, False, FOUR), (22, 1500, 64, False, 3), (40, 700, 64, False, TWO),
     (40, 699, 64, False, 3),
-    (26, 1000, 64, True, 37), (27, 1000, 64, True, FOUR), (27, 992, 64, True, 37), (46, 1000, 64, True, FOUR), (47, 1000, 64, True, 3),
-    (45, 1250, 64, True, FOUR), (46, 1250, 64, True, 3), (17, 4000, 64, True, FOUR), (18, 4000, 64, True, 3),
+    (21, 1250, 64, True, 37), (22, 1250, 64, True, FOUR), (27, 1249, 64, True, 37),
+    (45, 1250, 64, True, FOUR), (46, 1250, 64, True, 18), (41, 1250, 64, True, FOUR), (17, 4000, 64, True, FOUR), (18, 4000, 64, True, 3),
+    # d = 64 causal: a higher line of the key split from 300 keys on, three workgroups per unit for short rows
+    (110, 300, 64, True, 37), (111, 300, 64, True, 3), (96, 299, 64, True, 37), (97, 299, 64, True, 3), (51, 1000, 64, True, 3),
+    (52, 1000, 64, True, 18), (206, 256, 64, True, 18), (206, 255, 64, True, 3),
 ])
 def test_both_sides_of_every_line(heads, N, d, causal, want):
     for dtype in (A.ATTN_F16, A.ATTN_BF16):
