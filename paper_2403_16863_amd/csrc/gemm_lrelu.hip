@@ -112,7 +112,7 @@ static const BlockShape& choose_block(int M, int N, int K) {
 // ---- few tiles and a long K: the workgroups split K as well, and a second kernel adds their parts.
 // A compute unit draws about 50 bytes a clock from memory however many loads it keeps in flight, so 128
 // tiles on 128 units read the weights at half the card's rate and three tiles at a hundredth.  The second
-// launch costs 2.5 us, so K has to be long.  Measured, whole / split, on one set of buffers and, in
+// launch costs 2.1 us, so K has to be long.  Measured, whole / split, on one set of buffers and, in
 // brackets, on sets that together exceed the last-level cache, us:
 //   32 x 32   4 x 72 x 8136       9.9 / 6.3 (13.7 / 6.6)     2 x 880 x 7528     11.8 / 6.8 (20.1 / 8.5)
 //             520 x 72 x 5192     7.7 / 7.7 (14.3 / 8.9)     222 x 280 x 4512    7.0 / 8.1 (13.4 / 9.1)
