@@ -627,7 +627,12 @@ __global__ __launch_bounds__(KN::NW * 64, KN::WAVES) void attn_fwd_kernel(
         // (The scaled reference is formed as a fused multiply-add with 0, which is the product: with a plain one the
         // compiler orders the free-running loop differently, 298 us instead of 288 at 1 x 4 heads x 16384 keys, d = 64.)
         auto mask = [&](f32x16(&s)[QB][KT], int k0) __attribute__((always_inline)) {  // keys past the end, and keys after the query
-            const bool need_mask = (k0 + BNW > N) || (CAUSAL && (k0 + BNW - 1 > qw0));
+            bool need_mask = (k0 + BNW > N) || (CAUSAL && (k0 + BNW - 1 > qw0));
+            // (The same in one comparison of scalars for the key split on eight waves under a causal mask.  There the compiler has
+            // all operands of the two in scalar registers and places their instructions between the last MFMAs of S, which costs the
+            // whole loop 2 to 5 % at d = 128: 1 x 5213 25.5 us, this way 24.4; 2 x 1816 12.6 and 12.0; the code without it is the
+            // faster one or equal for the other orders, which have other operands in vector registers.)
+            if constexpr (KEYSPLIT && NW == 8 && CAUSAL) need_mask = __builtin_amdgcn_readfirstlane(k0 + BNW) > min(N, qw0 + 1);
             if (need_mask) {
 #pragma unroll
                 for (int qb = 0; qb < QB; ++qb) {
