@@ -65,14 +65,32 @@ constexpr unsigned kBufferSize = 0x80000000u;
 
 // SPLIT: workgroup b computes the products of k range b / (ntm ntn) (kc values of k, a multiple of 64 WK) into its
 // part of the workspace, [range][M][N] floats; gemm_sum_kernel adds them.  `out` is C, or that workspace.
-// The arguments arrive in scalar registers (see Params in attn_kernel.h).
-typedef void (*BlockFn)(const char* a, const char* b, void* out, uint64_t m_n, uint64_t k_kc, float slope);
-inline uint64_t two(int low, int high) { return (unsigned)low | (uint64_t)(unsigned)high << 32; }
+// The arguments arrive in scalar registers (see Params in attn_kernel.h), packed into two vectors: a launch costs the host 20 ns
+// for every further argument, and calls that end sooner than the next launch can be made are bound by that.  Six
+// arguments 2.74 us a launch, these two 2.62, one struct, which is not preloaded, 2.61.
+typedef unsigned u32x8 __attribute__((ext_vector_type(8)));
+struct Arguments {
+    u32x8 pointers_m_n;   // A, B, `out`, M, N
+    u32x4 k_kc_slope;
+    Arguments(const void* a, const void* b, const void* out, int M, int N, int K, int kc, float slope) {
+        const uint64_t p[3] = {(uint64_t)a, (uint64_t)b, (uint64_t)out};
+        for (int i = 0; i < 3; ++i) pointers_m_n[2 * i] = (unsigned)p[i], pointers_m_n[2 * i + 1] = (unsigned)(p[i] >> 32);
+        pointers_m_n[6] = (unsigned)M, pointers_m_n[7] = (unsigned)N;
+        k_kc_slope = u32x4{(unsigned)K, (unsigned)kc, __builtin_bit_cast(unsigned, slope), 0u};
+    }
+};
+typedef void (*BlockFn)(u32x8 pointers_m_n, u32x4 k_kc_slope);
 
 template <class T, class BL, bool SPLIT = false>
 __global__ __launch_bounds__(BL::WM * BL::WN * BL::WK * 64, (BL::OCC * BL::WM * BL::WN * BL::WK + 3) / 4) void gemm_block_kernel(
-    const char* a, const char* b, void* out, uint64_t m_n, uint64_t k_kc, float slope) {
-    const int M = (int)m_n, N = (int)(m_n >> 32), K = (int)k_kc, kc = (int)(k_kc >> 32);
+    u32x8 pointers_m_n, u32x4 k_kc_slope) {
+    auto address = [&](int i) __attribute__((always_inline)) { return (uint64_t)pointers_m_n[2 * i + 1] << 32 | pointers_m_n[2 * i]; };
+    const char* const a = reinterpret_cast<const char*>(address(0));
+    const char* const b = reinterpret_cast<const char*>(address(1));
+    // (named global: of an address made of two numbers the compiler does not know it)
+    char __attribute__((address_space(1)))* const out = (char __attribute__((address_space(1)))*)address(2);
+    const int M = (int)pointers_m_n[6], N = (int)pointers_m_n[7], K = (int)k_kc_slope[0], kc = (int)k_kc_slope[1];
+    const float slope = __builtin_bit_cast(float, (unsigned)k_kc_slope[2]);
     constexpr int BM = BL::BM, BN = BL::BN, WM = BL::WM, WN = BL::WN, WK = BL::WK, NB = BL::NB;
     constexpr int NW = WM * WN, BK = BL::BK, KS = BK / 32;
     constexpr int TM = BM / WM, TN = BN / WN, MT = TM / 16, NT = TN / 16;
@@ -271,15 +289,15 @@ __global__ __launch_bounds__(BL::WM * BL::WN * BL::WK * 64, (BL::OCC * BL::WM * 
         const int m = m0 + wm * TM + mt * 16 + (lane & 15);
         if constexpr (SPLIT) {
             const int n = n0 + wn * TN + nt * 16 + g * 4;
-            float* const row = reinterpret_cast<float*>(out) + ((size_t)range * M + m) * N;
-            if (m < M && n < N) *reinterpret_cast<f32x4*>(row + n) = x;
-            if (m < M && n + 16 < N) *reinterpret_cast<f32x4*>(row + n + 16) = y;
+            auto* const row = (float __attribute__((address_space(1)))*)out + ((size_t)range * M + m) * N;
+            if (m < M && n < N) *(f32x4 __attribute__((address_space(1)))*)(row + n) = x;
+            if (m < M && n + 16 < N) *(f32x4 __attribute__((address_space(1)))*)(row + n + 16) = y;
             return;
         }
         const auto s0 = __builtin_amdgcn_permlane16_swap(T::pack2(act(x[0]), act(x[1])), T::pack2(act(y[0]), act(y[1])), false, false);
         const auto s1 = __builtin_amdgcn_permlane16_swap(T::pack2(act(x[2]), act(x[3])), T::pack2(act(y[2]), act(y[3])), false, false);
         const int n = n0 + wn * TN + nt * 16 + (g & 1) * 16 + (g >> 1) * 8;
-        if (m < M && n < N) *reinterpret_cast<u32x4*>(reinterpret_cast<uint16_t*>(out) + (size_t)m * N + n) = u32x4{s0[0], s1[0], s0[1], s1[1]};
+        if (m < M && n < N) *(u32x4 __attribute__((address_space(1)))*)(out + ((size_t)m * N + n) * 2) = u32x4{s0[0], s1[0], s0[1], s1[1]};
     };
     if constexpr (WK == 1) {
 #pragma unroll

@@ -146,9 +146,9 @@ static int launch_split(const Split& sp, const void* a, const void* b, void* c, 
                         void* stream, void* workspace) {
     const BlockShape& s = kBlocks[sp.shape];
     int ranges = sp.ranges;
-    uint64_t m_n = two(M, N), k_kc = two(K, sp.kc);
+    Arguments to(a, b, workspace, M, N, K, sp.kc, slope);
     unsigned chunks = (unsigned)((long long)M * N / 8);
-    void* args[] = {&a, &b, &workspace, &m_n, &k_kc, &slope};
+    void* args[] = {&to.pointers_m_n, &to.k_kc_slope};
     void* sum_args[] = {&workspace, &c, &ranges, &chunks, &slope};
     const void* const sum = dtype == GEMM_F16 ? (const void*)gemm_sum_kernel<Mfma16F16> : (const void*)gemm_sum_kernel<Mfma16BF16>;
     if (hipLaunchKernel((const void*)kSplitFns[sp.shape][dtype], dim3(cover(M, s.bm) * cover(N, s.bn) * ranges), dim3(s.threads), args, 0, (hipStream_t)stream) != hipSuccess ||
@@ -162,8 +162,8 @@ static int launch_split(const Split& sp, const void* a, const void* b, void* c, 
 // (arguments checked by the caller)
 static int launch_block(const void* a, const void* b, void* c, int M, int N, int K, float slope, int dtype, void* stream) {
     const BlockShape& s = choose_block(M, N, K);
-    uint64_t m_n = two(M, N), k_kc = two(K, K);
-    void* args[] = {&a, &b, &c, &m_n, &k_kc, &slope};
+    Arguments to(a, b, c, M, N, K, K, slope);
+    void* args[] = {&to.pointers_m_n, &to.k_kc_slope};
     if (hipLaunchKernel((const void*)s.fn[dtype], dim3(cover(M, s.bm) * cover(N, s.bn)), dim3(s.threads), args, 0, (hipStream_t)stream) != hipSuccess) {
         (void)hipGetLastError();
         return GEMM_ELAUNCH;
