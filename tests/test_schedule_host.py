@@ -169,3 +169,49 @@ def test_short_launches_keep_a_head_on_few_xcds(grid, BH, nqt):
             else:
                 place = [b * nqt + nqt - 1 - q for b, q in seq]
                 assert groups == 8 or place == list(range(place[0], place[0] + len(seq)))
+
+
+def deal(grid, BH, nqt, causal, resident):
+    """{workgroup: item} of workgroups with one item each, `resident` of them to a unit."""
+    import ctypes
+    L = A.binding.lib()
+    bh, qt, out = ctypes.c_int(0), ctypes.c_int(0), {}
+    for g in range(grid):
+        if L.attn_schedule_item_of(grid, g, BH, nqt, 0, causal + 2 * resident, ctypes.byref(bh), ctypes.byref(qt)):
+            out[g] = (bh.value, qt.value)
+        assert L.attn_schedule_item_of(grid, g, BH, nqt, 1, causal + 2 * resident, ctypes.byref(bh), ctypes.byref(qt)) == 0
+    return out
+
+
+@pytest.mark.parametrize("grid,BH,nqt,resident", [
+    (315, 5, 63, 1), (257, 1, 257, 1), (288, 18, 16, 1), (320, 10, 32, 1), (264, 8, 33, 1), (776, 36, 20, 1), (776, 36, 20, 2), (1030, 10, 103, 2), (513, 1, 513, 2),
+])
+def test_what_does_not_start_at_once_is_the_lightest(grid, BH, nqt, resident):
+    """Causal, more items than the units hold: in the order in which an XCD's workgroups start the weight never rises."""
+    items = deal(grid, BH, nqt, 1, resident)
+    assert len(set(items.values())) == BH * nqt
+    for x in range(8):
+        weights = [items[g][1] for g in range(x, grid, 8) if g in items]
+        assert weights == sorted(weights, reverse=True)
+
+
+@pytest.mark.parametrize("grid,BH,nqt,resident", [(256, 4, 64, 1), (512, 4, 128, 2), (512, 16, 32, 2), (300, 5, 60, 2)])
+def test_what_starts_at_once_is_dealt_in_layers(grid, BH, nqt, resident):
+    """A unit's two workgroups hold items of one weight sum, the heads of a round stay together."""
+    items = deal(grid, BH, nqt, 1, resident)
+    heads = next(n for n in (8, 4, 2, 1) if grid % n == 0 and BH % n == 0)
+    for layer in range(0, grid, 256):
+        for x in range(heads):
+            group = [items[g] for g in range(layer + x, min(grid, layer + 256), heads)]
+            assert len({b for b, _ in group}) <= -(-len(group) // nqt) + 1
+
+
+@pytest.mark.parametrize("resident", [1, 2])
+@pytest.mark.parametrize("causal", [0, 1], ids=["full", "causal"])
+def test_one_item_per_workgroup_names_every_item_once(causal, resident):
+    """Over heads that divide by 8, 4, 2 and nothing and any number of tiles, with the padding to 776 workgroups."""
+    for BH in (*range(1, 18), 20, 24, 33, 36, 64):
+        for nqt in (1, 2, 3, 4, 5, 7, 8, 9, 16, 17, 31, 40):
+            total = BH * nqt
+            grid = 776 if 512 < total <= 768 else total
+            assert sorted(deal(grid, BH, nqt, causal, resident).values()) == [(b, q) for b in range(BH) for q in range(nqt)]
