@@ -495,11 +495,11 @@ int attn_schedule_grid(int variant_id, int compute_units, int B, int H, int N) {
     return (int)g;
 }
 
-// The item for either mask: causal + 2 * resident (exported for the tests; not part of the interface).
+// The item for either mask: causal + 2 * resident + 16 * mirrored (exported for the tests; not part of the interface).
 int attn_schedule_item_of(int grid, int workgroup, int BH, int nqt, int round, int causal, int* bh, int* qt) {
     if (grid < 1 || workgroup < 0 || workgroup >= grid || BH < 1 || nqt < 1 || round < 0 || causal < 0 || !bh || !qt) return ATTN_EINVAL;
     int b = 0, q = 0;
-    if (!attn::schedule_item(grid, workgroup, BH, nqt, round, b, q, (causal & 1) != 0, causal >> 1)) return 0;
+    if (!attn::schedule_item(grid, workgroup, BH, nqt, round, b, q, (causal & 1) != 0, causal >> 1 & 7, causal >> 4)) return 0;
     *bh = b;
     *qt = q;
     return 1;

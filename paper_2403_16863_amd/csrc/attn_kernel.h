@@ -225,14 +225,16 @@ __device__ __forceinline__ int v_swz_slot(int row, int slot) {
 // which a unit holds `resident` at a time.  What starts at once is dealt in layers as above; a causal launch of more goes by
 // weight and unmirrored, because the units take the rest as they become free and the heads' heavy tiles must not come last
 // (6 x 4295, d = 128, four waves: 61 us by heads, 50 by weight; one workgroup per unit: 5 x 2002 on eight waves 22.5 us and 16.6,
-// two wave groups 18 x 1989 55.8 and 33.3, 9 x 4096 96.6 and 58.2).  Heads
+// two wave groups 18 x 1989 55.8 and 33.3, 9 x 4096 96.6 and 58.2).  Up to `mirrored` layers of those are dealt forward
+// and backward all the same, by weight: for the key split on four waves, of which a unit takes up four at once at d = 64 (513 to
+// 1024 items: 1.04 times as fast, 14 x 1781 15.0 us unmirrored, 14.3 this way; d = 128, two at once: 1.03).  Heads
 // that do not divide by 8 are kept on few XCDs too (short launches read K and V from memory once per XCD that works
 // on the head: 6 heads x 1000 keys, d = 128, 26 MB for 4.6).  Without a mask, where all items weigh the same, every XCD
 // takes an eighth of the items in head-major order: 11.2 us dealt over all heads, 9.9 this way; 36 x 400, d = 64: 8.7 and
 // 6.9.  With one, where 2 or 4 divide both, groups of 4 or 2 XCDs have heads of their own: 4 x 2354, d = 64, eight
 // waves 11.4 and 9.9; 4 x 865, d = 128: 9.0 and 8.0.  (Persistent workgroups, whose weights come out even over all
 // units only, lose 1 to 5 % that way, and the longer code costs a short launch 3 %.)
-__host__ __device__ inline bool schedule_item(int G, int gidx, int BH, int nqt, int round, int& bh, int& qt, bool causal = true, int resident = 0) {
+__host__ __device__ inline bool schedule_item(int G, int gidx, int BH, int nqt, int round, int& bh, int& qt, bool causal = true, int resident = 0, int mirrored = 0) {
     const bool free = resident > 0;
     const int both = G | BH;
     int split = (both & 1) ? 0 : (both & 2) ? 1 : (both & 4) ? 2 : 3;  // 2^split groups of XCDs
@@ -246,14 +248,15 @@ __host__ __device__ inline bool schedule_item(int G, int gidx, int BH, int nqt, 
     }
     if (split < 3 && !free) split = 0;
     const int C = G >> split, idx = gidx >> split, shift = 8 - split, units = 1 << shift;
-    const bool layers = C <= (free ? resident : 3) * units;
+    const bool late = C > resident * units;  // (free:) some items do not start at once
+    const bool layers = C <= (!free ? 3 : late ? mirrored : resident) * units;
     const int layer = layers ? idx >> shift : 0, first = layer << shift;
     const int last = (layers && first + units < C ? first + units : C) - 1;
     const int r = round * C + (((round + layer) & 1) ? first + last - idx : idx);
     const int nh = BH >> split, h0 = gidx & ((1 << split) - 1), hs = 1 << split;
     const int n = nh * nqt;
     if (r >= n) return false;
-    const bool by_weight = causal && (free ? !layers : n > C ? n / 6 < C && n % (2u * (unsigned)C) != 0 : C > 2 * units);
+    const bool by_weight = causal && (free ? late : n > C ? n / 6 < C && n % (2u * (unsigned)C) != 0 : C > 2 * units);
     const int per = by_weight ? nh : nqt, q = r / per, rest = r - q * per;
     qt = nqt - 1 - (by_weight ? q : rest);
     bh = h0 + hs * (by_weight ? rest : q);
@@ -285,8 +288,9 @@ struct Knobs {
     static constexpr int KG = KEYSPLIT ? NW : GROUPS ? 2 << ILV : 1;  // wave groups that split the keys
     static constexpr int BM = 32 * QB * NW / KG;                     // query rows of a workgroup
     // What schedule_item takes: 0, or for the key split and the wave groups the workgroups that the LDS of a unit has room
-    // for (four waves at d = 64: four; counted as two, which the lines of the choice were measured with)
+    // for (four waves at d = 64: four, counted as two), and the layers up to which they are mirrored
     static constexpr int resident(int d) { return KG == 1 ? 0 : NW == 8 && d == 128 ? 1 : 2; }
+    static constexpr int mirrored() { return KEYSPLIT && NW == 4 ? 4 : 0; }
     // second argument of the launch bounds: waves per SIMD
     static constexpr int WAVES = KG > 1 ? OCC * NW / 4 : OCC;
 };
@@ -349,7 +353,7 @@ __global__ __launch_bounds__(KN::NW * 64, KN::WAVES) void attn_fwd_kernel(
     const int c = lane & 31;
 
     auto item_of_round = [&](int round, int& bh, int& qt) __attribute__((always_inline)) -> bool {
-        return schedule_item(p.grid, (int)blockIdx.x, p.BH, p.nqt, round, bh, qt, CAUSAL, KN::resident(D));
+        return schedule_item(p.grid, (int)blockIdx.x, p.BH, p.nqt, round, bh, qt, CAUSAL, KN::resident(D), KN::mirrored());
     };
     const int N = p.N;
     // binary16 only: a finite result above the largest finite binary16 value is stored as that

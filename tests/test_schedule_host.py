@@ -171,15 +171,15 @@ def test_short_launches_keep_a_head_on_few_xcds(grid, BH, nqt):
                 assert groups == 8 or place == list(range(place[0], place[0] + len(seq)))
 
 
-def deal(grid, BH, nqt, causal, resident):
+def deal(grid, BH, nqt, causal, resident, mirrored=0):
     """{workgroup: item} of workgroups with one item each, `resident` of them to a unit."""
     import ctypes
-    L = A.binding.lib()
+    L, kind = A.binding.lib(), causal + 2 * resident + 16 * mirrored
     bh, qt, out = ctypes.c_int(0), ctypes.c_int(0), {}
     for g in range(grid):
-        if L.attn_schedule_item_of(grid, g, BH, nqt, 0, causal + 2 * resident, ctypes.byref(bh), ctypes.byref(qt)):
+        if L.attn_schedule_item_of(grid, g, BH, nqt, 0, kind, ctypes.byref(bh), ctypes.byref(qt)):
             out[g] = (bh.value, qt.value)
-        assert L.attn_schedule_item_of(grid, g, BH, nqt, 1, causal + 2 * resident, ctypes.byref(bh), ctypes.byref(qt)) == 0
+        assert L.attn_schedule_item_of(grid, g, BH, nqt, 1, kind, ctypes.byref(bh), ctypes.byref(qt)) == 0
     return out
 
 
@@ -206,12 +206,22 @@ def test_what_starts_at_once_is_dealt_in_layers(grid, BH, nqt, resident):
             assert len({b for b, _ in group}) <= -(-len(group) // nqt) + 1
 
 
-@pytest.mark.parametrize("resident", [1, 2])
+@pytest.mark.parametrize("grid,BH,nqt", [(830, 10, 83), (1008, 18, 56), (864, 9, 96), (1024, 16, 64), (776, 12, 63)])
+def test_four_waves_on_a_unit_have_even_sums(grid, BH, nqt):
+    """Key split on four waves, d = 64, 513 to 1024 items: all start at once, four to a unit (g, g + 256, ...); no unit has
+    more than a fifth of the heaviest item above the mean (dealt forward only: half of it)."""
+    items = deal(grid, BH, nqt, 1, 2, 4)
+    assert len(set(items.values())) == BH * nqt
+    units = [[items[g][1] + 1 for g in range(u, grid, 256) if g in items] for u in range(256)]
+    assert max(map(sum, units)) <= sum(map(sum, units)) / 256 + nqt / 5
+
+
+@pytest.mark.parametrize("resident,mirrored", [(1, 0), (2, 0), (2, 4)])
 @pytest.mark.parametrize("causal", [0, 1], ids=["full", "causal"])
-def test_one_item_per_workgroup_names_every_item_once(causal, resident):
+def test_one_item_per_workgroup_names_every_item_once(causal, resident, mirrored):
     """Over heads that divide by 8, 4, 2 and nothing and any number of tiles, with the padding to 776 workgroups."""
     for BH in (*range(1, 18), 20, 24, 33, 36, 64):
         for nqt in (1, 2, 3, 4, 5, 7, 8, 9, 16, 17, 31, 40):
             total = BH * nqt
             grid = 776 if 512 < total <= 768 else total
-            assert sorted(deal(grid, BH, nqt, causal, resident).values()) == [(b, q) for b in range(BH) for q in range(nqt)]
+            assert sorted(deal(grid, BH, nqt, causal, resident, mirrored).values()) == [(b, q) for b in range(BH) for q in range(nqt)]
