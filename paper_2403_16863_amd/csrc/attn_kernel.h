@@ -217,7 +217,11 @@ __device__ __forceinline__ int v_swz_slot(int row, int slot) {
 // The sawtooth only evens out over pairs of whole rounds.  Under a causal mask, a deal of few rounds that
 // are no such pairs, or of three layers at once, goes by weight over all heads instead, heaviest first: the
 // last, partial pass then holds the lightest items and falls to the units with least (32 x 2950, d = 128, 384
-// items on 256 units: 115 us by heads, 77 by weight; 48 x 2554, d = 64: 63 and 47).
+// items on 256 units: 115 us by heads, 77 by weight; 48 x 2554, d = 64: 63 and 47).  So does a single round with a partial second
+// layer where the heads have few tiles: by heads its units are even only if the dispatcher pairs the workgroups as counted above,
+// and since their arguments are preloaded short launches lost 2 to 4 % that way (d = 64: 200 x 256 9.0 us before, 9.4 by heads,
+// 8.5 by weight; 96 x 384 9.8, 10.1 and 9.0; 72 x 640 12.6, 12.9 and 12.0; d = 128, up to eight tiles: 1.05 times as fast; from nine on
+// by heads and by weight come out alike).
 // Workgroups are placed round-robin on the 8 XCDs, each with its own L2: when G and the number of heads
 // BH are multiples of 8, the deal runs inside each XCD (32 units) over that XCD's heads (x, x+8, ...), so
 // all query tiles of a head share one L2.  Every item is named exactly once over all (gidx, round).
@@ -256,7 +260,9 @@ __host__ __device__ inline bool schedule_item(int G, int gidx, int BH, int nqt, 
     const int nh = BH >> split, h0 = gidx & ((1 << split) - 1), hs = 1 << split;
     const int n = nh * nqt;
     if (r >= n) return false;
-    const bool by_weight = causal && (free ? late : n > C ? n / 6 < C && n % (2u * (unsigned)C) != 0 : C > 2 * units);
+    const bool by_weight = causal && (free    ? late
+                                      : n > C ? n / 6 < C && n % (2u * (unsigned)C) != 0
+                                              : C > 2 * units || (C > units && C < 2 * units && nqt <= 8));
     const int per = by_weight ? nh : nqt, q = r / per, rest = r - q * per;
     qt = nqt - 1 - (by_weight ? q : rest);
     bh = h0 + hs * (by_weight ? rest : q);

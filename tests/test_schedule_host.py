@@ -171,6 +171,17 @@ def test_short_launches_keep_a_head_on_few_xcds(grid, BH, nqt):
                 assert groups == 8 or place == list(range(place[0], place[0] + len(seq)))
 
 
+@pytest.mark.parametrize("BH,nqt", [(200, 2), (96, 3), (128, 3), (72, 5), (56, 7), (61, 6), (50, 8), (35, 8)])
+def test_a_partial_second_layer_of_short_heads_holds_the_lightest(BH, nqt):
+    """One round, workgroups 256 and up share the units of the first 256: no item of theirs weighs more than one of those."""
+    sched = items_of(BH * nqt, BH, nqt)
+    assert len({it for seq in sched.values() for it in seq}) == BH * nqt
+    for x in range(8):
+        first = [sched[g][0][1] for g in range(x, 256, 8)]
+        second = [sched[g][0][1] for g in range(256 + x, BH * nqt, 8)]
+        assert min(first) >= max(second, default=0)
+
+
 def deal(grid, BH, nqt, causal, resident, mirrored=0):
     """{workgroup: item} of workgroups with one item each, `resident` of them to a unit."""
     import ctypes
