@@ -584,51 +584,68 @@ constexpr int kDefaultD64Short = 3;
 // d = 64, three workgroups per unit (18) against two (3): 4 x 16384 (j 512)  281 / 281, 6 x 10900 (516)  257 / 286, 24 x 2809 (528)  70.4 / 77.5;
 //   causal  26 x 3000 (624)  43.1 / 41.5, 16 x 6000 (752)  85.4 / 83.4, 40 x 2400 (760)  39.2 / 39.6, 36 x 2800 (792)  45.5 / 46.8,
 //           48 x 2300 (864)  38.2 / 40.2, 64 x 1706 (896)  34.3 / 35.9, 96 x 1397 (1056)  34.7 / 37.4.
-// The wave groups (39: two groups, 128 rows; 40: four, 64 rows), one workgroup of eight waves per compute unit, three at
-// d = 64: they pay where the tiles of their rows fill the units about once, where 128-row tiles of four waves leave
-// half the waves of a unit out and the key split reads K and V two to four times as often.  us, replays of a graph of
-// thirty calls; heads x keys (g, j): the best of the others / 39 / 40
-//   d = 128          24 x 500 (384)    10.5 / 12.6 / 10.1      32 x 350 (352)     8.9 / 10.9 /  8.9    12 x 1151 (432)    18.6 / 20.4 / 16.0
-//                    8 x 1120 (280)    15.0 / 19.3 / 14.4      24 x 624 (480)    13.3 / 14.3 / 11.5    16 x 535 (272)     10.4 / 13.0 / 10.4
-//                    16 x 1028 (j 144) 22.9 / 20.0 / 28.3      8 x 2183 (j 144)  40.5 / 33.2 / 47.4    12 x 2625 (j 252)  53.7 / 47.4 / 58.9
-//                    48 x 450 (j 192)  14.4 / 13.8 / 19.3      64 x 499 (j 256)  15.9 / 16.1 / 20.5    16 x 2080 (j 272)  45.6 / 65.5 / 68.3
-//   d = 128, causal  32 x 661 (672)    14.9 / 15.1 / 19.3      32 x 727 (736)    18.1 / 16.6 / 21.0    32 x 960 (960)     21.7 / 19.2 / 25.0
-//                    12 x 1923 (732)   28.3 / 29.4 / 32.9      8 x 3394 (856)    43.9 / 46.7 / 44.2    6 x 5374 (1008)    75.4 / 71.5 / 78.6
-//                    12 x 3278 (1236)  59.6 / 48.2 / 54.3      24 x 1575 (1200)  32.5 / 30.8 / 33.9    24 x 2043 (1536)   43.1 / 48.9 / 45.1
-//   d = 64           8 x 1074 (272)     9.7 / 15.0 / 10.0      16 x 999 (512)    10.3 / 14.7 /  9.9    2 x 5390 (338)     33.0 / 54.2 / 30.8
-//                    24 x 1009 (768)   15.4 / 15.0 / 15.6      48 x 553 (864)    11.1 / 11.1 / 11.5    6 x 4849 (912)     56.8 / 51.7 / 50.4
-//                    16 x 1916 (960)   25.9 / 24.1 / 23.9      16 x 2221 (1120)  33.4 / 39.9 / 38.0
-//   d = 64, causal   16 x 1376 (688)   11.2 / 17.7 / 12.0      8 x 3002 (752)    20.9 / 31.8 / 20.8    16 x 1885 (944)    19.7 / 22.8 / 16.9
-//                    24 x 1429 (1080)  19.4 / 18.9 / 16.3      6 x 7550 (1416)   71.7 / 75.4 / 61.0    32 x 1755 (1760)   26.7 / 26.1 / 25.8
-//                    6 x 11620 (2184)  142.5 / 138 / 129.7     48 x 1306 (1968)  21.7 / 23.1 / 23.8    64 x 991 (1984)    19.0 / 19.4 / 21.1
-//                    24 x 1200 (912)   11.9 / 16.1 / 12.5      40 x 1100 (1400)  17.0 / 17.9 / 17.7
-// d = 64, causal, 37 / 3 / 18: 64 x 500 (1024)  8.8 / 10.5 / 10.5   128 x 300 (1280)  10.0 / 9.4 / 9.5   64 x 591 (1216)  14.0 / 13.6 / 13.3;  3 / 18:
-// 64 x 1024 (j 512)  19.5 / 19.2   128 x 512 (512)  13.4 / 13.1   96 x 767 (576)  16.8 / 15.8   48 x 1306 (528)  21.1 / 21.1.
-// With heads on few XCDs eight waves (38) gain more than four (37), measured in the same way: d = 64 8 x 427 (112) 5.5 / 5.3, 12 x 224
-// (84) 4.3 / 4.5; causal 8 x 199 4.3 / 4.2, 8 x 1957 (496) 12.5 / 11.2, 3 x 3663 (345) 17.5 / 16.0, 8 x 2076 (520) 13.3 / 13.1; d = 128 causal
-// 4 x 2085 (264) 17.4 / 15.1, 4 x 2682 (336) 21.1 / 19.8, 4 x 2871 (360) 22.5 / 22.6; d = 128 6 x 1094 (210) 11.5 / 10.7, 6 x 1277 (240) 11.9 / 14.3.
+// The wave groups (39: two groups, 128 rows; 40: four, 64 rows), one workgroup of eight waves per compute unit, two at
+// d = 64: they pay where the tiles of their rows fill the units about once, under a mask, where they come by weight, up to twice;
+// there 128-row tiles of four waves leave half the waves of a unit out and the key split reads K and V two to four times as
+// often.  us, graphs of sixteen calls replayed in shuffled order; heads x keys (g, or tiles of 64 rows t, or j): the key split on four
+// waves / 39 / 40 / the best of the long launches, on both sides of each line
+//   d = 128          256 < g, t <= 256           12 x 617 (g 240)   8.4 / 13.6 / 10.6 / 15.2     15 x 558 (270)     10.6 / 12.9 / 10.5 / 14.5
+//                                                32 x 512 (t 256)  11.1 / 12.9 / 10.6 / 13.6     24 x 666 (264)     13.3 / 15.7 / 22.5 / 17.3
+//                    512 < g, j <= 256           32 x 1015 (j 256) 31.6 / 23.0 / 29.4 / 24.5     36 x 1024 (288)    37.3 / 39.2 / 41.0 / 28.9
+//                    400 <= N for both           32 x 364 (g 384)   9.2 / 11.0 /  8.9 / 11.4     80 x 248 (640)     11.7 / 10.3 / 14.6 / 10.3
+//                                                40 x 414 (g 520)  14.9 / 12.3 / 18.0 / 12.8
+//   d = 128, causal  39: g > 700, N < 640        36 x 519 (g 612)  12.5 / 13.7 / 14.4 / 15.3     48 x 512 (768)     14.5 / 13.9 / 15.0 / 14.9
+//                    g > 800, N < 900            28 x 819 (g 728)  16.2 / 17.0 / 16.9 / 19.9     40 x 660 (840)     16.2 / 15.5 / 16.6 / 16.9
+//                    g > 960, N >= 900           28 x 970 (g 868)  19.8 / 20.1 / 20.5 / 23.6     28 x 1126 (1008)   23.4 / 22.4 / 22.4 / 26.2
+//                    j <= 256, N < 1200          80 x 313 (j 240)  12.3 / 10.8 / 13.3 / 11.0     96 x 296 (288)     12.8 / 15.3 / 14.1 / 11.8
+//                    j <= 480, N >= 1200         40 x 1308 (j 440) 38.2 / 32.2 / 38.8 / 32.4     40 x 1536 (480)    46.8 / 36.0 / 46.8 / 36.7
+//                                                48 x 1349 (j 528) 51.2 / 43.1 / 50.0 / 35.8     18 x 3690 (522)   108.4 / 78.4 / 97.2 / 76.8
+//                    40: g > 768, N >= 1500      14 x 1692 (g 742) 23.4 / 28.0 / 23.5 / 33.3     16 x 1617 (816)    22.9 / 26.6 / 22.4 / 31.6
+//                    t <= 512                    16 x 2048 (t 512) 33.1 / 33.4 / 30.2 / 39.3     16 x 2061 (528)    32.7 / 32.9 / 35.1 / 39.8
+//   d = 64           g > 300, N >= 960            6 x 1496 (g 282) 12.5 / 19.0 / 12.3 / 19.8      8 x 1280 (320)    11.1 / 16.5 / 10.8 / 16.9
+//                                                15 x 896 (g 420)   9.1 / 13.1 /  9.0 / 13.0     16 x 1024 (512)    10.6 / 14.5 / 10.2 / 14.6
+//                    t <= 256                     5 x 3142 (t 250) 24.3 / 35.4 / 22.2 / 39.3      9 x 2048 (288)    21.6 / 24.7 / 22.7 / 25.9
+//                    (N >= 6000: g <= 768)        4 x 4599 (t 288) 42.8 / 49.4 / 42.5 / 55.6      3 x 6144 (288)    54.7 / 61.5 / 52.4 / 69.6
+//                    g > 768, N >= 700           16 x 1536 (g 768) 19.2 / 20.9 / 19.7 / 21.5     12 x 2113 (804)    29.6 / 27.3 / 25.6 / 29.8
+//                    (860 for heads that divide  38 x 700 (g 836)  13.7 / 13.0 / 13.1 / 13.9     36 x 768 (864)     13.9 / 12.7 / 12.6 / 13.2
+//                    by 8: on one XCD each       40 x 768 (g 960)  14.3 / 13.3 / 13.1 / 13.0     32 x 830 (832)     15.2 / 14.4 / 14.4 / 14.2
+//                    in the long launches)       40 x 694 (g 880)  13.6 / 12.9 / 12.9 / 12.6     32 x 878 (896)     15.4 / 14.4 / 14.0 / 14.2
+//                    j <= 256                    32 x 969 (j 256)  17.0 / 16.1 / 15.4 / 16.1     18 x 2048 (288)    34.8 / 38.1 / 34.5 / 33.3
+//   d = 64, causal   g > 1536, 1250 <= N < 2000  28 x 1697 (1512)  23.5 / 25.9 / 23.6 / 27.3     28 x 1943 (1708)   27.8 / 28.7 / 27.1 / 30.7
+//                    g > 960, N >= 2000           9 x 3376 (g 954) 25.4 / 37.7 / 26.4 / 42.7     15 x 2141 (1005)   20.3 / 26.5 / 20.1 / 29.8
+//                    g <= 1800, N < 2000         36 x 1500 (1692)  23.4 / 23.8 / 23.3 / 25.1     46 x 1300 (1886)   26.3 / 23.8 / 24.2 / 24.6
+//                    g <= 2050, N < 4000         24 x 2637 (1992)  37.5 / 36.0 / 35.4 / 38.2     28 x 2461 (2156)   39.9 / 37.8 / 37.9 / 37.4
+//                    g <= 2200, N >= 4000         8 x 8634 (2160) 110.1 / 102  / 94.1 / 110.0    18 x 4096 (2304)   67.6 / 57.2 / 57.8 / 58.6
+// (Not taken, though measured: 40 for one head from 12000 keys at d = 64, 1 x 12500 75.2 / 68.7.)
+// d = 64, causal, 37 / 3 / 18: 64 x 500 (1024)  8.8 / 10.5 / 10.5   120 x 400 (g 1560)  15.2 / 10.1 / 10.1;  3 and 18 between j = 410 and 512: alike,
+// within 1 %; beyond, up to 1600 keys: 112 x 640 (j 560) 16.3 / 13.9.
+// Eight waves (38) against four (37) where each has a unit to itself: d = 64 8 x 427 (112) 5.5 / 5.3, 12 x 224 (84) 4.3 / 4.5;
+// causal 8 x 199 4.3 / 4.2, 8 x 1957 (496) 12.5 / 11.2, 3 x 3663 (345) 17.5 / 16.0, 8 x 2076 (520) 13.3 / 13.1; d = 128 causal
+// 4 x 2085 (264) 17.4 / 15.1, 5 x 2002 (315) 17.7 / 16.6, 4 x 2682 (336) 21.1 / 19.8, 4 x 2871 (360) 22.5 / 22.6; d = 128 9 x 790 (225) 9.7 / 9.1, 12 x
+// 617 (240) 8.4 / 8.2, 2 x 4096 (256) 30.8 / 27.0, 10 x 819 (260) 12.9 / 16.1.
 constexpr int kKeySplit4 = 37, kKeySplit8 = 38, kGroups2 = 39, kGroups4 = 40, kRows128 = 1;
 
 static int choose_variant(long long heads, int N, int d, int causal) {
-    const long long g = heads * ((N + 31LL) / 32), j = heads * ((N + 127LL) / 128);
+    const long long g = heads * ((N + 31LL) / 32), t = heads * ((N + 63LL) / 64), j = heads * ((N + 127LL) / 128);
     const int most = d == 128 ? (!causal ? 512 : N < 768 ? 736 : N < 1024 ? 1056 : 1152)
                               : !causal ? (N < 640 ? 704 : 768) : N < 300 ? 960 : N < 600 ? 1100 : N < 768 ? 1280 : N < 1200 ? 1440 : 1536;
     // the wave groups
     if (d == 128 && !causal) {
-        if (N >= 400 && g > 256 && g <= 512) return kGroups4;
+        if (N >= 400 && g > 256 && t <= 256) return kGroups4;
         if (N >= 400 && g > 512 && j <= 256) return kGroups2;
     } else if (d == 128) {
-        if (N < 1500 ? N >= 300 && g > 700 && j <= 256 : g > 950 && g <= 1400) return kGroups2;
+        if (N >= 1500 && g > 768 && t <= 512) return kGroups4;
+        if (N >= 300 && g > (N < 640 ? 700 : N < 900 ? 800 : 960) && j <= (N < 1200 ? 256 : 480)) return kGroups2;
     } else if (!causal) {
-        if (N >= 960 && N < 12000 && g > 300 && g <= 700) return kGroups4;
-        if (N >= 700 && (N >= 960 ? g > 700 : g > most) && j <= 256) return N >= 1500 ? kGroups4 : kGroups2;
-    } else if (N >= 1250 && g > 850 && g <= (N < 4000 ? 1800 : 2200)) {
+        if (N >= 960 && N < 12000 && g > 300 && (t <= 256 || (N >= 6000 && g <= most))) return kGroups4;
+        if (N >= (heads & 7 ? 700 : 860) && g > most && j <= 256) return N >= 960 ? kGroups4 : kGroups2;
+    } else if (N >= 1250 && g > (N < 2000 ? most : 960) && g <= (N < 2000 ? 1800 : N < 4000 ? 2050 : 2200)) {
         return kGroups4;
     }
     // the key split: eight waves up to the line `alone`
     const int alone = causal && N >= 6000 ? (N >= 12000 ? 512 : 384)
                       : causal && d == 64 && N >= 1200 && N <= 5000 ? 512
-                      : causal && d == 128 && N >= 2000 && N <= 5500 ? 352 : !causal && d == 128 ? 224 : 256;
+                      : causal && d == 128 && N >= 2000 && N <= 5500 ? 352 : 256;
     if (g <= most) return N >= (d == 128 ? 512 : causal ? 160 : 400) && g <= alone ? kKeySplit8 : kKeySplit4;
     if (d == 128) return (causal ? j <= 576 : j <= 256 || (j > 512 && j <= 640)) ? kRows128 : kDefaultD128;
     return j > (!causal ? 512 : N >= 256 && N < 1600 ? 410 : 755) ? kDefaultD64Long : kDefaultD64Short;

@@ -21,18 +21,37 @@ def test_the_groups_rows_and_grids():
 
 
 @pytest.mark.parametrize("heads,N,d,causal,want", [
-    (20, 399, 128, False, 37), (20, 400, 128, False, FOUR), (8, 1024, 128, False, 37), (8, 1025, 128, False, FOUR),
-    (16, 1024, 128, False, FOUR), (16, 1025, 128, False, TWO), (16, 2048, 128, False, TWO), (16, 2049, 128, False, 36),
-    (28, 800, 128, True, 37), (29, 800, 128, True, TWO), (64, 300, 128, True, 37), (71, 299, 128, True, 37), (71, 300, 128, True, TWO),
-    (20, 1500, 128, True, 37), (21, 1500, 128, True, TWO), (29, 1500, 128, True, TWO), (30, 1500, 128, True, 1),
+    # d = 128: four groups, two, both from 400 keys on
+    (20, 399, 128, False, 37), (20, 400, 128, False, FOUR), (8, 1024, 128, False, 38), (8, 1025, 128, False, FOUR),
+    (16, 1024, 128, False, FOUR), (16, 1025, 128, False, TWO), (24, 640, 128, False, FOUR), (24, 641, 128, False, 37),
+    (16, 2048, 128, False, TWO), (16, 2049, 128, False, 36), (40, 399, 128, False, 1), (40, 400, 128, False, TWO),
+    # causal: two
+    (28, 800, 128, True, 37), (64, 300, 128, True, 37), (71, 299, 128, True, 37), (71, 300, 128, True, TWO),
+    (36, 639, 128, True, TWO), (36, 640, 128, True, 37), (32, 800, 128, True, 37), (33, 800, 128, True, TWO),
+    (32, 899, 128, True, TWO), (32, 900, 128, True, 37), (32, 960, 128, True, 37), (32, 961, 128, True, TWO),
+    (32, 1024, 128, True, TWO), (32, 1025, 128, True, 37), (36, 1199, 128, True, 1), (36, 1200, 128, True, TWO),
+    (43, 1400, 128, True, TWO), (44, 1400, 128, True, 1), (40, 1536, 128, True, TWO), (40, 1537, 128, True, 1),
+    # four
+    (16, 1500, 128, True, 37), (17, 1500, 128, True, FOUR), (17, 1499, 128, True, 37), (21, 1500, 128, True, FOUR), (22, 1500, 128, True, TWO),
+    (29, 1500, 128, True, TWO), (30, 1500, 128, True, TWO),
+    # d = 64
     (10, 960, 64, False, 37), (11, 960, 64, False, FOUR), (11, 959, 64, False, 37), (1, 11999, 64, False, FOUR), (1, 12000, 64, False, 37),
-    (23, 960, 64, False, FOUR), (24, 960, 64, False, TWO), (21, 1500, 64, False, FOUR), (22, 1500, 64, False, 3), (40, 700, 64, False, TWO),
-    (40, 699, 64, False, 3),
-    (21, 1250, 64, True, 37), (22, 1250, 64, True, FOUR), (27, 1249, 64, True, 37),
-    (45, 1250, 64, True, FOUR), (46, 1250, 64, True, 18), (41, 1250, 64, True, FOUR), (17, 4000, 64, True, FOUR), (18, 4000, 64, True, 3),
+    (17, 960, 64, False, FOUR), (18, 960, 64, False, 37), (4, 5999, 64, False, 37), (4, 6000, 64, False, FOUR), (25, 960, 64, False, 37),
+    (26, 960, 64, False, FOUR), (26, 959, 64, False, TWO), (21, 1500, 64, False, FOUR), (22, 1500, 64, False, 3), (36, 700, 64, False, TWO),
+    (36, 699, 64, False, 3), (32, 859, 64, False, 3), (32, 860, 64, False, TWO),
+    # causal
+    (38, 1250, 64, True, 37), (39, 1250, 64, True, FOUR), (39, 1249, 64, True, 3), (27, 1249, 64, True, 37),
+    (45, 1250, 64, True, FOUR), (46, 1250, 64, True, 18), (41, 1250, 64, True, FOUR), (28, 1999, 64, True, FOUR), (29, 1999, 64, True, 3),
+    (15, 2000, 64, True, 37), (16, 2000, 64, True, FOUR), (32, 2000, 64, True, FOUR), (33, 2000, 64, True, 3),
+    (17, 3999, 64, True, 3), (17, 4000, 64, True, FOUR), (18, 4000, 64, True, 3),
     # d = 64 causal: a higher line of the key split from 300 keys on, three workgroups per unit for short rows
     (110, 300, 64, True, 37), (111, 300, 64, True, 3), (96, 299, 64, True, 37), (97, 299, 64, True, 3), (51, 1000, 64, True, 3),
-    (52, 1000, 64, True, 18), (206, 256, 64, True, 18), (206, 255, 64, True, 3),
+    (52, 1000, 64, True, 18), (206, 256, 64, True, 18), (206, 255, 64, True, 3), (32, 1599, 64, True, FOUR), (37, 1599, 64, True, 18), (37, 1600, 64, True, 3),
+    # the key split on eight waves: how many tiles, from how many keys on
+    (7, 1024, 128, False, 38), (16, 512, 128, False, 38), (16, 511, 128, False, 37), (4, 2048, 128, False, 38), (9, 900, 128, False, FOUR),
+    (5, 1999, 128, True, 37), (5, 2000, 128, True, 38), (11, 1024, 128, True, 37), (5, 2240, 128, True, 38), (5, 2241, 128, True, 37), (2, 5500, 128, True, 38),
+    (2, 5501, 128, True, 37), (13, 1199, 64, True, 37), (13, 1200, 64, True, 38), (13, 1248, 64, True, 38), (13, 1249, 64, True, 37), (3, 5000, 64, True, 38),
+    (3, 5001, 64, True, 37), (51, 159, 64, True, 37), (51, 160, 64, True, 38), (19, 399, 64, False, 37), (19, 400, 64, False, 38),
 ])
 def test_both_sides_of_every_line(heads, N, d, causal, want):
     for dtype in (A.ATTN_F16, A.ATTN_BF16):
@@ -93,9 +112,13 @@ def test_keys_masked_by_their_scores(d, causal):
 @pytest.mark.parametrize("B,H,N,d,causal,dtype", [
     (1, 12, 1151, 128, False, I.F16),    # four groups, one workgroup per unit at most
     (2, 8, 1500, 128, False, I.BF16),    # two
-    (1, 12, 3278, 128, True, I.BF16),    # two, by weight over groups of XCDs
+    (1, 12, 3278, 128, True, I.BF16),    # two, by weight over groups of two XCDs
+    (1, 18, 2000, 128, True, I.F16),     # the same, of four
+    (1, 5, 6200, 128, True, I.F16),      # four groups, by weight over all
     (4, 4, 1900, 64, False, I.F16),      # four at d = 64, more than one workgroup per unit
-    (3, 11, 1291, 64, True, I.BF16),     # the padded grid, heads that divide by nothing
+    (2, 9, 2600, 64, True, I.F16),       # by weight over groups of four XCDs, the padded grid
+    (4, 5, 2500, 64, True, I.F16),       # the same of two, more than three layers
+    (3, 11, 1600, 64, True, I.BF16),     # heads that divide by nothing
 ])
 def test_attn_fwd_takes_the_groups(B, H, N, d, causal, dtype):
     from gpu_util import check, run_gpu
