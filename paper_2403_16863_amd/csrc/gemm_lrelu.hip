@@ -72,22 +72,27 @@ static int check_args(const void* a, const void* b, const void* c, int M, int N,
 // (The 64 x 64 tile on eight waves, two groups of four that split K, came later; its numbers are from 36 to 144 tiles
 // with K from 2056 to 8200.  It pays while a unit has one tile: four waves there draw 60 to 65 GB/s, as much as one wave per SIMD
 // has LDS reads and loads in flight for, eight 83.  768 x 768 x 3072 14.8 -> 12.2 us, 533 x 1152 x 3976 18.8 -> 16.3, 3802 x 200 x
-// 2560 13.5 -> 12.9.  Rings of six and nine stages in place of three: nothing.)
+// 2560 13.5 -> 12.9.  Rings of six and nine stages in place of three: nothing.
+// The model takes it for 130 to 256 tiles from K of about 1100 on.  Time against the four waves', 500 shapes there, one set of buffers /
+// five: with K a multiple of 64, where the rows of A start on whole lines, 0.98 / 0.97 at 1120, 0.95 at 1600, 0.90 / 0.92 from 2080 on; with
+// other K 1.05 / 1.03 below 1440, 1.03 / 1.03 at 1600, 1.02 at 1920, 1.00 / 1.01 at 2080 and 0.99 / 1.00 from 2240 on (979 x 912 x 1272 8.35 us
+// on four waves, 9.1 on eight; 3676 x 232 x 1456 8.6 and 9.5): there from 2112 on.  Above 2600: 0.96 over 56 shapes.)
 struct BlockShape {
     int bm, bn, bk, wk, threads, occ;
+    int ragged;  // the least K that it is taken for where K is no multiple of 64
     float alone, full, ends;
     BlockFn fn[2];
 };
 template <class BL>
-constexpr BlockShape block_shape(float alone, float full, float ends) {
-    return {BL::BM, BL::BN, BL::BK, BL::WK, BL::WM * BL::WN * BL::WK * 64, BL::OCC, alone, full, ends,
+constexpr BlockShape block_shape(float alone, float full, float ends, int ragged = 0) {
+    return {BL::BM, BL::BN, BL::BK, BL::WK, BL::WM * BL::WN * BL::WK * 64, BL::OCC, ragged, alone, full, ends,
             {gemm_block_kernel<Mfma16F16, BL>, gemm_block_kernel<Mfma16BF16, BL>}};
 }
 static const BlockShape kBlocks[] = {
     block_shape<Block<32, 32, 32, 1, 1, 4, 4, 2>>(0.21f, 0.22f, 0.5f),
     block_shape<Block<32, 64, 64, 1, 2, 2, 3, 2>>(0.27f, 0.31f, 0.58f),
     block_shape<Block<64, 64, 64, 2, 2, 1, 3, 3>>(0.24f, 0.17f, 0.22f),
-    block_shape<Block<64, 64, 64, 2, 2, 2, 4, 1>>(0.40f, 0.f, 0.9f),
+    block_shape<Block<64, 64, 64, 2, 2, 2, 4, 1>>(0.40f, 0.f, 0.9f, 2112),
     block_shape<Block<64, 128, 64, 1, 4, 1, 3, 2>>(0.27f, 0.28f, 0.88f),
     block_shape<Block<128, 128, 64, 2, 4, 1, 4, 1>>(0.41f, 0.f, 0.9f),
     block_shape<Block<128, 256, 64, 2, 4, 1, 3, 1>>(0.64f, 0.f, 1.8f),
@@ -100,6 +105,7 @@ static const BlockShape& choose_block(int M, int N, int K) {
     float best_us = 0.f;
     for (const BlockShape& s : kBlocks) {
         if ((long long)(s.bm - 1) * K * 2 + s.bk * 2 >= (long long)kBufferSize) continue;  // 32-bit offsets in a tile's rows
+        if (K < s.ragged && (K & 63)) continue;
         const unsigned long long tiles = (unsigned long long)cover(M, s.bm) * cover(N, s.bn);
         const long long n = (tiles + kComputeUnits - 1) / kComputeUnits, stages = cover(K, s.bk * s.wk);
         const float alone = (float)(n <= s.occ ? 1 : (n + s.occ - 1) / s.occ) * s.alone, full = (float)n * s.full;

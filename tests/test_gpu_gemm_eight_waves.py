@@ -8,7 +8,7 @@ from paper_2403_16863_amd import inputs as I
 from test_gpu_gemm import check, run_gpu
 from test_gpu_gemm_block import block_of
 
-SHAPES = [(833, 840, 1928), (449, 1096, 2440), (1023, 968, 2184), (769, 776, 3000), (833, 832, 2048)]
+SHAPES = [(833, 840, 2120), (833, 840, 1280), (449, 1096, 2440), (1023, 968, 2184), (769, 776, 3000), (833, 832, 2048)]
 
 
 def test_which_calls_take_it():
@@ -17,8 +17,11 @@ def test_which_calls_take_it():
     for M, N, K in SHAPES:
         assert block_of(M, N, K) == (64, 64) and L.gemm_lrelu_block_threads_of(M, N, K) == 512
     # a short K
-    for M, N, K in ((705, 712, 1000), (193, 2824, 384)):
+    for M, N, K in ((705, 712, 1000), (193, 2824, 384), (705, 712, 960)):
         assert block_of(M, N, K) == (64, 64) and L.gemm_lrelu_block_threads_of(M, N, K) == 256
+    # K a multiple of 64 (whole lines of A) or not, on both sides of the line for the latter
+    for K, threads in ((1152, 512), (1144, 256), (1160, 256), (1920, 512), (1928, 256), (2104, 256), (2112, 512), (2120, 512)):
+        assert block_of(833, 840, K) == (64, 64) and L.gemm_lrelu_block_threads_of(833, 840, K) == threads
 
 
 @pytest.mark.gpu
