@@ -63,9 +63,9 @@ enum {
  *            scaled scores over the visible keys.  Every element is written.
  *  B,H,N   : >= 1, any N (ragged last tiles are masked).  Limits, reported as
  *            ATTN_EUNSUPPORTED: B*H*N*d <= 2^40 elements, and B*H*ceil(N/bm) <= 2^31-1
- *            work items (bm = the variant's query tile, 32, 128 or 256 rows); with the key split,
- *            which attn_fwd itself takes for a few hundred items only, fewer than 2^32 threads and
- *            N*d*2 <= 2^31-1 bytes.
+ *            work items (bm = the variant's query tile, 32, 64, 128 or 256 rows); with the key split
+ *            and the wave groups, which attn_fwd itself takes for up to about two thousand items,
+ *            fewer than 2^32 threads, and with the key split N*d*2 <= 2^31-1 bytes.
  *  d       : 64 or 128.
  *  causal  : 0 = every key visible, otherwise key j is visible to query i iff j <= i.
  *  scale   : finite; multiplies q.k before the softmax (callers pass 1/sqrt(d)).
@@ -133,18 +133,23 @@ int attn_variant_coords(int variant_id, int* coords);
 int attn_variant_from_coords(const int* coords);
 
 /* How work reaches the device (host logic, no device call).  A work item is one
- * query tile of one head (the outer, data-parallel loop of the tiled forward pass);
- * a launch uses a grid of persistent workgroups, each of which takes items round
+ * query tile of one head (the outer, data-parallel loop of the tiled forward pass).
+ * Most variants launch a grid of persistent workgroups, each of which takes items round
  * after round from a fixed schedule: items sorted by weight (under a causal mask the
  * last query tiles see the most keys) are dealt to the workgroups in serpentine
  * order, inside each of the 8 XCDs over that XCD's own heads when the grid and the
  * number of heads are multiples of 8 (what attn_schedule_item names is the order under a
  * causal mask; without one the items of a head always follow each other).
+ * The variants whose waves split the keys (ldpos=1 or 2 with pipe=0) launch one workgroup
+ * per item instead and have orders of their own, which attn_schedule_item does not name:
+ * under a causal mask by weight where not all of them start at once, and heads that 8 does
+ * not divide on few XCDs.
  * attn_schedule_grid returns the grid size a launch of this variant uses for the
  * shape on a device with `compute_units` CUs (ATTN_EINVAL / ATTN_EUNSUPPORTED on bad
- * or oversized arguments).
- * attn_schedule_item names the item of workgroup `workgroup` (0 <= workgroup < grid)
- * in round `round` for BH = B*H heads of nqt query tiles each: returns 1 and writes
+ * or oversized arguments); with one workgroup per item that is the number of items, 513 to
+ * 768 padded to 776.
+ * attn_schedule_item names the item of workgroup `workgroup` (0 <= workgroup < grid) of a
+ * persistent grid in round `round` for BH = B*H heads of nqt query tiles each: returns 1 and writes
  * *bh (0 .. BH-1) and *qt (0 .. nqt-1), 0 when that workgroup has no item in that
  * round (nor in any later one), ATTN_EINVAL on bad arguments.  Over all workgroups
  * and rounds every item is named exactly once. */

@@ -328,7 +328,7 @@ def attn_variant_from_coords(coords):
 
 
 def attn_schedule_grid(variant: int, compute_units: int, B: int, H: int, N: int) -> int:
-    """Grid size (persistent workgroups) a launch of this variant uses."""
+    """Grid size a launch of this variant uses: persistent workgroups, or one per item where the waves split the keys."""
     rc = lib().attn_schedule_grid(int(variant), int(compute_units), int(B), int(H), int(N))
     if rc < 0:
         raise AttnError(rc, "attn_schedule_grid")
@@ -336,7 +336,7 @@ def attn_schedule_grid(variant: int, compute_units: int, B: int, H: int, N: int)
 
 
 def attn_schedule_item(grid: int, workgroup: int, BH: int, nqt: int, rnd: int):
-    """(bh, qt) of the item a workgroup takes in a round, or None when it has none."""
+    """(bh, qt) of the item a workgroup of a persistent grid takes in a round, or None when it has none."""
     bh, qt = ctypes.c_int(0), ctypes.c_int(0)
     rc = lib().attn_schedule_item(int(grid), int(workgroup), int(BH), int(nqt), int(rnd),
                                   ctypes.byref(bh), ctypes.byref(qt))

@@ -19,6 +19,7 @@ struct Variant {
     // kernels by [dtype][causal] for head dimension 64 and 128; null = not built for it
     const attn::KernelFn (*fn64)[2];
     const attn::KernelFn (*fn128)[2];
+    int resident[2], mirrored;                          // what schedule_item takes, head dimension 64 and 128
     bool keysplit() const { return pipe == 0 && ldpos == 1; }
     int groups() const { return keysplit() ? nw : pipe == 0 && ldpos == 2 ? 2 << ilv : 1; }  // of waves that split the keys
     int bm() const { return 32 * qb * nw / groups(); }  // query rows of a work item
@@ -58,10 +59,12 @@ constexpr int kNumKnobs = 10;
     BN, NW, QB, OCC, LDP, PIPE, PF, PRIO, ILV, LDPOS,                                               \
     {IDX_BN(BN), IDX_NW(NW), IDX_QB(QB), LDP, PIPE, IDX_PF(PF), PRIO, IDX_DENSE(NW, QB, OCC), ILV, LDPOS}
 
-#define ROW_D64(...) {VARIANT_HEAD(__VA_ARGS__), attn::KernelSet<64, attn::Knobs<__VA_ARGS__>>::fn, nullptr},
-#define ROW_D128(...) {VARIANT_HEAD(__VA_ARGS__), nullptr, attn::KernelSet<128, attn::Knobs<__VA_ARGS__>>::fn},
+#define VARIANT_DEAL(...) {attn::Knobs<__VA_ARGS__>::resident(64), attn::Knobs<__VA_ARGS__>::resident(128)}, attn::Knobs<__VA_ARGS__>::mirrored()
+
+#define ROW_D64(...) {VARIANT_HEAD(__VA_ARGS__), attn::KernelSet<64, attn::Knobs<__VA_ARGS__>>::fn, nullptr, VARIANT_DEAL(__VA_ARGS__)},
+#define ROW_D128(...) {VARIANT_HEAD(__VA_ARGS__), nullptr, attn::KernelSet<128, attn::Knobs<__VA_ARGS__>>::fn, VARIANT_DEAL(__VA_ARGS__)},
 #define ROW_BOTH(...) \
-    {VARIANT_HEAD(__VA_ARGS__), attn::KernelSet<64, attn::Knobs<__VA_ARGS__>>::fn, attn::KernelSet<128, attn::Knobs<__VA_ARGS__>>::fn},
+    {VARIANT_HEAD(__VA_ARGS__), attn::KernelSet<64, attn::Knobs<__VA_ARGS__>>::fn, attn::KernelSet<128, attn::Knobs<__VA_ARGS__>>::fn, VARIANT_DEAL(__VA_ARGS__)},
 
 const Variant kVariants[] = {ATTN_ALL_VARIANTS(ROW_BOTH, ROW_D64, ROW_D128)};
 constexpr int kNumVariants = (int)(sizeof(kVariants) / sizeof(kVariants[0]));
@@ -503,6 +506,13 @@ int attn_schedule_item_of(int grid, int workgroup, int BH, int nqt, int round, i
     *bh = b;
     *qt = q;
     return 1;
+}
+
+// The item that a launch of this variant takes (the same).
+int attn_schedule_item_launched(int variant_id, int d, int causal, int grid, int workgroup, int BH, int nqt, int round, int* bh, int* qt) {
+    if (variant_id < 0 || variant_id >= kNumVariants || (d != 64 && d != 128)) return ATTN_EINVAL;
+    const Variant& v = kVariants[variant_id];
+    return attn_schedule_item_of(grid, workgroup, BH, nqt, round, (causal ? 1 : 0) + 2 * v.resident[d == 128] + 16 * v.mirrored, bh, qt);
 }
 
 int attn_schedule_item(int grid, int workgroup, int BH, int nqt, int round, int* bh, int* qt) {

@@ -27,8 +27,19 @@ def test_every_row_block_has_a_workgroup():
             nqt = -(-N // 32)
             grid = A.attn_schedule_grid(v, 256, B, H, N)
             assert grid == B * H * nqt
-            items = [A.attn_schedule_item(grid, g, B * H, nqt, 0) for g in range(grid)]
-            assert len(set(items)) == grid and all(A.attn_schedule_item(grid, g, B * H, nqt, 1) is None for g in range(grid))
+            for d in (64, 128):
+                for causal in (False, True):
+                    items = [launched_item(v, d, causal, grid, g, B * H, nqt, 0) for g in range(grid)]
+                    assert sorted(items) == [(b, q) for b in range(B * H) for q in range(nqt)]
+                    assert all(launched_item(v, d, causal, grid, g, B * H, nqt, 1) is None for g in range(grid))
+
+
+def launched_item(variant, d, causal, grid, workgroup, BH, nqt, rnd):
+    import ctypes
+    bh, qt = ctypes.c_int(0), ctypes.c_int(0)
+    rc = A.binding.lib().attn_schedule_item_launched(variant, d, int(causal), grid, workgroup, BH, nqt, rnd, ctypes.byref(bh), ctypes.byref(qt))
+    assert rc in (0, 1)
+    return (bh.value, qt.value) if rc else None
 
 
 @pytest.mark.gpu

@@ -80,12 +80,12 @@ def test_rounds_by_weight_go_from_heavy_to_light():
 
 @pytest.mark.parametrize("causal", [False, True], ids=["full", "causal"])
 @pytest.mark.parametrize("grid,BH,nqt", [
-    (300, 5, 60), (304, 8, 38), (512, 16, 32), (776, 9, 57), (776, 8, 96), (776, 3, 171), (769, 1, 769), (776, 8, 97), (1008, 16, 63),  # key split
+    (300, 5, 60), (304, 8, 38), (512, 16, 32), (776, 9, 57), (776, 8, 96), (776, 3, 171), (769, 1, 769), (776, 8, 97), (1008, 16, 63),  # layers, and more
     (256, 32, 12), (256, 64, 16), (512, 64, 16), (512, 12, 50), (768, 128, 18), (768, 48, 20), (256, 3, 100), (255, 64, 16), (8, 8, 1),
 ])
 def test_either_mask_names_every_item_once(grid, BH, nqt, causal):
-    """Grids of one workgroup per item (a second layer; 513 to 768 items padded to 776; more than three layers) and
-    persistent ones.  Without a mask the items of a head follow each other."""
+    """The persistent deal, over grids with a second layer, with more workgroups than items, of more than three layers,
+    and of several rounds.  Without a mask the items of a head follow each other."""
     import ctypes
     L = A.binding.lib()
     bh, qt, seen, rounds = ctypes.c_int(0), ctypes.c_int(0), [], 0
@@ -192,6 +192,28 @@ def deal(grid, BH, nqt, causal, resident, mirrored=0):
             out[g] = (bh.value, qt.value)
         assert L.attn_schedule_item_of(grid, g, BH, nqt, 1, kind, ctypes.byref(bh), ctypes.byref(qt)) == 0
     return out
+
+
+@pytest.mark.parametrize("causal", [0, 1], ids=["full", "causal"])
+@pytest.mark.parametrize("BH,nqt", [(6, 32), (5, 63), (10, 83), (18, 40), (8, 97), (36, 20)])
+def test_what_each_variant_deals(BH, nqt, causal):
+    """The order that a variant launches: the key split and the wave groups with what a unit holds of their workgroups, the
+    persistent ones as attn_schedule_item names it (under a mask)."""
+    from test_gpu_key_split import launched_item
+    for v in range(A.attn_num_variants()):
+        knobs = dict(kv.split("=") for kv in A.attn_variant_desc(v).split())
+        splits = knobs["pipe"] == "0" and knobs["ldpos"] != "0"
+        if not splits and v % 9:
+            continue
+        grid = A.attn_schedule_grid(v, 256, 1, BH, nqt * int(knobs["bm"]))
+        for d in (64, 128):
+            got = {g: launched_item(v, d, causal, grid, g, BH, nqt, 0) for g in range(grid)}
+            if splits:
+                resident = 1 if knobs["nw"] == "8" and d == 128 else 2
+                mirrored = 4 if knobs["ldpos"] == "1" and knobs["nw"] == "4" else 0
+                assert {g: it for g, it in got.items() if it} == deal(grid, BH, nqt, causal, resident, mirrored)
+            elif causal:
+                assert got == {g: A.attn_schedule_item(grid, g, BH, nqt, 0) for g in range(grid)}
 
 
 @pytest.mark.parametrize("grid,BH,nqt,resident", [
