@@ -1,6 +1,7 @@
 """What attn_fwd launches where nothing is deployed: the choice on both sides of every line (host), and, on the
-GPU, that attn_fwd runs what attn_choose_variant names, against the fp64 oracle, in every regime of the key
-split's grids (one layer, a second one, the padded grid, by weight; heads that divide over the XCDs and not)."""
+GPU, that attn_fwd runs what attn_choose_variant names, against the fp64 oracle, in every regime of the key split's
+grids and orders (one layer, a second one, the padded grid, by weight mirrored and not; heads that divide over the XCDs
+and not), each case with the variant and the grid that it stands for."""
 import numpy as np
 import pytest
 
@@ -45,25 +46,39 @@ def test_bad_problems_have_no_choice():
         assert e.value.code == code
 
 
+CASES = [
+    # key split, four waves: a second layer, heads that divide over the XCDs and not
+    (1, 16, 640, 64, False, I.F16, 37, 320), (1, 9, 930, 64, False, I.BF16, 37, 270), (1, 20, 860, 128, True, I.F16, 37, 776),
+    # the padded grid, per XCD and dealt over all
+    (1, 24, 1024, 64, False, I.BF16, 37, 776), (1, 32, 680, 64, False, I.F16, 37, 776), (1, 5, 3290, 64, True, I.F16, 37, 776),
+    # by weight in mirrored layers, over groups of XCDs, over all and per XCD; more than four layers
+    (1, 10, 2600, 64, True, I.BF16, 37, 820), (1, 7, 3700, 64, True, I.F16, 37, 812), (1, 64, 512, 64, True, I.BF16, 37, 1024), (1, 32, 1150, 128, True, I.F16, 37, 1152),
+    # eight waves: one to a unit, a second one, by weight where there is only one
+    (1, 7, 1100, 128, True, I.F16, 38, 245), (1, 3, 3663, 64, True, I.BF16, 38, 345), (1, 5, 2002, 128, True, I.BF16, 38, 315),
+    # wave groups
+    (1, 8, 1200, 64, False, I.F16, 40, 152), (1, 3, 5000, 128, False, I.BF16, 40, 237), (1, 5, 5000, 128, True, I.F16, 40, 395),
+    (2, 8, 2000, 128, True, I.BF16, 40, 512),
+    # 256-row tiles, 128-row tiles; a partial second layer of short heads, whole ones, three workgroups per unit
+    (1, 33, 1000, 128, False, I.F16, 36, 132), (1, 96, 250, 128, False, I.F16, 1, 192), (1, 100, 384, 64, True, I.BF16, 3, 300),
+    (4, 16, 1024, 64, True, I.F16, 18, 512), (8, 12, 700, 64, False, I.BF16, 18, 576),
+]
+
+
+def test_the_cases_are_what_they_stand_for():
+    for B, H, N, d, causal, dtype, want, grid in CASES:
+        assert A.attn_choose_variant(B, H, N, d, dtype, causal) == want, (B, H, N, d, causal)
+        assert A.attn_schedule_grid(want, 256, B, H, N) == grid, (B, H, N, d, causal)
+
+
 @pytest.mark.gpu
-@pytest.mark.parametrize("B,H,N,d,causal,dtype", [
-    (1, 8, 1200, 64, False, I.F16),      # 304 items: a second layer, per XCD
-    (1, 3, 5000, 128, False, I.BF16),    # 471: the same, heads that do not divide over the XCDs
-    (1, 24, 1024, 64, False, I.BF16),    # 768: the padded grid, per XCD
-    (1, 5, 3290, 64, True, I.F16),       # 515: the padded grid
-    (1, 5, 5000, 128, True, I.F16),      # 785: by weight, one item per workgroup
-    (2, 8, 2000, 128, True, I.BF16),     # 1008: the same, per XCD
-    (1, 7, 1100, 128, True, I.F16),      # 245: eight waves
-    (1, 33, 1000, 128, False, I.F16),    # 128-row tiles
-    (4, 16, 1024, 64, True, I.F16),      # two workgroups per unit
-    (8, 12, 700, 64, False, I.BF16),     # three
-])
-def test_attn_fwd_runs_the_choice(B, H, N, d, causal, dtype):
+@pytest.mark.parametrize("B,H,N,d,causal,dtype,want,grid", CASES)
+def test_attn_fwd_runs_the_choice(B, H, N, d, causal, dtype, want, grid):
     from gpu_util import check, run_gpu
     from oracle import ref
     w = I.Workload("choice", B, H, N, d, causal, dtype)
     qb, kb, vb = I.make_qkv(w, seed=N)
     var = A.attn_choose_variant(B, H, N, d, dtype, causal)
+    assert (var, A.attn_schedule_grid(var, 256, B, H, N)) == (want, grid)
     print(f"case {w.label} variant {var}", flush=True)
     O, l = run_gpu(qb, kb, vb, causal, w.scale, dtype)
     O2, l2 = run_gpu(qb, kb, vb, causal, w.scale, dtype, variant=var)
