@@ -47,6 +47,10 @@ def test_the_groups_rows_and_grids():
     # d = 64 causal: a higher line of the key split from 300 keys on, three workgroups per unit for short rows
     (110, 300, 64, True, 37), (111, 300, 64, True, 3), (96, 299, 64, True, 37), (97, 299, 64, True, 3), (51, 1000, 64, True, 3),
     (52, 1000, 64, True, 18), (206, 256, 64, True, 18), (206, 255, 64, True, 3), (32, 1599, 64, True, FOUR), (37, 1599, 64, True, 18), (37, 1600, 64, True, 3),
+    # the most tiles of the key split, by the number of keys
+    (31, 767, 128, True, 1), (31, 768, 128, True, 37), (34, 1023, 128, True, 1), (34, 1024, 128, True, 37), (36, 639, 64, False, 3), (36, 640, 64, False, 37),
+    (59, 599, 64, True, 3), (59, 600, 64, True, 37), (55, 767, 64, True, 3), (55, 768, 64, True, 37), (39, 1199, 64, True, 3), (39, 1200, 64, True, 37),
+    (20, 1999, 64, True, 37), (20, 2000, 64, True, FOUR),
     # the key split on eight waves: how many tiles, from how many keys on
     (7, 1024, 128, False, 38), (16, 512, 128, False, 38), (16, 511, 128, False, 37), (4, 2048, 128, False, 38), (9, 900, 128, False, FOUR),
     (5, 1999, 128, True, 37), (5, 2000, 128, True, 38), (11, 1024, 128, True, 37), (5, 2240, 128, True, 38), (5, 2241, 128, True, 37), (2, 5500, 128, True, 38),
