@@ -84,9 +84,8 @@ int cu_count() {
 
 // Persistent workgroups: as many as the device keeps resident (occ per CU), a multiple of 8
 // when every XCD can be given whole heads, never more than there are work items.
-// The workgroups of the key split and of the wave groups are not persistent, one per item: they come in the order of the schedule, the
-// heaviest of a head first, as units become free (dealt out ahead, 4 heads x 8000 causal keys, d = 128, took
-// 170 us instead of 122).
+// The workgroups of the key split and of the wave groups are not persistent, one per item: they come in the order of the schedule
+// as units become free (dealt out ahead, 4 heads x 8000 causal keys, d = 128, took 170 us instead of 122).
 long long grid_size(int cus, const Variant& var, int BH, long long nqt) {
     const long long total = (long long)BH * nqt, resident = (long long)cus * var.occ;
     // (513 to 768 items: padded, which costs nothing that can be measured, 0.2 % at most; the schedule does not need it)

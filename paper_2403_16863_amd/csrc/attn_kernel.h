@@ -51,7 +51,7 @@ typedef s16x4 __attribute__((address_space(3))) * lds_s16x4_ptr;
 // before the first wave starts (-amdgpu-kernarg-preload-count; the first 14 words: up to BH): a kernel that
 // fetches them begins with a load from memory that everything waits for, 0.1 to 0.25 us of every launch
 // (a 512 x 512 x 512 GEMM: 3.38 us, preloaded 3.15).  Pairs of numbers travel as one 64-bit argument: an
-// argument costs the host 7 ns a launch.
+// argument costs the host about 20 ns a launch.
 struct Params {
     const uint16_t* q;
     const uint16_t* k;
