@@ -22,6 +22,16 @@
 //    NB = 4 on 2048 x 2048 x 2048: 18.7 us spread, 19.9 us in one step.
 //  * BK = 64 because rows of A in a stage are then 128 bytes, a whole line: with 32 (64-byte rows) the
 //    256 x 256 tile takes 102 us instead of 98 on the 4096 cube, the 128 x 256 tile 122 instead of 112.
+//  * By whole lines (LINES), for rows of A that do not all start on a 128-byte line (K no multiple of 64, or a base off
+//    the line): 64 k values of a row then lie in two lines, and a load instruction, 8 rows of 128 bytes, is 16 requests to the
+//    texture path in place of 8, which is what holds every tile but the largest.  So a stage loads the line that the
+//    row's next k values END in, of which the stage behind it reads the rest, and the ring of A holds one stage more.
+//    A fragment read takes each 16-byte chunk from one stage or the next, by a lane's own row (rows 16 apart
+//    agree).  bfloat16, us before and after: 1394 x 7384 x 5480 144.7 -> 127.3 (256 x 256 tiles), 2622 x 1016 x 6224 72.3 ->
+//    61.4 (128 x 128), 4096 x 4096 x 4088 114.7 -> 105.2, 5963 x 1528 x 1272 39.7 -> 36.2 (128 x 256), 1000 x 1032 x 2056
+//    15.0 -> 14.2 (64 x 128), 1000 x 1024 x 2056 10.8 -> 10.1 (64 x 64 on eight waves).  Where the rows start on lines the
+//    longer ring costs 0 to 3 %: such calls keep the ring without.  (B has no such form: its rows would need a line each in
+//    addition, so N off the line costs the wider tiles least.)
 //  * Workgroups of WK > 1 groups split K between the groups, each with a ring of its own (a group of
 //    one wave then needs no barrier at all), and sum in LDS at the end, in group order.
 //
@@ -49,7 +59,7 @@ struct Mfma16BF16 {
     static __device__ __forceinline__ unsigned pack2(float a, float b) { return attn::BF16::pack2(a, b); }
 };
 
-template <int BM_, int BN_, int BK_, int WM_, int WN_, int WK_, int NB_, int OCC_>
+template <int BM_, int BN_, int BK_, int WM_, int WN_, int WK_, int NB_, int OCC_, bool LINES_ = false>
 struct Block {
     static constexpr int BM = BM_, BN = BN_;  // tile of C of one workgroup
     static constexpr int BK = BK_;            // k extent of one stage: 32 or 64
@@ -57,6 +67,7 @@ struct Block {
     static constexpr int WK = WK_;            // groups of WM x WN waves that split K between them, each with a ring of its own
     static constexpr int NB = NB_;            // stages of a ring
     static constexpr int OCC = OCC_;          // workgroups per compute unit
+    static constexpr bool LINES = LINES_;     // A by whole lines (below)
 };
 
 // Size of the descriptors and, as a lane's offset, the mark of a chunk outside the matrix.  Real offsets
@@ -93,14 +104,17 @@ __global__ __launch_bounds__(BL::WM * BL::WN * BL::WK * 64, (BL::OCC * BL::WM * 
     const float slope = __builtin_bit_cast(float, (unsigned)k_kc_slope[2]);
     constexpr int BM = BL::BM, BN = BL::BN, WM = BL::WM, WN = BL::WN, WK = BL::WK, NB = BL::NB;
     constexpr int NW = WM * WN, BK = BL::BK, KS = BK / 32;
+    constexpr bool LINES = BL::LINES;
+    constexpr int NA = NB + LINES;  // stages of the ring of A
     constexpr int TM = BM / WM, TN = BN / WN, MT = TM / 16, NT = TN / 16;
     constexpr int A_STAGE = BM * BK * 2, B_STAGE = BN * BK * 2;
     constexpr int LA = A_STAGE / 1024 / NW, LB = B_STAGE / 1024 / NW, LPS = LA + LB;
     constexpr int CPA = BK / 8, CPB = BN / 8, SLOTS = BN / 16;
-    constexpr int RING = NB * (A_STAGE + B_STAGE);
+    constexpr int RING = NA * A_STAGE + NB * B_STAGE;
     static_assert(LA * 1024 * NW == A_STAGE && LB * 1024 * NW == B_STAGE, "whole load instructions per wave");
     static_assert(NT % 2 == 0, "C is stored in pairs of 16-column tiles");
     static_assert(NB >= 2 && (NB - 1) * LPS <= 63, "the counted waits must fit s_waitcnt's field");
+    static_assert(!LINES || BK == 64, "a line of A per row and stage");
     static_assert(WK == 1 || RING >= BM * BN * 4, "a ring also holds its group's partial sums");
 
     __shared__ __attribute__((aligned(256))) u32x4 smem[WK * RING / 16];
@@ -123,6 +137,14 @@ __global__ __launch_bounds__(BL::WM * BL::WN * BL::WK * 64, (BL::OCC * BL::WM * 
         tile_of_block((int)blockIdx.x, ntm, ntn, tm, tn);
     }
     const int m0 = tm * BM, n0 = tn * BN;
+    // a group's k: every WK-th stage, or, by lines, a run of stages
+    const int nkt = (K1 - k0 + WK * BK - 1) / (WK * BK), step = LINES ? BK : WK * BK;
+    k0 += wk * (LINES ? nkt * BK : BK);
+    if (LINES) K1 = min(K1, k0 + nkt * BK);
+    // 16-byte chunks from the start of a line to a row of A.  (The same for rows 16 apart: K is a multiple of 8.  m0 and k0
+    // do not change it either.)
+    auto shift = [&](int row) __attribute__((always_inline)) { return LINES ? (int)(((unsigned)((uintptr_t)a >> 4) + (unsigned)row * ((unsigned)K >> 3)) & 7) : 0; };
+    constexpr int BEFORE = LINES ? 7 * 16 : 0;  // bytes of a line that can lie ahead of a row
 
     // B piece: rows (k) of 32-byte slots, one slot per 16 columns.  The transposing read takes 4 rows x 32
     // bytes per 16 lanes and two such groups, 8 rows apart, per clock: the slot index is XOR-ed with a
@@ -139,8 +161,8 @@ __global__ __launch_bounds__(BL::WM * BL::WN * BL::WK * 64, (BL::OCC * BL::WM * 
 #pragma unroll
     for (int i = 0; i < LA; ++i) {
         const int ci = (wave * LA + i) * 64 + lane, row = ci / CPA;
-        kA[i] = ((ci % CPA) ^ a_code<CPA>(row)) * 8;
-        voffA[i] = m0 + row < M ? (unsigned)row * (unsigned)(K * 2) + kA[i] * 2 : kBufferSize;
+        kA[i] = (((ci % CPA) ^ a_code<CPA>(row)) - shift(row)) * 8;
+        voffA[i] = m0 + row < M ? (unsigned)row * (unsigned)(K * 2) + (unsigned)(kA[i] * 2 + BEFORE) : kBufferSize;
     }
 #pragma unroll
     for (int i = 0; i < LB; ++i) {
@@ -149,45 +171,57 @@ __global__ __launch_bounds__(BL::WM * BL::WN * BL::WK * 64, (BL::OCC * BL::WM * 
         kB[i] = row;
         voffB[i] = n0 + col < N ? (unsigned)row * (unsigned)(N * 2) + col * 2 : kBufferSize;
     }
-    const int nkt = (K1 - k0 + WK * BK - 1) / (WK * BK);
-    const char* pa = a + (size_t)m0 * K * 2 + (size_t)(k0 + wk * BK) * 2;
-    const char* pb = b + (size_t)n0 * 2 + (size_t)(k0 + wk * BK) * N * 2;
-    int kload = k0 + wk * BK;  // first k of the next stage to be requested
-    auto issue_a = [&](int i, unsigned buf, u32x4 r) __attribute__((always_inline)) {
-        attn::buffer_to_lds_16(r, voffA[i], lds0 + buf * A_STAGE + (wave * LA + i) * 1024);
+    const char* pa = a + (size_t)m0 * K * 2 + (size_t)k0 * 2 - BEFORE;
+    const char* pb = b + (size_t)n0 * 2 + (size_t)k0 * N * 2;
+    int kload = k0;  // first k of the next stage to be requested
+    auto issue_a = [&](unsigned voff, int i, unsigned buf, u32x4 r) __attribute__((always_inline)) {
+        attn::buffer_to_lds_16(r, voff, lds0 + buf * A_STAGE + (wave * LA + i) * 1024);
     };
     auto issue_b = [&](int i, unsigned buf, u32x4 r) __attribute__((always_inline)) {
-        attn::buffer_to_lds_16(r, voffB[i], lds0 + NB * A_STAGE + buf * B_STAGE + (wave * LB + i) * 1024);
+        attn::buffer_to_lds_16(r, voffB[i], lds0 + NA * A_STAGE + buf * B_STAGE + (wave * LB + i) * 1024);
     };
+    if constexpr (LINES) {  // line 0: nothing ahead of the row
+        const u32x4 r = attn::buffer_resource(pa, kBufferSize);
+#pragma unroll
+        for (int i = 0; i < LA; ++i) issue_a(kA[i] < 0 || k0 + kA[i] >= K1 ? kBufferSize : voffA[i], i, 0, r);
+        pa += BK * 2;
+    }
     // the last, partial stage: chunks past K deliver zeros on both sides
     auto clip_tail = [&]() __attribute__((always_inline)) {
-        if (kload + BK > K1) {
+        if (kload + (1 + LINES) * BK > K1) {
 #pragma unroll
-            for (int i = 0; i < LA; ++i) if (kload + kA[i] >= K1) voffA[i] = kBufferSize;
+            for (int i = 0; i < LA; ++i) if (kload + LINES * BK + kA[i] >= K1) voffA[i] = kBufferSize;
 #pragma unroll
             for (int i = 0; i < LB; ++i) if (kload + kB[i] >= K1) voffB[i] = kBufferSize;
         }
     };
     auto advance = [&]() __attribute__((always_inline)) {
-        pa += WK * BK * 2;
-        pb += (size_t)(WK * BK) * N * 2;
-        kload += WK * BK;
+        pa += step * 2;
+        pb += (size_t)step * N * 2;
+        kload += step;
     };
 
     unsigned a_base[KS];
+    bool a_next[KS];  // the chunk lies in the next line
 #pragma unroll
-    for (int j = 0; j < KS; ++j)
-        a_base[j] = lds0 + (wm * TM + (lane & 15)) * (BK * 2) + (((j * 4 + (lane >> 4)) ^ a_code<CPA>(lane & 15)) * 16);
+    for (int j = 0; j < KS; ++j) {
+        const int chunk = j * 4 + (lane >> 4) + shift(lane & 15);
+        a_next[j] = LINES && chunk >= CPA;
+        a_base[j] = lds0 + (wm * TM + (lane & 15)) * (BK * 2) + (((chunk & (CPA - 1)) ^ a_code<CPA>(lane & 15)) * 16);
+    }
     unsigned b_base[NT];
     {
         const int i16 = lane & 15, row = 8 * (lane >> 4) + (i16 >> 2);
 #pragma unroll
         for (int nt = 0; nt < NT; ++nt)
-            b_base[nt] = lds0 + NB * A_STAGE + row * (BN * 2) + (((wn * NT + nt) ^ b_code(row)) * 32) + (i16 & 3) * 8;
+            b_base[nt] = lds0 + NA * A_STAGE + row * (BN * 2) + (((wn * NT + nt) ^ b_code(row)) * 32) + (i16 & 3) * 8;
     }
     typedef const u32x4 __attribute__((address_space(3))) * lds_u32x4_ptr;
-    auto read_a = [&](int mt, int j, unsigned buf) __attribute__((always_inline)) -> u32x4 {
-        return *(lds_u32x4_ptr)(unsigned long)(a_base[j] + buf * A_STAGE + mt * 16 * (BK * 2));
+    auto a_address = [&](int j, unsigned buf) __attribute__((always_inline)) {
+        return a_base[j] + (a_next[j] ? (buf + 1 == NA ? 0 : buf + 1) : buf) * A_STAGE;
+    };
+    auto read_a = [&](int mt, unsigned address) __attribute__((always_inline)) -> u32x4 {
+        return *(lds_u32x4_ptr)(unsigned long)(address + mt * 16 * (BK * 2));
     };
     auto read_b = [&](int nt, int j, unsigned buf) __attribute__((always_inline)) -> u32x4 {
         const unsigned a = b_base[nt] + buf * B_STAGE + j * 32 * (BN * 2);
@@ -207,7 +241,7 @@ __global__ __launch_bounds__(BL::WM * BL::WN * BL::WK * 64, (BL::OCC * BL::WM * 
     constexpr int FIRST = NB == 2 ? 0 : KS == 1 ? MT * NT / 2 : MT * NT / 4, SPAN = (NB == 2 ? 1 : KS) * MT * NT;
     auto slot = [](int l) constexpr { return FIRST + l * (SPAN - FIRST) / LPS; };
     auto first_loads = [=]() constexpr { int n = 0; for (int l = 0; l < LPS; ++l) n += slot(l) < MT * NT; return n; };
-    unsigned lbuf = 0;  // the stage being requested: its buffer and sources
+    unsigned lbuf = 0, lbuf_a = 0;  // the stage being requested: its buffers (by lines, of A the line behind the stage's first) and sources
     u32x4 ra, rb;
     auto next_stage = [&](int t) __attribute__((always_inline)) {
         clip_tail();
@@ -217,13 +251,13 @@ __global__ __launch_bounds__(BL::WM * BL::WN * BL::WK * 64, (BL::OCC * BL::WM * 
     };
     auto issue = [&](auto l_c) __attribute__((always_inline)) {
         constexpr int l = decltype(l_c)::value;
-        if constexpr (l < LA) issue_a(l, lbuf, ra);
+        if constexpr (l < LA) issue_a(voffA[l], l, lbuf_a, ra);
         else issue_b(l - LA, lbuf, rb);
     };
 #pragma unroll
     for (int t = 0; t < NB; ++t) {
         next_stage(t);
-        lbuf = t;
+        lbuf = t, lbuf_a = t + LINES;
         attn::static_for<LPS>([&](auto l_c) __attribute__((always_inline)) {
             if (t < NB - 1 || slot(decltype(l_c)::value) < MT * NT) issue(l_c);
         });
@@ -235,11 +269,11 @@ __global__ __launch_bounds__(BL::WM * BL::WN * BL::WK * 64, (BL::OCC * BL::WM * 
 #pragma unroll
     for (int nt = 0; nt < NT; ++nt) fb[0][nt] = read_b(nt, 0, 0);
 #pragma unroll
-    for (int mt = 0; mt < MT; ++mt) fa[0][mt] = read_a(mt, 0, 0);
+    for (int mt = 0; mt < MT; ++mt) fa[0][mt] = read_a(mt, a_address(0, 0));
 
-    unsigned buf = 0;  // t % NB
+    unsigned buf = 0, abuf = 0;  // t % NB, t % NA
     auto stage = [&](auto par_c, int t) __attribute__((always_inline)) {
-        const unsigned nbuf = buf + 1 == NB ? 0 : buf + 1;
+        const unsigned nbuf = buf + 1 == NB ? 0 : buf + 1, nabuf = abuf + 1 == NA ? 0 : abuf + 1;
         attn::static_for<KS>([&](auto j_c) __attribute__((always_inline)) {
             constexpr int j = decltype(j_c)::value, P = (decltype(par_c)::value + j) & 1, Q = P ^ 1;
             constexpr bool LAST = j == KS - 1;
@@ -249,8 +283,9 @@ __global__ __launch_bounds__(BL::WM * BL::WN * BL::WK * 64, (BL::OCC * BL::WM * 
                 asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" ::"n"((NB - 2) * LPS) : "memory");
                 meet();
                 next_stage(t + NB);
-                lbuf = buf;
+                lbuf = buf, lbuf_a = abuf;
             }
+            const unsigned from_a = a_address(nj, LAST ? nabuf : abuf);
             attn::static_for<MT * NT>([&](auto i_c) __attribute__((always_inline)) {
                 constexpr int i = decltype(i_c)::value, mt = i / NT, nt = i % NT;
                 acc[mt][nt] = T::mfma(fb[P][nt], fa[P][mt], acc[mt][nt]);
@@ -260,7 +295,7 @@ __global__ __launch_bounds__(BL::WM * BL::WN * BL::WK * 64, (BL::OCC * BL::WM * 
                     constexpr int q = decltype(r_c)::value;
                     if constexpr (i == q * STEPS / R) {
                         if constexpr (q < NT) fb[Q][q] = read_b(q, nj, rbuf);
-                        else fa[Q][q - NT] = read_a(q - NT, nj, rbuf);
+                        else fa[Q][q - NT] = read_a(q - NT, from_a);
                     }
                 });
                 attn::static_for<LPS>([&](auto l_c) __attribute__((always_inline)) {
@@ -269,7 +304,7 @@ __global__ __launch_bounds__(BL::WM * BL::WN * BL::WK * 64, (BL::OCC * BL::WM * 
                 __builtin_amdgcn_sched_barrier(0);
             });
         });
-        buf = nbuf;
+        buf = nbuf, abuf = nabuf;
     };
     if constexpr (KS % 2 == 0) {
         for (int t = 0; t < nkt; ++t) stage(std::integral_constant<int, 0>{}, t);

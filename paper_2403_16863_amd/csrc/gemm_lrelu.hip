@@ -81,22 +81,37 @@ struct BlockShape {
     int bm, bn, bk, wk, threads, occ;
     int ragged;  // the least K that it is taken for where K is no multiple of 64
     float alone, full, ends;
-    BlockFn fn[2];
+    BlockFn fn[2], lines[2];  // by dtype; the second, where there is one, takes A by whole lines
 };
 template <class BL>
 constexpr BlockShape block_shape(float alone, float full, float ends, int ragged = 0) {
     return {BL::BM, BL::BN, BL::BK, BL::WK, BL::WM * BL::WN * BL::WK * 64, BL::OCC, ragged, alone, full, ends,
-            {gemm_block_kernel<Mfma16F16, BL>, gemm_block_kernel<Mfma16BF16, BL>}};
+            {gemm_block_kernel<Mfma16F16, BL>, gemm_block_kernel<Mfma16BF16, BL>}, {nullptr, nullptr}};
 }
+// (the same tile with A by whole lines; measured at `Block`)
+template <class BL>
+constexpr BlockShape with_lines(BlockShape s) {
+    using Lines = Block<BL::BM, BL::BN, BL::BK, BL::WM, BL::WN, BL::WK, BL::NB, BL::OCC, true>;
+    s.lines[0] = gemm_block_kernel<Mfma16F16, Lines>;
+    s.lines[1] = gemm_block_kernel<Mfma16BF16, Lines>;
+    return s;
+}
+template <class BL>
+constexpr BlockShape lines_shape(float alone, float full, float ends, int ragged = 0) {
+    return with_lines<BL>(block_shape<BL>(alone, full, ends, ragged));
+}
+// Rows of A that do not all start on a line: of the 64 x 64 tiles on four waves the line that the rings would have in addition
+// costs the third workgroup of a unit, and the two smaller tiles are held by latency (32 x 64: 0.93 to 1.02 of the time).
+static bool off_lines(const void* a, int K) { return (K & 63) || ((uintptr_t)a & 127); }
 static const BlockShape kBlocks[] = {
     block_shape<Block<32, 32, 32, 1, 1, 4, 4, 2>>(0.21f, 0.22f, 0.5f),
     block_shape<Block<32, 64, 64, 1, 2, 2, 3, 2>>(0.27f, 0.31f, 0.58f),
     block_shape<Block<64, 64, 64, 2, 2, 1, 3, 3>>(0.24f, 0.17f, 0.22f),
-    block_shape<Block<64, 64, 64, 2, 2, 2, 4, 1>>(0.40f, 0.f, 0.9f, 2112),
-    block_shape<Block<64, 128, 64, 1, 4, 1, 3, 2>>(0.27f, 0.28f, 0.88f),
-    block_shape<Block<128, 128, 64, 2, 4, 1, 4, 1>>(0.41f, 0.f, 0.9f),
-    block_shape<Block<128, 256, 64, 2, 4, 1, 3, 1>>(0.64f, 0.f, 1.8f),
-    block_shape<Block<256, 256, 64, 2, 4, 1, 2, 1>>(1.1f, 0.f, 3.0f),
+    lines_shape<Block<64, 64, 64, 2, 2, 2, 4, 1>>(0.40f, 0.f, 0.9f, 2112),
+    lines_shape<Block<64, 128, 64, 1, 4, 1, 3, 2>>(0.27f, 0.28f, 0.88f),
+    lines_shape<Block<128, 128, 64, 2, 4, 1, 4, 1>>(0.41f, 0.f, 0.9f),
+    lines_shape<Block<128, 256, 64, 2, 4, 1, 3, 1>>(0.64f, 0.f, 1.8f),
+    lines_shape<Block<256, 256, 64, 2, 4, 1, 2, 1>>(1.1f, 0.f, 3.0f),
 };
 
 static const BlockShape& choose_block(int M, int N, int K) {
@@ -104,7 +119,7 @@ static const BlockShape& choose_block(int M, int N, int K) {
     const BlockShape* best = &kBlocks[0];
     float best_us = 0.f;
     for (const BlockShape& s : kBlocks) {
-        if ((long long)(s.bm - 1) * K * 2 + s.bk * 2 >= (long long)kBufferSize) continue;  // 32-bit offsets in a tile's rows
+        if ((long long)(s.bm - 1) * K * 2 + s.bk * 2 + 128 >= (long long)kBufferSize) continue;  // 32-bit offsets in a tile's rows
         if (K < s.ragged && (K & 63)) continue;
         const unsigned long long tiles = (unsigned long long)cover(M, s.bm) * cover(N, s.bn);
         const long long n = (tiles + kComputeUnits - 1) / kComputeUnits, stages = cover(K, s.bk * s.wk);
@@ -170,7 +185,8 @@ static int launch_block(const void* a, const void* b, void* c, int M, int N, int
     const BlockShape& s = choose_block(M, N, K);
     Arguments to(a, b, c, M, N, K, K, slope);
     void* args[] = {&to.pointers_m_n, &to.k_kc_slope};
-    if (hipLaunchKernel((const void*)s.fn[dtype], dim3(cover(M, s.bm) * cover(N, s.bn)), dim3(s.threads), args, 0, (hipStream_t)stream) != hipSuccess) {
+    const BlockFn fn = s.lines[dtype] && off_lines(a, K) ? s.lines[dtype] : s.fn[dtype];
+    if (hipLaunchKernel((const void*)fn, dim3(cover(M, s.bm) * cover(N, s.bn)), dim3(s.threads), args, 0, (hipStream_t)stream) != hipSuccess) {
         (void)hipGetLastError();
         return GEMM_ELAUNCH;
     }

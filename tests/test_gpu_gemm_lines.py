@@ -1,0 +1,51 @@
+"""GEMM + LeakyReLU where rows of A do not start on 128-byte lines: every phase of a row against the lines (K / 8 modulo
+8, and the base of A in 16-byte steps), on every tile that takes A by whole lines.  Tolerance as in test_gpu_gemm.py."""
+import numpy as np
+import pytest
+
+from paper_2403_16863_amd import inputs as I
+
+from test_gpu_gemm import check
+from test_gpu_gemm_block import block_of
+
+# tile: (M, N, K of the eight phases): one row and one column chunk past a tile
+SHAPES = {
+    (64, 64): (833, 840, 2112),
+    (64, 128): (1025, 1000, 768),
+    (128, 128): (1281, 1544, 512),
+    (128, 256): (1889, 2224, 960),
+    (256, 256): (3841, 2128, 136),
+}
+
+
+def run(ab, bb, dtype, offset):
+    """C with A at `offset` 16-byte chunks behind a line, and NaN in front of and behind it."""
+    import torch
+    from paper_2403_16863_amd import gemm
+    M, K = ab.shape
+    room = torch.full((M * K + 128,), 0x7FFF, dtype=torch.int16, device="cuda:0")
+    a = room[64 + 8 * offset:][:M * K].view(M, K)
+    a.copy_(torch.from_numpy(ab.view(np.int16)))
+    tdt = torch.bfloat16 if dtype == I.BF16 else torch.float16
+    b = torch.from_numpy(bb.view(np.int16)).to("cuda:0").view(tdt)
+    assert (a.data_ptr() & 127) == 16 * offset
+    c = torch.full((M, bb.shape[1]), float("nan"), dtype=tdt, device="cuda:0")
+    gemm.gemm_lrelu(a.view(tdt), b, c, 0.1)
+    torch.cuda.synchronize()
+    return c.double().cpu().numpy()
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("tile", sorted(SHAPES), ids=lambda t: f"{t[0]}x{t[1]}")
+def test_every_phase_of_the_rows(tile):
+    M, N, K0 = SHAPES[tile]
+    for n in range(8):
+        K, offset, dtype = K0 + 8 * n, (0, 1, 0, 7, 4, 0, 2, 5)[n], (I.F16, I.BF16)[n & 1]
+        assert block_of(M, N, K) == tile
+        print(f"M{M} N{N} K{K} base {offset} dtype {dtype}", flush=True)
+        ab, bb = I.make_gemm(M, N, K, dtype, seed=700 + n)
+        check(run(ab, bb, dtype, offset), ab, bb, 0.1, dtype, f"M{M} N{N} K{K} base {offset}")
+    K, dtype = (K0 + 63) // 64 * 64, I.BF16     # rows that are whole lines, off the lines by the base alone
+    assert block_of(M, N, K) == tile
+    ab, bb = I.make_gemm(M, N, K, dtype, seed=710)
+    check(run(ab, bb, dtype, 3), ab, bb, 0.1, dtype, f"M{M} N{N} K{K} base 3")
