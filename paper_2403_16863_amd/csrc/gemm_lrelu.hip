@@ -46,6 +46,8 @@ constexpr int kDefault = 1;  // where the schedule search starts
 // Tiles of `size` (a power of two) that cover n >= 1 (n may be the largest int).  Shifts, here and below: the choices
 // run on every call, and their forty divisions took 0.1 us of it.
 static int cover(int n, int size) { return 1 + ((n - 1) >> __builtin_ctz(size)); }
+// Of any size.
+static int cover_any(int n, int size) { return 1 + (n - 1) / size; }
 
 static int check_args(const void* a, const void* b, const void* c, int M, int N, int K, int dtype, int variant_id) {
     if (!a || !b || !c) return GEMM_EINVAL;
@@ -81,11 +83,12 @@ struct BlockShape {
     int bm, bn, bk, wk, threads, occ;
     int ragged;  // the least K that it is taken for where K is no multiple of 64
     float alone, full, ends;
+    struct Large { float alone, full, load, off, ends; } large;  // of the model for large calls (choose_large)
     BlockFn fn[2], lines[2];  // by dtype; the second, where there is one, takes A by whole lines
 };
 template <class BL>
-constexpr BlockShape block_shape(float alone, float full, float ends, int ragged = 0) {
-    return {BL::BM, BL::BN, BL::BK, BL::WK, BL::WM * BL::WN * BL::WK * 64, BL::OCC, ragged, alone, full, ends,
+constexpr BlockShape block_shape(float alone, float full, float ends, BlockShape::Large large, int ragged = 0) {
+    return {BL::BM, BL::BN, BL::BK, BL::WK, BL::WM * BL::WN * BL::WK * 64, BL::OCC, ragged, alone, full, ends, large,
             {gemm_block_kernel<Mfma16F16, BL>, gemm_block_kernel<Mfma16BF16, BL>}, {nullptr, nullptr}};
 }
 // (the same tile with A by whole lines; measured at `Block`)
@@ -97,25 +100,33 @@ constexpr BlockShape with_lines(BlockShape s) {
     return s;
 }
 template <class BL>
-constexpr BlockShape lines_shape(float alone, float full, float ends, int ragged = 0) {
-    return with_lines<BL>(block_shape<BL>(alone, full, ends, ragged));
+constexpr BlockShape lines_shape(float alone, float full, float ends, BlockShape::Large large, int ragged = 0) {
+    return with_lines<BL>(block_shape<BL>(alone, full, ends, large, ragged));
 }
 // Rows of A that do not all start on a line: of the 64 x 64 tiles on four waves the line that the rings would have in addition
 // costs the third workgroup of a unit, and the two smaller tiles are held by latency (32 x 64: 0.93 to 1.02 of the time).
 static bool off_lines(const void* a, int K) { return (K & 63) || ((uintptr_t)a & 127); }
 static const BlockShape kBlocks[] = {
-    block_shape<Block<32, 32, 32, 1, 1, 4, 4, 2>>(0.21f, 0.22f, 0.5f),
-    block_shape<Block<32, 64, 64, 1, 2, 2, 3, 2>>(0.27f, 0.31f, 0.58f),
-    block_shape<Block<64, 64, 64, 2, 2, 1, 3, 3>>(0.24f, 0.17f, 0.22f),
-    lines_shape<Block<64, 64, 64, 2, 2, 2, 4, 1>>(0.40f, 0.f, 0.9f, 2112),
-    lines_shape<Block<64, 128, 64, 1, 4, 1, 3, 2>>(0.27f, 0.28f, 0.88f),
-    lines_shape<Block<128, 128, 64, 2, 4, 1, 4, 1>>(0.41f, 0.f, 0.9f),
-    lines_shape<Block<128, 256, 64, 2, 4, 1, 3, 1>>(0.64f, 0.f, 1.8f),
-    lines_shape<Block<256, 256, 64, 2, 4, 1, 2, 1>>(1.1f, 0.f, 3.0f),
+    block_shape<Block<32, 32, 32, 1, 1, 4, 4, 2>>(0.21f, 0.22f, 0.5f, {0.275f, 0.253f, 0.02f, 0.15f, 0.17f}),
+    block_shape<Block<32, 64, 64, 1, 2, 2, 3, 2>>(0.27f, 0.31f, 0.58f, {0.229f, 0.288f, 0.06f, 0.25f, 0.11f}),
+    block_shape<Block<64, 64, 64, 2, 2, 1, 3, 3>>(0.24f, 0.17f, 0.22f, {0.215f, 0.181f, 0.25f, 0.16f, 0.f}),
+    lines_shape<Block<64, 64, 64, 2, 2, 2, 4, 1>>(0.40f, 0.f, 0.9f, {0.310f, 0.f, 0.61f, 0.17f, 0.37f}, 2112),
+    lines_shape<Block<64, 128, 64, 1, 4, 1, 3, 2>>(0.27f, 0.28f, 0.88f, {0.261f, 0.213f, 0.54f, 0.09f, 0.32f}),
+    lines_shape<Block<128, 128, 64, 2, 4, 1, 4, 1>>(0.41f, 0.f, 0.9f, {0.327f, 0.f, 0.62f, 0.09f, 1.02f}),
+    lines_shape<Block<128, 256, 64, 2, 4, 1, 3, 1>>(0.64f, 0.f, 1.8f, {0.502f, 0.f, 0.80f, 0.f, 2.39f}),
+    lines_shape<Block<256, 256, 64, 2, 4, 1, 2, 1>>(1.1f, 0.f, 3.0f, {0.982f, 0.f, 0.66f, 0.01f, 4.20f}),
+};
+// Tiles for large calls only: heights between the powers of two, for the calls whose tiles of those leave units
+// without work or fill the units a little more than once.
+static const BlockShape kLargeBlocks[] = {
+    lines_shape<Block<96, 64, 64, 2, 2, 2, 3, 1>>(0.f, 0.f, 0.f, {0.382f, 0.f, 0.60f, 0.15f, 0.77f}),
+    lines_shape<Block<192, 128, 64, 2, 4, 1, 3, 1>>(0.f, 0.f, 0.f, {0.443f, 0.f, 0.56f, 0.05f, 1.83f}),
+    lines_shape<Block<192, 256, 64, 2, 4, 1, 2, 1>>(0.f, 0.f, 0.f, {0.768f, 0.f, 0.77f, 0.06f, 2.94f}),
 };
 
-static const BlockShape& choose_block(int M, int N, int K) {
-    constexpr unsigned long long kComputeUnits = 256;
+constexpr unsigned long long kComputeUnits = 256;
+
+static const BlockShape& choose_table(int M, int N, int K) {
     const BlockShape* best = &kBlocks[0];
     float best_us = 0.f;
     for (const BlockShape& s : kBlocks) {
@@ -126,6 +137,39 @@ static const BlockShape& choose_block(int M, int N, int K) {
         const float alone = (float)(n <= s.occ ? 1 : (n + s.occ - 1) / s.occ) * s.alone, full = (float)n * s.full;
         const float us = (float)stages * (alone > full ? alone : full) + (float)n * s.ends;
         if (&s == &kBlocks[0] || us < best_us) best = &s, best_us = us;
+    }
+    return *best;
+}
+
+// ---- large calls: a second model, of more terms, puts the choice above against the tiles of kLargeBlocks.  With n tiles on the
+// busiest unit, and f of the units' n rounds filled, a tile shape takes about
+//     ceil(K / kstage) * max(ceil(n / occ) * alone, n * full) * (1 + load * f) * (1 + off) + n * ends + 2.7      (us)
+// (load: what the units take from each other, in memory and clock; off: only where N is no multiple of 64, where every row of
+// a piece of B begins and ends inside a line; 2.7: the launch).  Fitted to 190 shapes of 3e8 products and more, M 33 .. 8192, N 64 ..
+// 8192 and K 256 .. 8192, a third of them with N and K multiples of 64, each timed with every tile, bfloat16; the
+// standard deviation of the time over the model is 6 to 13 % by tile, so one of the new tiles has to be 5 % ahead, or, with a short
+// K, where what is not a stage weighs more, 11 %.  Of those shapes 26 take another tile and run in 0.89 of the time (geometric
+// mean; one takes longer, 3 %).  us:
+//   96 x 64    247 x 4160 x 1704 12.0 -> 10.1, 3353 x 384 x 1264 9.6 -> 8.3, 1138 x 1088 x 2880 16.8 -> 14.0, 1000 x 1032 x 2056 14.2 -> 12.6
+//   192 x 128  7798 x 2280 x 1000 52.8 -> 49.0, 1504 x 5624 x 2272 62.8 -> 51.8, 3430 x 1536 x 1856 25.3 -> 20.1
+//   192 x 256  5963 x 1528 x 1272 36.0 -> 31.9, 7028 x 1216 x 4608 107.9 -> 93.7, 4297 x 2176 x 576 18.6 -> 16.2
+static float large_us(const BlockShape& s, int M, int N, int K) {
+    const unsigned long long tiles = (unsigned long long)cover_any(M, s.bm) * cover(N, s.bn);
+    const int n = (int)((tiles + kComputeUnits - 1) / kComputeUnits), stages = cover(K, s.bk * s.wk);
+    const float alone = (float)(n <= s.occ ? 1 : (n + s.occ - 1) / s.occ) * s.large.alone, full = (float)n * s.large.full;
+    const float filled = (float)tiles / (float)(n * (int)kComputeUnits);
+    return (float)stages * (alone > full ? alone : full) * (1.f + s.large.load * filled) * (N & 63 ? 1.f + s.large.off : 1.f) + (float)n * s.large.ends + 2.7f;
+}
+static bool is_large(int M, int N, int K) { return M > 32 && K >= 256 && (double)M * N * K >= 3e8; }
+
+static const BlockShape& choose_block(int M, int N, int K) {
+    const BlockShape* best = &choose_table(M, N, K);
+    if (!is_large(M, N, K)) return *best;
+    float best_us = (K < 960 ? 0.89f : 0.95f) * large_us(*best, M, N, K);
+    for (const BlockShape& s : kLargeBlocks) {
+        if ((long long)(s.bm - 1) * K * 2 + s.bk * 2 + 128 >= (long long)kBufferSize) continue;
+        const float us = large_us(s, M, N, K);
+        if (us < best_us) best = &s, best_us = us;
     }
     return *best;
 }
@@ -186,7 +230,7 @@ static int launch_block(const void* a, const void* b, void* c, int M, int N, int
     Arguments to(a, b, c, M, N, K, K, slope);
     void* args[] = {&to.pointers_m_n, &to.k_kc_slope};
     const BlockFn fn = s.lines[dtype] && off_lines(a, K) ? s.lines[dtype] : s.fn[dtype];
-    if (hipLaunchKernel((const void*)fn, dim3(cover(M, s.bm) * cover(N, s.bn)), dim3(s.threads), args, 0, (hipStream_t)stream) != hipSuccess) {
+    if (hipLaunchKernel((const void*)fn, dim3(cover_any(M, s.bm) * cover(N, s.bn)), dim3(s.threads), args, 0, (hipStream_t)stream) != hipSuccess) {
         (void)hipGetLastError();
         return GEMM_ELAUNCH;
     }

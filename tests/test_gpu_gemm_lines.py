@@ -13,7 +13,7 @@ SHAPES = {
     (64, 64): (833, 840, 2112),
     (64, 128): (1025, 1000, 768),
     (128, 128): (1281, 1544, 512),
-    (128, 256): (1889, 2224, 960),
+    (128, 256): (2113, 2824, 960),
     (256, 256): (3841, 2128, 136),
 }
 
