@@ -251,7 +251,7 @@ __global__ __launch_bounds__(BL::WM * BL::WN * BL::WK * 64, (BL::OCC * BL::WM * 
     };
     auto issue = [&](auto l_c) __attribute__((always_inline)) {
         constexpr int l = decltype(l_c)::value;
-        if constexpr (l < LA) issue_a(voffA[l], l, lbuf_a, ra);
+        if constexpr (l < LA) issue_a(voffA[l], l, LINES ? lbuf_a : lbuf, ra);
         else issue_b(l - LA, lbuf, rb);
     };
 #pragma unroll
@@ -271,9 +271,9 @@ __global__ __launch_bounds__(BL::WM * BL::WN * BL::WK * 64, (BL::OCC * BL::WM * 
 #pragma unroll
     for (int mt = 0; mt < MT; ++mt) fa[0][mt] = read_a(mt, a_address(0, 0));
 
-    unsigned buf = 0, abuf = 0;  // t % NB, t % NA
+    unsigned buf = 0, line = 0;  // t % NB, and by lines t % NA
     auto stage = [&](auto par_c, int t) __attribute__((always_inline)) {
-        const unsigned nbuf = buf + 1 == NB ? 0 : buf + 1, nabuf = abuf + 1 == NA ? 0 : abuf + 1;
+        const unsigned nbuf = buf + 1 == NB ? 0 : buf + 1, abuf = LINES ? line : buf, nabuf = abuf + 1 == NA ? 0 : abuf + 1;
         attn::static_for<KS>([&](auto j_c) __attribute__((always_inline)) {
             constexpr int j = decltype(j_c)::value, P = (decltype(par_c)::value + j) & 1, Q = P ^ 1;
             constexpr bool LAST = j == KS - 1;
@@ -285,7 +285,7 @@ __global__ __launch_bounds__(BL::WM * BL::WN * BL::WK * 64, (BL::OCC * BL::WM * 
                 next_stage(t + NB);
                 lbuf = buf, lbuf_a = abuf;
             }
-            const unsigned from_a = a_address(nj, LAST ? nabuf : abuf);
+            const unsigned from_a = LINES ? a_address(nj, LAST ? nabuf : abuf) : 0;
             attn::static_for<MT * NT>([&](auto i_c) __attribute__((always_inline)) {
                 constexpr int i = decltype(i_c)::value, mt = i / NT, nt = i % NT;
                 acc[mt][nt] = T::mfma(fb[P][nt], fa[P][mt], acc[mt][nt]);
@@ -295,7 +295,7 @@ __global__ __launch_bounds__(BL::WM * BL::WN * BL::WK * 64, (BL::OCC * BL::WM * 
                     constexpr int q = decltype(r_c)::value;
                     if constexpr (i == q * STEPS / R) {
                         if constexpr (q < NT) fb[Q][q] = read_b(q, nj, rbuf);
-                        else fa[Q][q - NT] = read_a(q - NT, from_a);
+                        else fa[Q][q - NT] = read_a(q - NT, LINES ? from_a : a_base[nj] + rbuf * A_STAGE);
                     }
                 });
                 attn::static_for<LPS>([&](auto l_c) __attribute__((always_inline)) {
@@ -304,7 +304,8 @@ __global__ __launch_bounds__(BL::WM * BL::WN * BL::WK * 64, (BL::OCC * BL::WM * 
                 __builtin_amdgcn_sched_barrier(0);
             });
         });
-        buf = nbuf, abuf = nabuf;
+        buf = nbuf;
+        if constexpr (LINES) line = nabuf;
     };
     if constexpr (KS % 2 == 0) {
         for (int t = 0; t < nkt; ++t) stage(std::integral_constant<int, 0>{}, t);

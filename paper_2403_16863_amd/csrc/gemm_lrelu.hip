@@ -103,9 +103,13 @@ template <class BL>
 constexpr BlockShape lines_shape(float alone, float full, float ends, BlockShape::Large large, int ragged = 0) {
     return with_lines<BL>(block_shape<BL>(alone, full, ends, large, ragged));
 }
-// Rows of A that do not all start on a line: of the 64 x 64 tiles on four waves the line that the rings would have in addition
-// costs the third workgroup of a unit, and the two smaller tiles are held by latency (32 x 64: 0.93 to 1.02 of the time).
-static bool off_lines(const void* a, int K) { return (K & 63) || ((uintptr_t)a & 127); }
+// Whether A is taken by whole lines: its rows do not all start on one, and K is long enough for the line that the first
+// stage needs in addition.  Time without over time with, at K = 296 / 520 / 712 / 808 / 1064 / 1288: 128 x 128 tiles (4181 x 568)
+// 0.95 / 0.98 / 1.01 / 1.03 / 1.05 / 1.09, 64 x 128 (403 x 4288) 0.97 / 0.98 / 0.98 / 1.00 / 1.01 / 1.02, 256 x 256 (3841 x 2128)
+// 0.98 / 1.00 / 1.01 / 1.02 / 1.05 / 1.15, 128 x 256 (4095 x 1520) 1.01 / 1.01 / 1.02 / 0.99 / 1.02 / 1.04.  (Not for the three smallest
+// tiles: of the 64 x 64 tiles on four waves the longer ring costs the third workgroup of a unit, and the others are held by
+// latency, 32 x 64: 0.93 to 1.02 of the time.)
+static bool off_lines(const void* a, int K) { return K >= 768 && ((K & 63) || ((uintptr_t)a & 127)); }
 static const BlockShape kBlocks[] = {
     block_shape<Block<32, 32, 32, 1, 1, 4, 4, 2>>(0.21f, 0.22f, 0.5f, {0.275f, 0.253f, 0.02f, 0.15f, 0.17f}),
     block_shape<Block<32, 64, 64, 1, 2, 2, 3, 2>>(0.27f, 0.31f, 0.58f, {0.229f, 0.288f, 0.06f, 0.25f, 0.11f}),
