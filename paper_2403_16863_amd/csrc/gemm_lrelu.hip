@@ -83,13 +83,16 @@ struct BlockShape {
     int bm, bn, bk, wk, threads, occ;
     int ragged;  // the least K that it is taken for where K is no multiple of 64
     float alone, full, ends;
-    struct Large { float alone, full, load, off, ends; } large;  // of the model for large calls (choose_large)
+    struct Large { float alone, full, load, off, ends; } large;  // of the model for large calls (large_us)
     BlockFn fn[2], lines[2];  // by dtype; the second, where there is one, takes A by whole lines
+    BlockFn split[2], split_lines[2];  // the same for a range of K (or null)
+    const BlockFn& whole_for(int dtype, bool off_lines) const { return off_lines && lines[dtype] ? lines[dtype] : fn[dtype]; }
+    const BlockFn& range_for(int dtype, bool off_lines) const { return off_lines && split_lines[dtype] ? split_lines[dtype] : split[dtype]; }
 };
 template <class BL>
 constexpr BlockShape block_shape(float alone, float full, float ends, BlockShape::Large large, int ragged = 0) {
     return {BL::BM, BL::BN, BL::BK, BL::WK, BL::WM * BL::WN * BL::WK * 64, BL::OCC, ragged, alone, full, ends, large,
-            {gemm_block_kernel<Mfma16F16, BL>, gemm_block_kernel<Mfma16BF16, BL>}, {nullptr, nullptr}};
+            {gemm_block_kernel<Mfma16F16, BL>, gemm_block_kernel<Mfma16BF16, BL>}, {nullptr, nullptr}, {nullptr, nullptr}, {nullptr, nullptr}};
 }
 // (the same tile with A by whole lines; measured at `Block`)
 template <class BL>
@@ -103,6 +106,17 @@ template <class BL>
 constexpr BlockShape lines_shape(float alone, float full, float ends, BlockShape::Large large, int ragged = 0) {
     return with_lines<BL>(block_shape<BL>(alone, full, ends, large, ragged));
 }
+template <class BL, bool LINES>
+constexpr BlockShape with_split(BlockShape s) {
+    s.split[0] = gemm_block_kernel<Mfma16F16, BL, true>;
+    s.split[1] = gemm_block_kernel<Mfma16BF16, BL, true>;
+    if constexpr (LINES) {
+        using Lines = Block<BL::BM, BL::BN, BL::BK, BL::WM, BL::WN, BL::WK, BL::NB, BL::OCC, true>;
+        s.split_lines[0] = gemm_block_kernel<Mfma16F16, Lines, true>;
+        s.split_lines[1] = gemm_block_kernel<Mfma16BF16, Lines, true>;
+    }
+    return s;
+}
 // Whether A is taken by whole lines: its rows do not all start on one, and K is long enough for the line that the first
 // stage needs in addition.  Time without over time with, at K = 296 / 520 / 712 / 808 / 1064 / 1288: 128 x 128 tiles (4181 x 568)
 // 0.95 / 0.98 / 1.01 / 1.03 / 1.05 / 1.09, 64 x 128 (403 x 4288) 0.97 / 0.98 / 0.98 / 1.00 / 1.01 / 1.02, 256 x 256 (3841 x 2128)
@@ -111,12 +125,12 @@ constexpr BlockShape lines_shape(float alone, float full, float ends, BlockShape
 // latency, 32 x 64: 0.93 to 1.02 of the time.)
 static bool off_lines(const void* a, int K) { return K >= 768 && ((K & 63) || ((uintptr_t)a & 127)); }
 static const BlockShape kBlocks[] = {
-    block_shape<Block<32, 32, 32, 1, 1, 4, 4, 2>>(0.21f, 0.22f, 0.5f, {0.275f, 0.253f, 0.02f, 0.15f, 0.17f}),
-    block_shape<Block<32, 64, 64, 1, 2, 2, 3, 2>>(0.27f, 0.31f, 0.58f, {0.229f, 0.288f, 0.06f, 0.25f, 0.11f}),
-    block_shape<Block<64, 64, 64, 2, 2, 1, 3, 3>>(0.24f, 0.17f, 0.22f, {0.215f, 0.181f, 0.25f, 0.16f, 0.f}),
+    with_split<Block<32, 32, 32, 1, 1, 4, 4, 2>, false>(block_shape<Block<32, 32, 32, 1, 1, 4, 4, 2>>(0.21f, 0.22f, 0.5f, {0.275f, 0.253f, 0.02f, 0.15f, 0.17f})),
+    with_split<Block<32, 64, 64, 1, 2, 2, 3, 2>, false>(block_shape<Block<32, 64, 64, 1, 2, 2, 3, 2>>(0.27f, 0.31f, 0.58f, {0.229f, 0.288f, 0.06f, 0.25f, 0.11f})),
+    with_split<Block<64, 64, 64, 2, 2, 1, 3, 3>, false>(block_shape<Block<64, 64, 64, 2, 2, 1, 3, 3>>(0.24f, 0.17f, 0.22f, {0.215f, 0.181f, 0.25f, 0.16f, 0.f})),
     lines_shape<Block<64, 64, 64, 2, 2, 2, 4, 1>>(0.40f, 0.f, 0.9f, {0.310f, 0.f, 0.61f, 0.17f, 0.37f}, 2112),
     lines_shape<Block<64, 128, 64, 1, 4, 1, 3, 2>>(0.27f, 0.28f, 0.88f, {0.261f, 0.213f, 0.54f, 0.09f, 0.32f}),
-    lines_shape<Block<128, 128, 64, 2, 4, 1, 4, 1>>(0.41f, 0.f, 0.9f, {0.327f, 0.f, 0.62f, 0.09f, 1.02f}),
+    with_split<Block<128, 128, 64, 2, 4, 1, 4, 1>, true>(lines_shape<Block<128, 128, 64, 2, 4, 1, 4, 1>>(0.41f, 0.f, 0.9f, {0.327f, 0.f, 0.62f, 0.09f, 1.02f})),
     lines_shape<Block<128, 256, 64, 2, 4, 1, 3, 1>>(0.64f, 0.f, 1.8f, {0.502f, 0.f, 0.80f, 0.f, 2.39f}),
     lines_shape<Block<256, 256, 64, 2, 4, 1, 2, 1>>(1.1f, 0.f, 3.0f, {0.982f, 0.f, 0.66f, 0.01f, 4.20f}),
 };
@@ -124,7 +138,7 @@ static const BlockShape kBlocks[] = {
 // without work or fill the units a little more than once.
 static const BlockShape kLargeBlocks[] = {
     lines_shape<Block<96, 64, 64, 2, 2, 2, 3, 1>>(0.f, 0.f, 0.f, {0.382f, 0.f, 0.60f, 0.15f, 0.77f}),
-    lines_shape<Block<192, 128, 64, 2, 4, 1, 3, 1>>(0.f, 0.f, 0.f, {0.443f, 0.f, 0.56f, 0.05f, 1.83f}),
+    with_split<Block<192, 128, 64, 2, 4, 1, 3, 1>, true>(lines_shape<Block<192, 128, 64, 2, 4, 1, 3, 1>>(0.f, 0.f, 0.f, {0.443f, 0.f, 0.56f, 0.05f, 1.83f})),
     lines_shape<Block<192, 256, 64, 2, 4, 1, 2, 1>>(0.f, 0.f, 0.f, {0.768f, 0.f, 0.77f, 0.06f, 2.94f}),
 };
 
@@ -159,9 +173,9 @@ static const BlockShape& choose_table(int M, int N, int K) {
 //   192 x 256  5963 x 1528 x 1272 36.0 -> 31.9, 7028 x 1216 x 4608 107.9 -> 93.7, 4297 x 2176 x 576 18.6 -> 16.2
 static float large_us(const BlockShape& s, int M, int N, int K) {
     const unsigned long long tiles = (unsigned long long)cover_any(M, s.bm) * cover(N, s.bn);
-    const int n = (int)((tiles + kComputeUnits - 1) / kComputeUnits), stages = cover(K, s.bk * s.wk);
+    const long long n = (long long)((tiles + kComputeUnits - 1) / kComputeUnits), stages = cover(K, s.bk * s.wk);
     const float alone = (float)(n <= s.occ ? 1 : (n + s.occ - 1) / s.occ) * s.large.alone, full = (float)n * s.large.full;
-    const float filled = (float)tiles / (float)(n * (int)kComputeUnits);
+    const float filled = (float)tiles / (float)(n * (long long)kComputeUnits);
     return (float)stages * (alone > full ? alone : full) * (1.f + s.large.load * filled) * (N & 63 ? 1.f + s.large.off : 1.f) + (float)n * s.large.ends + 2.7f;
 }
 static bool is_large(int M, int N, int K) { return M > 32 && K >= 256 && (double)M * N * K >= 3e8; }
@@ -190,37 +204,69 @@ static const BlockShape& choose_block(int M, int N, int K) {
 //   64 x 64   428 x 728 x 6168   22.4 / 16.3 (28.3 / 18.9)   170 x 456 x 4736   12.4 / 8.9 (14.1 / 9.5)
 //             130 x 2448 x 6576  23.7 / 21.1 (30.0 / 27.0)   64 x 4096 x 4096   13.4 / 12.4 (20.7 / 14.8)
 // Over 60 random shapes that the rule below takes: 1.2 times as fast on one set, 1.7 on fresh ones.
-static const BlockFn kSplitFns[][2] = {  // tiles of kBlocks[0], [1], [2]
-    {gemm_block_kernel<Mfma16F16, Block<32, 32, 32, 1, 1, 4, 4, 2>, true>, gemm_block_kernel<Mfma16BF16, Block<32, 32, 32, 1, 1, 4, 4, 2>, true>},
-    {gemm_block_kernel<Mfma16F16, Block<32, 64, 64, 1, 2, 2, 3, 2>, true>, gemm_block_kernel<Mfma16BF16, Block<32, 64, 64, 1, 2, 2, 3, 2>, true>},
-    {gemm_block_kernel<Mfma16F16, Block<64, 64, 64, 2, 2, 1, 3, 3>, true>, gemm_block_kernel<Mfma16BF16, Block<64, 64, 64, 2, 2, 1, 3, 3>, true>},
-};
 struct Split {
-    int shape, ranges, kc;  // ranges of kc values of k; 0: not split
+    const BlockShape* shape;
+    int ranges, kc;  // ranges of kc values of k; 0: not split
 };
-static Split choose_split(int M, int N, int K) {
-    if (K < 4000) return {0, 0, K};
+static Split choose_few(int M, int N, int K) {
+    if (K < 4000) return {nullptr, 0, K};
     auto tiles = [&](int s) { return (long long)cover(M, kBlocks[s].bm) * cover(N, kBlocks[s].bn); };
     const int s = tiles(0) <= 64 ? 0 : M <= 32 ? 1 : 2;
     const long long n = tiles(s);
-    if (K < (s == 0 ? 4864 : M <= 64 ? 4000 : 4608) || n > (s == 1 ? 96 : 128) || K > (1 << 16)) return {s, 0, K};
+    if (K < (s == 0 ? 4864 : M <= 64 ? 4000 : 4608) || n > (s == 1 ? 96 : 128) || K > (1 << 16)) return {nullptr, 0, K};
     long long ranges = 256 / n;  // one workgroup per compute unit
     ranges = ranges < K / 512 ? ranges : K / 512;
     ranges = ranges < (s == 0 ? 16 : 8) ? ranges : s == 0 ? 16 : 8;
     const int step = kBlocks[s].bk * kBlocks[s].wk, kc = (int)((K + ranges - 1) / ranges + step - 1) / step * step;
-    return {s, (K + kc - 1) / kc, kc};
+    return {&kBlocks[s], (K + kc - 1) / kc, kc};
+}
+
+// Large calls that the rule above leaves whole: tiles of 128 x 128 or 192 x 128, which read A and B the fewest times but are
+// too few, with K split into up to 8 ranges of 512 and more, one workgroup per unit.  The time is modelled as
+//     stages of a range * alone * (1 + load * f) * (1 + off) + ends + 2.7 + 2.3 (the second launch) + 0.4 per MB of parts   (us)
+// and has to be 5 % below that of the call in one piece.  From 1e9 products on (162 x 800 x 4512 took
+// 12.9 us instead of 12.4), and at most 32 MB of parts.  Of the 190 shapes above 23 are split and run in 0.81 of the time (geometric
+// mean, none longer; beside them 339 x 2256 x 4288 18.2 -> 18.9 us): 2856 x 256 x 7288 33.9 -> 24.3, 969 x 664 x 7256 28.8 -> 21.5,
+// 180 x 2880 x 8192 37.5 -> 23.8, 118 x 7464 x 5592 35.7 -> 27.2, 4939 x 264 x 6464 48.7 -> 33.9, 2622 x 1016 x 6224 61.4 -> 48.7.  (128 x 256
+// and 256 x 128 tiles with K split: within 3 % of these; the parts in the accumulators' own order, 1 KB a store: the same.)
+static Split choose_large_split(int M, int N, int K) {
+    const Split whole = {nullptr, 0, K};
+    if (!is_large(M, N, K) || (double)M * N * K < 1e9 || K > (1 << 16)) return whole;
+    static const struct { const BlockShape* shape; float alone, load, off, ends; } kRanges[] = {
+        {&kBlocks[5], 0.325f, 0.59f, 0.01f, 1.28f}, {&kLargeBlocks[1], 0.523f, 0.20f, 0.f, 1.21f}};
+    constexpr double kMost = 32 << 20;
+    Split best = whole;
+    float best_us = 0.f;
+    for (const auto& s : kRanges) {
+        const long long tiles = (long long)cover_any(M, s.shape->bm) * cover(N, s.shape->bn);
+        if ((long long)(s.shape->bm - 1) * K * 2 + s.shape->bk * 2 + 128 >= (long long)kBufferSize) continue;
+        for (int r = 2; r <= 8 && tiles * r <= (long long)kComputeUnits && r * 512 <= K && (double)M * N * 4 * r <= kMost; ++r) {
+            if (best_us == 0.f) best_us = 0.95f * large_us(choose_block(M, N, K), M, N, K);
+            const int kc = ((K + r - 1) / r + 63) / 64 * 64;
+            if ((K + kc - 1) / kc != r) continue;
+            const float filled = (float)(tiles * r) / (float)kComputeUnits;
+            const float us = (float)(kc / 64) * s.alone * (1.f + s.load * filled) * (N & 63 ? 1.f + s.off : 1.f) + s.ends + 5.f + 0.4e-6f * (float)M * (float)N * (float)(4 * r);
+            if (us < best_us) best = {s.shape, r, kc}, best_us = us;
+        }
+    }
+    return best;
+}
+
+static Split choose_split(int M, int N, int K) {
+    const Split few = choose_few(M, N, K);
+    return few.ranges ? few : choose_large_split(M, N, K);
 }
 
 static int launch_split(const Split& sp, const void* a, const void* b, void* c, int M, int N, int K, float slope, int dtype,
                         void* stream, void* workspace) {
-    const BlockShape& s = kBlocks[sp.shape];
+    const BlockShape& s = *sp.shape;
     int ranges = sp.ranges;
     Arguments to(a, b, workspace, M, N, K, sp.kc, slope);
     unsigned chunks = (unsigned)((long long)M * N / 8);
     void* args[] = {&to.pointers_m_n, &to.k_kc_slope};
     void* sum_args[] = {&workspace, &c, &ranges, &chunks, &slope};
     const void* const sum = dtype == GEMM_F16 ? (const void*)gemm_sum_kernel<Mfma16F16> : (const void*)gemm_sum_kernel<Mfma16BF16>;
-    if (hipLaunchKernel((const void*)kSplitFns[sp.shape][dtype], dim3(cover(M, s.bm) * cover(N, s.bn) * ranges), dim3(s.threads), args, 0, (hipStream_t)stream) != hipSuccess ||
+    if (hipLaunchKernel((const void*)s.range_for(dtype, off_lines(a, K)), dim3(cover_any(M, s.bm) * cover(N, s.bn) * ranges), dim3(s.threads), args, 0, (hipStream_t)stream) != hipSuccess ||
         hipLaunchKernel(sum, dim3((chunks + 63) / 64), dim3(64), sum_args, 0, (hipStream_t)stream) != hipSuccess) {
         (void)hipGetLastError();
         return GEMM_ELAUNCH;
@@ -233,8 +279,7 @@ static int launch_block(const void* a, const void* b, void* c, int M, int N, int
     const BlockShape& s = choose_block(M, N, K);
     Arguments to(a, b, c, M, N, K, K, slope);
     void* args[] = {&to.pointers_m_n, &to.k_kc_slope};
-    const BlockFn fn = s.lines[dtype] && off_lines(a, K) ? s.lines[dtype] : s.fn[dtype];
-    if (hipLaunchKernel((const void*)fn, dim3(cover_any(M, s.bm) * cover(N, s.bn)), dim3(s.threads), args, 0, (hipStream_t)stream) != hipSuccess) {
+    if (hipLaunchKernel((const void*)s.whole_for(dtype, off_lines(a, K)), dim3(cover_any(M, s.bm) * cover(N, s.bn)), dim3(s.threads), args, 0, (hipStream_t)stream) != hipSuccess) {
         (void)hipGetLastError();
         return GEMM_ELAUNCH;
     }
