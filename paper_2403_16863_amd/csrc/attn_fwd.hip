@@ -634,6 +634,41 @@ constexpr int kDefaultD64Short = 3;
 // 617 (240) 8.4 / 8.2, 2 x 4096 (256) 30.8 / 27.0, 10 x 819 (260) 12.9 / 16.1.
 constexpr int kKeySplit4 = 37, kKeySplit8 = 38, kGroups2 = 39, kGroups4 = 40, kRows128 = 1;
 
+// d = 128 beyond those lines: 128-row tiles (two workgroups of four waves per unit) against 256-row tiles (one of eight), where
+// neither has many rounds and the larger tiles leave more of the last one, or of a head's last tile, empty.  Time of the busiest
+// unit, us, with tiles of 64 keys per item (nk; causal: of the items that a unit is dealt, heaviest first, forward and backward, in sum):
+//   256 rows   1.40 nk + 9.4 a round;                                               causal  1.51 per tile + 8.05 an item
+//   128 rows   1.70 nk + 6.9 a round (0.86 nk with one workgroup on every unit);    causal  1.87 per tile of a workgroup's mean share + 6.17 a round
+// Fitted to 181 and 188 launches of 24 to 128 heads, 257 to 8000 keys and up to 16 rounds (standard deviation of the time over the
+// model 3 to 7 %).  6 % ahead, 128 rows take 16 and 45 of them: 0.87 and 0.94 of their time in the mean, 2 % more at most.  256 / 128 rows, us:
+//   96 x 599  39.9 / 24.8    128 x 642  46.6 / 40.1    128 x 1041  98.6 / 90.0    24 x 3790  171 / 170 (not taken, as all beyond 3000 keys)
+//   causal  128 x 561  31.6 / 25.5    96 x 846  37.3 / 32.1    128 x 1101  68.2 / 59.4    48 x 2111  67.2 / 63.6    64 x 1545  54.2 / 55.4
+static bool rows128_sooner(long long heads, int N, int causal) {
+    if (N <= 256 || N > (causal ? 8000 : 3000)) return false;
+    const long long nq = (N + 255) / 256, items = heads * nq, rounds = (items + 255) / 256;
+    const long long n128 = (N + 127) / 128, j = heads * n128;
+    if (rounds > 16) return false;
+    const float nk = (float)((N + 63) / 64);
+    if (!causal) {
+        const long long full = j / 512, rest = j % 512;
+        const float t128 = (float)full * (1.70f * nk + 6.9f) + (rest ? (rest <= 256 ? 0.86f : 1.70f) * nk + 6.9f : 0.f);
+        return t128 < 0.94f * (float)rounds * (1.40f * nk + 9.4f);
+    }
+    float t256 = 0.f;
+    for (int unit = 0; unit < 256; unit += 255) {
+        float t = 0.f;
+        for (long long r = 0; r < rounds; ++r) {
+            const long long rank = r * 256 + (r & 1 ? 255 - unit : unit);
+            if (rank >= items) break;
+            const long long keys = (nq - rank / heads) * 256;
+            t += 1.51f * (float)(((keys < N ? keys : N) + 63) / 64) + 8.05f;
+        }
+        t256 = t > t256 ? t : t256;
+    }
+    const float tiles = (float)heads * ((float)(n128 * (n128 - 1)) + nk);
+    return 1.87f * tiles / 512.f + 6.17f * (float)((j + 511) / 512) < 0.94f * t256;
+}
+
 static int choose_variant(long long heads, int N, int d, int causal) {
     const long long g = heads * ((N + 31LL) / 32), t = heads * ((N + 63LL) / 64), j = heads * ((N + 127LL) / 128);
     const int most = d == 128 ? (!causal ? 512 : N < 768 ? 736 : N < 1024 ? 1056 : 1152)
@@ -656,7 +691,7 @@ static int choose_variant(long long heads, int N, int d, int causal) {
                       : causal && d == 64 && N >= 1200 && N <= 5000 ? 512
                       : causal && d == 128 && N >= 2000 && N <= 5500 ? 352 : 256;
     if (g <= most) return N >= (d == 128 ? 512 : causal ? 160 : 400) && g <= alone ? kKeySplit8 : kKeySplit4;
-    if (d == 128) return (causal ? j <= 576 : j <= 256 || (j > 512 && j <= 640)) ? kRows128 : kDefaultD128;
+    if (d == 128) return (causal ? j <= 576 : j <= 256 || (j > 512 && j <= 640)) || rows128_sooner(heads, N, causal) ? kRows128 : kDefaultD128;
     return j > (!causal ? 512 : N >= 256 && N < 1600 ? 410 : 755) ? kDefaultD64Long : kDefaultD64Short;
 }
 
