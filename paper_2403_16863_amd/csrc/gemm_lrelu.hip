@@ -222,31 +222,37 @@ static Split choose_few(int M, int N, int K) {
 }
 
 // Large calls that the rule above leaves whole: tiles of 128 x 128 or 192 x 128, which read A and B the fewest times but are
-// too few, with K split into up to 8 ranges of 512 and more, one workgroup per unit.  The time is modelled as
-//     stages of a range * alone * (1 + load * f) * (1 + off) + ends + 2.7 + 2.3 (the second launch) + 0.4 per MB of parts   (us)
-// and has to be 5 % below that of the call in one piece.  From 1e9 products on (162 x 800 x 4512 took
-// 12.9 us instead of 12.4), and at most 32 MB of parts.  Of the 190 shapes above 23 are split and run in 0.81 of the time (geometric
-// mean, none longer; beside them 339 x 2256 x 4288 18.2 -> 18.9 us): 2856 x 256 x 7288 33.9 -> 24.3, 969 x 664 x 7256 28.8 -> 21.5,
-// 180 x 2880 x 8192 37.5 -> 23.8, 118 x 7464 x 5592 35.7 -> 27.2, 4939 x 264 x 6464 48.7 -> 33.9, 2622 x 1016 x 6224 61.4 -> 48.7.  (128 x 256
-// and 256 x 128 tiles with K split: within 3 % of these; the parts in the accumulators' own order, 1 KB a store: the same.)
+// too few, or of 64 x 64, with K split into up to 8 ranges of 512 and more, one workgroup per unit.  The time is modelled as
+//     stages of a range * alone * (1 + load * f) * (1 + off) + ends + 2.7 + second (the second launch) + per_mb per MB of parts   (us)
+// and has to be 7 % below that of the call in one piece (64 x 64: 10 %).  At most 32 MB of parts.  Whole / split, us, on sets of
+// buffers that exceed the caches of the XCDs and, in brackets, on one:
+//   128 x 128   969 x 664 x 7256  28.8 / 21.5     2335 x 216 x 7256  44.4 / 21.1 (33.5 / 18.7)    998 x 528 x 4552   21.8 / 16.0 (21.8 / 15.8)
+//               118 x 7464 x 5592 35.7 / 27.2     91 x 5920 x 4112   23.5 / 18.3 (19.0 / 16.1)    2080 x 352 x 4504  20.7 / 17.3 (20.8 / 17.4)
+//               a model's ratio of 0.89 and 0.94: 339 x 2256 x 4288  18.2 / 18.9,  451 x 1184 x 3648  14.7 / 16.2 (14.6 / 16.0; not taken)
+//   192 x 128   180 x 2880 x 8192 37.5 / 23.8     167 x 3656 x 6536  40.9 / 23.6 (32.0 / 21.1)    3115 x 136 x 5296  30.2 / 19.3 (25.0 / 17.2)
+//   64 x 64     162 x 800 x 4512  12.4 / 10.1 (12.0 / 8.9)    78 x 1264 x 3560  11.7 / 10.1 (10.4 / 8.7)    214 x 888 x 3960  13.4 / 11.2 (12.9 / 11.1)
+//               not below 512 columns: 410 x 200 x 3800  11.8 / 8.1 (6.6 / 7.0),  2114 x 64 x 3992  11.4 / 9.8 (6.9 / 8.3)
+// (128 x 256 and 256 x 128 tiles with K split: within 3 % of these; the parts in the accumulators' own order, 1 KB a store: the same.)
 static Split choose_large_split(int M, int N, int K) {
     const Split whole = {nullptr, 0, K};
-    if (!is_large(M, N, K) || (double)M * N * K < 1e9 || K > (1 << 16)) return whole;
-    static const struct { const BlockShape* shape; float alone, load, off, ends; } kRanges[] = {
-        {&kBlocks[5], 0.325f, 0.59f, 0.01f, 1.28f}, {&kLargeBlocks[1], 0.523f, 0.20f, 0.f, 1.21f}};
+    if (!is_large(M, N, K) || K > (1 << 16)) return whole;
+    static const struct { const BlockShape* shape; float alone, load, off, ends, second, per_mb, ahead; double least; int width; } kRanges[] = {
+        {&kBlocks[2], 0.179f, 0.67f, 0.08f, 0.55f, 2.5f, 0.22f, 0.90f, 3e8, 512},
+        {&kBlocks[5], 0.325f, 0.59f, 0.01f, 1.28f, 2.3f, 0.40f, 0.93f, 1e9, 8},
+        {&kLargeBlocks[1], 0.523f, 0.20f, 0.f, 1.21f, 2.3f, 0.40f, 0.93f, 1e9, 8}};
     constexpr double kMost = 32 << 20;
     Split best = whole;
-    float best_us = 0.f;
+    float best_us = 0.f, whole_us = 0.f;
     for (const auto& s : kRanges) {
         const long long tiles = (long long)cover_any(M, s.shape->bm) * cover(N, s.shape->bn);
-        if ((long long)(s.shape->bm - 1) * K * 2 + s.shape->bk * 2 + 128 >= (long long)kBufferSize) continue;
+        if ((double)M * N * K < s.least || N < s.width || (long long)(s.shape->bm - 1) * K * 2 + s.shape->bk * 2 + 128 >= (long long)kBufferSize) continue;
         for (int r = 2; r <= 8 && tiles * r <= (long long)kComputeUnits && r * 512 <= K && (double)M * N * 4 * r <= kMost; ++r) {
-            if (best_us == 0.f) best_us = 0.95f * large_us(choose_block(M, N, K), M, N, K);
+            if (whole_us == 0.f) whole_us = large_us(choose_block(M, N, K), M, N, K);
             const int kc = ((K + r - 1) / r + 63) / 64 * 64;
             if ((K + kc - 1) / kc != r) continue;
             const float filled = (float)(tiles * r) / (float)kComputeUnits;
-            const float us = (float)(kc / 64) * s.alone * (1.f + s.load * filled) * (N & 63 ? 1.f + s.off : 1.f) + s.ends + 5.f + 0.4e-6f * (float)M * (float)N * (float)(4 * r);
-            if (us < best_us) best = {s.shape, r, kc}, best_us = us;
+            const float us = (float)(kc / 64) * s.alone * (1.f + s.load * filled) * (N & 63 ? 1.f + s.off : 1.f) + s.ends + 2.7f + s.second + s.per_mb * 1e-6f * (float)M * (float)N * (float)(4 * r);
+            if (us < s.ahead * whole_us && (!best.ranges || us < best_us)) best = {s.shape, r, kc}, best_us = us;
         }
     }
     return best;

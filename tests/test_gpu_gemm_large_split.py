@@ -1,4 +1,4 @@
-"""Large GEMMs with K split between workgroups on 128 x 128 and 192 x 128 tiles: which calls take it and how much scratch
+"""Large GEMMs with K split between workgroups on 128 x 128, 192 x 128 and 64 x 64 tiles: which calls take it and how much scratch
 memory, those against the fp64 oracle at the edges of tiles and ranges, with rows of A on lines and off them, and the call that
 gets none.  Tolerance as in test_gpu_gemm.py."""
 import numpy as np
@@ -10,7 +10,8 @@ from paper_2403_16863_amd import inputs as I
 from test_gpu_gemm import check, run_gpu
 
 # (M, N, K, ranges)
-SPLIT = [(969, 664, 7256, 5), (2097, 464, 5744, 5), (1153, 648, 7240, 6), (180, 2880, 8192, 8), (4385, 192, 6976, 5), (577, 616, 4552, 6)]
+SPLIT = [(969, 664, 7256, 5), (2097, 464, 5744, 5), (1153, 648, 7240, 6), (180, 2880, 8192, 8), (4385, 192, 6976, 5), (577, 616, 4552, 6),
+         (162, 800, 4512, 6), (127, 1272, 3560, 6)]
 
 
 def ranges_of(M, N, K):
@@ -22,7 +23,8 @@ def ranges_of(M, N, K):
 def test_which_calls_are_split():
     for M, N, K, ranges in SPLIT:
         assert ranges_of(M, N, K) == ranges, (M, N, K)
-    for M, N, K in ((4096, 4096, 4096), (2048, 8192, 2048), (1000, 1032, 2056), (969, 664, 1016), (8192, 8192, 8192), (300, 8192, 1 << 17)):
+    for M, N, K in ((4096, 4096, 4096), (2048, 8192, 2048), (1000, 1032, 2056), (969, 664, 1016), (8192, 8192, 8192), (300, 8192, 1 << 17),
+                    (451, 1184, 3648), (410, 200, 3800), (65, 2016, 3536)):
         assert ranges_of(M, N, K) == 0, (M, N, K)
 
 
