@@ -142,6 +142,13 @@ static const BlockShape kLargeBlocks[] = {
     lines_shape<Block<192, 256, 64, 2, 4, 1, 2, 1>>(0.f, 0.f, 0.f, {0.768f, 0.f, 0.77f, 0.06f, 2.94f}),
 };
 
+// 128 x 128 tiles with two workgroups on a unit, each with a ring of two stages, for the calls of more than one round and a K below
+// 640: one multiplies while the other waits for its first stages or stores its tile, which is most of such a tile's time.  us, one
+// workgroup / two: 2744 x 6672 x 112 19.9 / 15.4, 5826 x 2944 x 128 19.5 / 15.3, 4722 x 1584 x 104 9.1 / 7.4, 3499 x 5696 x 320 26.3 / 22.3,
+// 3656 x 2080 x 448 12.2 / 10.8; over 37 shapes of 270 to 4032 tiles 1.10 to 1.39 at K up to 504, 1.02 to 1.25 up to 624, 0.99 to 1.13 from
+// 704 on, and with longer K the shorter ring is the slower one (1504 x 5624 x 2272 0.88).
+static const BlockShape kShortBlock = block_shape<Block<128, 128, 64, 2, 4, 1, 2, 2>>(0.f, 0.f, 0.f, {0.579f, 0.395f, 0.39f, 0.05f, 0.41f});
+
 constexpr unsigned long long kComputeUnits = 256;
 
 static const BlockShape& choose_table(int M, int N, int K) {
@@ -182,6 +189,7 @@ static bool is_large(int M, int N, int K) { return M > 32 && K >= 256 && (double
 
 static const BlockShape& choose_block(int M, int N, int K) {
     const BlockShape* best = &choose_table(M, N, K);
+    if (best == &kBlocks[5] && K < 640 && (unsigned long long)cover(M, 128) * cover(N, 128) > kComputeUnits) best = &kShortBlock;
     if (!is_large(M, N, K)) return *best;
     float best_us = (K < 960 ? 0.89f : 0.95f) * large_us(*best, M, N, K);
     for (const BlockShape& s : kLargeBlocks) {
