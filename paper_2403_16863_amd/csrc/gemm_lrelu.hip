@@ -259,7 +259,8 @@ static Split choose_large_split(int M, int N, int K) {
             const int kc = ((K + r - 1) / r + 63) / 64 * 64;
             if ((K + kc - 1) / kc != r) continue;
             const float filled = (float)(tiles * r) / (float)kComputeUnits;
-            const float us = (float)(kc / 64) * s.alone * (1.f + s.load * filled) * (N & 63 ? 1.f + s.off : 1.f) + s.ends + 2.7f + s.second + s.per_mb * 1e-6f * (float)M * (float)N * (float)(4 * r);
+            const float loop = (float)(kc / 64) * s.alone * (1.f + s.load * filled) * (N & 63 ? 1.f + s.off : 1.f);
+            const float us = loop + s.ends + 2.7f + s.second + s.per_mb * 1e-6f * (float)M * (float)N * (float)(4 * r);
             if (us < s.ahead * whole_us && (!best.ranges || us < best_us)) best = {s.shape, r, kc}, best_us = us;
         }
     }
@@ -280,7 +281,8 @@ static int launch_split(const Split& sp, const void* a, const void* b, void* c, 
     void* args[] = {&to.pointers_m_n, &to.k_kc_slope};
     void* sum_args[] = {&workspace, &c, &ranges, &chunks, &slope};
     const void* const sum = dtype == GEMM_F16 ? (const void*)gemm_sum_kernel<Mfma16F16> : (const void*)gemm_sum_kernel<Mfma16BF16>;
-    if (hipLaunchKernel((const void*)s.range_for(dtype, off_lines(a, K)), dim3(cover_any(M, s.bm) * cover(N, s.bn) * ranges), dim3(s.threads), args, 0, (hipStream_t)stream) != hipSuccess ||
+    const dim3 grid(cover_any(M, s.bm) * cover(N, s.bn) * ranges);
+    if (hipLaunchKernel((const void*)s.range_for(dtype, off_lines(a, K)), grid, dim3(s.threads), args, 0, (hipStream_t)stream) != hipSuccess ||
         hipLaunchKernel(sum, dim3((chunks + 63) / 64), dim3(64), sum_args, 0, (hipStream_t)stream) != hipSuccess) {
         (void)hipGetLastError();
         return GEMM_ELAUNCH;
@@ -293,7 +295,8 @@ static int launch_block(const void* a, const void* b, void* c, int M, int N, int
     const BlockShape& s = choose_block(M, N, K);
     Arguments to(a, b, c, M, N, K, K, slope);
     void* args[] = {&to.pointers_m_n, &to.k_kc_slope};
-    if (hipLaunchKernel((const void*)s.whole_for(dtype, off_lines(a, K)), dim3(cover_any(M, s.bm) * cover(N, s.bn)), dim3(s.threads), args, 0, (hipStream_t)stream) != hipSuccess) {
+    const dim3 grid(cover_any(M, s.bm) * cover(N, s.bn));
+    if (hipLaunchKernel((const void*)s.whole_for(dtype, off_lines(a, K)), grid, dim3(s.threads), args, 0, (hipStream_t)stream) != hipSuccess) {
         (void)hipGetLastError();
         return GEMM_ELAUNCH;
     }
