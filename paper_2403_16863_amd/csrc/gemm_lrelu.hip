@@ -86,8 +86,9 @@ struct BlockShape {
     struct Large { float alone, full, load, off, ends; } large;  // of the model for large calls (large_us)
     BlockFn fn[2], lines[2];  // by dtype; the second, where there is one, takes A by whole lines
     BlockFn split[2], split_lines[2];  // the same for a range of K (or null)
-    const BlockFn& whole_for(int dtype, bool off_lines) const { return off_lines && lines[dtype] ? lines[dtype] : fn[dtype]; }
-    const BlockFn& range_for(int dtype, bool off_lines) const { return off_lines && split_lines[dtype] ? split_lines[dtype] : split[dtype]; }
+    bool off_lines(const void* a, int K) const;
+    const BlockFn& whole_for(int dtype, const void* a, int K) const { return lines[dtype] && off_lines(a, K) ? lines[dtype] : fn[dtype]; }
+    const BlockFn& range_for(int dtype, const void* a, int K) const { return split_lines[dtype] && off_lines(a, K) ? split_lines[dtype] : split[dtype]; }
 };
 template <class BL>
 constexpr BlockShape block_shape(float alone, float full, float ends, BlockShape::Large large, int ragged = 0) {
@@ -123,7 +124,10 @@ constexpr BlockShape with_split(BlockShape s) {
 // 0.98 / 1.00 / 1.01 / 1.02 / 1.05 / 1.15, 128 x 256 (4095 x 1520) 1.01 / 1.01 / 1.02 / 0.99 / 1.02 / 1.04.  (Not for the three smallest
 // tiles: of the 64 x 64 tiles on four waves the longer ring costs the third workgroup of a unit, and the others are held by
 // latency, 32 x 64: 0.93 to 1.02 of the time.)
-static bool off_lines(const void* a, int K) { return K >= 768 && ((K & 63) || ((uintptr_t)a & 127)); }
+// The base counts only where the order of the sums stays the same, so that the bits of C do not depend on where A lies: two groups
+// of waves take alternate stages of K without whole lines and a run of stages each with them.  (Base 64 bytes off a line, us, without /
+// with: 768 x 768 x 3072 13.5 / 12.2, 961 x 1096 x 2048 14.9 / 12.5, 247 x 4160 x 1664 10.9 / 9.6; on a line 12.0, 12.2 and 9.2.)
+bool BlockShape::off_lines(const void* a, int K) const { return K >= 768 && ((K & 63) || (wk == 1 && ((uintptr_t)a & 127))); }
 static const BlockShape kBlocks[] = {
     with_split<Block<32, 32, 32, 1, 1, 4, 4, 2>, false>(block_shape<Block<32, 32, 32, 1, 1, 4, 4, 2>>(0.21f, 0.22f, 0.5f, {0.275f, 0.253f, 0.02f, 0.15f, 0.17f})),
     with_split<Block<32, 64, 64, 1, 2, 2, 3, 2>, false>(block_shape<Block<32, 64, 64, 1, 2, 2, 3, 2>>(0.27f, 0.31f, 0.58f, {0.229f, 0.288f, 0.06f, 0.25f, 0.11f})),
@@ -282,7 +286,7 @@ static int launch_split(const Split& sp, const void* a, const void* b, void* c, 
     void* sum_args[] = {&workspace, &c, &ranges, &chunks, &slope};
     const void* const sum = dtype == GEMM_F16 ? (const void*)gemm_sum_kernel<Mfma16F16> : (const void*)gemm_sum_kernel<Mfma16BF16>;
     const dim3 grid(cover_any(M, s.bm) * cover(N, s.bn) * ranges);
-    if (hipLaunchKernel((const void*)s.range_for(dtype, off_lines(a, K)), grid, dim3(s.threads), args, 0, (hipStream_t)stream) != hipSuccess ||
+    if (hipLaunchKernel((const void*)s.range_for(dtype, a, K), grid, dim3(s.threads), args, 0, (hipStream_t)stream) != hipSuccess ||
         hipLaunchKernel(sum, dim3((chunks + 63) / 64), dim3(64), sum_args, 0, (hipStream_t)stream) != hipSuccess) {
         (void)hipGetLastError();
         return GEMM_ELAUNCH;
@@ -296,7 +300,7 @@ static int launch_block(const void* a, const void* b, void* c, int M, int N, int
     Arguments to(a, b, c, M, N, K, K, slope);
     void* args[] = {&to.pointers_m_n, &to.k_kc_slope};
     const dim3 grid(cover_any(M, s.bm) * cover(N, s.bn));
-    if (hipLaunchKernel((const void*)s.whole_for(dtype, off_lines(a, K)), grid, dim3(s.threads), args, 0, (hipStream_t)stream) != hipSuccess) {
+    if (hipLaunchKernel((const void*)s.whole_for(dtype, a, K), grid, dim3(s.threads), args, 0, (hipStream_t)stream) != hipSuccess) {
         (void)hipGetLastError();
         return GEMM_ELAUNCH;
     }

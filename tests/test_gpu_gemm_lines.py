@@ -18,8 +18,8 @@ SHAPES = {
 }
 
 
-def run(ab, bb, dtype, offset):
-    """C with A at `offset` 16-byte chunks behind a line, and NaN in front of and behind it."""
+def run_tensor(ab, bb, dtype, offset):
+    """C (a tensor) with A at `offset` 16-byte chunks behind a line, and NaN in front of and behind it."""
     import torch
     from paper_2403_16863_amd import gemm
     M, K = ab.shape
@@ -32,7 +32,11 @@ def run(ab, bb, dtype, offset):
     c = torch.full((M, bb.shape[1]), float("nan"), dtype=tdt, device="cuda:0")
     gemm.gemm_lrelu(a.view(tdt), b, c, 0.1)
     torch.cuda.synchronize()
-    return c.double().cpu().numpy()
+    return c
+
+
+def run(ab, bb, dtype, offset):
+    return run_tensor(ab, bb, dtype, offset).double().cpu().numpy()
 
 
 @pytest.mark.gpu
@@ -49,3 +53,18 @@ def test_every_phase_of_the_rows(tile):
     assert block_of(M, N, K) == tile
     ab, bb = I.make_gemm(M, N, K, dtype, seed=710)
     check(run(ab, bb, dtype, 3), ab, bb, 0.1, dtype, f"M{M} N{N} K{K} base 3")
+
+
+# both forms of every tile that has two, and K no multiple of 64; the last two split K (128 x 128 and 192 x 128 tiles)
+PLACES = [(833, 840, 2112), (833, 840, 2120), (1055, 1024, 1984), (1055, 1024, 1992), (1025, 1000, 1024), (1281, 1544, 1024), (3455, 1544, 1024),
+          (2113, 2824, 1024), (3071, 3576, 1024), (3841, 2128, 1024), (969, 640, 7232), (180, 2880, 8192)]
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("M,N,K", PLACES)
+def test_the_place_of_a_does_not_change_a_bit(M, N, K):
+    import torch
+    ab, bb = I.make_gemm(M, N, K, I.BF16, seed=720)
+    want = run_tensor(ab, bb, I.BF16, 0).view(torch.int16)
+    for offset in (1, 4):
+        assert torch.equal(run_tensor(ab, bb, I.BF16, offset).view(torch.int16), want), offset
