@@ -27,11 +27,13 @@
 //    texture path in place of 8, which is what holds every tile but the largest.  So a stage loads the line that the
 //    row's next k values END in, of which the stage behind it reads the rest, and the ring of A holds one stage more.
 //    A fragment read takes each 16-byte chunk from one stage or the next, by a lane's own row (rows 16 apart
-//    agree).  bfloat16, us before and after: 1394 x 7384 x 5480 144.7 -> 127.3 (256 x 256 tiles), 2622 x 1016 x 6224 72.3 ->
-//    61.4 (128 x 128), 4096 x 4096 x 4088 114.7 -> 105.2, 5963 x 1528 x 1272 39.7 -> 36.2 (128 x 256), 1000 x 1032 x 2056
-//    15.0 -> 14.2 (64 x 128), 1000 x 1024 x 2056 10.8 -> 10.1 (64 x 64 on eight waves).  Where the rows start on lines the
-//    longer ring costs 0 to 3 %: such calls keep the ring without.  (B has no such form: its rows would need a line each in
-//    addition, so N off the line costs the wider tiles least.)
+//    agree), and a chunk's place in its LDS row goes by its k as in the form without lines: by its place in the line, the
+//    fragment reads of odd K / 8 met in banks (2573 x 512 x 840: 304 k of 761 k LDS clocks, now none of 457 k).  bfloat16, us
+//    before and after: 1394 x 7384 x 5480 144.7 -> 127.3 (256 x 256 tiles), 2622 x 1016 x 6224 72.3 -> 61.4 (128 x 128), 4096 x
+//    4096 x 4088 114.7 -> 105.2, 5963 x 1528 x 1272 39.7 -> 36.2 (128 x 256), 1000 x 1032 x 2056 15.0 -> 14.2 (64 x 128), 1000 x
+//    1024 x 2056 10.8 -> 10.1 (64 x 64 on eight waves).  Where the rows start on lines the longer ring costs 0 to 3 %: such calls
+//    keep the ring without.  (B has no such form: its rows would need a line each in addition, so N off the line costs the
+//    wider tiles least.)
 //  * Workgroups of WK > 1 groups split K between the groups, each with a ring of its own (a group of
 //    one wave then needs no barrier at all), and sum in LDS at the end, in group order.
 //
@@ -161,7 +163,8 @@ __global__ __launch_bounds__(BL::WM * BL::WN * BL::WK * 64, (BL::OCC * BL::WM * 
 #pragma unroll
     for (int i = 0; i < LA; ++i) {
         const int ci = (wave * LA + i) * 64 + lane, row = ci / CPA;
-        kA[i] = (((ci % CPA) ^ a_code<CPA>(row)) - shift(row)) * 8;
+        const int ch = (ci % CPA) ^ a_code<CPA>(row);  // of the row's k; by lines, the one of the line that lies as far behind the row's start
+        kA[i] = (ch + shift(row) < CPA ? ch : ch - CPA) * 8;
         voffA[i] = m0 + row < M ? (unsigned)row * (unsigned)(K * 2) + (unsigned)(kA[i] * 2 + BEFORE) : kBufferSize;
     }
 #pragma unroll
@@ -205,9 +208,9 @@ __global__ __launch_bounds__(BL::WM * BL::WN * BL::WK * 64, (BL::OCC * BL::WM * 
     bool a_next[KS];  // the chunk lies in the next line
 #pragma unroll
     for (int j = 0; j < KS; ++j) {
-        const int chunk = j * 4 + (lane >> 4) + shift(lane & 15);
-        a_next[j] = LINES && chunk >= CPA;
-        a_base[j] = lds0 + (wm * TM + (lane & 15)) * (BK * 2) + (((chunk & (CPA - 1)) ^ a_code<CPA>(lane & 15)) * 16);
+        const int chunk = j * 4 + (lane >> 4);
+        a_next[j] = LINES && chunk + shift(lane & 15) >= CPA;
+        a_base[j] = lds0 + (wm * TM + (lane & 15)) * (BK * 2) + ((chunk ^ a_code<CPA>(lane & 15)) * 16);
     }
     unsigned b_base[NT];
     {
