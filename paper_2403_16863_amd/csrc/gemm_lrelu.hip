@@ -86,6 +86,7 @@ struct BlockShape {
     struct Large { float alone, full, load, off, ends; } large;  // of the model for large calls (large_us)
     BlockFn fn[2], lines[2];  // by dtype; the second, where there is one, takes A by whole lines
     BlockFn split[2], split_lines[2];  // the same for a range of K (or null)
+    int lines_from;  // the least K that whole lines are taken for
     bool off_lines(const void* a, int K) const;
     const BlockFn& whole_for(int dtype, const void* a, int K) const { return lines[dtype] && off_lines(a, K) ? lines[dtype] : fn[dtype]; }
     const BlockFn& range_for(int dtype, const void* a, int K) const { return split_lines[dtype] && off_lines(a, K) ? split_lines[dtype] : split[dtype]; }
@@ -93,19 +94,17 @@ struct BlockShape {
 template <class BL>
 constexpr BlockShape block_shape(float alone, float full, float ends, BlockShape::Large large, int ragged = 0) {
     return {BL::BM, BL::BN, BL::BK, BL::WK, BL::WM * BL::WN * BL::WK * 64, BL::OCC, ragged, alone, full, ends, large,
-            {gemm_block_kernel<Mfma16F16, BL>, gemm_block_kernel<Mfma16BF16, BL>}, {nullptr, nullptr}, {nullptr, nullptr}, {nullptr, nullptr}};
+            {gemm_block_kernel<Mfma16F16, BL>, gemm_block_kernel<Mfma16BF16, BL>}, {nullptr, nullptr}, {nullptr, nullptr}, {nullptr, nullptr}, 0};
 }
-// (the same tile with A by whole lines; measured at `Block`)
+// (the same tile with A by whole lines too; measured at `Block`)
 template <class BL>
-constexpr BlockShape with_lines(BlockShape s) {
+constexpr BlockShape lines_shape(float alone, float full, float ends, BlockShape::Large large, int ragged = 0, int lines_from = 768) {
     using Lines = Block<BL::BM, BL::BN, BL::BK, BL::WM, BL::WN, BL::WK, BL::NB, BL::OCC, true>;
+    BlockShape s = block_shape<BL>(alone, full, ends, large, ragged);
     s.lines[0] = gemm_block_kernel<Mfma16F16, Lines>;
     s.lines[1] = gemm_block_kernel<Mfma16BF16, Lines>;
+    s.lines_from = lines_from;
     return s;
-}
-template <class BL>
-constexpr BlockShape lines_shape(float alone, float full, float ends, BlockShape::Large large, int ragged = 0) {
-    return with_lines<BL>(block_shape<BL>(alone, full, ends, large, ragged));
 }
 template <class BL, bool LINES>
 constexpr BlockShape with_split(BlockShape s) {
@@ -118,22 +117,29 @@ constexpr BlockShape with_split(BlockShape s) {
     }
     return s;
 }
-// Whether A is taken by whole lines: its rows do not all start on one, and K is long enough for the line that the first
-// stage needs in addition.  Time without over time with, at K = 296 / 520 / 712 / 808 / 1064 / 1288: 128 x 128 tiles (4181 x 568)
-// 0.95 / 0.98 / 1.01 / 1.03 / 1.05 / 1.09, 64 x 128 (403 x 4288) 0.97 / 0.98 / 0.98 / 1.00 / 1.01 / 1.02, 256 x 256 (3841 x 2128)
-// 0.98 / 1.00 / 1.01 / 1.02 / 1.05 / 1.15, 128 x 256 (4095 x 1520) 1.01 / 1.01 / 1.02 / 0.99 / 1.02 / 1.04.  (Not for the three smallest
-// tiles: of the 64 x 64 tiles on four waves the longer ring costs the third workgroup of a unit, and the others are held by
-// latency, 32 x 64: 0.93 to 1.02 of the time.)
+// Whether A is taken by whole lines: its rows do not all start on one, and K is long enough for what that costs: the line that the first
+// stage needs in addition, and in every stage a lane's choice between two of them.  Time without over time with, mean over 7 shapes each
+// of K about 530 / 790 / 1050 / 1300 / 1560 / 2060, on buffers that exceed the caches and, in brackets, on the same ones:
+//   64 x 128   0.98 / 1.00 / 1.02 / 1.04 / 1.03 / 1.04  (0.92 / 0.92 / 0.95 / 0.95 / 1.02 / 1.04): from 1280 on
+//   128 x 128  1.01 / 1.05 / 1.06 / 1.08 / 1.10 / 1.15  (0.93 / 0.97 / 0.98 / 1.00 / 1.06 / 1.12)
+//   128 x 256  1.03 / 1.04 / 1.04 / 1.06 / 1.07 / 1.07  (1.00 / 1.00 / 1.00 / 1.01 / 1.01 / 1.01)
+//   256 x 256  1.03 / 1.05 / 1.06 / 1.07 / 1.08 / 1.09  (1.00 / 1.00 / 1.01 / 1.01 / 1.01 / 1.01)
+//   192 x 128  1.04 / 1.10 / 1.11 / 1.17 / 1.20 / 1.21  (0.98 / 1.00 / 1.04 / 1.07 / 1.09 / 1.10)
+//   192 x 256  1.01 / 1.04 / 1.03 / 1.03 / 1.02 / 1.05  (0.99 / 1.01 / 1.03 / 1.04 / 1.04 / 1.05)
+//   96 x 64    taken from K of about 1100 on: 1.09 / 1.12 / 1.14 / 1.17  (1.03 / 1.03 / 1.09 / 1.14)
+//   64 x 64 on eight waves, at 2600: 1.12 (1.08)
+// (Not for the three smallest tiles: of the 64 x 64 tiles on four waves the longer ring costs the third workgroup of a unit, and the
+// others are held by latency, 32 x 64: 0.93 to 1.02 of the time.)
 // The base counts only where the order of the sums stays the same, so that the bits of C do not depend on where A lies: two groups
 // of waves take alternate stages of K without whole lines and a run of stages each with them.  (Base 64 bytes off a line, us, without /
 // with: 768 x 768 x 3072 13.5 / 12.2, 961 x 1096 x 2048 14.9 / 12.5, 247 x 4160 x 1664 10.9 / 9.6; on a line 12.0, 12.2 and 9.2.)
-bool BlockShape::off_lines(const void* a, int K) const { return K >= 768 && ((K & 63) || (wk == 1 && ((uintptr_t)a & 127))); }
+bool BlockShape::off_lines(const void* a, int K) const { return K >= lines_from && ((K & 63) || (wk == 1 && ((uintptr_t)a & 127))); }
 static const BlockShape kBlocks[] = {
     with_split<Block<32, 32, 32, 1, 1, 4, 4, 2>, false>(block_shape<Block<32, 32, 32, 1, 1, 4, 4, 2>>(0.21f, 0.22f, 0.5f, {0.275f, 0.253f, 0.02f, 0.15f, 0.17f})),
     with_split<Block<32, 64, 64, 1, 2, 2, 3, 2>, false>(block_shape<Block<32, 64, 64, 1, 2, 2, 3, 2>>(0.27f, 0.31f, 0.58f, {0.229f, 0.288f, 0.06f, 0.25f, 0.11f})),
     with_split<Block<64, 64, 64, 2, 2, 1, 3, 3>, false>(block_shape<Block<64, 64, 64, 2, 2, 1, 3, 3>>(0.24f, 0.17f, 0.22f, {0.215f, 0.181f, 0.25f, 0.16f, 0.f})),
     lines_shape<Block<64, 64, 64, 2, 2, 2, 4, 1>>(0.40f, 0.f, 0.9f, {0.310f, 0.f, 0.61f, 0.17f, 0.37f}, 2112),
-    lines_shape<Block<64, 128, 64, 1, 4, 1, 3, 2>>(0.27f, 0.28f, 0.88f, {0.261f, 0.213f, 0.54f, 0.09f, 0.32f}),
+    lines_shape<Block<64, 128, 64, 1, 4, 1, 3, 2>>(0.27f, 0.28f, 0.88f, {0.261f, 0.213f, 0.54f, 0.09f, 0.32f}, 0, 1280),
     with_split<Block<128, 128, 64, 2, 4, 1, 4, 1>, true>(lines_shape<Block<128, 128, 64, 2, 4, 1, 4, 1>>(0.41f, 0.f, 0.9f, {0.327f, 0.f, 0.62f, 0.09f, 1.02f})),
     lines_shape<Block<128, 256, 64, 2, 4, 1, 3, 1>>(0.64f, 0.f, 1.8f, {0.502f, 0.f, 0.80f, 0.f, 2.39f}),
     lines_shape<Block<256, 256, 64, 2, 4, 1, 2, 1>>(1.1f, 0.f, 3.0f, {0.982f, 0.f, 0.66f, 0.01f, 4.20f}),
@@ -430,6 +436,19 @@ int gemm_lrelu_block_of(int M, int N, int K, int* bm, int* bn) {
 
 // The threads of its workgroups (the same).
 int gemm_lrelu_block_threads_of(int M, int N, int K) { return M < 1 || N < 1 || K < 1 ? GEMM_EINVAL : gemm::choose_block(M, N, K).threads; }
+
+// What gemm_lrelu (scratch 0) or gemm_lrelu_in with scratch memory (1) launches for A at `base` bytes behind a line (the same): tile,
+// threads, workgroups per unit, 1 for A by whole lines, ranges of K (0: whole) and their kc.
+int gemm_lrelu_launch_of(int M, int N, int K, int base, int scratch, int* out) {
+    if (!out || M < 1 || N < 8 || K < 8 || base < 0) return GEMM_EINVAL;
+    const gemm::Split sp = scratch ? gemm::choose_split(M, N, K) : gemm::Split{nullptr, 0, K};
+    const gemm::BlockShape& s = sp.ranges ? *sp.shape : gemm::choose_block(M, N, K);
+    const void* const a = (const void*)(uintptr_t)base;
+    const bool lines = sp.ranges ? s.range_for(0, a, K) == s.split_lines[0] : s.whole_for(0, a, K) == s.lines[0];
+    const int what[7] = {s.bm, s.bn, s.threads, s.occ, lines, sp.ranges, sp.kc};
+    for (int i = 0; i < 7; ++i) out[i] = what[i];
+    return GEMM_OK;
+}
 
 int gemm_lrelu_time(const void* a, const void* b, void* c, int M, int N, int K, float slope, int dtype, void* stream,
                     int variant_id, int warmup, int iters, float* ms_total) {

@@ -18,6 +18,14 @@ def block_of(M, N, K):
     return bm.value, bn.value
 
 
+def launch_of(M, N, K, base=0, scratch=True):
+    """(bm, bn, threads, workgroups per unit, 1 for A by whole lines, ranges of K, kc) for A at `base` bytes behind a line."""
+    from paper_2403_16863_amd import gemm
+    out = (ctypes.c_int * 7)()
+    assert gemm.lib().gemm_lrelu_launch_of(M, N, K, base, int(scratch), out) == 0
+    return tuple(out)
+
+
 SHAPES = {
     (32, 32): [(1, 8, 240), (31, 264, 520), (65, 40, 1000), (33, 608, 2384)],
     (32, 64): [(97, 2088, 328), (511, 720, 392), (2047, 256, 1000)],

@@ -6,12 +6,12 @@ import pytest
 from paper_2403_16863_amd import inputs as I
 
 from test_gpu_gemm import check
-from test_gpu_gemm_block import block_of
+from test_gpu_gemm_block import block_of, launch_of
 
 # tile: (M, N, K of the eight phases): one row and one column chunk past a tile
 SHAPES = {
     (64, 64): (833, 840, 2112),
-    (64, 128): (1025, 1000, 768),
+    (64, 128): (2049, 776, 1344),
     (128, 128): (1281, 1544, 768),
     (128, 256): (2113, 2824, 960),
     (256, 256): (3841, 2128, 768),
@@ -39,6 +39,17 @@ def run(ab, bb, dtype, offset):
     return run_tensor(ab, bb, dtype, offset).double().cpu().numpy()
 
 
+@pytest.mark.parametrize("M,N,K,base,tile,lines", [
+    (1025, 1000, 776, 0, (64, 128), 0), (2049, 776, 1272, 0, (64, 128), 0), (2049, 776, 1280, 0, (64, 128), 0),
+    (2049, 776, 1280, 16, (64, 128), 1), (2049, 776, 1288, 0, (64, 128), 1), (1281, 1544, 760, 0, (128, 128), 0),
+    (1281, 1544, 768, 0, (128, 128), 0), (1281, 1544, 768, 112, (128, 128), 1), (1281, 1544, 776, 0, (128, 128), 1),
+    (833, 840, 2112, 16, (64, 64), 0), (833, 840, 2120, 0, (64, 64), 1), (961, 1032, 1664, 16, (96, 64), 0), (961, 1032, 1672, 16, (96, 64), 1)])
+def test_which_calls_take_a_by_whole_lines(M, N, K, base, tile, lines):
+    """From a K on that is measured for each tile; a base off the line alone only where the order of the sums stays the same."""
+    got = launch_of(M, N, K, base)
+    assert (got[:2], got[4], got[5]) == (tile, lines, 0)
+
+
 @pytest.mark.gpu
 @pytest.mark.parametrize("tile", sorted(SHAPES), ids=lambda t: f"{t[0]}x{t[1]}")
 def test_every_phase_of_the_rows(tile):
@@ -56,7 +67,7 @@ def test_every_phase_of_the_rows(tile):
 
 
 # both forms of every tile that has two, and K no multiple of 64; the last two split K (128 x 128 and 192 x 128 tiles)
-PLACES = [(833, 840, 2112), (833, 840, 2120), (1055, 1024, 1984), (1055, 1024, 1992), (1025, 1000, 1024), (1281, 1544, 1024), (3455, 1544, 1024),
+PLACES = [(833, 840, 2112), (833, 840, 2120), (1055, 1024, 1984), (1055, 1024, 1992), (2049, 776, 1280), (1281, 1544, 1024), (3455, 1544, 1024),
           (2113, 2824, 1024), (3071, 3576, 1024), (3841, 2128, 1024), (969, 640, 7232), (180, 2880, 8192)]
 
 
