@@ -8,9 +8,9 @@ extern "C" {
 #endif
 
 /* gemm_lrelu with scratch memory to use where that is faster: with few tiles of C and a long K (in
- * a large call, few of the larger tiles) the workgroups split K and write fp32 parts, which a second kernel
- * on the same stream adds in a fixed order.
- * gemm_lrelu_workspace names the bytes a shape asks for (0: none, at most 32 MB).  workspace: device memory
+ * a large call, few tiles of 64 x 64, 128 x 128 or 192 x 128) the workgroups split K and write fp32 parts, which a
+ * second kernel on the same stream adds in a fixed order.
+ * gemm_lrelu_workspace names the bytes a shape asks for (0: none, at most 24 MiB).  workspace: device memory
  * aligned to 16 bytes that meets none of A, B, C, with any contents, not used by anybody else until the
  * call's two kernels have run (a pool that goes by the stream's handle does not see to that where a handle
  * is several queues, as the per-thread stream's, or is destroyed while its work runs); null or fewer

@@ -242,7 +242,7 @@ static Split choose_few(int M, int N, int K) {
 // Large calls that the rule above leaves whole: tiles of 128 x 128 or 192 x 128, which read A and B the fewest times but are
 // too few, or of 64 x 64, with K split into up to 8 ranges of 512 and more, one workgroup per unit.  The time is modelled as
 //     stages of a range * alone * (1 + load * f) * (1 + off) + ends + 2.7 + second (the second launch) + per_mb per MB of parts   (us)
-// and has to be 7 % below that of the call in one piece (64 x 64: 10 %).  At most 32 MB of parts.  Whole / split, us, on sets of
+// and has to be 7 % below that of the call in one piece (64 x 64: 10 %).  At most 24 MiB of parts: a tile of 192 x 128 floats for each unit.  Whole / split, us, on sets of
 // buffers that exceed the caches of the XCDs and, in brackets, on one:
 //   128 x 128   969 x 664 x 7256  28.8 / 21.5     2335 x 216 x 7256  44.4 / 21.1 (33.5 / 18.7)    998 x 528 x 4552   21.8 / 16.0 (21.8 / 15.8)
 //               118 x 7464 x 5592 35.7 / 27.2     91 x 5920 x 4112   23.5 / 18.3 (19.0 / 16.1)    2080 x 352 x 4504  20.7 / 17.3 (20.8 / 17.4)
@@ -258,13 +258,12 @@ static Split choose_large_split(int M, int N, int K) {
         {&kBlocks[2], 0.179f, 0.67f, 0.08f, 0.55f, 2.5f, 0.22f, 0.90f, 3e8, 512},
         {&kBlocks[5], 0.325f, 0.59f, 0.01f, 1.28f, 2.3f, 0.40f, 0.93f, 1e9, 8},
         {&kLargeBlocks[1], 0.523f, 0.20f, 0.f, 1.21f, 2.3f, 0.40f, 0.93f, 1e9, 8}};
-    constexpr double kMost = 32 << 20;
     Split best = whole;
     float best_us = 0.f, whole_us = 0.f;
     for (const auto& s : kRanges) {
         const long long tiles = (long long)cover_any(M, s.shape->bm) * cover(N, s.shape->bn);
         if ((double)M * N * K < s.least || N < s.width || (long long)(s.shape->bm - 1) * K * 2 + s.shape->bk * 2 + 128 >= (long long)kBufferSize) continue;
-        for (int r = 2; r <= 8 && tiles * r <= (long long)kComputeUnits && r * 512 <= K && (double)M * N * 4 * r <= kMost; ++r) {
+        for (int r = 2; r <= 8 && tiles * r <= (long long)kComputeUnits && r * 512 <= K; ++r) {
             if (whole_us == 0.f) whole_us = large_us(choose_block(M, N, K), M, N, K);
             const int kc = ((K + r - 1) / r + 63) / 64 * 64;
             if ((K + kc - 1) / kc != r) continue;

@@ -103,7 +103,7 @@ _plain_call = _first_call       # the native module's gemm_lrelu from the first 
 def gemm_lrelu(a, b, c, slope: float, stream=None) -> None:
     """c <- leaky_relu(a @ b) for device tensors a [M,K], b [K,N], c [M,N]; asynchronous on `stream`
     (an integer hipStream_t; default: torch's current stream).  On the current stream, few tiles of c and a long
-    K take up to 32 MB of scratch memory from torch's allocator for the call (gemm_workspace.h); other streams,
+    K take up to 24 MiB of scratch memory from torch's allocator for the call (gemm_workspace.h); other streams,
     the per-thread stream and recordings do without."""
     rc = _plain_call(a, b, c, slope, stream)
     if not rc:

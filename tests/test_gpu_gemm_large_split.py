@@ -16,7 +16,7 @@ SPLIT = [(969, 664, 7256, 5), (2097, 464, 5744, 5), (1153, 648, 7240, 6), (180, 
 
 def ranges_of(M, N, K):
     need = gemm.lib().gemm_lrelu_workspace(M, N, K)
-    assert need % (M * N * 4) == 0 and need <= 32 << 20
+    assert need % (M * N * 4) == 0 and need <= 24 << 20
     return need // (M * N * 4)
 
 
@@ -29,6 +29,8 @@ def test_which_calls_are_split():
 
 
 def test_parts_stay_below_the_limit():
+    """One tile of 192 x 128 floats for each of 256 units at most, as the header says."""
+    assert ranges_of(384, 4096, 7936) * 384 * 4096 * 4 == 24 << 20
     for M in range(33, 8192, 411):
         for N in range(64, 8192, 808):
             for K in (1024, 2056, 4104, 8192, 65536):
