@@ -19,6 +19,13 @@ long long gemm_lrelu_workspace(int M, int N, int K);
 int gemm_lrelu_in(const void* a, const void* b, void* c, int M, int N, int K, float slope, int dtype, void* stream,
                   void* workspace, long long workspace_bytes);
 
+/* The same for callers that take the memory call by call, with one look at the shape: `scratch` is called at most once, with
+ * `owner` and the bytes that the shape asks for, after the arguments have been checked and only where there are any.
+ * It returns memory as above or null, which makes it the plain call, and must not throw; null in its place: no memory. */
+typedef void* (*gemm_scratch_fn)(void* owner, long long bytes);
+int gemm_lrelu_with(const void* a, const void* b, void* c, int M, int N, int K, float slope, int dtype, void* stream,
+                    gemm_scratch_fn scratch, void* owner);
+
 /* 1 while the stream records a graph (or cannot say), else 0: memory taken per call has no place in a graph. */
 int gemm_lrelu_capturing(void* stream);
 

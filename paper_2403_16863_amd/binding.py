@@ -121,7 +121,7 @@ def native():
             raise ImportError("_native.so is not built; run `python -c 'import __graft_entry__ as g; g.build()'` "
                               "from the repository root") from e
         n.bind(*(ctypes.cast(f, ctypes.c_void_p).value
-                 for f in (L.attn_fwd, L.gemm_lrelu_in, L.gemm_lrelu_workspace, L.gemm_lrelu_capturing)))
+                 for f in (L.attn_fwd, L.gemm_lrelu_with, L.gemm_lrelu_capturing)))
         _native = n
     return _native
 

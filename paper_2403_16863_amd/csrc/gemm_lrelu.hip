@@ -134,7 +134,7 @@ constexpr BlockShape with_split(BlockShape s) {
 // of waves take alternate stages of K without whole lines and a run of stages each with them.  (Base 64 bytes off a line, us, without /
 // with: 768 x 768 x 3072 13.5 / 12.2, 961 x 1096 x 2048 14.9 / 12.5, 247 x 4160 x 1664 10.9 / 9.6; on a line 12.0, 12.2 and 9.2.)
 bool BlockShape::off_lines(const void* a, int K) const { return K >= lines_from && ((K & 63) || (wk == 1 && ((uintptr_t)a & 127))); }
-static const BlockShape kBlocks[] = {
+static constexpr BlockShape kBlocks[] = {
     with_split<Block<32, 32, 32, 1, 1, 4, 4, 2>, false>(block_shape<Block<32, 32, 32, 1, 1, 4, 4, 2>>(0.21f, 0.22f, 0.5f, {0.275f, 0.253f, 0.02f, 0.15f, 0.17f})),
     with_split<Block<32, 64, 64, 1, 2, 2, 3, 2>, false>(block_shape<Block<32, 64, 64, 1, 2, 2, 3, 2>>(0.27f, 0.31f, 0.58f, {0.229f, 0.288f, 0.06f, 0.25f, 0.11f})),
     with_split<Block<64, 64, 64, 2, 2, 1, 3, 3>, false>(block_shape<Block<64, 64, 64, 2, 2, 1, 3, 3>>(0.24f, 0.17f, 0.22f, {0.215f, 0.181f, 0.25f, 0.16f, 0.f})),
@@ -146,7 +146,7 @@ static const BlockShape kBlocks[] = {
 };
 // Tiles for large calls only: heights between the powers of two, for the calls whose tiles of those leave units
 // without work or fill the units a little more than once.
-static const BlockShape kLargeBlocks[] = {
+static constexpr BlockShape kLargeBlocks[] = {
     lines_shape<Block<96, 64, 64, 2, 2, 2, 3, 1>>(0.f, 0.f, 0.f, {0.382f, 0.f, 0.60f, 0.15f, 0.77f}),
     with_split<Block<192, 128, 64, 2, 4, 1, 3, 1>, true>(lines_shape<Block<192, 128, 64, 2, 4, 1, 3, 1>>(0.f, 0.f, 0.f, {0.443f, 0.f, 0.56f, 0.05f, 1.83f})),
     lines_shape<Block<192, 256, 64, 2, 4, 1, 2, 1>>(0.f, 0.f, 0.f, {0.768f, 0.f, 0.77f, 0.06f, 2.94f}),
@@ -157,7 +157,7 @@ static const BlockShape kLargeBlocks[] = {
 // workgroup / two: 2744 x 6672 x 112 19.9 / 15.4, 5826 x 2944 x 128 19.5 / 15.3, 4722 x 1584 x 104 9.1 / 7.4, 3499 x 5696 x 320 26.3 / 22.3,
 // 3656 x 2080 x 448 12.2 / 10.8; over 37 shapes of 270 to 4032 tiles 1.10 to 1.39 at K up to 504, 1.02 to 1.25 up to 624, 0.99 to 1.13 from
 // 704 on, and with longer K the shorter ring is the slower one (1504 x 5624 x 2272 0.88).
-static const BlockShape kShortBlock = block_shape<Block<128, 128, 64, 2, 4, 1, 2, 2>>(0.f, 0.f, 0.f, {0.579f, 0.395f, 0.39f, 0.05f, 0.41f});
+static constexpr BlockShape kShortBlock = block_shape<Block<128, 128, 64, 2, 4, 1, 2, 2>>(0.f, 0.f, 0.f, {0.579f, 0.395f, 0.39f, 0.05f, 0.41f});
 
 constexpr unsigned long long kComputeUnits = 256;
 
@@ -202,6 +202,7 @@ static const BlockShape& choose_block(int M, int N, int K) {
     if (best == &kBlocks[5] && K < 640 && (unsigned long long)cover(M, 128) * cover(N, 128) > kComputeUnits) best = &kShortBlock;
     if (!is_large(M, N, K)) return *best;
     float best_us = (K < 960 ? 0.89f : 0.95f) * large_us(*best, M, N, K);
+#pragma unroll
     for (const BlockShape& s : kLargeBlocks) {
         if ((long long)(s.bm - 1) * K * 2 + s.bk * 2 + 128 >= (long long)kBufferSize) continue;
         const float us = large_us(s, M, N, K);
@@ -224,19 +225,20 @@ static const BlockShape& choose_block(int M, int N, int K) {
 // Over 60 random shapes that the rule below takes: 1.2 times as fast on one set, 1.7 on fresh ones.
 struct Split {
     const BlockShape* shape;
-    int ranges, kc;  // ranges of kc values of k; 0: not split
+    int ranges, kc;           // ranges of kc values of k; 0: not split
+    const BlockShape* whole;  // choose_block's, where the choice had to ask for it, or null
 };
 static Split choose_few(int M, int N, int K) {
-    if (K < 4000) return {nullptr, 0, K};
+    if (K < 4000) return {nullptr, 0, K, nullptr};
     auto tiles = [&](int s) { return (long long)cover(M, kBlocks[s].bm) * cover(N, kBlocks[s].bn); };
     const int s = tiles(0) <= 64 ? 0 : M <= 32 ? 1 : 2;
     const long long n = tiles(s);
-    if (K < (s == 0 ? 4864 : M <= 64 ? 4000 : 4608) || n > (s == 1 ? 96 : 128) || K > (1 << 16)) return {nullptr, 0, K};
+    if (K < (s == 0 ? 4864 : M <= 64 ? 4000 : 4608) || n > (s == 1 ? 96 : 128) || K > (1 << 16)) return {nullptr, 0, K, nullptr};
     long long ranges = 256 / n;  // one workgroup per compute unit
     ranges = ranges < K / 512 ? ranges : K / 512;
     ranges = ranges < (s == 0 ? 16 : 8) ? ranges : s == 0 ? 16 : 8;
     const int step = kBlocks[s].bk * kBlocks[s].wk, kc = (int)((K + ranges - 1) / ranges + step - 1) / step * step;
-    return {&kBlocks[s], (K + kc - 1) / kc, kc};
+    return {&kBlocks[s], (K + kc - 1) / kc, kc, nullptr};
 }
 
 // Large calls that the rule above leaves whole: tiles of 128 x 128 or 192 x 128, which read A and B the fewest times but are
@@ -252,25 +254,32 @@ static Split choose_few(int M, int N, int K) {
 //               not below 512 columns: 410 x 200 x 3800  11.8 / 8.1 (6.6 / 7.0),  2114 x 64 x 3992  11.4 / 9.8 (6.9 / 8.3)
 // (128 x 256 and 256 x 128 tiles with K split: within 3 % of these; the parts in the accumulators' own order, 1 KB a store: the same.)
 static Split choose_large_split(int M, int N, int K) {
-    const Split whole = {nullptr, 0, K};
-    if (!is_large(M, N, K) || K > (1 << 16)) return whole;
-    static const struct { const BlockShape* shape; float alone, load, off, ends, second, per_mb, ahead; double least; int width; } kRanges[] = {
+    Split best = {nullptr, 0, K, nullptr};
+    if (!is_large(M, N, K) || K > (1 << 16)) return best;
+    static constexpr struct { const BlockShape* shape; float alone, load, off, ends, second, per_mb, ahead; double least; int width; } kRanges[] = {
         {&kBlocks[2], 0.179f, 0.67f, 0.08f, 0.55f, 2.5f, 0.22f, 0.90f, 3e8, 512},
         {&kBlocks[5], 0.325f, 0.59f, 0.01f, 1.28f, 2.3f, 0.40f, 0.93f, 1e9, 8},
         {&kLargeBlocks[1], 0.523f, 0.20f, 0.f, 1.21f, 2.3f, 0.40f, 0.93f, 1e9, 8}};
-    Split best = whole;
+    const double products = (double)M * N * K;
     float best_us = 0.f, whole_us = 0.f;
+#pragma unroll
     for (const auto& s : kRanges) {
         const long long tiles = (long long)cover_any(M, s.shape->bm) * cover(N, s.shape->bn);
-        if ((double)M * N * K < s.least || N < s.width || (long long)(s.shape->bm - 1) * K * 2 + s.shape->bk * 2 + 128 >= (long long)kBufferSize) continue;
-        for (int r = 2; r <= 8 && tiles * r <= (long long)kComputeUnits && r * 512 <= K; ++r) {
-            if (whole_us == 0.f) whole_us = large_us(choose_block(M, N, K), M, N, K);
+        if (products < s.least || N < s.width || (long long)(s.shape->bm - 1) * K * 2 + s.shape->bk * 2 + 128 >= (long long)kBufferSize) continue;
+        if (tiles * 2 > (long long)kComputeUnits || 1024 > K) continue;
+        if (!best.whole) best.whole = &choose_block(M, N, K), whole_us = large_us(*best.whole, M, N, K);
+        const float off = N & 63 ? 1.f + s.off : 1.f, parts_us = s.per_mb * 1e-6f * (float)M * (float)N, limit_us = s.ahead * whole_us;
+        // no number of ranges comes below this (each takes 6 ns to look at)
+        if ((float)K * (1.f / 512) * s.alone + s.ends + 2.7f + s.second + parts_us * 8.f >= 1.0001f * limit_us) continue;
+#pragma unroll
+        for (int r = 2; r <= 8; ++r) {
+            if (tiles * r > (long long)kComputeUnits || r * 512 > K) break;
             const int kc = ((K + r - 1) / r + 63) / 64 * 64;
-            if ((K + kc - 1) / kc != r) continue;
-            const float filled = (float)(tiles * r) / (float)kComputeUnits;
-            const float loop = (float)(kc / 64) * s.alone * (1.f + s.load * filled) * (N & 63 ? 1.f + s.off : 1.f);
-            const float us = loop + s.ends + 2.7f + s.second + s.per_mb * 1e-6f * (float)M * (float)N * (float)(4 * r);
-            if (us < s.ahead * whole_us && (!best.ranges || us < best_us)) best = {s.shape, r, kc}, best_us = us;
+            if ((r - 1) * kc >= K) continue;
+            const float filled = (float)((int)tiles * r) / (float)kComputeUnits;
+            const float loop = (float)(kc / 64) * s.alone * (1.f + s.load * filled) * off;
+            const float us = loop + s.ends + 2.7f + s.second + parts_us * (float)(4 * r);
+            if (us < limit_us && (!best.ranges || us < best_us)) best = {s.shape, r, kc, best.whole}, best_us = us;
         }
     }
     return best;
@@ -300,8 +309,7 @@ static int launch_split(const Split& sp, const void* a, const void* b, void* c, 
 }
 
 // (arguments checked by the caller)
-static int launch_block(const void* a, const void* b, void* c, int M, int N, int K, float slope, int dtype, void* stream) {
-    const BlockShape& s = choose_block(M, N, K);
+static int launch_block(const BlockShape& s, const void* a, const void* b, void* c, int M, int N, int K, float slope, int dtype, void* stream) {
     Arguments to(a, b, c, M, N, K, K, slope);
     void* args[] = {&to.pointers_m_n, &to.k_kc_slope};
     const dim3 grid(cover_any(M, s.bm) * cover(N, s.bn));
@@ -393,7 +401,7 @@ int gemm_lrelu_variant(const void* a, const void* b, void* c, int M, int N, int 
 
 int gemm_lrelu(const void* a, const void* b, void* c, int M, int N, int K, float slope, int dtype, void* stream) {
     const int rc = gemm::check_args(a, b, c, M, N, K, dtype, 0);
-    return rc == GEMM_OK ? gemm::launch_block(a, b, c, M, N, K, slope, dtype, stream) : rc;
+    return rc == GEMM_OK ? gemm::launch_block(gemm::choose_block(M, N, K), a, b, c, M, N, K, slope, dtype, stream) : rc;
 }
 
 static long long parts_bytes(const gemm::Split& sp, int M, int N) { return (long long)sp.ranges * M * N * 4; }
@@ -402,17 +410,30 @@ long long gemm_lrelu_workspace(int M, int N, int K) {
     return M < 1 || N < 8 || K < 8 ? 0 : parts_bytes(gemm::choose_split(M, N, K), M, N);
 }
 
-int gemm_lrelu_in(const void* a, const void* b, void* c, int M, int N, int K, float slope, int dtype, void* stream,
-                  void* workspace, long long workspace_bytes) {
+// (one look at the shape for the scratch memory, the tile and the launch: with a query for the bytes ahead of it the choice took 204 ns of
+// a call of 512 x 512 x 2048 and 315 of 700 x 700 x 4000, now 60 and 104; without large calls' tiles and ranges it was 34)
+int gemm_lrelu_with(const void* a, const void* b, void* c, int M, int N, int K, float slope, int dtype, void* stream,
+                    gemm_scratch_fn scratch, void* owner) {
     const int rc = gemm::check_args(a, b, c, M, N, K, dtype, 0);
     if (rc != GEMM_OK) return rc;
     const gemm::Split sp = gemm::choose_split(M, N, K);
     const long long need = parts_bytes(sp, M, N);
-    if (!need || !workspace || workspace_bytes < need) return gemm::launch_block(a, b, c, M, N, K, slope, dtype, stream);
+    void* const workspace = need && scratch ? scratch(owner, need) : nullptr;
+    if (!workspace) return gemm::launch_block(sp.whole ? *sp.whole : gemm::choose_block(M, N, K), a, b, c, M, N, K, slope, dtype, stream);
     const uintptr_t w0 = (uintptr_t)workspace, w1 = w0 + need;
     auto meets = [&](const void* p, size_t bytes) { return w0 < (uintptr_t)p + bytes && (uintptr_t)p < w1; };
     if ((w0 & 15) || meets(a, (size_t)M * K * 2) || meets(b, (size_t)K * N * 2) || meets(c, (size_t)M * N * 2)) return GEMM_EINVAL;
     return gemm::launch_split(sp, a, b, c, M, N, K, slope, dtype, stream, workspace);
+}
+
+int gemm_lrelu_in(const void* a, const void* b, void* c, int M, int N, int K, float slope, int dtype, void* stream,
+                  void* workspace, long long workspace_bytes) {
+    struct Given {
+        void* p;
+        long long bytes;
+    } given = {workspace, workspace_bytes};
+    const gemm_scratch_fn enough = [](void* owner, long long bytes) { return ((Given*)owner)->bytes < bytes ? nullptr : ((Given*)owner)->p; };
+    return gemm_lrelu_with(a, b, c, M, N, K, slope, dtype, stream, enough, &given);
 }
 
 int gemm_lrelu_capturing(void* stream) {
@@ -440,7 +461,7 @@ int gemm_lrelu_block_threads_of(int M, int N, int K) { return M < 1 || N < 1 || 
 // threads, workgroups per unit, 1 for A by whole lines, ranges of K (0: whole) and their kc.
 int gemm_lrelu_launch_of(int M, int N, int K, int base, int scratch, int* out) {
     if (!out || M < 1 || N < 8 || K < 8 || base < 0) return GEMM_EINVAL;
-    const gemm::Split sp = scratch ? gemm::choose_split(M, N, K) : gemm::Split{nullptr, 0, K};
+    const gemm::Split sp = scratch ? gemm::choose_split(M, N, K) : gemm::Split{nullptr, 0, K, nullptr};
     const gemm::BlockShape& s = sp.ranges ? *sp.shape : gemm::choose_block(M, N, K);
     const void* const a = (const void*)(uintptr_t)base;
     const bool lines = sp.ranges ? s.range_for(0, a, K) == s.split_lines[0] : s.whole_for(0, a, K) == s.lines[0];

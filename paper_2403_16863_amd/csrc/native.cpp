@@ -21,12 +21,11 @@ namespace {
 constexpr long kNotPlain = 1;  // library codes are 0 or negative
 
 typedef int (*AttnFn)(const void*, const void*, const void*, void*, float*, int, int, int, int, int, float, int, void*);
-typedef int (*GemmFn)(const void*, const void*, void*, int, int, int, float, int, void*, void*, long long);
-typedef long long (*WorkspaceFn)(int, int, int);
+typedef void* (*ScratchFn)(void*, long long);
+typedef int (*GemmFn)(const void*, const void*, void*, int, int, int, float, int, void*, ScratchFn, void*);
 typedef int (*CapturingFn)(void*);
 AttnFn g_attn = nullptr;
 GemmFn g_gemm = nullptr;
-WorkspaceFn g_workspace = nullptr;
 CapturingFn g_capturing = nullptr;
 
 // Scratch memory of one call, from torch's caching allocator: it belongs to the stream the call runs on, so it
@@ -37,18 +36,9 @@ CapturingFn g_capturing = nullptr;
 // call then does without.
 class Workspace {
   public:
-    Workspace(long long bytes, void* stream, int device) : bytes_(bytes) {
-        if (bytes <= 0 || stream != (void*)c10::hip::getCurrentHIPStream(device).stream() || stream == (void*)hipStreamPerThread ||
-            c10::hip::current_device() != device || g_capturing(stream))
-            return;
-        try {
-            // A recording in another thread (in the default mode) forbids this thread the allocator's calls to the
-            // device, and one such call would end it; they have nothing to do with it.
-            const c10::hip::HIPStreamCaptureModeGuard beside(hipStreamCaptureModeRelaxed);
-            p_ = c10::hip::HIPCachingAllocator::raw_alloc_with_stream((size_t)bytes, (hipStream_t)stream);
-        } catch (const std::exception&) {
-        }
-    }
+    Workspace(void* stream, int device) : stream_(stream), device_(device) {}
+    // What the library calls if it has a use for the memory (without the interpreter's lock: torch takes it where its allocator needs it).
+    static void* take(void* self, long long bytes) { return ((Workspace*)self)->take(bytes); }
     ~Workspace() {
         try {
             if (p_) c10::hip::HIPCachingAllocator::raw_delete(p_);
@@ -57,11 +47,24 @@ class Workspace {
     }
     Workspace(const Workspace&) = delete;
     Workspace& operator=(const Workspace&) = delete;
-    void* ptr() const { return p_; }
-    long long bytes() const { return p_ ? bytes_ : 0; }
 
   private:
-    long long bytes_;
+    void* take(long long bytes) {
+        try {
+            if (stream_ != (void*)c10::hip::getCurrentHIPStream(device_).stream() || stream_ == (void*)hipStreamPerThread ||
+                c10::hip::current_device() != device_ || g_capturing(stream_))
+                return nullptr;
+            // A recording in another thread (in the default mode) forbids this thread the allocator's calls to the
+            // device, and one such call would end it; they have nothing to do with it.
+            const c10::hip::HIPStreamCaptureModeGuard beside(hipStreamCaptureModeRelaxed);
+            p_ = c10::hip::HIPCachingAllocator::raw_alloc_with_stream((size_t)bytes, (hipStream_t)stream_);
+        } catch (const std::exception&) {
+        }
+        return p_;
+    }
+
+    void* stream_;
+    int device_;
     void* p_ = nullptr;
 };
 
@@ -144,20 +147,19 @@ PyObject* gemm_lrelu(PyObject* const* args, Py_ssize_t nargs) {
     if ((slope == -1.0 && PyErr_Occurred()) || !stream_of(args[4], *a, &stream)) return not_plain();
     void *const pa = a->data_ptr(), *const pb = b->data_ptr(), *const pc = c->data_ptr();
     const int M = (int)a->size(0), N = (int)b->size(1), K = (int)a->size(1);
-    const Workspace ws(g_workspace(M, N, K), stream, a->device().index());
+    Workspace ws(stream, a->device().index());
     int rc;
     Py_BEGIN_ALLOW_THREADS
-    rc = g_gemm(pa, pb, pc, M, N, K, (float)slope, dt, stream, ws.ptr(), ws.bytes());
+    rc = g_gemm(pa, pb, pc, M, N, K, (float)slope, dt, stream, &Workspace::take, &ws);
     Py_END_ALLOW_THREADS
     return PyLong_FromLong(rc);
 }
 
-// bind(addresses of the library's attn_fwd, gemm_lrelu_in, gemm_lrelu_workspace and gemm_lrelu_capturing)
+// bind(addresses of the library's attn_fwd, gemm_lrelu_with and gemm_lrelu_capturing)
 PyObject* bind(PyObject*, PyObject* args) {
-    unsigned long long attn = 0, gemm = 0, workspace = 0, capturing = 0;
-    if (!PyArg_ParseTuple(args, "KKKK", &attn, &gemm, &workspace, &capturing)) return nullptr;
+    unsigned long long attn = 0, gemm = 0, capturing = 0;
+    if (!PyArg_ParseTuple(args, "KKK", &attn, &gemm, &capturing)) return nullptr;
     g_attn = (AttnFn)attn;
-    g_workspace = (WorkspaceFn)workspace;
     g_capturing = (CapturingFn)capturing;
     g_gemm = (GemmFn)gemm;
     Py_RETURN_NONE;

@@ -19,6 +19,8 @@ SYMBOLS = ("gemm_lrelu", "gemm_lrelu_variant", "gemm_lrelu_num_variants", "gemm_
            "gemm_lrelu_variant_knobs", "gemm_lrelu_time", "gemm_lrelu_tile_of_block", "gemm_lrelu_codeobj_load",
            "gemm_lrelu_codeobj_unload", "gemm_lrelu_codeobj", "gemm_lrelu_time_codeobj")
 
+SCRATCH_FN = ctypes.CFUNCTYPE(ctypes.c_void_p, ctypes.c_void_p, ctypes.c_longlong)  # gemm_scratch_fn
+
 _ready = False
 
 
@@ -41,6 +43,8 @@ def lib():
         L.gemm_lrelu_in.argtypes = common + [vp, ctypes.c_longlong]
         L.gemm_lrelu_workspace.restype = ctypes.c_longlong
         L.gemm_lrelu_workspace.argtypes = [i, i, i]
+        L.gemm_lrelu_with.restype = i
+        L.gemm_lrelu_with.argtypes = common + [SCRATCH_FN, vp]
         L.gemm_lrelu_capturing.restype = i
         L.gemm_lrelu_capturing.argtypes = [vp]
         L.gemm_lrelu_variant.restype = i

@@ -39,6 +39,48 @@ def test_bad_scratch_memory_is_refused_before_any_launch():
     assert L.gemm_lrelu_in(a, b, c, M, N, K + 4, 0.1, 0, None, 1 << 43, need) == gemm.GEMM_EINVAL
 
 
+def test_scratch_memory_is_asked_for_once_in_the_call():
+    """After the checks, for the bytes that the shape asks for; what comes back is checked before any launch (fake pointers).
+    The native path of a call goes this way, so that a shape is looked at once."""
+    L = gemm.lib()
+    a, b, c, asked = 1 << 40, 1 << 41, 1 << 42, []
+
+    @gemm.SCRATCH_FN
+    def give(owner, nbytes):
+        asked.append((owner, nbytes))
+        return (1 << 43) + 8
+    for M, N, K in ((24, 4096, 4096), (969, 664, 7256)):
+        del asked[:]
+        assert L.gemm_lrelu_with(a, b, c, M, N, K, 0.1, 0, None, give, 77) == gemm.GEMM_EINVAL
+        assert asked == [(77, L.gemm_lrelu_workspace(M, N, K))]
+        assert L.gemm_lrelu_with(a, b, a, M, N, K, 0.1, 0, None, give, 77) == gemm.GEMM_EINVAL
+        assert L.gemm_lrelu_with(a, b, c, M, N, K + 4, 0.1, 0, None, give, 77) == gemm.GEMM_EINVAL
+        assert len(asked) == 1
+
+
+@pytest.mark.gpu
+def test_scratch_memory_that_is_given_given_not_or_not_asked_for():
+    import torch
+    L = gemm.lib()
+    for (M, N, K), split in (((33, 40, 5000), True), ((577, 616, 4552), True), ((100, 72, 328), False)):
+        g = torch.Generator(device="cuda")
+        g.manual_seed(3)
+        a, b = (torch.randn(s, device="cuda", generator=g).half() for s in ((M, K), (K, N)))
+        plain, want, out = (torch.empty(M, N, device="cuda", dtype=torch.float16) for _ in range(3))
+        args = (M, N, K, 0.1, 0, torch.cuda.current_stream().cuda_stream)
+        ws, asked = torch.empty(1 << 22, device="cuda"), []
+        assert L.gemm_lrelu(a.data_ptr(), b.data_ptr(), plain.data_ptr(), *args) == 0
+        assert L.gemm_lrelu_in(a.data_ptr(), b.data_ptr(), want.data_ptr(), *args, ws.data_ptr(), 16 << 20) == 0
+        give = gemm.SCRATCH_FN(lambda owner, nbytes: asked.append(nbytes) or owner)
+        for fn, owner, expect in ((give, ws.data_ptr(), want), (give, None, plain), (gemm.SCRATCH_FN(0), ws.data_ptr(), plain)):
+            out.fill_(float("nan"))
+            assert L.gemm_lrelu_with(a.data_ptr(), b.data_ptr(), out.data_ptr(), *args, fn, owner) == 0
+            torch.cuda.synchronize()
+            assert torch.equal(out.view(torch.int16), expect.view(torch.int16))
+        assert len(asked) == (2 if split else 0) and all(n <= 16 << 20 for n in asked)
+        assert torch.equal(want.view(torch.int16), plain.view(torch.int16)) != split
+
+
 @pytest.mark.gpu
 @pytest.mark.parametrize("dtype", [I.F16, I.BF16], ids=["f16", "bf16"])
 def test_split_against_the_oracle(dtype):
