@@ -640,9 +640,14 @@ constexpr int kKeySplit4 = 37, kKeySplit8 = 38, kGroups2 = 39, kGroups4 = 40, kR
 //   256 rows   1.40 nk + 9.4 a round;                                               causal  1.51 per tile + 8.05 an item
 //   128 rows   1.70 nk + 6.9 a round (0.86 nk with one workgroup on every unit);    causal  1.87 per tile of a workgroup's mean share + 6.17 a round
 // Fitted to 181 and 188 launches of 24 to 128 heads, 257 to 8000 keys and up to 16 rounds (standard deviation of the time over the
-// model 3 to 7 %).  6 % ahead, 128 rows take 16 and 45 of them: 0.87 and 0.94 of their time in the mean, 2 % more at most.  256 / 128 rows, us:
-//   96 x 599  39.9 / 24.8    128 x 642  46.6 / 40.1    128 x 1041  98.6 / 90.0    24 x 3790  171 / 170 (not taken, as all beyond 3000 keys)
-//   causal  128 x 561  31.6 / 25.5    96 x 846  37.3 / 32.1    128 x 1101  68.2 / 59.4    48 x 2111  67.2 / 63.6    64 x 1545  54.2 / 55.4
+// model 3 to 7 %).  128 rows have to be 6 % ahead; under a mask that is the model of heads that divide by 8, which stay on an XCD
+// each (schedule_item).  Of other heads, whose tiles every XCD reads, 128 rows take up to 1.16 of the time where they are modelled 6 to
+// 18 % ahead (45 launches; 12 of them more than 1.02 on one set of buffers and on several), unless the keys are few: from 640 on
+// they have to be 18 % ahead.  Time against 256 rows', one set / several, mean and largest: without a mask (173 launches) 0.89 / 0.87, 1.07 /
+// 1.03; under it 0.92 / 0.91, 1.00 / 0.99 (70 of heads that divide by 8) and 0.94 / 0.91, 1.02 / 0.99 (48 others).  256 / 128 rows, us, several sets:
+//   96 x 599  43.9 / 27.1    128 x 642  48.5 / 40.4    128 x 1041  97.9 / 86.7    24 x 3790  172 / 170 (not taken, as all beyond 3000 keys)
+//   causal  128 x 561  32.9 / 27.5    96 x 846  38.0 / 32.7    128 x 1101  70.1 / 60.5    48 x 2111  69.5 / 65.7    64 x 1545  57.9 / 55.8
+//           17 x 4256  98.9 / 90.7    119 x 568  32.2 / 28.7    not taken: 43 x 2059  65.2 / 71.7    90 x 1811  110.7 / 117.8
 static bool rows128_sooner(long long heads, int N, int causal) {
     if (N <= 256 || N > (causal ? 8000 : 3000)) return false;
     const long long nq = (N + 255) / 256, items = heads * nq, rounds = (items + 255) / 256;
@@ -666,7 +671,7 @@ static bool rows128_sooner(long long heads, int N, int causal) {
         t256 = t > t256 ? t : t256;
     }
     const float tiles = (float)heads * ((float)(n128 * (n128 - 1)) + nk);
-    return 1.87f * tiles / 512.f + 6.17f * (float)((j + 511) / 512) < 0.94f * t256;
+    return 1.87f * tiles / 512.f + 6.17f * (float)((j + 511) / 512) < (heads % 8 == 0 || N < 640 ? 0.94f : 0.82f) * t256;
 }
 
 static int choose_variant(long long heads, int N, int d, int causal) {

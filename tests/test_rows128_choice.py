@@ -16,6 +16,9 @@ ROWS128, D128 = 1, 36
     (128, 896, True, ROWS128), (128, 897, True, D128), (128, 1024, True, D128), (128, 1025, True, ROWS128), (96, 1152, True, ROWS128),
     (96, 1153, True, D128), (32, 2560, True, ROWS128), (32, 2561, True, D128), (64, 4096, True, D128), (32, 16384, True, D128),
     (300, 256, True, D128), (1 << 20, 2048, True, D128),
+    # heads that XCDs share, under a mask: only far ahead, or with few keys
+    (43, 2059, True, D128), (43, 2362, True, D128), (55, 1597, True, D128), (90, 1811, True, D128), (75, 1541, True, D128), (87, 1004, True, D128),
+    (86, 806, True, ROWS128), (17, 4256, True, ROWS128), (127, 537, True, ROWS128), (119, 639, True, ROWS128), (119, 640, True, D128), (64, 1373, True, ROWS128),
 ])
 def test_the_choice(heads, N, causal, want):
     for dtype in (A.ATTN_F16, A.ATTN_BF16):
