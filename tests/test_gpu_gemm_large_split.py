@@ -8,10 +8,12 @@ from paper_2403_16863_amd import gemm
 from paper_2403_16863_amd import inputs as I
 
 from test_gpu_gemm import check, run_gpu
+from test_gpu_gemm_block import launch_of
 
-# (M, N, K, ranges)
-SPLIT = [(969, 664, 7256, 5), (2097, 464, 5744, 5), (1153, 648, 7240, 6), (180, 2880, 8192, 8), (4385, 192, 6976, 5), (577, 616, 4552, 6),
-         (162, 800, 4512, 6), (127, 1272, 3560, 6)]
+# (M, N, K, ranges, tile, 1 for A by whole lines)
+SPLIT = [(969, 664, 7256, 5, (128, 128), 1), (2097, 464, 5744, 5, (192, 128), 1), (1153, 648, 7240, 6, (192, 128), 1), (180, 2880, 8192, 8, (192, 128), 0),
+         (4385, 192, 6976, 5, (192, 128), 0), (577, 616, 4552, 6, (128, 128), 1), (162, 800, 4512, 6, (64, 64), 0), (127, 1272, 3560, 6, (64, 64), 0),
+         (969, 640, 7232, 6, (128, 128), 0), (577, 616, 4544, 6, (128, 128), 0)]
 
 
 def ranges_of(M, N, K):
@@ -21,8 +23,10 @@ def ranges_of(M, N, K):
 
 
 def test_which_calls_are_split():
-    for M, N, K, ranges in SPLIT:
-        assert ranges_of(M, N, K) == ranges, (M, N, K)
+    for M, N, K, ranges, tile, lines in SPLIT:
+        got = launch_of(M, N, K)
+        assert ranges_of(M, N, K) == ranges and (got[:2], got[4], got[5]) == (tile, lines, ranges), (M, N, K)
+        assert launch_of(M, N, K, scratch=False)[5] == 0
     for M, N, K in ((4096, 4096, 4096), (2048, 8192, 2048), (1000, 1032, 2056), (969, 664, 1016), (8192, 8192, 8192), (300, 8192, 1 << 17),
                     (451, 1184, 3648), (410, 200, 3800), (65, 2016, 3536)):
         assert ranges_of(M, N, K) == 0, (M, N, K)
@@ -40,9 +44,7 @@ def test_parts_stay_below_the_limit():
 @pytest.mark.gpu
 @pytest.mark.parametrize("dtype", [I.F16, I.BF16], ids=["f16", "bf16"])
 def test_split_against_the_oracle(dtype):
-    for n, (M, N, K, _) in enumerate(SPLIT):
-        if n % 2 != (dtype == I.BF16):
-            continue
+    for n, (M, N, K, *_) in enumerate(SPLIT):
         print(f"M{M} N{N} K{K} dtype {dtype}", flush=True)
         ab, bb = I.make_gemm(M, N, K, dtype, seed=950 + n)
         check(run_gpu(ab, bb, 0.1, dtype), ab, bb, 0.1, dtype, f"split M{M} N{N} K{K}")
@@ -51,7 +53,7 @@ def test_split_against_the_oracle(dtype):
 @pytest.mark.gpu
 def test_zero_fill_past_a_range_never_meets_an_infinity():
     """An infinity in the last column of A, and one in the first column of a range, stay in their rows of C."""
-    M, N, K, ranges = SPLIT[2]
+    M, N, K, ranges = SPLIT[2][:4]
     ab, bb = I.make_gemm(M, N, K, I.BF16, seed=4)
     ab, bb = ab.copy(), np.where(bb == 0, np.uint16(0x3F80), bb).astype(np.uint16)
     kc = (-(-K // ranges) + 63) // 64 * 64
@@ -65,7 +67,7 @@ def test_zero_fill_past_a_range_never_meets_an_infinity():
 def test_without_scratch_memory_the_whole_call_runs():
     import torch
     L = gemm.lib()
-    M, N, K, _ = SPLIT[0]
+    M, N, K = SPLIT[0][:3]
     g = torch.Generator(device="cuda")
     g.manual_seed(1)
     a, b = (torch.randn(s, device="cuda", generator=g).half() for s in ((M, K), (K, N)))

@@ -32,10 +32,10 @@ def test_calls_that_are_not_large_keep_to_the_other_tiles():
 @pytest.mark.parametrize("tile", sorted(SHAPES), ids=lambda t: f"{t[0]}x{t[1]}")
 def test_tile_against_the_oracle(tile):
     for n, (M, N, K) in enumerate(SHAPES[tile]):
-        dtype = (I.F16, I.BF16)[n & 1]
-        print(f"M{M} N{N} K{K} tile {tile} dtype {dtype}", flush=True)
-        ab, bb = I.make_gemm(M, N, K, dtype, seed=900 + n)
-        check(run_gpu(ab, bb, 0.1, dtype), ab, bb, 0.1, dtype, f"M{M} N{N} K{K} tile {tile}")
+        for dtype in (I.F16, I.BF16):
+            print(f"M{M} N{N} K{K} tile {tile} dtype {dtype}", flush=True)
+            ab, bb = I.make_gemm(M, N, K, dtype, seed=900 + n)
+            check(run_gpu(ab, bb, 0.1, dtype), ab, bb, 0.1, dtype, f"M{M} N{N} K{K} tile {tile}")
 
 
 @pytest.mark.gpu

@@ -1,20 +1,25 @@
 """GEMM + LeakyReLU where rows of A do not start on 128-byte lines: every phase of a row against the lines (K / 8 modulo
-8, and the base of A in 16-byte steps), on every tile that takes A by whole lines.  Tolerance as in test_gpu_gemm.py."""
+8, and the base of A in 16-byte steps), on every tile that takes A by whole lines, and both that do so with K split.  Tolerance as in test_gpu_gemm.py."""
 import numpy as np
 import pytest
 
 from paper_2403_16863_amd import inputs as I
 
 from test_gpu_gemm import check
-from test_gpu_gemm_block import block_of, launch_of
+from test_gpu_gemm_block import launch_of
 
-# tile: (M, N, K of the eight phases): one row and one column chunk past a tile
+# (tile, ranges of K): (M, N, K of the eight phases): a row and a column chunk past a tile, or one short of it
 SHAPES = {
-    (64, 64): (833, 840, 2112),
-    (64, 128): (2049, 776, 1344),
-    (128, 128): (1281, 1544, 768),
-    (128, 256): (2113, 2824, 960),
-    (256, 256): (3841, 2128, 768),
+    (64, 64, 0): (833, 840, 2112),
+    (64, 128, 0): (2049, 776, 1344),
+    (96, 64, 0): (961, 1096, 2048),
+    (128, 128, 0): (1281, 1544, 768),
+    (128, 256, 0): (2113, 2824, 960),
+    (192, 128, 0): (3455, 1544, 1024),
+    (192, 256, 0): (3071, 3576, 960),
+    (256, 256, 0): (3841, 2128, 768),
+    (128, 128, 6): (577, 616, 4544),
+    (192, 128, 8): (180, 2888, 8128),
 }
 
 
@@ -50,18 +55,31 @@ def test_which_calls_take_a_by_whole_lines(M, N, K, base, tile, lines):
     assert (got[:2], got[4], got[5]) == (tile, lines, 0)
 
 
+def offset_of(n):
+    return (0, 1, 0, 7, 4, 0, 2, 5)[n]
+
+
+@pytest.mark.parametrize("tile", sorted(SHAPES), ids=lambda t: f"{t[0]}x{t[1]}" + f" {t[2]} ranges" * (t[2] > 0))
+def test_shapes_take_the_kernel_they_are_meant_for(tile):
+    M, N, K0 = SHAPES[tile]
+    groups = tile in ((64, 64, 0), (96, 64, 0))     # two groups of waves: off the lines by K alone
+    for n in range(9):
+        K, offset = (K0 + 8 * n, offset_of(n)) if n < 8 else (K0, 3)
+        bm, bn, threads, _, lines, ranges, _ = launch_of(M, N, K, 16 * offset)
+        assert (bm, bn, ranges) == tile and lines == (K % 64 != 0 or (offset > 0 and not groups)), (K, offset)
+        assert tile != (64, 64, 0) or threads == 512
+
+
 @pytest.mark.gpu
-@pytest.mark.parametrize("tile", sorted(SHAPES), ids=lambda t: f"{t[0]}x{t[1]}")
+@pytest.mark.parametrize("tile", sorted(SHAPES), ids=lambda t: f"{t[0]}x{t[1]}" + f" {t[2]} ranges" * (t[2] > 0))
 def test_every_phase_of_the_rows(tile):
     M, N, K0 = SHAPES[tile]
     for n in range(8):
-        K, offset, dtype = K0 + 8 * n, (0, 1, 0, 7, 4, 0, 2, 5)[n], (I.F16, I.BF16)[n & 1]
-        assert block_of(M, N, K) == tile
+        K, offset, dtype = K0 + 8 * n, offset_of(n), (I.F16, I.BF16)[n & 1]
         print(f"M{M} N{N} K{K} base {offset} dtype {dtype}", flush=True)
         ab, bb = I.make_gemm(M, N, K, dtype, seed=700 + n)
         check(run(ab, bb, dtype, offset), ab, bb, 0.1, dtype, f"M{M} N{N} K{K} base {offset}")
     K, dtype = K0, I.BF16               # rows that are whole lines, off the lines by the base alone
-    assert block_of(M, N, K) == tile
     ab, bb = I.make_gemm(M, N, K, dtype, seed=710)
     check(run(ab, bb, dtype, 3), ab, bb, 0.1, dtype, f"M{M} N{N} K{K} base 3")
 

@@ -6,20 +6,23 @@ import pytest
 from paper_2403_16863_amd import inputs as I
 
 from test_gpu_gemm import check, run_gpu
-from test_gpu_gemm_block import block_of
+from test_gpu_gemm_block import launch_of
 
 SHAPES = [(6529, 1032, 8), (6655, 1032, 64), (5377, 1288, 72), (6529, 1032, 136), (6655, 1032, 504), (6529, 1032, 632)]
 
 
 def test_shapes_are_what_they_stand_for():
+    """Two workgroups on a unit for these; one from K = 640 on and for 256 tiles."""
     for M, N, K in SHAPES:
-        assert block_of(M, N, K) == (128, 128) and -(-M // 128) * -(-N // 128) > 256, (M, N, K)
+        assert launch_of(M, N, K)[:4] == (128, 128, 512, 2) and -(-M // 128) * -(-N // 128) > 256, (M, N, K)
+    for M, N, K in ((6529, 1032, 640), (2048, 2048, 504), (2048, 2048, 632)):
+        assert launch_of(M, N, K)[:4] == (128, 128, 512, 1), (M, N, K)
 
 
 @pytest.mark.gpu
+@pytest.mark.parametrize("dtype", [I.F16, I.BF16], ids=["f16", "bf16"])
 @pytest.mark.parametrize("M,N,K", SHAPES)
-def test_against_the_oracle(M, N, K):
-    dtype = I.BF16 if K % 16 else I.F16
+def test_against_the_oracle(M, N, K, dtype):
     ab, bb = I.make_gemm(M, N, K, dtype, seed=K)
     check(run_gpu(ab, bb, 0.1, dtype), ab, bb, 0.1, dtype, f"M{M} N{N} K{K}")
 
