@@ -184,7 +184,8 @@ static const BlockShape& choose_table(int M, int N, int K) {
 // 8192 and K 256 .. 8192, a third of them with N and K multiples of 64, each timed with every tile, bfloat16; the
 // standard deviation of the time over the model is 6 to 13 % by tile, so one of the new tiles has to be 5 % ahead, or, with a short
 // K, where what is not a stage weighs more, 11 %.  Of those shapes 26 take another tile and run in 0.89 of the time (geometric
-// mean; one takes longer, 3 %).  us:
+// mean; one takes longer, 3 %); of 250 drawn ones that do, each in 0.84 to 0.86 on several sets of buffers and on one (with whole lines of A where
+// it has them), the slowest 1.01 on several (3219 x 5360 x 608) and 1.09 on one (2394 x 600 x 1240 8.0 -> 8.7; 13.8 -> 12.4 on several).  us:
 //   96 x 64    247 x 4160 x 1704 12.0 -> 10.1, 3353 x 384 x 1264 9.6 -> 8.3, 1138 x 1088 x 2880 16.8 -> 14.0, 1000 x 1032 x 2056 14.2 -> 12.6
 //   192 x 128  7798 x 2280 x 1000 52.8 -> 49.0, 1504 x 5624 x 2272 62.8 -> 51.8, 3430 x 1536 x 1856 25.3 -> 20.1
 //   192 x 256  5963 x 1528 x 1272 36.0 -> 31.9, 7028 x 1216 x 4608 107.9 -> 93.7, 4297 x 2176 x 576 18.6 -> 16.2
@@ -252,6 +253,9 @@ static Split choose_few(int M, int N, int K) {
 //   192 x 128   180 x 2880 x 8192 37.5 / 23.8     167 x 3656 x 6536  40.9 / 23.6 (32.0 / 21.1)    3115 x 136 x 5296  30.2 / 19.3 (25.0 / 17.2)
 //   64 x 64     162 x 800 x 4512  12.4 / 10.1 (12.0 / 8.9)    78 x 1264 x 3560  11.7 / 10.1 (10.4 / 8.7)    214 x 888 x 3960  13.4 / 11.2 (12.9 / 11.1)
 //               not below 512 columns: 410 x 200 x 3800  11.8 / 8.1 (6.6 / 7.0),  2114 x 64 x 3992  11.4 / 9.8 (6.9 / 8.3)
+// 250 drawn calls, split over whole, means on several sets (on one): 128 x 128 0.67 (0.81), 192 x 128 0.67 (0.82), 64 x 64 0.67 (0.86).  On
+// several sets none is slower; on one 17 are by more than 3 %, those whose whole call finds A and B in the caches: 1420 x 176 x 4304
+// 21.2 / 14.4 (9.7 / 12.7), 182 x 512 x 3456 15.0 / 9.1 (5.8 / 7.4).
 // (128 x 256 and 256 x 128 tiles with K split: within 3 % of these; the parts in the accumulators' own order, 1 KB a store: the same.)
 static Split choose_large_split(int M, int N, int K) {
     Split best = {nullptr, 0, K, nullptr};
