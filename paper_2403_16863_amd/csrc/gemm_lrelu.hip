@@ -414,8 +414,8 @@ long long gemm_lrelu_workspace(int M, int N, int K) {
     return M < 1 || N < 8 || K < 8 ? 0 : parts_bytes(gemm::choose_split(M, N, K), M, N);
 }
 
-// (one look at the shape for the scratch memory, the tile and the launch: with a query for the bytes ahead of it the choice took 204 ns of
-// a call of 512 x 512 x 2048 and 315 of 700 x 700 x 4000, now 60 and 104; without large calls' tiles and ranges it was 34)
+// (one look at the shape for the scratch memory, the tile and the launch: with a query for the bytes ahead of it the choice took 203 ns of
+// a call of 512 x 512 x 2048 and 313 of 704 x 704 x 4000, now 60 and 89; without large calls' tiles and ranges it was 34)
 int gemm_lrelu_with(const void* a, const void* b, void* c, int M, int N, int K, float slope, int dtype, void* stream,
                     gemm_scratch_fn scratch, void* owner) {
     const int rc = gemm::check_args(a, b, c, M, N, K, dtype, 0);
